@@ -30,8 +30,9 @@
 
 // ---------------------------------------------------------------- decode
 
+// The format check of the runs; the lengths go out widened for their scan.
 __global__ __launch_bounds__(256) void k_check_runs(const u64 *run_off, u32 k, const u32 *e, const u32 *d,
-                                                    u32 n, u32 *bad)
+                                                    u32 n, u32 *bad, u64 *len)
 {
     const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0 && (run_off[0] != 0 || run_off[k] != n)) atomicOr(bad, 1u);
@@ -41,7 +42,9 @@ __global__ __launch_bounds__(256) void k_check_runs(const u64 *run_off, u32 k, c
         else if (run_off[i + 1] > s && e[s] != 0) atomicOr(bad, 2u);
     }
     if (i < n) {
-        if (e[i] > d[i]) atomicOr(bad, 4u);
+        const u32 di = d[i];
+        len[i] = di;
+        if (e[i] > di) atomicOr(bad, 4u);
         if (i > 0 && e[i] > d[i - 1]) atomicOr(bad, 4u);
     }
 }
@@ -256,94 +259,369 @@ static int psv_build(const u32 *e, u64 n, u32 *psv, u32 *T, u32 *cm, u32 *farl, 
 }
 
 #define DC_NT 256
-#define DC_PER 16
+#define DC_SPAN 16384  // output bytes a chunk covers at most (64 per thread)
+#define DC_WU 2        // words a thread has in flight
+// copy words of a chunk: 16-byte words of the span, and two shared ones per piece
+#define DC_WORDS (DC_SPAN / 16 + 4 * DC_NT + 2)
 
-// Decoded bytes of output chunk c0 .. c0 + DC_NT*DC_PER, 16 per thread, in
-// output order (called by the whole workgroup; range is LDS).
-__device__ __forceinline__ void decode_chunk(u64 c0, const u32 *e, const u32 *d, const u64 *suf_off, const u8 *suf,
-                                             const u32 *psv, u32 n, const u64 *out_off, u64 total, u8 *out,
-                                             u32 *range)
+// What a decoded string takes from the strings before it, as a scan along the
+// front-coded order: the string's first 8 bytes (win, little-endian), and its
+// head, the nearest entry with e <= 8 at or before it, whose literal holds all
+// its bytes from 8 on (byte k at hsuf + k) and whose first F bytes the string
+// shares.  An entry keeps the first p = min(e, 8) bytes of its predecessor's
+// window and brings the rest; one with e <= 8 is a new head.
+struct DOp {
+    u64 win, hsuf;
+    u32 F;
+    u32 rp;  // bits 0..3: p, bit 4: a head
+};
+
+__device__ __forceinline__ u64 low_bytes(u32 k) { return k >= 8 ? ~0ull : ((1ull << (8 * k)) - 1ull); }
+
+// a, then b
+__device__ __forceinline__ DOp dop_cat(const DOp &a, const DOp &b)
 {
-    const u64 c1 = (c0 + DC_NT * DC_PER < total) ? c0 + DC_NT * DC_PER : total;
-    if (threadIdx.x < 2) {
-        const u64 q = threadIdx.x == 0 ? c0 : c1 - 1;
-        u32 lo = 0, hi = n;
-        while (hi - lo > 1) {
-            u32 mid = (lo + hi) >> 1;
-            if (out_off[mid] <= q) lo = mid;
-            else hi = mid;
+    const bool head = (b.rp & 16u) != 0;
+    const u32 pa = a.rp & 15u, pb = b.rp & 15u;
+    const u64 keep = low_bytes(pb);
+    DOp r;
+    r.win = (a.win & keep) | (b.win & ~keep);
+    r.hsuf = head ? b.hsuf : a.hsuf;
+    r.F = head || b.F < a.F ? b.F : a.F;
+    r.rp = ((a.rp | b.rp) & 16u) | (pa < pb ? pa : pb);
+    return r;
+}
+
+__device__ __forceinline__ DOp dop_shfl_up(const DOp &a, u32 d)
+{
+    DOp r;
+    r.win = __shfl_up(a.win, d, 64);
+    r.hsuf = __shfl_up(a.hsuf, d, 64);
+    r.F = __shfl_up(a.F, d, 64);
+    r.rp = __shfl_up(a.rp, d, 64);
+    return r;
+}
+
+// Largest i in [0, n) with a[i] <= x (a[0] <= x), by one wavefront: 64 probes
+// a step, so four dependent loads serve 16M entries.
+__device__ __forceinline__ u32 wave_find(const u64 *a, u32 n, u64 x)
+{
+    u32 lo = 0, len = n;  // the answer lies in [lo, lo + len)
+    const u32 lane = threadIdx.x & 63;
+    while (len > 1) {
+        const u32 step = (len + 63) / 64;
+        const u64 q = (u64)lane * step;
+        const bool le = q < len && a[lo + q] <= x;
+        const u32 c = (u32)__popcll(__ballot(le));  // (monotone: a prefix of the lanes)
+        const u32 k = c ? c - 1 : 0u;
+        lo += k * step;
+        len = len - k * step < step ? len - k * step : step;
+    }
+    return lo;
+}
+
+// Bytes v (little-endian) or-ed into an LDS buffer at byte position `at`.
+__device__ __forceinline__ void buf_or(u64 *buf, u32 at, u64 v)
+{
+    const u32 r = at & 7u;
+    atomicOr((unsigned long long *)&buf[at >> 3], (unsigned long long)(v << (8 * r)));
+    if (r) atomicOr((unsigned long long *)&buf[(at >> 3) + 1], (unsigned long long)(v >> (64 - 8 * r)));
+}
+
+// Decode: the output [0, out_off[n]) is dealt to the workgroups in contiguous
+// ranges, and each walks its range in chunks of at most DC_NT strings and
+// DC_SPAN bytes.  A chunk's strings are read once, one per thread, with a scan
+// that gives every string its first 8 bytes and its head (DOp); the state
+// after a chunk is carried to the next, and only the first string of a range
+// is found by walking its psv chain.  Then the chunk is assembled in LDS: a
+// string's bytes below 8 come from its window, those from e on from its own
+// literal, those below F from its head's (all of an equal string's, as runs of
+// equal strings share their head), and only what lies between walks the psv
+// chain.  The two literal pieces of every string are cut at the buffer's
+// 16-byte words, and the words dealt evenly to the threads, which keep DC_WU
+// of them in flight.
+//
+// The bytes in and out bound it at best; in practice the latency of the loads
+// and the vector instructions per word.  2M text strings (132 MB out): 566 us
+// with a global search per thread and single bytes moved, each piece by a
+// chain walk; 180 us with threads owning 16-byte words of the output (a search,
+// up to four pieces and their shifts: 560 instructions a word); 160 us with
+// four lanes per string (one load in flight per lane); 103 us in this form.
+// Nothing is written unless status is null or 0.
+__global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, const u64 *suf_off, const u8 *suf,
+                                                  const u32 *psv, u32 n, const u64 *out_off, const u32 *status,
+                                                  u8 *out)
+{
+    __shared__ u64 s_src[2 * DC_NT], s_cend;
+    __shared__ u16 s_at[2 * DC_NT], s_end[2 * DC_NT], s_base[2 * DC_NT], s_own[DC_WORDS];
+    __shared__ u32 s_wsum[DC_NT / 64];
+    __shared__ DOp s_tot[DC_NT / 64], s_carry;
+    __shared__ u32 s_r0;
+    __shared__ __attribute__((aligned(16))) u64 buf[DC_SPAN / 8 + 2];
+    if (status && *status != 0) return;  // (uniform)
+    const u64 total = out_off[n], sufN = suf_off[n];
+    const u32 mis = (u32)((uintptr_t)out & 15);
+    // this workgroup's range, its bounds on 16-byte words of the output
+    u64 per = (total + mis + gridDim.x - 1) / gridDim.x;
+    per = (per + 15) & ~15ull;
+    u64 c0 = blockIdx.x * per, r1 = c0 + per;
+    c0 = c0 > mis ? c0 - mis : 0;
+    r1 = r1 - mis < total ? r1 - mis : total;  // (per >= 16 > mis)
+    if (c0 >= r1) return;
+    const u32 lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (u32 w = threadIdx.x; w < DC_SPAN / 8 + 2; w += DC_NT) buf[w] = 0;
+    if (wv == 0) {
+        const u32 r = wave_find(out_off, n, c0);
+        if (lane == 0) {
+            // the first string's own state, along its psv chain (its operator
+            // applied to that state gives it again)
+            DOp c{0ull, 0ull, 0xFFFFFFFFu, 16u};
+            u32 j = r, ej = e[r], h = d[r];
+            bool found = false;  // the head
+            for (;;) {
+                const u64 so = suf_off[j];
+                if (ej <= 8 && !found) {
+                    found = true;
+                    c.hsuf = so - ej;
+                }
+                if (!found) c.F = ej;
+                const u32 m = h < 8 ? h : 8u;
+                if (ej < m) c.win |= load_le(suf, sufN, so, m - ej) << (8 * ej);
+                if (ej == 0) break;
+                h = ej;
+                j = psv[j];
+                ej = e[j];
+            }
+            s_carry = c;
+            s_r0 = r;
         }
-        range[threadIdx.x] = lo;
     }
     __syncthreads();
-    const u64 q0 = c0 + (u64)threadIdx.x * DC_PER;
-    if (q0 >= c1) return;  // (after the only barrier)
-    u32 lo = range[0], hi = range[1] + 1;
-    while (hi - lo > 1) {
-        u32 mid = (lo + hi) >> 1;
-        if (out_off[mid] <= q0) lo = mid;
-        else hi = mid;
+    const u32 t = threadIdx.x;
+    u32 ei = 0, di = 0;  // this thread's string of the chunk
+    u64 so = 0, oo = 0;
+    if (s_r0 + t < n) {
+        ei = e[s_r0 + t];
+        di = d[s_r0 + t];
+        so = suf_off[s_r0 + t];
+        oo = out_off[s_r0 + t];
     }
-    u32 i = lo;
-    u64 so = out_off[i], se = out_off[i + 1];
-    const u32 cnt = (u32)((c1 - q0) < DC_PER ? (c1 - q0) : DC_PER);
-    u8 buf[DC_PER];
-    u32 pj = 0, plo = 1, phi = 0;  // current piece: string pj covers bytes [plo, phi)
-#pragma unroll
-    for (u32 t = 0; t < DC_PER; t++) {
-        if (t < cnt) {
-            const u64 q = q0 + t;
-            while (q >= se) {
-                i++;
-                so = se;
-                se = out_off[i + 1];
-                plo = 1; phi = 0;
-            }
-            const u32 kk = (u32)(q - so);
-            if (kk < plo || kk >= phi) {
-                u32 j = i, h = d[i];
-                while (e[j] > kk) { h = e[j]; j = psv[j]; }
-                pj = j; plo = e[j]; phi = h;
-            }
-            buf[t] = suf[suf_off[pj] + (kk - plo)];
-        } else {
-            buf[t] = 0;
+    for (;;) {  // chunks (uniform over the workgroup)
+        const u32 r0 = s_r0;
+        const u32 ns = n - r0 < DC_NT ? n - r0 : DC_NT;
+        DOp o{0ull, 0ull, 0xFFFFFFFFu, 8u};
+        if (t < ns) {
+            if (t == ns - 1) s_cend = oo + di;
+            o.rp = (ei < 8 ? ei : 8u) | (ei <= 8 ? 16u : 0u);
+            o.F = ei <= 8 ? 0xFFFFFFFFu : ei;
+            o.hsuf = so - ei;
+            const u32 m = di < 8 ? di : 8u;
+            if (ei < m) o.win = load_le(suf, sufN, so, m - ei) << (8 * ei);
         }
-    }
-    u8 *dst = out + q0;
-    if (cnt == DC_PER && (((uintptr_t)dst) & 15) == 0) {
-        uint4 v;
-        v.x = buf[0] | (buf[1] << 8) | (buf[2] << 16) | ((u32)buf[3] << 24);
-        v.y = buf[4] | (buf[5] << 8) | (buf[6] << 16) | ((u32)buf[7] << 24);
-        v.z = buf[8] | (buf[9] << 8) | (buf[10] << 16) | ((u32)buf[11] << 24);
-        v.w = buf[12] | (buf[13] << 8) | (buf[14] << 16) | ((u32)buf[15] << 24);
-        *(uint4 *)dst = v;
-    } else {
-        for (u32 t = 0; t < cnt; t++) dst[t] = buf[t];
+        // The scan over the wavefront: a string's head is the highest lane at
+        // or below its own that is one; windows and minima in six steps.
+        const u64 heads = __ballot((o.rp & 16u) != 0), upto = heads & (lane == 63 ? ~0ull : (2ull << lane) - 1ull);
+        const u32 hl = upto ? 63u - (u32)__clzll(upto) : 0u;  // (0: no head below, minima from lane 0 on)
+        DOp inc = o;
+        inc.hsuf = __shfl(o.hsuf, hl, 64);
+        u32 p = o.rp & 15u;
+#pragma unroll
+        for (u32 q = 1; q < 64; q <<= 1) {
+            const u64 yw = __shfl_up(inc.win, q, 64);
+            const u32 yF = __shfl_up(inc.F, q, 64), yp = __shfl_up(p, q, 64);
+            if (lane >= q) {
+                const u64 keep = low_bytes(p);
+                inc.win = (yw & keep) | (inc.win & ~keep);
+                p = yp < p ? yp : p;
+            }
+            if (lane >= hl + q) inc.F = yF < inc.F ? yF : inc.F;
+        }
+        inc.rp = p | (upto ? 16u : 0u);
+        if (lane == 63) s_tot[wv] = inc;
+        DOp st = s_carry;
+        __syncthreads();
+        for (u32 w = 0; w < wv; w++) st = dop_cat(st, s_tot[w]);
+        const DOp pre0 = st;  // the state before this wavefront
+        st = dop_cat(st, inc);
+        // the chunk's end; the string that holds it starts the next chunk
+        const u64 cend = s_cend;
+        u64 c1 = c0 + DC_SPAN - ((uintptr_t)(out + c0) & 15);
+        c1 = c1 < r1 ? c1 : r1;
+        c1 = c1 < cend ? c1 : cend;
+        {
+            const DOp up = dop_shfl_up(st, 1);
+            if (t < ns) {
+                if (c1 == cend) {
+                    if (t == ns - 1) {
+                        s_carry = st;
+                        s_r0 = r0 + ns;
+                    }
+                } else if (oo <= c1 && c1 < oo + di) {
+                    // the state before the string
+                    s_carry.win = lane ? up.win : pre0.win;
+                    s_carry.hsuf = lane ? up.hsuf : pre0.hsuf;
+                    s_carry.F = lane ? up.F : pre0.F;
+                    s_carry.rp = lane ? up.rp : pre0.rp;
+                    s_r0 = r0 + t;
+                }
+            }
+        }
+        // This thread's string in the chunk.  Its window bytes and what only
+        // its psv chain holds go to the buffer (buf[lead] = output byte c0) at
+        // once; the piece of its head's literal and the one of its own become
+        // copies of as many 16-byte words as they touch.
+        const u32 lead = (u32)((uintptr_t)(out + c0) & 15);
+        u32 wc0 = 0, wc1 = 0;  // words of the two pieces
+        if (t < ns && oo < c1) {
+            const u64 k0 = oo < c0 ? c0 - oo : 0ull;  // bytes [k0, kend) lie in the chunk
+            const u64 kend = (oo + di < c1 ? oo + di : c1) - oo;
+            const u64 rel = oo - c0 + lead;           // byte k is at buffer position k + rel (mod 2^64)
+            u64 k = k0;
+            if (k < 8 && k < kend) {
+                const u64 m = kend < 8 ? kend : 8ull;
+                buf_or(buf, (u32)(k + rel), (st.win & low_bytes((u32)m)) >> (8 * k));
+                k = m;
+            }
+            const u64 eb = ei < kend ? ei : kend, fb = st.F < eb ? st.F : eb;
+            u64 src = st.hsuf + k, q = k;
+            if (k < fb) q = fb;
+            s_at[2 * t] = (u16)(k + rel);
+            s_end[2 * t] = (u16)(q + rel);
+            s_src[2 * t] = src;
+            if (q > k) wc0 = (u32)((q + rel + 15) / 16 - (k + rel) / 16);
+            k = q;
+            while (k < eb) {
+                u32 h = ei, j = psv[r0 + t], ej = e[j];
+                while (ej > k) {
+                    h = ej;
+                    j = psv[j];
+                    ej = e[j];
+                }
+                const u64 m = h < eb ? h : eb, pos = suf_off[j] - ej;
+                for (; k < m; k += 8)
+                    buf_or(buf, (u32)(k + rel), load_le(suf, sufN, pos + k, m - k < 8 ? (u32)(m - k) : 8u));
+                k = m;
+            }
+            s_at[2 * t + 1] = (u16)(k + rel);
+            s_end[2 * t + 1] = (u16)(kend + rel);
+            s_src[2 * t + 1] = so + (k - ei);
+            if (k < kend) wc1 = (u32)((kend + rel + 15) / 16 - (k + rel) / 16);
+        }
+        // every word of every piece gets a place of its own in the copy list
+        u32 base = wc0 + wc1;
+#pragma unroll
+        for (u32 q = 1; q < 64; q <<= 1) {
+            const u32 y = __shfl_up(base, q, 64);
+            if (lane >= q) base += y;
+        }
+        if (lane == 63) s_wsum[wv] = base;
+        __syncthreads();
+        for (u32 w = 0; w < wv; w++) base += s_wsum[w];
+        u32 nwords = 0;
+        for (u32 w = 0; w < DC_NT / 64; w++) nwords += s_wsum[w];
+        base -= wc0 + wc1;
+        s_base[2 * t] = (u16)base;
+        s_base[2 * t + 1] = (u16)(base + wc0);
+        for (u32 q = 0; q < wc0 + wc1; q++) s_own[base + q] = (u16)(2 * t + (q < wc0 ? 0u : 1u));
+        // the next chunk's strings, while this one's words are assembled
+        u32 ei_n = 0, di_n = 0;
+        u64 so_n = 0, oo_n = 0;
+        const u32 rn = s_r0 + t;
+        if (c1 < r1 && rn < n) {
+            ei_n = e[rn];
+            di_n = d[rn];
+            so_n = suf_off[rn];
+            oo_n = out_off[rn];
+        }
+        __syncthreads();
+        // The copies: DC_WU words a thread in flight, each loaded as five
+        // 4-byte words and shifted into place (a piece's end words, shared with
+        // the pieces beside it, are or-ed in)
+        for (u32 g0 = t; g0 < nwords; g0 += DC_WU * DC_NT) {
+            u32 x[DC_WU][5], w[DC_WU], b0[DC_WU], b1[DC_WU], r[DC_WU];
+            u64 ps[DC_WU];
+            bool safe[DC_WU];
+#pragma unroll
+            for (u32 u = 0; u < DC_WU; u++) {
+                const u32 g = g0 + u * DC_NT;
+                b0[u] = b1[u] = 0;
+                safe[u] = true;
+                w[u] = 0;
+                r[u] = 0;
+                ps[u] = 0;
+                if (g < nwords) {
+                    const u32 o2 = s_own[g], at = s_at[o2], end = s_end[o2];
+                    w[u] = at / 16 + (g - s_base[o2]);
+                    b0[u] = 16 * w[u] < at ? at - 16 * w[u] : 0u;             // bytes [b0, b1) of the word
+                    b1[u] = end - 16 * w[u] < 16 ? end - 16 * w[u] : 16u;
+                    ps[u] = s_src[o2] + (u64)((long long)(16 * w[u]) - (long long)at);  // suf offset of the word's byte 0
+                    const u8 *a = suf + ps[u];
+                    r[u] = (u32)((uintptr_t)a & 3);
+                    safe[u] = (long long)ps[u] >= 4 && ps[u] + 20 <= sufN;
+                    const u32 *q = (const u32 *)(a - r[u]);
+                    if (safe[u]) {
+#pragma unroll
+                        for (int y = 0; y < 5; y++) x[u][y] = q[y];
+                    }
+                }
+            }
+#pragma unroll
+            for (u32 u = 0; u < DC_WU; u++) {
+                if (b0[u] >= b1[u]) continue;
+                u64 v0 = 0, v1 = 0;
+                if (safe[u]) {
+#pragma unroll
+                    for (int y = 0; y < 4; y++) x[u][y] = __builtin_amdgcn_alignbyte(x[u][y + 1], x[u][y], r[u]);
+                    v0 = (u64)x[u][0] | ((u64)x[u][1] << 32);
+                    v1 = (u64)x[u][2] | ((u64)x[u][3] << 32);
+                } else {  // (near suf's ends)
+                    for (u32 y = b0[u]; y < b1[u]; y++) {
+                        const u64 z = suf[ps[u] + y];
+                        if (y < 8) v0 |= z << (8 * y);
+                        else v1 |= z << (8 * (y - 8));
+                    }
+                }
+                if (b1[u] - b0[u] == 16) {
+                    *(ulonglong2 *)&buf[2 * w[u]] = make_ulonglong2(v0, v1);
+                } else {
+                    v0 &= low_bytes(b1[u]) & ~low_bytes(b0[u]);
+                    v1 &= (b1[u] > 8 ? low_bytes(b1[u] - 8) : 0ull) & (b0[u] > 8 ? ~low_bytes(b0[u] - 8) : ~0ull);
+                    if (v0) atomicOr((unsigned long long *)&buf[2 * w[u]], (unsigned long long)v0);
+                    if (v1) atomicOr((unsigned long long *)&buf[2 * w[u] + 1], (unsigned long long)v1);
+                }
+            }
+        }
+        __syncthreads();
+        const u32 span = (u32)(c1 - c0);
+        // and out, in aligned 16-byte words; the buffer is cleared behind
+        const u32 nw = (span + lead + 15) / 16;
+        for (u32 w = t; w < nw; w += DC_NT) {
+            const u64 v0 = buf[2 * w], v1 = buf[2 * w + 1];
+            buf[2 * w] = 0;
+            buf[2 * w + 1] = 0;
+            u8 *dst = out + c0 - lead + 16 * w;
+            const u32 b0 = w == 0 ? lead : 0u, b1 = span + lead - 16 * w < 16 ? span + lead - 16 * w : 16u;
+            if (b1 - b0 == 16) *(ulonglong2 *)dst = make_ulonglong2(v0, v1);
+            else
+                for (u32 x = b0; x < b1; x++) dst[x] = (u8)((x < 8 ? v0 >> (8 * x) : v1 >> (8 * (x - 8))) & 0xFF);
+        }
+        c0 = c1;
+        if (c0 >= r1) break;
+        ei = ei_n;
+        di = di_n;
+        so = so_n;
+        oo = oo_n;
+        __syncthreads();  // the tables are rewritten by the next chunk
     }
 }
 
-__global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, const u64 *suf_off,
-                                                  const u8 *suf, const u32 *psv, u32 n, const u64 *out_off,
-                                                  u64 total, u8 *out)
+// Workgroups of a decode of at most `cap` bytes: as many as the device holds
+// at once (a range's first string costs a search and a chain walk), each at
+// least one span.
+static unsigned decode_grid(u64 cap)
 {
-    __shared__ u32 range[2];
-    decode_chunk((u64)blockIdx.x * DC_NT * DC_PER, e, d, suf_off, suf, psv, n, out_off, total, out, range);
-}
-
-// The same with the total read on the device (out_off[n]) and the chunks
-// taken in a grid-stride loop; nothing is written unless *status is 0.
-__global__ __launch_bounds__(DC_NT) void k_decode_dev(const u32 *e, const u32 *d, const u64 *suf_off,
-                                                      const u8 *suf, const u32 *psv, u32 n, const u64 *out_off,
-                                                      const u32 *status, u8 *out)
-{
-    __shared__ u32 range[2];
-    if (*status != 0) return;
-    const u64 total = out_off[n];
-    for (u64 c0 = (u64)blockIdx.x * DC_NT * DC_PER; c0 < total; c0 += (u64)gridDim.x * DC_NT * DC_PER) {
-        decode_chunk(c0, e, d, suf_off, suf, psv, n, out_off, total, out, range);
-        __syncthreads();  // range is rewritten by the next chunk
-    }
+    const u64 g = ceil_div(cap + 15, DC_SPAN), r = resident(k_decode, DC_NT);
+    return (unsigned)(g < r ? g : r);
 }
 
 // status = 0 (runs well formed, decoded bytes fit), 1 (malformed runs) or 2
@@ -353,11 +631,8 @@ __global__ void k_decode_status(const u32 *bad, const u64 *out_off, u32 n, u64 c
     *status = *bad ? 1u : (out_off[n] > cap ? 2u : 0u);
 }
 
-__global__ void k_widen(const u32 *d, u32 n, u64 *out)
-{
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = d[i];
-}
+// The check flag and the decoded total side by side, for one read-back.
+__global__ void k_decode_total(const u64 *total, u32 *bad) { *(u64 *)(bad + 2) = *total; }
 
 struct DecWs {
     u32 *psv, *tree, *cmin, *bad, *far, *fcnt;
@@ -392,17 +667,16 @@ static int decode_impl(u32 k, const u64 *run_off, const u32 *e, const u32 *d, co
     k_fill_u32<<<1, 64, 0, st>>>(w.bad, 0u, 1);
     SS_CHECK_LAUNCH();
     const u64 grid = ceil_div((n > k ? n : k) + 1, 256);
-    k_check_runs<<<(unsigned)grid, 256, 0, st>>>(run_off, k, e, d, (u32)n, w.bad);
+    k_check_runs<<<(unsigned)grid, 256, 0, st>>>(run_off, k, e, d, (u32)n, w.bad, out_off);
     SS_CHECK_LAUNCH();
-    if (n > 0) {
-        k_widen<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(d, (u32)n, out_off);
-        SS_CHECK_LAUNCH();
-    }
     SS_TRY(ss_scan_exclusive<u64>(out_off, out_off, n, w.scratch, st));
-    u32 bad;
+    k_decode_total<<<1, 1, 0, st>>>(out_off + n, w.bad);
+    SS_CHECK_LAUNCH();
+    u32 hw[4];
+    SS_TRY(ss_read_u32(w.bad, hw, 4, st));
+    const u32 bad = hw[0];
     u64 total;
-    SS_TRY(ss_read_u32(w.bad, &bad, 1, st));
-    SS_TRY(ss_read_u64(out_off + n, &total, 1, st));
+    memcpy(&total, hw + 2, sizeof(u64));
     if (bad) {
         ss_set_error("malformed front-coded runs (code %u): runs must start with e = 0 and e_i <= d_i, "
                      "e_i <= d_{i-1}", bad);
@@ -415,8 +689,7 @@ static int decode_impl(u32 k, const u64 *run_off, const u32 *e, const u32 *d, co
     }
     if (n == 0 || total == 0) return SS_OK;
     SS_TRY(psv_build(e, n, w.psv, w.tree, w.cmin, w.far, w.fcnt, st));
-    k_decode<<<(unsigned)ceil_div(total, DC_NT * DC_PER), DC_NT, 0, st>>>(e, d, suf_off, suf, w.psv, (u32)n, out_off,
-                                                                       total, out);
+    k_decode<<<decode_grid(total), DC_NT, 0, st>>>(e, d, suf_off, suf, w.psv, (u32)n, out_off, nullptr, out);
     SS_CHECK_LAUNCH();
     return SS_OK;
 }
@@ -521,12 +794,8 @@ extern "C" int ss_fc_decode_noalloc(uint32_t k, const uint64_t *run_off, const u
     k_fill_u32<<<1, 64, 0, st>>>(w.bad, 0u, 1);
     SS_CHECK_LAUNCH();
     const u64 grid = ceil_div((n > k ? n : k) + 1, 256);
-    k_check_runs<<<(unsigned)grid, 256, 0, st>>>(run_off, k, e, d, (u32)n, w.bad);
+    k_check_runs<<<(unsigned)grid, 256, 0, st>>>(run_off, k, e, d, (u32)n, w.bad, out_offsets);
     SS_CHECK_LAUNCH();
-    if (n > 0) {
-        k_widen<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(d, (u32)n, out_offsets);
-        SS_CHECK_LAUNCH();
-    }
     SS_TRY(ss_scan_exclusive<u64>(out_offsets, out_offsets, n, w.scratch, st));
     k_decode_status<<<1, 1, 0, st>>>(w.bad, out_offsets, (u32)n, out_cap, status);
     SS_CHECK_LAUNCH();
@@ -534,9 +803,8 @@ extern "C" int ss_fc_decode_noalloc(uint32_t k, const uint64_t *run_off, const u
     // the psv chains only read e (any values are safe); bytes are decoded
     // only when the status is 0
     SS_TRY(psv_build(e, n, w.psv, w.tree, w.cmin, w.far, w.fcnt, st));
-    const u64 chunks = ceil_div(out_cap, (u64)DC_NT * DC_PER);
-    k_decode_dev<<<(unsigned)(chunks < 4096 ? chunks : 4096), DC_NT, 0, st>>>(e, d, suf_off, suf, w.psv, (u32)n,
-                                                                            out_offsets, status, out_bytes);
+    k_decode<<<decode_grid(out_cap), DC_NT, 0, st>>>(e, d, suf_off, suf, w.psv, (u32)n, out_offsets, status,
+                                                   out_bytes);
     SS_CHECK_LAUNCH();
     return SS_OK;
 }
