@@ -161,11 +161,18 @@ __device__ __forceinline__ void flags_reduce32(u64 &mn, u64 &mx, u64 &sh)
     }
 }
 
+// A workgroup's flags of one round into the round's words.  All workgroups
+// meet on these few words, and atomics on one address queue (about 3 ns each:
+// committing every wavefront half on its own cost the first pass over 4M text
+// strings 380 of its 534 us), so one lane commits for the workgroup, and only
+// what would change the word as it reads it: the words only ever move one way,
+// so a stale value costs at most an atomic that changes nothing.
 __device__ __forceinline__ void flags_commit(u64 *f, u64 mn, u64 mx, u64 sh)
 {
-    if (mn != ~0ull) atomicMin((unsigned long long *)&f[0], (unsigned long long)mn);
-    if (mx != 0ull) atomicMax((unsigned long long *)&f[1], (unsigned long long)mx);
-    if (sh) atomicOr((unsigned long long *)&f[2], 1ull);
+    auto now = [&](int w) { return __hip_atomic_load(&f[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (mn < now(0)) atomicMin((unsigned long long *)&f[0], (unsigned long long)mn);
+    if (mx > now(1)) atomicMax((unsigned long long *)&f[1], (unsigned long long)mx);
+    if (sh && !now(2)) atomicOr((unsigned long long *)&f[2], 1ull);
 }
 
 __global__ void k_flag_init(u64 *f, u32 words, u32 zero_from)
@@ -310,6 +317,7 @@ __global__ __launch_bounds__(256, 4) void k_hash_first(u32 n, const u8 *bytes, u
     __shared__ u64 pwa[4][32];  // per wavefront: copy start (16-aligned, relative) of each string
     __shared__ u32 pwn[4][32];  // ... and its chunk count (0: not copied)
     __shared__ u64 s_ib[16], s_l[PRE_SLOTS];
+    __shared__ u64 s_fl[4][2 * HF_ACC][3];  // per wavefront and round: its flags
     // kernel-argument arrays are read with constant indices only
     if (threadIdx.x < 16) {
         u64 v = 0;
@@ -485,8 +493,23 @@ __global__ __launch_bounds__(256, 4) void k_hash_first(u32 n, const u8 *bytes, u
 #pragma unroll
     for (int a = 0; a < HF_ACC; a++) {
         flags_reduce32(fmn[a], fmx[a], fsh[a]);
-        const u32 r = 2 * a + h;
-        if (col == 0 && r < P.count) flags_commit(fl + 3 * r, fmn[a], fmx[a], fsh[a]);
+        if (col == 0) {
+            s_fl[wv][2 * a + h][0] = fmn[a];
+            s_fl[wv][2 * a + h][1] = fmx[a];
+            s_fl[wv][2 * a + h][2] = fsh[a];
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < P.count) {
+        u64 mn = ~0ull, mx = 0, sh = 0;
+#pragma unroll
+        for (int w = 0; w < 4; w++) {
+            const u64 *f = s_fl[w][threadIdx.x];
+            mn = f[0] < mn ? f[0] : mn;
+            mx = f[1] > mx ? f[1] : mx;
+            sh |= f[2];
+        }
+        flags_commit(fl + 3 * threadIdx.x, mn, mx, sh);
     }
 }
 
@@ -734,33 +757,34 @@ __device__ __forceinline__ void hash_pass(const PassArgs &A, const RoundW &rw, c
         fb |= hv | ((seen && key != fk[slot]) ? hv << 1 : 0u) | (shrt ? hv << 2 : 0u);
         fk[slot] = seen ? fk[slot] : key;
     };
-    // The flags of one slot as a minimum, maximum and short flag.  In the
-    // deep first pass each wavefront half's go to LDS and the workgroup's are
-    // committed once per lane half (the few global words take 4x fewer
-    // atomics); round passes commit per wavefront half.
+    // The flags of one slot as a minimum, maximum and short flag: each
+    // wavefront half's go to LDS and the workgroup's are committed once per
+    // lane half.
     __shared__ u64 s_fmn[FIRST ? HF_ACC + 1 : 1][NW][2], s_fmx[FIRST ? HF_ACC + 1 : 1][NW][2];
     __shared__ u32 s_fsh[FIRST ? HF_ACC + 1 : 1][NW][2];
-    auto stage = [&](int slot) {
+    auto stage = [&](int slot) {  // (round passes have one slot, HF_ACC, kept at 0)
         const u32 b = fb >> (3 * slot);
         u64 mn = (b & 1) ? ((b & 2) ? 0ull : fk[slot]) : ~0ull;
         u64 mx = (b & 1) ? ((b & 2) ? ~0ull : fk[slot]) : 0ull;
         u64 sh = (b >> 2) & 1;
         flags_reduce32(mn, mx, sh);
+        const int at = FIRST ? slot : 0;
         if (col == 0) {
-            s_fmn[slot][wv][h] = mn;
-            s_fmx[slot][wv][h] = mx;
-            s_fsh[slot][wv][h] = (u32)sh;
+            s_fmn[at][wv][h] = mn;
+            s_fmx[at][wv][h] = mx;
+            s_fsh[at][wv][h] = (u32)sh;
         }
     };
     auto commit = [&](int slot, u64 *f, bool doit) {  // (after a barrier)
         if (wv == 0 && col == 0 && doit) {
             u64 mn = ~0ull, mx = 0, sh = 0;
+            const int at = FIRST ? slot : 0;
 #pragma unroll
             for (int w = 0; w < NW; w++) {
-                const u64 a = s_fmn[slot][w][h], b = s_fmx[slot][w][h];
+                const u64 a = s_fmn[at][w][h], b = s_fmx[at][w][h];
                 mn = a < mn ? a : mn;
                 mx = b > mx ? b : mx;
-                sh |= s_fsh[slot][w][h];
+                sh |= s_fsh[at][w][h];
             }
             flags_commit(f, mn, mx, sh);
         }
@@ -1158,13 +1182,10 @@ __device__ __forceinline__ void hash_pass(const PassArgs &A, const RoundW &rw, c
                 commit(a, A.fl + 3 * r, r < c0);
             }
         }
-    } else {  // A.rf[0..2] round l1, A.rf[3..5] round l2, per wavefront half
-        const u32 b = fb >> (3 * HF_ACC);
-        u64 mn = (b & 1) ? ((b & 2) ? 0ull : fk[HF_ACC]) : ~0ull;
-        u64 mx = (b & 1) ? ((b & 2) ? ~0ull : fk[HF_ACC]) : 0ull;
-        u64 sh = (b >> 2) & 1;
-        flags_reduce32(mn, mx, sh);
-        if (col == 0 && (!h || two)) flags_commit(A.rf + ((two && !h) ? 3 : 0), mn, mx, sh);
+    } else {  // A.rf[0..2] round l1, A.rf[3..5] round l2
+        stage(HF_ACC);
+        __syncthreads();
+        commit(HF_ACC, A.rf + ((two && !h) ? 3 : 0), !h || two);
     }
 }
 
