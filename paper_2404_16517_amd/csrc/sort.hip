@@ -145,6 +145,12 @@ __global__ void k_round_begin(u32 *ctr, u32 *hdr)
     if (threadIdx.x < C_NCTR && threadIdx.x != C_BADSET) ctr[threadIdx.x] = 0;
 }
 
+// The next round's counters, before its list is made anew.
+__global__ void k_next_reset(u32 *ctr)
+{
+    if (threadIdx.x == 0) ctr[C_NEXT] = ctr[C_NTILES] = ctr[C_NELEM] = 0;
+}
+
 // Tile counts of the active segments for a round; also resets the segments'
 // skip minima.
 __global__ void k_round_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u32 *skipv)
@@ -485,40 +491,186 @@ __global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart
 }
 
 // Apply the skip, route each active segment to the LDS list or the radix list.
-__global__ void k_classify(const Seg *act, const u32 *nactp, const u32 *skipv, u32 small_max, u32 tile, Seg *tiny,
-                           Seg *small, Seg *large, u32 *ctr)
+// The lists' lengths and totals are counted in LDS and added by one atomic per
+// counter and 256 segments: one per wavefront made 446K small segments queue
+// on the few counters for 246 us; 11K of them now take 5 us.
+__global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nactp, const u32 *skipv, u32 small_max,
+                                                  u32 tile, Seg *tiny, Seg *small, Seg *large, u32 *ctr)
 {
+    enum { TY = 0, SM, LG, TYN, SMN, LGT, LGN, CNT };  // list lengths, then their totals
+    __shared__ u32 c[CNT], base[3];
+    __shared__ u64 sk;  // sum of size * skip
     const u32 nact = *nactp;
     for (u32 j0 = blockIdx.x * blockDim.x; j0 < nact; j0 += gridDim.x * blockDim.x) {
+    if (threadIdx.x < CNT) c[threadIdx.x] = 0;
+    if (threadIdx.x == CNT) sk = 0;
+    __syncthreads();
     const u32 j = j0 + threadIdx.x;
-    bool valid = j < nact;
+    const bool valid = j < nact;
     Seg g = {0, 0, 0, 0};
+    u64 skn = 0;
     if (valid) {
         g = act[j];
-        if (g.aux & SEG_SKIP) g.depth += skipv[j];
+        if (g.aux & SEG_SKIP) {
+            g.depth += skipv[j];
+            skn = (u64)(g.end - g.begin) * skipv[j];
+        }
         g.aux = 0;
     }
-    const bool ty = valid && (g.end - g.begin) <= WS_MAX;
-    const bool sm = valid && !ty && (g.end - g.begin) <= small_max;
-    const bool lg = valid && !ty && !sm;
-    const u32 c = wave_append(ty, &ctr[C_TINY]);
-    if (ty) tiny[c] = g;
-    u32 a = wave_append(sm, &ctr[C_SMALL]);
-    if (sm) small[a] = g;
-    u32 b = wave_append(lg, &ctr[C_LARGE]);
-    if (lg) large[b] = g;
     const u32 sz = g.end - g.begin;
-    {
-        u64 sk = (valid && (act[j].aux & SEG_SKIP)) ? (u64)sz * skipv[j] : 0ull;
+    const u32 kind = !valid ? 3u : (sz <= WS_MAX ? (u32)TY : (sz <= small_max ? (u32)SM : (u32)LG));
+    u32 slot = 0;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sk += __shfl_xor(sk, o, 64);
-        if (__lane_id() == 0 && sk) atomicAdd((unsigned long long *)&ctr[10], (unsigned long long)sk);
+    for (u32 k = 0; k < 3; k++) {
+        const u64 m = __ballot(kind == k);
+        if (!m) continue;  // (uniform over the wavefront)
+        u32 v = kind == k ? sz : 0u, t = kind == k ? (sz + tile - 1) / tile : 0u, at = 0;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            v += __shfl_xor(v, o, 64);
+            if (k == LG) t += __shfl_xor(t, o, 64);
+        }
+        if (__lane_id() == 0) {
+            at = atomicAdd(&c[k], (u32)__popcll(m));
+            atomicAdd(&c[k == TY ? TYN : (k == SM ? SMN : LGN)], v);
+            if (k == LG) atomicAdd(&c[LGT], t);
+        }
+        at = __shfl(at, 0, 64);
+        if (kind == k) slot = at + (u32)__popcll(m & lanemask_lt());
     }
-    wave_add(ty ? sz : 0u, &ctr[C_TINYN]);
-    wave_add(sm ? sz : 0u, &ctr[C_SMALLN]);
-    wave_add(lg ? (sz + tile - 1) / tile : 0u, &ctr[C_LTILES]);
-    wave_add(lg ? sz : 0u, &ctr[C_LELEM]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) skn += __shfl_xor(skn, o, 64);
+    if (__lane_id() == 0 && skn) atomicAdd((unsigned long long *)&sk, (unsigned long long)skn);
+    __syncthreads();
+    if (threadIdx.x < CNT && c[threadIdx.x]) {
+        const u32 to[CNT] = {C_TINY, C_SMALL, C_LARGE, C_TINYN, C_SMALLN, C_LTILES, C_LELEM};
+        u32 w = 0;
+#pragma unroll
+        for (u32 q = 0; q < CNT; q++)
+            if (threadIdx.x == q) w = to[q];
+        const u32 at = atomicAdd(&ctr[w], c[threadIdx.x]);
+        if (threadIdx.x < 3) base[threadIdx.x] = at;
     }
+    if (threadIdx.x == CNT && sk) atomicAdd((unsigned long long *)&ctr[10], (unsigned long long)sk);
+    __syncthreads();
+    if (kind == TY) tiny[base[TY] + slot] = g;
+    else if (kind == SM) small[base[SM] + slot] = g;
+    else if (kind == LG) large[base[LG] + slot] = g;
+    __syncthreads();  // the counters are reset for the next segments
+    }
+}
+
+#define RS_MAX 16     // runs of up to this many tied strings are compared directly
+#define RS_CMP 1024   // ... over this many bytes past their common prefix
+
+// Runs of tied strings that a round hands to the next, most of them two or
+// three equal strings: eight lanes per run compare every member with the
+// first, 64 bytes a step.  Equal strings end here (LCP = length; they are in
+// input order already), two unequal ones too; a longer run with unequal
+// members goes on from its exact common prefix (no skip needed), and runs too
+// long or tied for too long go on as they are.  `in` (count *nin) to `out`,
+// whose counters (C_NEXT, C_NTILES, C_NELEM) are zero before.
+//
+// Bounded by the latency of scattered reads: two lines per string.  A round's
+// skip, keys, routing and sort took 1.1 ms for 446K such runs (4M text
+// strings); this takes 190 us, and the whole sort 2.6 -> 1.9 ms.
+__global__ __launch_bounds__(256) void k_resolve(const Seg *in, u32 nin, const u8 *bytes, u64 N, const u64 *off,
+                                                 u32 *vals, u32 *lcp, Seg *out, u32 *ctr)
+{
+    __shared__ u32 s_cnt, s_tiles, s_elems, s_base;
+    if (threadIdx.x == 0) s_cnt = s_tiles = s_elems = 0;
+    __syncthreads();
+    const u32 s = blockIdx.x * 32 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
+    bool keep = false;
+    Seg g = {0, 0, 0, 0};
+    if (s < nin) {
+        g = in[s];
+        const u32 m = g.end - g.begin;
+        if (m > RS_MAX) {
+            keep = true;
+        } else {
+            // every member's index, offset and length first, two per lane
+            u32 pm[2], lm[2];
+            u64 om[2];
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const u32 j = gl + 8 * h;
+                pm[h] = j < m ? vals[g.begin + j] : 0u;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                om[h] = off[pm[h]];
+                lm[h] = (u32)(off[pm[h] + 1] - om[h]);
+            }
+            const u32 p0 = __shfl(pm[0], 0, 8), l0 = __shfl(lm[0], 0, 8);
+            const u64 o0 = __shfl(om[0], 0, 8);
+            bool same = true, open = false;
+            u32 dmin = 0xFFFFFFFFu;
+            u64 oj = 0;
+            u32 pj = 0, lj = 0;
+            for (u32 j = 1; j < m && !open; j++) {  // (the same for the run's eight lanes)
+                pj = __shfl(j < 8 ? pm[0] : pm[1], j & 7, 8);
+                oj = __shfl(j < 8 ? om[0] : om[1], j & 7, 8);
+                lj = __shfl(j < 8 ? lm[0] : lm[1], j & 7, 8);
+                const u32 lim = l0 < lj ? l0 : lj;
+                u32 pos = g.depth, mis = 0xFFFFFFFFu;
+                while (pos < lim && mis == 0xFFFFFFFFu && pos - g.depth < RS_CMP) {
+                    const u32 q = pos + 8 * gl;
+                    const u32 take = q < lim ? (lim - q < 8 ? lim - q : 8u) : 0u;
+                    const Raw8 ra = raw8_issue(bytes, N, o0 + q, take), rb = raw8_issue(bytes, N, oj + q, take);
+                    const u64 d = raw8_le(bytes, ra) ^ raw8_le(bytes, rb);
+                    u32 f = d ? q + (u32)(__builtin_ctzll(d) >> 3) : 0xFFFFFFFFu;
+#pragma unroll
+                    for (int x = 1; x < 8; x <<= 1) {
+                        const u32 y = __shfl_xor(f, x, 8);
+                        f = y < f ? y : f;
+                    }
+                    mis = f;
+                    pos += 64;
+                }
+                open = mis == 0xFFFFFFFFu && pos < lim;
+                const u32 l = mis == 0xFFFFFFFFu ? lim : mis;
+                same = same && mis == 0xFFFFFFFFu && l0 == lj;
+                dmin = l < dmin ? l : dmin;
+            }
+            if (open) {
+                keep = true;
+            } else if (same) {
+                for (u32 j = 1 + gl; j < m; j += 8) lcp[g.begin + j] = l0;
+            } else if (m == 2) {
+                if (gl == 0) {
+                    lcp[g.begin + 1] = dmin;
+                    const bool first = dmin == l0 || (dmin < lj && bytes[o0 + dmin] < bytes[oj + dmin]);
+                    if (!first) {
+                        vals[g.begin] = pj;
+                        vals[g.begin + 1] = p0;
+                    }
+                }
+            } else {
+                keep = true;
+                g.depth = dmin;
+                g.aux = 0;
+            }
+        }
+    }
+    const u64 b = __ballot(keep && gl == 0);
+    u32 slot = 0;
+    if (b) {  // (uniform over the wavefront)
+        if (__lane_id() == 0) slot = atomicAdd(&s_cnt, (u32)__popcll(b));
+        slot = __shfl(slot, 0, 64) + (u32)__popcll(b & lanemask_lt());
+        if (keep && gl == 0) {
+            atomicAdd(&s_tiles, (g.end - g.begin + ETILE - 1) / ETILE);
+            atomicAdd(&s_elems, g.end - g.begin);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_cnt) {
+        s_base = atomicAdd(&ctr[C_NEXT], s_cnt);
+        atomicAdd(&ctr[C_NTILES], s_tiles);
+        atomicAdd(&ctr[C_NELEM], s_elems);
+    }
+    __syncthreads();
+    if (keep && gl == 0) out[s_base + slot] = g;
 }
 
 // ------------------------------------------------------------ radix passes
@@ -1563,10 +1715,23 @@ int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles)
         }
         SS_TRY(round_tail(C, h));
         SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
+        if (h[C_NEXT] > 0) {
+            // the tied runs compared directly; what is left goes back to the
+            // first list (its segments are all done) as the next round's
+            k_next_reset<<<1, 64, 0, J.stream>>>(w.ctr);
+            SS_CHECK_LAUNCH();
+            {
+                // offsets and payload of every string; the bytes compared are not known
+                SS_PROF("k_resolve", J.stream, (double)h[C_NELEM] * 20.0);
+                k_resolve<<<grid_of(h[C_NEXT], 32, 1u << 30), 256, 0, J.stream>>>(w.nxt, h[C_NEXT], J.bytes, J.N, J.off,
+                                                                                  J.vals, J.lcp, w.act, w.ctr);
+            }
+            SS_CHECK_LAUNCH();
+            SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
+        }
         nact = h[C_NEXT];
         atiles = h[C_NTILES];
         round_elems = h[C_NELEM];
-        Seg *tmp = w.act; w.act = w.nxt; w.nxt = tmp;
     }
     return SS_OK;
 }
