@@ -524,8 +524,9 @@ size_t ss_profile_names(char *buf, size_t cap);
 /* ------------------------------------------------------------- tuning */
 
 /* Tunable launch parameters (chosen by the autotuner; defaults are safe).
- *   SS_TUNE_SMALL_MAX  segments up to this many strings are sorted in LDS
- *                      (128, 256, 512 or 1024; default 1024).
+ *   SS_TUNE_SMALL_MAX  segments up to twice this many strings are sorted in
+ *                      LDS without further radix levels (128, 256, 512 or
+ *                      1024; default 1024).
  *   SS_TUNE_TILE       elements per workgroup in radix passes (1024..16384,
  *                      power of two; default 4096).
  *   SS_TUNE_DIGIT_BITS radix digit width: 8 (a level per key byte, 256

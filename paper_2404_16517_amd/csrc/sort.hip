@@ -32,17 +32,15 @@
 #include "sort_core.hpp"
 
 #define NT 256
-#define ETILE 2048  // elements per workgroup in element-wise round kernels
+#define ETILE 2048  // elements per workgroup in element-wise round kernels (fewer in small sorts)
 #define RX_PF 8     // 256-element chunks a radix pass loads ahead
-#define LDS_NT 512
-#define LDS_CAP 2048  // elements per LDS tile (2 x the largest cutover)
 
 // counters: list lengths, and the tile / element totals of the lists being
 // built (so that grids are known without reading the lists back)
 enum {
     C_SMALL = 0, C_LARGE = 1, C_NEXT = 2, C_IDENT = 3, C_BND = 4,
     C_LTILES = 5, C_SMALLN = 6, C_NTILES = 7, C_ITILES = 8, C_LELEM = 9, C_NELEM = 12, C_TINY = 13,
-    C_TINYN = 14, C_BADSET = 15, C_NCTR = 16
+    C_TINYN = 14, C_BADSET = 15, C_MID = 16, C_NCTR = 17
 };
 // Headers that the round and level kernels read their list lengths from
 // (copied from the counters by k_round_begin / k_level_begin, so that the
@@ -50,7 +48,10 @@ enum {
 // segments, hdr[H_LARGE] radix segments of the current level, hdr[H_HIST]
 // their histogram length (256 per tile).
 enum { H_ACT = 0, H_LARGE = 1, H_HIST = 2, H_REMAIN = 3, H_NHDR = 4 };
-#define WS_MAX 128  // segments of up to this many strings: one wavefront each
+#define WS_MAX 128   // segments of up to this many strings: one wavefront each, in registers
+#define BS_IPT 8     // elements per thread in the block sort
+#define BS_SMALL 512  // ... segments of up to this many: one wavefront each
+#define BS_MID 2048   // ... and up to this many: four wavefronts
 // ctr[10..11]: 64-bit sum of size * skip over the routed segments
 
 // ------------------------------------------------------------ wave helpers
@@ -187,12 +188,6 @@ __global__ void k_level_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *
     }
 }
 
-__global__ void k_sizes(const Seg *segs, const u32 *nsegp, u32 *out)
-{
-    const u32 nseg = *nsegp;
-    GSTRIDE(j, nseg) out[j] = segs[j].end - segs[j].begin;
-}
-
 // ------------------------------------------------------------ round kernels
 
 #define SKB 16      // strings per wavefront batch in the skip kernel
@@ -296,7 +291,7 @@ __device__ __forceinline__ u32 skip_cmp(const u8 *bytes, u64 N, const u8 *R, con
 // (the grid-stride form keeps its loop state live as well: five workgroups
 // per compute unit give it the registers to do so without spilling)
 template <bool LOOP, bool SEED = false, int NTB = NT>
-__global__ __launch_bounds__(NTB, (LOOP ? 5 : 6) * (NT / NTB)) void k_skip(const Seg *segs, const u32 *tstart, const u32 *nsegp,
+__global__ __launch_bounds__(NTB, (LOOP ? 5 : 6) * (NT / NTB)) void k_skip(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 et,
                                              const u8 *bytes, u64 N, const u64 *off,
                                              const u32 *perm, u32 *skipv, u64 *mword, uint2 *mpr,
                                              const u32 *seed_ok = nullptr)
@@ -313,8 +308,8 @@ __global__ __launch_bounds__(NTB, (LOOP ? 5 : 6) * (NT / NTB)) void k_skip(const
     const Seg g = segs[sg];
     if (!(g.aux & SEG_SKIP)) continue;  // uniform over the workgroup
     const u32 lt = t - tstart[sg];
-    const u32 b0 = g.begin + lt * ETILE;
-    const u32 b1 = min(g.end, b0 + ETILE);
+    const u32 b0 = g.begin + lt * et;
+    const u32 b1 = min(g.end, b0 + et);
     if (SEED && sok) {
         // the tile's records, one member per thread: when the seed resolved
         // every member, their minimum is the tile's part of the skip and no
@@ -322,7 +317,7 @@ __global__ __launch_bounds__(NTB, (LOOP ? 5 : 6) * (NT / NTB)) void k_skip(const
         u32 sb = 0xFFFFFFFFu;
         bool open = false;
 #pragma unroll 8
-        for (u32 k = 0; k < ETILE / NTB; k++) {
+        for (u32 k = 0; k < et / NTB; k++) {
             const u32 i = b0 + k * NTB + threadIdx.x;
             if (i < b1) {
                 const uint2 sp = mpr[i];
@@ -441,7 +436,7 @@ __global__ __launch_bounds__(NTB, (LOOP ? 5 : 6) * (NT / NTB)) void k_skip(const
 }
 
 template <bool LOOP, int NTB = NT>
-__global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart, const u32 *nsegp,
+__global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 et,
                                              const u8 *bytes, u64 N, const u64 *off,
                                              const u32 *perm, const u32 *skipv, const u64 *mword,
                                              const uint2 *mpr, u64 *keys)
@@ -453,8 +448,8 @@ __global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart
     const u32 s = seg_of_tile(tstart, nseg, t);
     const Seg g = segs[s];
     const u32 lt = t - tstart[s];
-    const u32 b0 = g.begin + lt * ETILE;
-    const u32 b1 = min(g.end, b0 + ETILE);
+    const u32 b0 = g.begin + lt * et;
+    const u32 b1 = min(g.end, b0 + et);
     if (!(g.aux & SEG_SKIP)) {
         const u64 d = g.depth;
         for (u32 i = b0 + threadIdx.x; i < b1; i += NTB) {
@@ -495,10 +490,11 @@ __global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart
 // counter and 256 segments: one per wavefront made 446K small segments queue
 // on the few counters for 246 us; 11K of them now take 5 us.
 __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nactp, const u32 *skipv, u32 small_max,
-                                                  u32 tile, Seg *tiny, Seg *small, Seg *large, u32 *ctr)
+                                                  u32 tile, Seg *tiny, Seg *small, Seg *mid, Seg *large,
+                                                  u32 *ctr)
 {
-    enum { TY = 0, SM, LG, TYN, SMN, LGT, LGN, CNT };  // list lengths, then their totals
-    __shared__ u32 c[CNT], base[3];
+    enum { TY = 0, SM, MD, LG, TYN, SMN, LGT, LGN, CNT };  // list lengths, then their totals
+    __shared__ u32 c[CNT], base[4];
     __shared__ u64 sk;  // sum of size * skip
     const u32 nact = *nactp;
     for (u32 j0 = blockIdx.x * blockDim.x; j0 < nact; j0 += gridDim.x * blockDim.x) {
@@ -518,10 +514,10 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
         g.aux = 0;
     }
     const u32 sz = g.end - g.begin;
-    const u32 kind = !valid ? 3u : (sz <= WS_MAX ? (u32)TY : (sz <= small_max ? (u32)SM : (u32)LG));
+    const u32 kind = !valid ? (u32)CNT : (sz <= WS_MAX ? (u32)TY : (sz > small_max ? (u32)LG : (sz <= BS_SMALL ? (u32)SM : (u32)MD)));
     u32 slot = 0;
 #pragma unroll
-    for (u32 k = 0; k < 3; k++) {
+    for (u32 k = 0; k < 4; k++) {
         const u64 m = __ballot(kind == k);
         if (!m) continue;  // (uniform over the wavefront)
         u32 v = kind == k ? sz : 0u, t = kind == k ? (sz + tile - 1) / tile : 0u, at = 0;
@@ -532,7 +528,7 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
         }
         if (__lane_id() == 0) {
             at = atomicAdd(&c[k], (u32)__popcll(m));
-            atomicAdd(&c[k == TY ? TYN : (k == SM ? SMN : LGN)], v);
+            atomicAdd(&c[k == TY ? TYN : (k == LG ? LGN : SMN)], v);
             if (k == LG) atomicAdd(&c[LGT], t);
         }
         at = __shfl(at, 0, 64);
@@ -543,18 +539,19 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
     if (__lane_id() == 0 && skn) atomicAdd((unsigned long long *)&sk, (unsigned long long)skn);
     __syncthreads();
     if (threadIdx.x < CNT && c[threadIdx.x]) {
-        const u32 to[CNT] = {C_TINY, C_SMALL, C_LARGE, C_TINYN, C_SMALLN, C_LTILES, C_LELEM};
+        const u32 to[CNT] = {C_TINY, C_SMALL, C_MID, C_LARGE, C_TINYN, C_SMALLN, C_LTILES, C_LELEM};
         u32 w = 0;
 #pragma unroll
         for (u32 q = 0; q < CNT; q++)
             if (threadIdx.x == q) w = to[q];
         const u32 at = atomicAdd(&ctr[w], c[threadIdx.x]);
-        if (threadIdx.x < 3) base[threadIdx.x] = at;
+        if (threadIdx.x < 4) base[threadIdx.x] = at;
     }
     if (threadIdx.x == CNT && sk) atomicAdd((unsigned long long *)&ctr[10], (unsigned long long)sk);
     __syncthreads();
     if (kind == TY) tiny[base[TY] + slot] = g;
     else if (kind == SM) small[base[SM] + slot] = g;
+    else if (kind == MD) mid[base[MD] + slot] = g;
     else if (kind == LG) large[base[LG] + slot] = g;
     __syncthreads();  // the counters are reset for the next segments
     }
@@ -575,7 +572,7 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
 // skip, keys, routing and sort took 1.1 ms for 446K such runs (4M text
 // strings); this takes 190 us, and the whole sort 2.6 -> 1.9 ms.
 __global__ __launch_bounds__(256) void k_resolve(const Seg *in, u32 nin, const u8 *bytes, u64 N, const u64 *off,
-                                                 u32 *vals, u32 *lcp, Seg *out, u32 *ctr)
+                                                 u32 *vals, u32 *lcp, Seg *out, u32 *ctr, u32 et)
 {
     __shared__ u32 s_cnt, s_tiles, s_elems, s_base;
     if (threadIdx.x == 0) s_cnt = s_tiles = s_elems = 0;
@@ -659,7 +656,7 @@ __global__ __launch_bounds__(256) void k_resolve(const Seg *in, u32 nin, const u
         if (__lane_id() == 0) slot = atomicAdd(&s_cnt, (u32)__popcll(b));
         slot = __shfl(slot, 0, 64) + (u32)__popcll(b & lanemask_lt());
         if (keep && gl == 0) {
-            atomicAdd(&s_tiles, (g.end - g.begin + ETILE - 1) / ETILE);
+            atomicAdd(&s_tiles, (g.end - g.begin + et - 1) / et);
             atomicAdd(&s_elems, g.end - g.begin);
         }
     }
@@ -766,16 +763,17 @@ __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart,
 }
 
 struct EmitOut {
-    Seg *tiny, *small, *large_next, *next, *ident;
+    Seg *tiny, *small, *mid, *large_next, *next, *ident;
     uint2 *bnd;
     u32 *ctr;
     u8 *scat;
     u8 *kinds;
     u32 small_max;
     u32 tile;
+    u32 et;
 };
 
-enum { K_NONE = 0, K_SMALL, K_LARGE, K_NEXT, K_IDENT, K_TINY, K_KINDS };
+enum { K_NONE = 0, K_SMALL, K_LARGE, K_NEXT, K_IDENT, K_TINY, K_MID, K_KINDS };
 
 // What digit d of radix segment s becomes: an entry for one of the lists
 // (kind, seg) and/or a bucket boundary (sb, depth) for the LCP pass.
@@ -838,7 +836,7 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
         } else if (cnt <= WS_MAX) {
             it.kind = K_TINY;
         } else if (cnt <= o.small_max) {
-            it.kind = K_SMALL;
+            it.kind = cnt <= BS_SMALL ? K_SMALL : K_MID;
         } else {
             it.kind = K_LARGE;
             it.ns.aux = (level + 1) | cf;
@@ -884,10 +882,10 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
         const u32 cnt = x.ns.end - x.ns.begin;
         if (x.bnd) atomicAdd(&lcount[0], 1u);
         if (x.kind) atomicAdd(&lcount[x.kind], 1u);
-        if (x.kind == K_SMALL) atomicAdd(&lsum[0], cnt);
+        if (x.kind == K_SMALL || x.kind == K_MID) atomicAdd(&lsum[0], cnt);
         if (x.kind == K_LARGE) { atomicAdd(&lsum[1], (cnt + o.tile - 1) / o.tile); atomicAdd(&lsum[2], cnt); }
-        if (x.kind == K_NEXT) { atomicAdd(&lsum[3], (cnt + ETILE - 1) / ETILE); atomicAdd(&lsum[4], cnt); }
-        if (x.kind == K_IDENT) atomicAdd(&lsum[5], (cnt + ETILE - 1) / ETILE);
+        if (x.kind == K_NEXT) { atomicAdd(&lsum[3], (cnt + o.et - 1) / o.et); atomicAdd(&lsum[4], cnt); }
+        if (x.kind == K_IDENT) atomicAdd(&lsum[5], (cnt + o.et - 1) / o.et);
         if (x.kind == K_TINY) atomicAdd(&lsum[6], cnt);
     }
     __syncthreads();
@@ -898,6 +896,7 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
         gbase[K_NEXT] = lcount[K_NEXT] ? atomicAdd(&o.ctr[C_NEXT], lcount[K_NEXT]) : 0u;
         gbase[K_IDENT] = lcount[K_IDENT] ? atomicAdd(&o.ctr[C_IDENT], lcount[K_IDENT]) : 0u;
         gbase[K_TINY] = lcount[K_TINY] ? atomicAdd(&o.ctr[C_TINY], lcount[K_TINY]) : 0u;
+        gbase[K_MID] = lcount[K_MID] ? atomicAdd(&o.ctr[C_MID], lcount[K_MID]) : 0u;
         if (lsum[0]) atomicAdd(&o.ctr[C_SMALLN], lsum[0]);
         if (lsum[1]) atomicAdd(&o.ctr[C_LTILES], lsum[1]);
         if (lsum[2]) atomicAdd(&o.ctr[C_LELEM], lsum[2]);
@@ -913,7 +912,7 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
         if (x.bnd) o.bnd[gbase[0] + atomicAdd(&lslot[0], 1u)] = x.bv;
         if (x.kind) {
             const u32 a = gbase[x.kind] + atomicAdd(&lslot[x.kind], 1u);
-            Seg *dst = x.kind == K_TINY ? o.tiny : x.kind == K_SMALL ? o.small
+            Seg *dst = x.kind == K_TINY ? o.tiny : x.kind == K_SMALL ? o.small : x.kind == K_MID ? o.mid
                      : x.kind == K_LARGE ? o.large_next : x.kind == K_NEXT ? o.next : o.ident;
             dst[a] = x.ns;
         }
@@ -1066,7 +1065,8 @@ __global__ void k_boundary(const uint2 *bnd, const u32 *nbp, const u64 *keys, u3
 
 // Equal strings: LCP = their length for every member after the first.
 template <bool LOOP>
-__global__ __launch_bounds__(NT) void k_ident(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 *lcp)
+__global__ __launch_bounds__(NT) void k_ident(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 et,
+                                              u32 *lcp)
 {
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
@@ -1074,142 +1074,166 @@ __global__ __launch_bounds__(NT) void k_ident(const Seg *segs, const u32 *tstart
         const u32 s = seg_of_tile(tstart, nseg, t);
         const Seg g = segs[s];
         const u32 lt = t - tstart[s];
-        const u32 b0 = g.begin + lt * ETILE;
-        const u32 b1 = min(g.end, b0 + ETILE);
+        const u32 b0 = g.begin + lt * et;
+        const u32 b1 = min(g.end, b0 + et);
         for (u32 i = b0 + threadIdx.x; i < b1; i += NT)
             if (i > g.begin) lcp[i] = g.depth;
     }
 }
 
-// ------------------------------------------------------------- LDS sort
+// ----------------------------------------------------------- block sort
 
-__device__ __forceinline__ bool lds_greater(u16 sa, u64 ka, u32 va, u16 sb, u64 kb, u32 vb)
-{
-    if (sa != sb) return sa > sb;
-    if (ka != kb) return ka > kb;
-    return va > vb;
-}
+// Segments of 129 .. 8 NTB strings, one workgroup of NTB threads each (NTB =
+// 64 or 256): a merge sort of (key, payload) in LDS.  Every thread sorts eight
+// consecutive elements in registers (odd-even transposition), then runs of 8,
+// 16, ... are merged pairwise: a thread finds where its eight outputs start
+// (the merge path, a binary search over two keys a step) and merges them
+// serially.  Keys alone are compared and every step is stable, so equal keys
+// keep the payload order the segment came in, which is index order.  The
+// sorted elements then give the LCPs where keys differ, and runs of equal
+// continuing keys become next-round segments.
+//
+// Bounded by vector instructions (about 25 per element and merge level) and
+// LDS latency; keys and payloads move through HBM once.  It replaces a bitonic
+// network over tiles of packed segments (up to 1024 strings, 66 exchanges per
+// element for 2048) and, for segments of up to 2048, a radix level before it:
+// 512 sets of 10^3..10^5 strings 349 -> 148 us; 16M D/N strings, whose segments
+// of 1,479 strings took a radix level (about 250 us) and 366 us in the register
+// sort, 266 us.
+__device__ __forceinline__ u32 bs_at(u32 i) { return i + i / BS_IPT; }  // (a pad per thread: no bank conflicts)
 
-// Small segments packed into tiles: tile t takes the segments whose start in
-// the concatenated small-segment space lies in [t*H, (t+1)*H); with segment
-// sizes <= H a tile holds < 2H elements.  Sorted by (segment, key, payload)
-// with a bitonic network in LDS.
-template <bool LOOP>
-__global__ __launch_bounds__(LDS_NT) void k_lds_sort(const Seg *small, const u32 *pref, const u32 *nsmallp,
-                                                     u32 H, u64 *keys, u32 *vals, const u64 *keyB,
-                                                     const u32 *valB, u32 *lcp, Seg *next, u32 *ctr)
+template <bool LOOP, int NTB>
+__global__ __launch_bounds__(NTB) void k_block_sort(const Seg *list, const u32 *cntp, u64 *keys, u32 *vals,
+                                                    const u64 *keyB, const u32 *valB, u32 *lcp, Seg *next, u32 *ctr,
+                                                    u32 et)
 {
-    __shared__ u64 skey[LDS_CAP];
-    __shared__ u32 sval[LDS_CAP];
-    __shared__ u16 sseg[LDS_CAP];
-    __shared__ u32 spref[LDS_CAP / 2 + 1];
-    __shared__ u32 sbeg[LDS_CAP / 2];
-    __shared__ u32 sdep[LDS_CAP / 2];
-    __shared__ u8 sinb[LDS_CAP / 2];
-    __shared__ Seg nq[LDS_CAP / 2];  // next-round segments found in this tile
+    constexpr u32 CAP = NTB * BS_IPT;
+    __shared__ u64 sk[CAP + NTB];
+    __shared__ u32 sv[CAP + NTB];
     __shared__ u32 nq_count, nq_tiles, nq_elems, nq_base;
-    const u32 nsmall = *nsmallp;
-    const u32 ntile = LOOP ? (pref[nsmall] + H - 1) / H : 0u;  // pref[nsmall]: strings in all small segments
-    TILE_LOOP(t, ntile) {
-    const u32 lo = t * H, hi = lo + H;
-    // j0 = first segment with pref >= lo, j1 = first with pref >= hi
-    u32 j0, j1;
-    {
-        u32 a = 0, b = nsmall;
-        while (a < b) { u32 m = (a + b) >> 1; if (pref[m] < lo) a = m + 1; else b = m; }
-        j0 = a;
-        a = j0; b = nsmall;
-        while (a < b) { u32 m = (a + b) >> 1; if (pref[m] < hi) a = m + 1; else b = m; }
-        j1 = a;
-    }
-    if (j0 >= j1) continue;  // (uniform over the workgroup)
-    const u32 ns = j1 - j0;
-    const u32 base = pref[j0];
-    const u32 cnt = pref[j1] - base;
-    if (threadIdx.x == 0) { nq_count = 0; nq_tiles = 0; nq_elems = 0; }
-    for (u32 k = threadIdx.x; k <= ns; k += LDS_NT) spref[k] = pref[j0 + k] - base;
-    for (u32 k = threadIdx.x; k < ns; k += LDS_NT) {
-        Seg g = small[j0 + k];
-        sbeg[k] = g.begin;
-        sdep[k] = g.depth;
-        sinb[k] = (g.aux & SEG_INB) ? 1 : 0;
-    }
-    __syncthreads();
-    u32 P = 2;
-    while (P < cnt) P <<= 1;
-    for (u32 e = threadIdx.x; e < P; e += LDS_NT) {
-        if (e < cnt) {
-            u32 a = 0, b = ns;  // largest k with spref[k] <= e
-            while (b - a > 1) { u32 m = (a + b) >> 1; if (spref[m] <= e) a = m; else b = m; }
-            const u32 pos = sbeg[a] + (e - spref[a]);
-            skey[e] = sinb[a] ? keyB[pos] : keys[pos];  // read where the segment is, write A
-            sval[e] = sinb[a] ? valB[pos] : vals[pos];
-            sseg[e] = (u16)a;
-        } else {
-            skey[e] = ~0ull;
-            sval[e] = 0xFFFFFFFFu;
-            sseg[e] = 0xFFFF;
+    const u32 nlist = LOOP ? *cntp : 0u;
+    TILE_LOOP(sg, nlist) {
+    const Seg g = list[sg];
+    const u32 cnt = g.end - g.begin;
+    const u64 *ks = (g.aux & SEG_INB) ? keyB : keys;  // read where the segment is, write A
+    const u32 *vs = (g.aux & SEG_INB) ? valB : vals;
+    const u32 e0 = threadIdx.x * BS_IPT;  // this thread's elements (padding sorts last)
+    u64 k[BS_IPT];
+    u32 v[BS_IPT];
+#pragma unroll
+    for (u32 q = 0; q < BS_IPT; q++) {
+        k[q] = ~0ull;
+        v[q] = 0xFFFFFFFFu;
+        if (e0 + q < cnt) {
+            k[q] = ks[g.begin + e0 + q];
+            v[q] = vs[g.begin + e0 + q];
         }
     }
+    if (threadIdx.x == 0) nq_count = nq_tiles = nq_elems = 0;
+#pragma unroll
+    for (u32 r = 0; r < BS_IPT; r++) {
+#pragma unroll
+        for (u32 q = r & 1; q + 1 < BS_IPT; q += 2) {
+            const bool sw = k[q] > k[q + 1];
+            const u64 a = sw ? k[q + 1] : k[q], b = sw ? k[q] : k[q + 1];
+            const u32 x = sw ? v[q + 1] : v[q], y = sw ? v[q] : v[q + 1];
+            k[q] = a;
+            k[q + 1] = b;
+            v[q] = x;
+            v[q + 1] = y;
+        }
+    }
+#pragma unroll
+    for (u32 q = 0; q < BS_IPT; q++) {
+        sk[bs_at(e0) + q] = k[q];
+        sv[bs_at(e0) + q] = v[q];
+    }
     __syncthreads();
-    for (u32 k = 2; k <= P; k <<= 1) {
-        for (u32 j = k >> 1; j > 0; j >>= 1) {
-            for (u32 i = threadIdx.x; i < P / 2; i += LDS_NT) {
-                const u32 x = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-                const u32 y = x + j;
-                const bool up = (x & k) == 0;
-                const u16 sx = sseg[x], sy = sseg[y];
-                const u64 kx = skey[x], ky = skey[y];
-                const u32 vx = sval[x], vy = sval[y];
-                if (lds_greater(sx, kx, vx, sy, ky, vy) == up) {
-                    sseg[x] = sy; sseg[y] = sx;
-                    skey[x] = ky; skey[y] = kx;
-                    sval[x] = vy; sval[y] = vx;
+    for (u32 w = BS_IPT; w < cnt; w *= 2) {  // (uniform)
+        const u32 pb = e0 & ~(2 * w - 1);  // the pair of runs [pb, pb + w), [pb + w, pb + 2w)
+        const u32 pa = pb + w;
+        if (pa < cnt) {  // (else the second run is padding: nothing to merge)
+            const u32 d = e0 - pb;
+            u32 lo = d > w ? d - w : 0u, hi = d < w ? d : w;
+            while (lo < hi) {
+                const u32 mid = (lo + hi) >> 1;
+                if (sk[bs_at(pb + mid)] <= sk[bs_at(pa + d - 1 - mid)]) lo = mid + 1;
+                else hi = mid;
+            }
+            u32 i = pb + lo, j = pa + d - lo;
+            const u32 ie = pa, je = pa + w;
+            u64 ka = i < ie ? sk[bs_at(i)] : ~0ull, kb = j < je ? sk[bs_at(j)] : ~0ull;
+#pragma unroll
+            for (u32 q = 0; q < BS_IPT; q++) {
+                const bool first = j >= je || (i < ie && ka <= kb);
+                const u32 at = first ? i : j;
+                k[q] = first ? ka : kb;
+                v[q] = sv[bs_at(at)];
+                i += first ? 1u : 0u;
+                j += first ? 0u : 1u;
+                const u32 nx = at + 1, ne = first ? ie : je;
+                const u64 kn = nx < ne ? sk[bs_at(nx)] : ~0ull;
+                ka = first ? kn : ka;
+                kb = first ? kb : kn;
+            }
+        }
+        __syncthreads();
+        if (pa < cnt) {
+#pragma unroll
+            for (u32 q = 0; q < BS_IPT; q++) {
+                sk[bs_at(e0) + q] = k[q];
+                sv[bs_at(e0) + q] = v[q];
+            }
+        }
+        __syncthreads();
+    }
+    // results, lanes on consecutive elements; only the segment's end keys are
+    // read again (for the LCPs across bucket boundaries)
+    u32 lasts = 0, it = 0;  // bit per element of this thread: the last of a run of tied keys
+    for (u32 e = threadIdx.x; e < cnt; e += NTB, it++) {
+        const u32 pos = g.begin + e;
+        const u64 kb = sk[bs_at(e)];
+        vals[pos] = sv[bs_at(e)];
+        if (e == 0 || e == cnt - 1) keys[pos] = kb;
+        if (e == 0) continue;
+        const u64 ka = sk[bs_at(e - 1)];
+        const u32 c8 = (u32)(kb & 0xFF);
+        if (ka != kb) lcp[pos] = key_lcp(ka, kb, g.depth);
+        else if (c8 < 8) lcp[pos] = g.depth + c8;
+        else if (e + 1 == cnt || sk[bs_at(e + 1)] != kb) lasts |= 1u << it;
+    }
+    if (__syncthreads_or(lasts != 0)) {
+        // tied runs, published with one atomic per counter: counted, then written
+        for (int pass = 0; pass < 2; pass++) {
+            for (u32 m = lasts; m; m &= m - 1) {
+                const u32 e = threadIdx.x + NTB * (u32)(__ffs((int)m) - 1);
+                const u64 kb = sk[bs_at(e)];
+                u32 x = 0, y = e;  // first element with this key
+                while (x < y) {
+                    const u32 mid = (x + y) >> 1;
+                    if (sk[bs_at(mid)] < kb) x = mid + 1;
+                    else y = mid;
                 }
+                const u32 sz = e + 1 - x;
+                const u32 slot = atomicAdd(&nq_count, 1u);
+                if (pass == 0) {
+                    atomicAdd(&nq_tiles, (sz + et - 1) / et);
+                    atomicAdd(&nq_elems, sz);
+                } else {
+                    next[nq_base + slot] = Seg{g.begin + x, g.begin + e + 1, g.depth + 7, SEG_SKIP};
+                }
+            }
+            __syncthreads();
+            if (pass == 0 && threadIdx.x == 0) {
+                nq_base = atomicAdd(&ctr[C_NEXT], nq_count);
+                atomicAdd(&ctr[C_NTILES], nq_tiles);
+                atomicAdd(&ctr[C_NELEM], nq_elems);
+                nq_count = 0;
             }
             __syncthreads();
         }
     }
-    for (u32 e = threadIdx.x; e < cnt; e += LDS_NT) {
-        const u32 a = sseg[e];
-        const u32 first = spref[a];
-        const u32 pos = sbeg[a] + (e - first);
-        const u64 kb = skey[e];
-        vals[pos] = sval[e];
-        keys[pos] = kb;
-        if (e == first) continue;
-        const u64 ka = skey[e - 1];
-        const u32 dep = sdep[a];
-        if (ka != kb) {
-            lcp[pos] = key_lcp(ka, kb, dep);
-            continue;
-        }
-        const u32 c8 = (u32)(kb & 0xFF);
-        if (c8 < 8) {
-            lcp[pos] = dep + c8;
-            continue;
-        }
-        const bool last = (e + 1 == spref[a + 1]) || skey[e + 1] != kb;
-        if (last) {
-            u32 x = first, y = e;  // first index in [first, e] with key == kb
-            while (x < y) { u32 m = (x + y) >> 1; if (skey[m] < kb) x = m + 1; else y = m; }
-            const Seg ns{sbeg[a] + (x - first), pos + 1, dep + 7, SEG_SKIP};
-            const u32 slot = atomicAdd(&nq_count, 1u);
-            nq[slot] = ns;
-            atomicAdd(&nq_tiles, (ns.end - ns.begin + ETILE - 1) / ETILE);
-            atomicAdd(&nq_elems, ns.end - ns.begin);
-        }
-    }
-    // publish this tile's next-round segments with one atomic per counter
-    __syncthreads();
-    if (threadIdx.x == 0 && nq_count) {
-        nq_base = atomicAdd(&ctr[C_NEXT], nq_count);
-        atomicAdd(&ctr[C_NTILES], nq_tiles);
-        atomicAdd(&ctr[C_NELEM], nq_elems);
-    }
-    __syncthreads();
-    for (u32 k = threadIdx.x; k < nq_count; k += LDS_NT) next[nq_base + k] = nq[k];
-    __syncthreads();  // the LDS tables are rewritten by the next tile
+    __syncthreads();  // the tables are rewritten by the next segment
     }
 }
 
@@ -1293,7 +1317,7 @@ __device__ __forceinline__ bool shfl_down_b(bool b, u32 lane, bool from_next)
 template <bool LOOP>
 __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *ntinyp, u64 *keys, u32 *vals,
                                                    const u64 *keyB, const u32 *valB, u32 *lcp, Seg *next, u32 *ctr,
-                                                   const u8 *bytes, u64 N, const u64 *off)
+                                                   const u8 *bytes, u64 N, const u64 *off, u32 et)
 {
     __shared__ Seg nq[WS_SPB * (WS_MAX / 2)];
     __shared__ u32 nq_count, nq_tiles, nq_elems, nq_base;
@@ -1348,8 +1372,9 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
                 }
             }
         }
-        if (e0 < cnt) keys[g.begin + e0] = k0;
-        if (e1 < cnt) keys[g.begin + e1] = k1;
+        // (only the segment's end keys are read again, for the LCPs across bucket boundaries)
+        if (e0 == 0 || e0 == cnt - 1) keys[g.begin + e0] = k0;
+        if (e1 == cnt - 1) keys[g.begin + e1] = k1;
         // neighbours in sorted order
         const u64 k0_last = __shfl(k0, 63, 64), k1_first = __shfl(k1, 0, 64);
         const u64 up0 = __shfl_up(k0, 1, 64), up1 = __shfl_up(k1, 1, 64);
@@ -1424,7 +1449,7 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
             const u32 f = hibit(s0 & le);
             const Seg ns{g.begin + f, g.begin + e0 + 1, dep + 7, SEG_SKIP};
             nq[atomicAdd(&nq_count, 1u)] = ns;
-            atomicAdd(&nq_tiles, (ns.end - ns.begin + ETILE - 1) / ETILE);
+            atomicAdd(&nq_tiles, (ns.end - ns.begin + et - 1) / et);
             atomicAdd(&nq_elems, ns.end - ns.begin);
         }
         if (end1) {
@@ -1432,7 +1457,7 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
             const u32 f = mm ? 64u + hibit(mm) : hibit(s0);
             const Seg ns{g.begin + f, g.begin + e1 + 1, dep + 7, SEG_SKIP};
             nq[atomicAdd(&nq_count, 1u)] = ns;
-            atomicAdd(&nq_tiles, (ns.end - ns.begin + ETILE - 1) / ETILE);
+            atomicAdd(&nq_tiles, (ns.end - ns.begin + et - 1) / et);
             atomicAdd(&nq_elems, ns.end - ns.begin);
         }
         }
@@ -1481,7 +1506,8 @@ void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c)
     TAKE(act, Seg, nseg);
     TAKE(nxt, Seg, nseg);
     TAKE(tiny, Seg, nseg);
-    TAKE(small, Seg, nseg);
+    TAKE(small, Seg, nlarge);
+    TAKE(mid, Seg, nlarge);
     TAKE(ident, Seg, nseg);
     TAKE(largeA, Seg, nlarge);
     TAKE(largeB, Seg, nlarge);
@@ -1492,7 +1518,6 @@ void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c)
     TAKE(scat, u8, nlarge);
     TAKE(kinds, u8, nkinds);
     TAKE(tstart, u32, nseg + 1);
-    TAKE(spref, u32, nseg + 1);
     TAKE(hist, u32, nscan);
     TAKE(scan_scratch, u64, ss_scan_scratch_elems<u64>(nscan));
     TAKE(dscan, u32, ss_scan_dev_scratch_elems<u32>());
@@ -1521,10 +1546,32 @@ struct RoundCtx {
     SortWs &w;
     u64 n;  // strings of the whole sort (bounds every list)
     u32 SM, TL;
-    u32 W;  // radix digit bits (8, or 11 with tiles >= 4096 and a cutover >= 512)
+    u32 W;   // radix digit bits (8, or 11 with tiles >= 4096 and a cutover >= 512)
+    u32 ET;  // elements per workgroup of the element-wise kernels
+    u32 BM;  // segments of up to this many strings are sorted in LDS
 };
 
+// Elements per workgroup of the element-wise round kernels in a sort of n
+// strings: ETILE, but fewer below 2M strings so that there are about 1024
+// workgroups (at 100,000 strings k_skip's 49 took 66 us, 391 take 15 us).  More
+// of them in large sorts only repeat the set-up: 16M D/N strings take 4 % longer
+// with 512.
+static u32 elem_tile(u64 n)
+{
+    u32 t = ETILE;
+    while (t > 256 && n < 1024ull * t) t /= 2;
+    return t;
+}
+
 static u32 digit_bits_for(u32 SM, u32 TL) { return (g_digit_bits == 11 && TL >= 4096 && SM >= 512) ? 11u : 8u; }
+
+// (the cutover's tiles hold two such segments' strings, one in the block sort)
+static RoundCtx round_ctx(const SortJob &J, SortWs &w)
+{
+    const u32 sm = (u32)g_small_max, tl = (u32)g_tile;
+    return RoundCtx{J, w, J.n_total, sm, tl, digit_bits_for(sm, tl), elem_tile(J.n_total),
+                    2 * sm < BS_MID ? 2 * sm : (u32)BS_MID};
+}
 
 static int scan_u32(RoundCtx &C, u32 *arr, const u32 *n_dev, Known k)
 {
@@ -1542,7 +1589,7 @@ static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bo
     k_round_begin<<<1, 64, 0, st>>>(w.ctr, w.hdr);
     SS_CHECK_LAUNCH();
     const u32 *nactp = w.hdr + H_ACT;
-    k_round_tiles<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, ETILE, w.tstart,
+    k_round_tiles<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, C.ET, w.tstart,
                                                                                w.skipv);
     SS_CHECK_LAUNCH();
     SS_TRY(scan_u32(C, w.tstart, nactp, nact));
@@ -1553,14 +1600,14 @@ static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bo
         // (seeded: the records in, the strings of members the seed left open)
         const bool sd = first && atiles.yes && J.seed_pos;
         SS_PROF("k_skip", st, (double)round_elems * (sd ? 8.0 : 44.0));
-        if (sd) k_skip<false, true><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, J.bytes, J.N, J.off, J.vals, w.skipv, J.seed_word, J.seed_pos, J.seed_ok);
+        if (sd) k_skip<false, true><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, J.seed_word, J.seed_pos, J.seed_ok);
         // (tiles of small segments, as later rounds leave them, hold few
         // members: one wavefront per tile then keeps four times as many in
         // flight)
         else if (atiles.yes && round_elems < 64ull * atiles.v)
-            k_skip<false, false, 64><<<tg, 64, 0, st>>>(w.act, w.tstart, nactp, J.bytes, J.N, J.off, J.vals, w.skipv, w.mword, w.mpr);
-        else if (atiles.yes) k_skip<false><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, J.bytes, J.N, J.off, J.vals, w.skipv, w.mword, w.mpr);
-        else k_skip<true><<<grid_of(n, ETILE, resident(k_skip<true>, NT)), NT, 0, st>>>(w.act, w.tstart, nactp, J.bytes, J.N, J.off, J.vals, w.skipv, w.mword, w.mpr);
+            k_skip<false, false, 64><<<tg, 64, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, w.mword, w.mpr);
+        else if (atiles.yes) k_skip<false><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, w.mword, w.mpr);
+        else k_skip<true><<<grid_of(n, C.ET, resident(k_skip<true>, NT)), NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, w.mword, w.mpr);
     }
     SS_CHECK_LAUNCH();
     {
@@ -1570,13 +1617,13 @@ static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bo
         uint2 *mp = sd ? J.seed_pos : w.mpr;
         SS_PROF("k_keys", st, (double)round_elems * 24.0);  // mismatch record in, key out
         if (atiles.yes && round_elems < 64ull * atiles.v)  // (small tiles: one wavefront each, as in the skip)
-            k_keys<false, 64><<<tg, 64, 0, st>>>(w.act, w.tstart, nactp, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
-        else if (atiles.yes) k_keys<false><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
-        else k_keys<true><<<grid_of(n, ETILE, resident(k_keys<true>, NT)), NT, 0, st>>>(w.act, w.tstart, nactp, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
+            k_keys<false, 64><<<tg, 64, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
+        else if (atiles.yes) k_keys<false><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
+        else k_keys<true><<<grid_of(n, C.ET, resident(k_keys<true>, NT)), NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
     }
     SS_CHECK_LAUNCH();
-    k_classify<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, w.skipv, C.SM, C.TL,
-                                                                             w.tiny, w.small, w.largeA, w.ctr);
+    k_classify<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, w.skipv, C.BM, C.TL,
+                                                                             w.tiny, w.small, w.mid, w.largeA, w.ctr);
     SS_CHECK_LAUNCH();
     return SS_OK;
 }
@@ -1607,7 +1654,7 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     SS_CHECK_LAUNCH();
     if (ltiles.yes) SS_TRY(ss_scan_exclusive<u32>(w.hist, w.hist, (u64)ltiles.v * NB, (u32 *)w.scan_scratch, st));
     else SS_TRY(ss_scan_exclusive_dev<u32>(w.hist, w.hist, w.hdr + H_HIST, 1, w.dscan, st));
-    EmitOut eo{w.tiny, w.small, LB, w.nxt, w.ident, w.bnd, w.ctr, w.scat, w.kinds, C.SM, C.TL};
+    EmitOut eo{w.tiny, w.small, w.mid, LB, w.nxt, w.ident, w.bnd, w.ctr, w.scat, w.kinds, C.BM, C.TL, C.ET};
     constexpr u32 SPG = EPB / Digits<W>::DPT;
     if (nlarge.yes) k_emit<false, W><<<grid_of(nlarge.v, SPG, 1u << 30), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, eo);
     else k_emit<true, W><<<grid_of(n / 128, SPG, resident(k_emit<true, W>, 256)), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, eo);
@@ -1647,23 +1694,29 @@ static int round_tail(RoundCtx &C, const u32 *h)
         SS_PROF("k_wave_sort", st, known ? (double)h[C_TINYN] * 28.0 : 0.0);  // key+payload in/out, LCP out
         if (known)
             k_wave_sort<false><<<grid_of(h[C_TINY], WS_SPB, 1u << 30), 256, 0, st>>>(
-                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off);
+                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, C.ET);
         else
             k_wave_sort<true><<<grid_of(n / 2, WS_SPB, resident(k_wave_sort<true>, 256)), 256, 0, st>>>(
-                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off);
+                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, C.ET);
         SS_CHECK_LAUNCH();
     }
-    if (!known || h[C_SMALL] > 0) {
-        k_sizes<<<grid_of(known ? h[C_SMALL] : n / 2, 256, 1024), 256, 0, st>>>(w.small, w.ctr + C_SMALL, w.spref);
-        SS_CHECK_LAUNCH();
-        SS_TRY(scan_u32(C, w.spref, w.ctr + C_SMALL, Known{known, known ? h[C_SMALL] : 0u}));
-        SS_PROF("k_lds_sort", st, known ? (double)h[C_SMALLN] * 28.0 : 0.0);  // key+payload in/out, LCP out
-        if (known)
-            k_lds_sort<false><<<grid_of(h[C_SMALLN], C.SM, 1u << 30), LDS_NT, 0, st>>>(
-                w.small, w.spref, w.ctr + C_SMALL, C.SM, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr);
-        else
-            k_lds_sort<true><<<grid_of(n, C.SM, resident(k_lds_sort<true>, LDS_NT)), LDS_NT, 0, st>>>(
-                w.small, w.spref, w.ctr + C_SMALL, C.SM, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr);
+    if (!known || h[C_SMALL] > 0 || h[C_MID] > 0) {
+        SS_PROF("k_block_sort", st, known ? (double)h[C_SMALLN] * 28.0 : 0.0);  // key+payload in/out, LCP out
+        if (known) {
+            if (h[C_SMALL])
+                k_block_sort<false, BS_SMALL / BS_IPT><<<h[C_SMALL], BS_SMALL / BS_IPT, 0, st>>>(
+                    w.small, w.ctr + C_SMALL, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+            if (h[C_MID])
+                k_block_sort<false, BS_MID / BS_IPT><<<h[C_MID], BS_MID / BS_IPT, 0, st>>>(
+                    w.mid, w.ctr + C_MID, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+        } else {
+            const auto ks = k_block_sort<true, BS_SMALL / BS_IPT>;
+            const auto km = k_block_sort<true, BS_MID / BS_IPT>;
+            ks<<<grid_of(n, WS_MAX, resident(ks, BS_SMALL / BS_IPT)), BS_SMALL / BS_IPT, 0, st>>>(
+                w.small, w.ctr + C_SMALL, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+            km<<<grid_of(n, BS_SMALL, resident(km, BS_MID / BS_IPT)), BS_MID / BS_IPT, 0, st>>>(
+                w.mid, w.ctr + C_MID, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+        }
         SS_CHECK_LAUNCH();
     }
     if (!known || h[C_BND] > 0) {
@@ -1672,13 +1725,13 @@ static int round_tail(RoundCtx &C, const u32 *h)
     }
     if (!known || h[C_IDENT] > 0) {
         k_tile_counts<<<grid_of(known ? h[C_IDENT] : n / 2, 256, 1024), 256, 0, st>>>(w.ident, w.ctr + C_IDENT,
-                                                                                    ETILE, w.tstart);
+                                                                                    C.ET, w.tstart);
         SS_CHECK_LAUNCH();
         SS_TRY(scan_u32(C, w.tstart, w.ctr + C_IDENT, Known{known, known ? h[C_IDENT] : 0u}));
         if (known)
-            k_ident<false><<<grid_of(h[C_ITILES], 1, 1u << 30), NT, 0, st>>>(w.ident, w.tstart, w.ctr + C_IDENT, lcp);
+            k_ident<false><<<grid_of(h[C_ITILES], 1, 1u << 30), NT, 0, st>>>(w.ident, w.tstart, w.ctr + C_IDENT, C.ET, lcp);
         else
-            k_ident<true><<<grid_of(n, ETILE, resident(k_ident<true>, NT)), NT, 0, st>>>(w.ident, w.tstart, w.ctr + C_IDENT, lcp);
+            k_ident<true><<<grid_of(n, C.ET, resident(k_ident<true>, NT)), NT, 0, st>>>(w.ident, w.tstart, w.ctr + C_IDENT, C.ET, lcp);
         SS_CHECK_LAUNCH();
     }
     return SS_OK;
@@ -1691,9 +1744,7 @@ static int round_tail(RoundCtx &C, const u32 *h)
 // ctr[C_NEXT], ctr[C_NTILES], ctr[C_NELEM].
 int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles)
 {
-    RoundCtx C{J, w, 0, (u32)g_small_max, (u32)g_tile, 8};
-    C.n = J.n_total;
-    C.W = digit_bits_for(C.SM, C.TL);
+    RoundCtx C = round_ctx(J, w);
     u32 h[C_NCTR];
     u64 round_elems = J.n_first;
     bool first = true;
@@ -1724,7 +1775,7 @@ int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles)
                 // offsets and payload of every string; the bytes compared are not known
                 SS_PROF("k_resolve", J.stream, (double)h[C_NELEM] * 20.0);
                 k_resolve<<<grid_of(h[C_NEXT], 32, 1u << 30), 256, 0, J.stream>>>(w.nxt, h[C_NEXT], J.bytes, J.N, J.off,
-                                                                                  J.vals, J.lcp, w.act, w.ctr);
+                                                                                  J.vals, J.lcp, w.act, w.ctr, C.ET);
             }
             SS_CHECK_LAUNCH();
             SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
@@ -1758,8 +1809,7 @@ __global__ void k_copy_segs(const Seg *src, const u32 *cnt, Seg *dst)
 static int sort_rounds_device(const SortJob &J, SortWs &w, u32 rounds, u32 *status)
 {
     Seg *const act0 = w.act;
-    RoundCtx C{J, w, J.n_total, (u32)g_small_max, (u32)g_tile, 8};
-    C.W = digit_bits_for(C.SM, C.TL);
+    RoundCtx C = round_ctx(J, w);
     const u32 levels = C.W == 11 ? Digits<11>::LEVELS : Digits<8>::LEVELS;
     const Known unknown{false, 0};
     for (u32 r = 0; r < rounds; r++) {
@@ -1796,13 +1846,13 @@ __global__ void k_zero_u32(u32 *p, u32 count)
 }
 
 // The whole array as the first round's one segment (n >= 2), with its counts.
-__global__ void k_init_single(Seg *act, u32 n, u32 *lcp, u32 *ctr)
+__global__ void k_init_single(Seg *act, u32 n, u32 *lcp, u32 *ctr, u32 et)
 {
     act[0] = Seg{0, n, 0, SEG_SKIP};
     lcp[0] = 0;
     for (u32 j = 0; j < C_NCTR; j++) ctr[j] = 0;
     ctr[C_NEXT] = 1;
-    ctr[C_NTILES] = (n + ETILE - 1) / ETILE;
+    ctr[C_NTILES] = (n + et - 1) / et;
     ctr[C_NELEM] = n;
 }
 
@@ -1810,7 +1860,7 @@ __global__ void k_init_single(Seg *act, u32 n, u32 *lcp, u32 *ctr)
 // A set whose bounds are not well placed (set_off non-decreasing from 0 to n)
 // raises ctr[C_BADSET] and writes nothing, so a malformed set_off never leads
 // outside the arrays.
-__global__ void k_init_sets(const u64 *set_off, u32 nsets, u64 n, Seg *act, u32 *ctr, u32 *lcp)
+__global__ void k_init_sets(const u64 *set_off, u32 nsets, u64 n, Seg *act, u32 *ctr, u32 *lcp, u32 et)
 {
     u32 j = blockIdx.x * blockDim.x + threadIdx.x;
     bool valid = j < nsets;
@@ -1829,7 +1879,7 @@ __global__ void k_init_sets(const u64 *set_off, u32 nsets, u64 n, Seg *act, u32 
     bool two = valid && e > b + 1;
     u32 a = wave_append(two, &ctr[C_NEXT]);
     if (two) act[a] = Seg{b, e, 0, SEG_SKIP};
-    wave_add(two ? (e - b + ETILE - 1) / ETILE : 0u, &ctr[C_NTILES]);
+    wave_add(two ? (e - b + et - 1) / et : 0u, &ctr[C_NTILES]);
     wave_add(two ? e - b : 0u, &ctr[C_NELEM]);
 }
 
@@ -1950,9 +2000,9 @@ static int sort_single(const uint8_t *bytes, uint64_t N, const uint64_t *offsets
     if (seed) attach_seed(J, seed, n);
     k_iota<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(perm, (u32)n);
     SS_CHECK_LAUNCH();
-    k_init_single<<<1, 1, 0, st>>>(w.act, (u32)n, J.lcp, w.ctr);
+    k_init_single<<<1, 1, 0, st>>>(w.act, (u32)n, J.lcp, w.ctr, elem_tile(n));
     SS_CHECK_LAUNCH();
-    return sort_rounds(J, w, 1, (u32)ceil_div(n, ETILE));
+    return sort_rounds(J, w, 1, (u32)ceil_div(n, elem_tile(n)));
 }
 
 extern "C" int ss_sort(const uint8_t *bytes, uint64_t N, const uint64_t *offsets, uint64_t n,
@@ -2001,7 +2051,8 @@ static int batch_setup(const uint8_t *bytes, uint64_t N, const uint64_t *offsets
     SS_CHECK_LAUNCH();
     k_zero_u32<<<1, 64, 0, st>>>(w.ctr, C_NCTR);
     SS_CHECK_LAUNCH();
-    k_init_sets<<<(unsigned)ceil_div(num_sets, 256), 256, 0, st>>>(set_off, num_sets, n, w.act, w.ctr, J.lcp);
+    k_init_sets<<<(unsigned)ceil_div(num_sets, 256), 256, 0, st>>>(set_off, num_sets, n, w.act, w.ctr, J.lcp,
+                                                                     elem_tile(n));
     SS_CHECK_LAUNCH();
     return SS_OK;
 }

@@ -16,13 +16,13 @@ struct SortWs {
     u64 *keyA, *keyB, *mword;  // mword, mpr: each member's first mismatch with its segment's first string
     uint2 *mpr;
     u32 *valB, *lcp_scratch;
-    Seg *act, *nxt, *tiny, *small, *ident, *largeA, *largeB;
+    Seg *act, *nxt, *tiny, *small, *mid, *ident, *largeA, *largeB;
     uint2 *bnd;
     u32 *skipv;
     u64 *smin, *smax;
     u8 *scat;
     u8 *kinds;  // per radix segment and digit: what the bucket became
-    u32 *tstart, *spref, *hist;
+    u32 *tstart, *hist;
     u64 *scan_scratch;
     u32 *dscan;  // scratch of the device-length scans
     u32 *ctr;
