@@ -35,25 +35,12 @@
 #define ETILE 2048  // elements per workgroup in element-wise round kernels (fewer in small sorts)
 #define RX_PF 8     // 256-element chunks a radix pass loads ahead
 
-// counters: list lengths, and the tile / element totals of the lists being
-// built (so that grids are known without reading the lists back)
-enum {
-    C_SMALL = 0, C_LARGE = 1, C_NEXT = 2, C_IDENT = 3, C_BND = 4,
-    C_LTILES = 5, C_SMALLN = 6, C_NTILES = 7, C_ITILES = 8, C_LELEM = 9, C_NELEM = 12, C_TINY = 13,
-    C_TINYN = 14, C_BADSET = 15, C_MID = 16, C_NCTR = 17
-};
 // Headers that the round and level kernels read their list lengths from
 // (copied from the counters by k_round_begin / k_level_begin, so that the
 // counters can be reset for the lists being built): hdr[H_ACT] active
 // segments, hdr[H_LARGE] radix segments of the current level, hdr[H_HIST]
 // their histogram length (256 per tile).
 enum { H_ACT = 0, H_LARGE = 1, H_HIST = 2, H_REMAIN = 3, H_NHDR = 4 };
-#define WS_MAX 128   // segments of up to this many strings: one wavefront each, in registers
-#define BS_IPT 8     // elements per thread in the block sort
-#define BS_SMALL 512  // ... segments of up to this many: one wavefront each
-#define BS_MID 2048   // ... and up to this many: four wavefronts
-// ctr[10..11]: 64-bit sum of size * skip over the routed segments
-
 // ------------------------------------------------------------ wave helpers
 
 // Wave-aggregated atomic add of per-lane values.
@@ -62,23 +49,6 @@ __device__ __forceinline__ void wave_add(u32 v, u32 *counter)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     if (__lane_id() == 0 && v) atomicAdd(counter, v);
-}
-
-__device__ __forceinline__ u32 seg_of_tile(const u32 *tstart, u32 nseg, u32 t)
-{
-    // largest s with tstart[s] <= t (tstart has nseg+1 entries, strictly
-    // increasing).  Every segment has a tile, so s <= t, and all but
-    // extra = tstart[nseg] - nseg segments have one, so s >= t - extra: with
-    // many small segments (one tile each) the search is short.
-    const u32 extra = tstart[nseg] - nseg;
-    u32 lo = t > extra ? t - extra : 0u;
-    u32 hi = (t < nseg - 1 ? t : nseg - 1) + 1;
-    while (hi - lo > 1) {
-        u32 mid = (lo + hi) >> 1;
-        if (tstart[mid] <= t) lo = mid;
-        else hi = mid;
-    }
-    return lo;
 }
 
 template <class T, int NTB = NT>
@@ -1313,8 +1283,9 @@ __device__ __forceinline__ bool shfl_down_b(bool b, u32 lane, bool from_next)
 // pairs each key separates; runs still tied then become next-round segments,
 // collected per workgroup and published with one atomic per counter.  (Equal
 // strings, common in text, so end inside the wavefront instead of costing a
-// workgroup per run in the next round's skip and key passes.)
-template <bool LOOP>
+// workgroup per run in the next round's skip and key passes.)  Without DEEP
+// (keys that are no string bytes) ties are published at once.
+template <bool LOOP, bool DEEP = true>
 __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *ntinyp, u64 *keys, u32 *vals,
                                                    const u64 *keyB, const u32 *valB, u32 *lcp, Seg *next, u32 *ctr,
                                                    const u8 *bytes, u64 N, const u64 *off, u32 et)
@@ -1393,7 +1364,7 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
         bool t1 = e1 < cnt && pa1 == k1 && (k1 & 0xFF) == 8;
         u32 dep = g.depth;
         if (__ballot(t0 || t1)) {  // (uniform: most segments have no run of equal keys)
-        for (u32 it = 0; it < WS_DEEP; it++) {
+        for (u32 it = 0; it < (DEEP ? WS_DEEP : 0); it++) {
             // in a run: tied with the predecessor or the successor (e0's successor
             // is e0 + 1, lane 63's is e1 of lane 0); every lane shuffles first
             const bool f1 = __shfl((int)t1, 0, 64) != 0;
@@ -1565,12 +1536,11 @@ static u32 elem_tile(u64 n)
 
 static u32 digit_bits_for(u32 SM, u32 TL) { return (g_digit_bits == 11 && TL >= 4096 && SM >= 512) ? 11u : 8u; }
 
-// (the cutover's tiles hold two such segments' strings, one in the block sort)
 static RoundCtx round_ctx(const SortJob &J, SortWs &w)
 {
     const u32 sm = (u32)g_small_max, tl = (u32)g_tile;
-    return RoundCtx{J, w, J.n_total, sm, tl, digit_bits_for(sm, tl), elem_tile(J.n_total),
-                    2 * sm < BS_MID ? 2 * sm : (u32)BS_MID};
+    const SortShape z = sort_shape(J.n_total);
+    return RoundCtx{J, w, J.n_total, sm, tl, digit_bits_for(sm, tl), z.et, z.block_max};
 }
 
 static int scan_u32(RoundCtx &C, u32 *arr, const u32 *n_dev, Known k)
@@ -1682,7 +1652,7 @@ static int radix_level(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltiles
 
 // The part of a round after the radix levels: small sorts, boundary LCPs,
 // equal strings.  h (when known) holds the counters after the last level.
-static int round_tail(RoundCtx &C, const u32 *h)
+static int round_tail(RoundCtx &C, const u32 *h, bool keyed = false)
 {
     SortWs &w = C.w;
     const SortJob &J = C.J;
@@ -1692,7 +1662,10 @@ static int round_tail(RoundCtx &C, const u32 *h)
     const bool known = h != nullptr;
     if (!known || h[C_TINY] > 0) {
         SS_PROF("k_wave_sort", st, known ? (double)h[C_TINYN] * 28.0 : 0.0);  // key+payload in/out, LCP out
-        if (known)
+        if (known && keyed)
+            k_wave_sort<false, false><<<grid_of(h[C_TINY], WS_SPB, 1u << 30), 256, 0, st>>>(
+                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, C.ET);
+        else if (known)
             k_wave_sort<false><<<grid_of(h[C_TINY], WS_SPB, 1u << 30), 256, 0, st>>>(
                 w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, C.ET);
         else
@@ -1737,6 +1710,19 @@ static int round_tail(RoundCtx &C, const u32 *h)
     return SS_OK;
 }
 
+// The radix levels of a round, from the counters after its routing (h), which
+// are read back after every level.
+static int radix_levels(RoundCtx &C, u32 *h)
+{
+    Seg *LA = C.w.largeA, *LB = C.w.largeB;
+    while (h[C_LARGE] > 0) {
+        SS_TRY(radix_level(C, LA, LB, Known{true, h[C_LARGE]}, Known{true, h[C_LTILES]}, h[C_LELEM]));
+        SS_TRY(ss_read_u32(C.w.ctr, h, C_NCTR, C.J.stream));
+        Seg *tmp = LA; LA = LB; LB = tmp;
+    }
+    return SS_OK;
+}
+
 // Host-driven rounds: the host reads the counters once after the routing,
 // once per radix level and once at the end of a round, sizes every grid from
 // them and stops when no segment is unresolved.  The caller has put the first
@@ -1754,16 +1740,7 @@ int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles)
         // (a seeded first round's common prefix was read by the pass that made the seed)
         if (!(first && J.seed_pos)) ss_prof_add_bytes("k_skip", (double)(h[10] | ((u64)h[11] << 32)));
         first = false;
-        u32 nlarge = h[C_LARGE], ltiles = h[C_LTILES], lelem = h[C_LELEM];
-        Seg *LA = w.largeA, *LB = w.largeB;
-        while (nlarge > 0) {
-            SS_TRY(radix_level(C, LA, LB, Known{true, nlarge}, Known{true, ltiles}, lelem));
-            SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
-            nlarge = h[C_LARGE];
-            ltiles = h[C_LTILES];
-            lelem = h[C_LELEM];
-            Seg *tmp = LA; LA = LB; LB = tmp;
-        }
+        SS_TRY(radix_levels(C, h));
         SS_TRY(round_tail(C, h));
         SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
         if (h[C_NEXT] > 0) {
@@ -1785,6 +1762,22 @@ int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles)
         round_elems = h[C_NELEM];
     }
     return SS_OK;
+}
+
+SortShape sort_shape(u64 n)
+{
+    const u32 bm = 2 * (u32)g_small_max;
+    return SortShape{elem_tile(n), (u32)g_tile, bm < BS_MID ? bm : (u32)BS_MID};
+}
+
+int sort_keyed(const SortJob &J, SortWs &w, u32 *h)
+{
+    RoundCtx C = round_ctx(J, w);
+    SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
+    if (!(h[C_TINY] | h[C_SMALL] | h[C_MID] | h[C_LARGE])) return SS_OK;
+    SS_TRY(radix_levels(C, h));
+    SS_TRY(round_tail(C, h, true));
+    return ss_read_u32(w.ctr, h, C_NCTR, J.stream);
 }
 
 // Device-driven rounds: `rounds` rounds of as many levels as a key has digits

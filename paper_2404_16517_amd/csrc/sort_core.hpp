@@ -12,6 +12,37 @@ struct Seg {
 };
 enum { SEG_SKIP = 16, SEG_INB = 32 };
 
+// counters: list lengths, and the tile / element totals of the lists being
+// built (so that grids are known without reading the lists back)
+enum {
+    C_SMALL = 0, C_LARGE = 1, C_NEXT = 2, C_IDENT = 3, C_BND = 4,
+    C_LTILES = 5, C_SMALLN = 6, C_NTILES = 7, C_ITILES = 8, C_LELEM = 9, C_NELEM = 12, C_TINY = 13,
+    C_TINYN = 14, C_BADSET = 15, C_MID = 16, C_NCTR = 17
+};
+// ctr[10..11]: 64-bit sum of size * skip over the routed segments
+
+#define WS_MAX 128   // segments of up to this many strings: one wavefront each, in registers
+#define BS_IPT 8     // elements per thread in the block sort
+#define BS_SMALL 512  // ... segments of up to this many: one wavefront each
+#define BS_MID 2048   // ... and up to this many: four wavefronts
+
+__device__ __forceinline__ u32 seg_of_tile(const u32 *tstart, u32 nseg, u32 t)
+{
+    // largest s with tstart[s] <= t (tstart has nseg+1 entries, strictly
+    // increasing).  Every segment has a tile, so s <= t, and all but
+    // extra = tstart[nseg] - nseg segments have one, so s >= t - extra: with
+    // many small segments (one tile each) the search is short.
+    const u32 extra = tstart[nseg] - nseg;
+    u32 lo = t > extra ? t - extra : 0u;
+    u32 hi = (t < nseg - 1 ? t : nseg - 1) + 1;
+    while (hi - lo > 1) {
+        u32 mid = (lo + hi) >> 1;
+        if (tstart[mid] <= t) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
 struct SortWs {
     u64 *keyA, *keyB, *mword;  // mword, mpr: each member's first mismatch with its segment's first string
     uint2 *mpr;
@@ -49,3 +80,15 @@ void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c);
 // Host-driven rounds from nact segments in w.act covering `atiles` element
 // tiles of 2048 (their count, tiles and strings also in the counters).
 int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles);
+// Elements per workgroup of the element-wise kernels, tile of the radix passes
+// and the size up to which segments are sorted in LDS, for a sort of n strings.
+struct SortShape {
+    u32 et, tile, block_max;
+};
+SortShape sort_shape(u64 n);
+// The sorts of one round over segments whose 64-bit keys (in w.keyA) the caller
+// computed and which it put into w.tiny, w.small, w.mid and w.largeA (counts
+// and totals in the counters): each is sorted by (key, payload order).  Runs of
+// equal keys whose low byte is 8 are appended to w.nxt.  h receives the
+// counters afterwards; J.lcp is written with values of no meaning.
+int sort_keyed(const SortJob &J, SortWs &w, u32 *h);
