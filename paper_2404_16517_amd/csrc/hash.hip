@@ -1486,6 +1486,148 @@ __global__ __launch_bounds__(256) void k_dedup(const u64 *keys, int kin, const u
     }
 }
 
+// --------------------------------------------------- few strings, one launch
+
+#define PS_MAX 2048   // strings of a one-launch prefix doubling
+#define PS_NT 1024
+#define PS_LOG 12     // log2 of its key table's slots (twice the strings)
+#define PS_LIMBS 32   // a round of up to this many limbs: one thread per string
+
+// All rounds of prefix doubling over up to PS_MAX strings by one workgroup,
+// nothing read back in between: the Horner value of every string in LDS,
+// continued limb by limb each round (the same key as the matrix form's: H B +
+// m), the keys' multiplicities in an LDS table whose slots hold a key and a
+// mark for a second one.  A round of few limbs has one thread per string; a
+// longer one (the few strings left by then) one wavefront per string, the
+// lanes on consecutive stretches of limbs, front-padded with zero limbs and
+// combined by a tree of products with B^(stretch 2^k).
+//
+// Latency bounds it: 2 to 4 us a round.  1,000 text strings took 65 launches and
+// 9 read-backs in the general form; now one launch of 30 us (with the sort's
+// short path the served job on them went from 568 to 130 us).
+__global__ __launch_bounds__(PS_NT) void k_pd_small(u32 n, const u8 *bytes, u64 N, const u64 *off, u32 init_len,
+                                                    u32 bits, u32 *dist, u32 *rounds_out)
+{
+    __shared__ u64 tab[1u << PS_LOG], H[PS_MAX], key[PS_MAX];
+    __shared__ u16 list[2][PS_MAX];
+    __shared__ u32 s_cnt[2];
+    const u32 t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    for (u32 j = t; j < n; j += PS_NT) {
+        H[j] = 0;
+        list[0][j] = (u16)j;
+    }
+    if (t < 2) s_cnt[t] = t == 0 ? n : 0u;
+    __syncthreads();
+    u64 lprev = 0, l = init_len;
+    u32 rounds = 0, cur = 0;
+    for (;;) {  // rounds (uniform over the workgroup)
+        const u32 A = s_cnt[cur];
+        if (A == 0) break;
+        rounds++;
+        const u16 *act = list[cur];
+        for (u32 x = t; x < (1u << PS_LOG); x += PS_NT) tab[x] = TAB_EMPTY;
+        // keys of the active strings' l-prefixes: limbs [lprev / 4, ceil(min(l, len) / 4))
+        if ((l - lprev) / 4 <= PS_LIMBS) {
+            for (u32 j = t; j < A; j += PS_NT) {
+                const u32 i = act[j];
+                const u64 o = off[i], len = off[i + 1] - o;
+                const u64 m = len < l ? len : l;
+                u64 h = H[i];
+                for (u64 x = lprev; x < m; x += 8) {  // two limbs a load
+                    const u32 take = m - x < 8 ? (u32)(m - x) : 8u;
+                    const u64 v = load_le(bytes, N, o + x, take);
+                    h = addmod61(mulmod61(h, KR_B), v & 0xFFFFFFFFull);
+                    if (take > 4) h = addmod61(mulmod61(h, KR_B), v >> 32);
+                }
+                H[i] = h;
+                const u64 k = addmod61(mulmod61(h, KR_B), m);
+                key[i] = bits >= 64 ? k : (k & ((1ull << bits) - 1));
+            }
+        } else {
+            for (u32 j = wv; j < A; j += PS_NT / 64) {  // (uniform over the wavefront)
+                const u32 i = act[j];
+                const u64 o = off[i], len = off[i + 1] - o;
+                const u64 m = len < l ? len : l;
+                const u64 limbs = m > lprev ? (m - lprev + 3) / 4 : 0ull;
+                const u64 c = (limbs + 63) / 64;            // limbs of a lane's stretch
+                const long long f = (long long)limbs - 64ll * (long long)c + (long long)(c * lane);  // its first (< 0: padding)
+                u64 h = 0;
+                for (u64 q = 0; q < c; q++) {
+                    const long long p = f + (long long)q;
+                    if (p < 0) continue;
+                    const u64 x = lprev + 4ull * (u64)p;
+                    const u32 take = m - x < 4 ? (u32)(m - x) : 4u;
+                    h = addmod61(mulmod61(h, KR_B), load_le(bytes, N, o + x, take));
+                }
+                u64 bc = 1;  // B^c
+                for (u64 e = c, b = KR_B; e; e >>= 1, b = mulmod61(b, b))
+                    if (e & 1) bc = mulmod61(bc, b);
+                u64 bl = 1;  // B^limbs, for the value so far
+                for (u64 e = limbs, b = KR_B; e; e >>= 1, b = mulmod61(b, b))
+                    if (e & 1) bl = mulmod61(bl, b);
+                for (u32 d = 1; d < 64; d <<= 1) {  // lanes [x, x + 2d) combine their halves
+                    const u64 right = __shfl_down(h, d, 64);
+                    if ((lane & (2 * d - 1)) == 0) {
+                        h = mulmod61(h, bc) + right;
+                        h = h >= KR_P ? h - KR_P : h;
+                    }
+                    bc = mulmod61(bc, bc);
+                }
+                if (lane == 0) {
+                    h = mulmod61(H[i], bl) + h;
+                    h = h >= KR_P ? h - KR_P : h;
+                    H[i] = h;
+                    const u64 k = addmod61(mulmod61(h, KR_B), m);
+                    key[i] = bits >= 64 ? k : (k & ((1ull << bits) - 1));
+                }
+            }
+        }
+        __syncthreads();
+        // multiplicities
+        for (u32 j = t; j < A; j += PS_NT) {
+            const u64 k = key[act[j]];
+            for (u32 s = (u32)tab_slot(k, PS_LOG);; s = (s + 1) & ((1u << PS_LOG) - 1)) {  // (half the slots stay empty)
+                u64 v = tab[s];
+                if (v == TAB_EMPTY) {
+                    v = atomicCAS((unsigned long long *)&tab[s], TAB_EMPTY, k);
+                    if (v == TAB_EMPTY) break;
+                }
+                if ((v & ~TAB_DUP) == k) {
+                    if (!(v & TAB_DUP)) atomicOr((unsigned long long *)&tab[s], TAB_DUP);
+                    break;
+                }
+            }
+        }
+        if (t == 0) s_cnt[cur ^ 1] = 0;
+        __syncthreads();
+        // unique or ended strings finish, the others stay
+        for (u32 j0 = 0; j0 < A; j0 += PS_NT) {
+            const u32 j = j0 + t;
+            bool stay = false;
+            u32 i = 0;
+            if (j < A) {
+                i = act[j];
+                const u64 k = key[i];
+                u32 s = (u32)tab_slot(k, PS_LOG);
+                while ((tab[s] & ~TAB_DUP) != k) s = (s + 1) & ((1u << PS_LOG) - 1);  // (every key is there)
+                const u64 len = off[i + 1] - off[i];
+                stay = (tab[s] & TAB_DUP) && len > l;
+                if (!stay) dist[i] = (u32)(len < l ? len : l);
+            }
+            const u64 b = __ballot(stay);
+            u32 base = 0;
+            if (b && lane == 0) base = atomicAdd(&s_cnt[cur ^ 1], (u32)__popcll(b));
+            base = __shfl(base, 0, 64);
+            if (stay) list[cur ^ 1][base + (u32)__popcll(b & lanemask_lt())] = (u16)i;
+        }
+        __syncthreads();
+        cur ^= 1;
+        lprev = l;
+        l *= 2;
+    }
+    if (t == 0) *rounds_out = rounds;
+}
+
 // hdr: words 0..7 hold the u32 counters, 8..28 the flags of the precomputed
 // rounds (three per round), 29 the first pass's deep decision, 30..35 the
 // flags of a hash launch (rounds l and 2l); the host reads them back together.
@@ -1804,6 +1946,20 @@ static int pd_run(const uint8_t *bytes, uint64_t N, const uint64_t *offsets, uin
     if (a.overflow || !ws) {
         ss_set_error("workspace too small: need %zu bytes", ss_dist_prefix_workspace(n));
         return SS_ERR_WORKSPACE;
+    }
+    // Few strings whose first pass nobody else continues: one launch (unless a
+    // form of the duplicate detection is asked for).  Above 2,048 strings the
+    // one workgroup's LDS is full.
+    if (parts == (PD_FIRST | PD_ROUNDS) && n <= PS_MAX && g_dedup_mode == 0) {
+        {
+            SS_PROF("k_pd_small", st, (double)n * 12.0);  // offsets in, dist out; not the bytes hashed
+            k_pd_small<<<1, PS_NT, 0, st>>>((u32)n, bytes, N, offsets, init_len, hash_bits, dist_approx, w.ctr);
+        }
+        SS_CHECK_LAUNCH();
+        u32 rounds = 0;
+        SS_TRY(ss_read_u32(w.ctr, &rounds, 1, st));
+        if (rounds_host) *rounds_host = rounds;
+        return SS_OK;
     }
     BPow bp;
     bp.p[0] = 1;

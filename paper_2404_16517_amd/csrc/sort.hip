@@ -107,19 +107,13 @@ __global__ void k_tile_counts(const Seg *segs, const u32 *nsegp, u32 tile, u32 *
     GSTRIDE(j, nseg) out[j] = (segs[j].end - segs[j].begin + tile - 1) / tile;
 }
 
-// Start of a round: the active list's length goes to the header, the
-// counters of the lists the round builds are reset.
-__global__ void k_round_begin(u32 *ctr, u32 *hdr)
+// Start of a round: the active list's length (counter `from`) goes to the
+// header, the counters of the lists the round builds are reset.
+__global__ void k_round_begin(u32 *ctr, u32 *hdr, u32 from)
 {
-    if (threadIdx.x == 0) hdr[H_ACT] = ctr[C_NEXT];
+    if (threadIdx.x == 0) hdr[H_ACT] = ctr[from];
     __syncthreads();
     if (threadIdx.x < C_NCTR && threadIdx.x != C_BADSET) ctr[threadIdx.x] = 0;
-}
-
-// The next round's counters, before its list is made anew.
-__global__ void k_next_reset(u32 *ctr)
-{
-    if (threadIdx.x == 0) ctr[C_NEXT] = ctr[C_NTILES] = ctr[C_NELEM] = 0;
 }
 
 // Tile counts of the active segments for a round; also resets the segments'
@@ -541,13 +535,15 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
 // Bounded by the latency of scattered reads: two lines per string.  A round's
 // skip, keys, routing and sort took 1.1 ms for 446K such runs (4M text
 // strings); this takes 190 us, and the whole sort 2.6 -> 1.9 ms.
-__global__ __launch_bounds__(256) void k_resolve(const Seg *in, u32 nin, const u8 *bytes, u64 N, const u64 *off,
+__global__ __launch_bounds__(256) void k_resolve(const Seg *in, const u8 *bytes, u64 N, const u64 *off,
                                                  u32 *vals, u32 *lcp, Seg *out, u32 *ctr, u32 et)
 {
     __shared__ u32 s_cnt, s_tiles, s_elems, s_base;
+    const u32 nin = ctr[C_NEXT];
+    for (u32 s0 = blockIdx.x * 32; s0 < nin; s0 += gridDim.x * 32) {  // (uniform over the workgroup)
     if (threadIdx.x == 0) s_cnt = s_tiles = s_elems = 0;
     __syncthreads();
-    const u32 s = blockIdx.x * 32 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
+    const u32 s = s0 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
     bool keep = false;
     Seg g = {0, 0, 0, 0};
     if (s < nin) {
@@ -632,12 +628,14 @@ __global__ __launch_bounds__(256) void k_resolve(const Seg *in, u32 nin, const u
     }
     __syncthreads();
     if (threadIdx.x == 0 && s_cnt) {
-        s_base = atomicAdd(&ctr[C_NEXT], s_cnt);
-        atomicAdd(&ctr[C_NTILES], s_tiles);
-        atomicAdd(&ctr[C_NELEM], s_elems);
+        s_base = atomicAdd(&ctr[C_RNEXT], s_cnt);
+        atomicAdd(&ctr[C_RTILES], s_tiles);
+        atomicAdd(&ctr[C_RELEM], s_elems);
     }
     __syncthreads();
     if (keep && gl == 0) out[s_base + slot] = g;
+    __syncthreads();  // the counts are reset for the next runs
+    }
 }
 
 // ------------------------------------------------------------ radix passes
@@ -1549,20 +1547,25 @@ static int scan_u32(RoundCtx &C, u32 *arr, const u32 *n_dev, Known k)
     return ss_scan_exclusive_dev<u32>(arr, arr, n_dev, 1, C.w.dscan, C.J.stream);
 }
 
-// The part of a round before the radix levels: skip, keys, routing.
-static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bool first = false)
+// The part of a round before the radix levels: skip, keys, routing.  The round's
+// segments are w.act, their number in counter `from` (or, `begun`, the header,
+// tiles and skip minima are set already).
+static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bool first = false, u32 from = C_NEXT,
+                      bool begun = false)
 {
     SortWs &w = C.w;
     const SortJob &J = C.J;
     hipStream_t st = J.stream;
     const u64 n = C.n;
-    k_round_begin<<<1, 64, 0, st>>>(w.ctr, w.hdr);
-    SS_CHECK_LAUNCH();
     const u32 *nactp = w.hdr + H_ACT;
-    k_round_tiles<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, C.ET, w.tstart,
-                                                                               w.skipv);
-    SS_CHECK_LAUNCH();
-    SS_TRY(scan_u32(C, w.tstart, nactp, nact));
+    if (!begun) {
+        k_round_begin<<<1, 64, 0, st>>>(w.ctr, w.hdr, from);
+        SS_CHECK_LAUNCH();
+        k_round_tiles<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, C.ET, w.tstart,
+                                                                                   w.skipv);
+        SS_CHECK_LAUNCH();
+        SS_TRY(scan_u32(C, w.tstart, nactp, nact));
+    }
     const unsigned tg = atiles.yes ? grid_of(atiles.v, 1, 1u << 30) : 0u;  // (one tile per workgroup)
     {
         // algorithmic bytes: perm + offsets + one word per string, its mismatch
@@ -1728,38 +1731,42 @@ static int radix_levels(RoundCtx &C, u32 *h)
 // them and stops when no segment is unresolved.  The caller has put the first
 // round's segments in w.act and their count, tiles and strings in
 // ctr[C_NEXT], ctr[C_NTILES], ctr[C_NELEM].
-int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles)
+// `whole`: one segment of at most C.BM strings, set up by k_init_whole; the sort
+// it is routed to is known without a read-back.
+int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles, bool whole)
 {
     RoundCtx C = round_ctx(J, w);
     u32 h[C_NCTR];
     u64 round_elems = J.n_first;
     bool first = true;
     while (nact > 0) {
-        SS_TRY(round_head(C, Known{true, nact}, Known{true, atiles}, round_elems, first));
-        SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
-        // (a seeded first round's common prefix was read by the pass that made the seed)
-        if (!(first && J.seed_pos)) ss_prof_add_bytes("k_skip", (double)(h[10] | ((u64)h[11] << 32)));
+        SS_TRY(round_head(C, Known{true, nact}, Known{true, atiles}, round_elems, first, first ? C_NEXT : C_RNEXT,
+                          first && whole));
+        if (first && whole) {
+            memset(h, 0, sizeof(h));
+            h[J.n_total <= WS_MAX ? C_TINY : (J.n_total <= BS_SMALL ? C_SMALL : C_MID)] = 1;
+            h[J.n_total <= WS_MAX ? C_TINYN : C_SMALLN] = (u32)J.n_total;
+        } else {
+            SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
+            // (a seeded first round's common prefix was read by the pass that made the seed)
+            if (!(first && J.seed_pos)) ss_prof_add_bytes("k_skip", (double)(h[10] | ((u64)h[11] << 32)));
+            SS_TRY(radix_levels(C, h));
+        }
         first = false;
-        SS_TRY(radix_levels(C, h));
         SS_TRY(round_tail(C, h));
-        SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
-        if (h[C_NEXT] > 0) {
+        {
             // the tied runs compared directly; what is left goes back to the
             // first list (its segments are all done) as the next round's
-            k_next_reset<<<1, 64, 0, J.stream>>>(w.ctr);
-            SS_CHECK_LAUNCH();
-            {
-                // offsets and payload of every string; the bytes compared are not known
-                SS_PROF("k_resolve", J.stream, (double)h[C_NELEM] * 20.0);
-                k_resolve<<<grid_of(h[C_NEXT], 32, 1u << 30), 256, 0, J.stream>>>(w.nxt, h[C_NEXT], J.bytes, J.N, J.off,
-                                                                                  J.vals, J.lcp, w.act, w.ctr, C.ET);
-            }
-            SS_CHECK_LAUNCH();
-            SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
+            SS_PROF("k_resolve", J.stream, 0.0);  // (the number of runs is not known)
+            k_resolve<<<grid_of(J.n_total / 2, 32, 2048), 256, 0, J.stream>>>(w.nxt, J.bytes, J.N, J.off, J.vals, J.lcp,
+                                                                              w.act, w.ctr, C.ET);
         }
-        nact = h[C_NEXT];
-        atiles = h[C_NTILES];
-        round_elems = h[C_NELEM];
+        SS_CHECK_LAUNCH();
+        SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
+        ss_prof_add_bytes("k_resolve", (double)h[C_NELEM] * 20.0);  // offsets, payload; not the bytes compared
+        nact = h[C_RNEXT];
+        atiles = h[C_RTILES];
+        round_elems = h[C_RELEM];
     }
     return SS_OK;
 }
@@ -1847,6 +1854,23 @@ __global__ void k_init_single(Seg *act, u32 n, u32 *lcp, u32 *ctr, u32 et)
     ctr[C_NEXT] = 1;
     ctr[C_NTILES] = (n + et - 1) / et;
     ctr[C_NELEM] = n;
+}
+
+// The same with the payload (input indices) and the first round begun: its
+// header, its tiles and the segment's skip minimum.
+__global__ void k_init_whole(SortWs w, u32 n, u32 *vals, u32 *lcp, u32 et)
+{
+    const u32 i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) vals[i] = i;
+    if (i < C_NCTR) w.ctr[i] = 0;
+    if (i == 0) {
+        w.act[0] = Seg{0, n, 0, SEG_SKIP};
+        w.hdr[H_ACT] = 1;
+        w.tstart[0] = 0;
+        w.tstart[1] = (n + et - 1) / et;
+        w.skipv[0] = 0xFFFFFFFFu;
+        lcp[0] = 0;
+    }
 }
 
 // One segment per set of two or more strings (the counters are zero before).
@@ -1991,6 +2015,15 @@ static int sort_single(const uint8_t *bytes, uint64_t N, const uint64_t *offsets
     }
     SortJob J{bytes, N, offsets, perm, lcp ? lcp : w.lcp_scratch, st, n, n};
     if (seed) attach_seed(J, seed, n);
+    // Few enough for one segment sort: the first round begins in the launch
+    // that writes the indices, and its one routing is known (1,000 text
+    // strings: 8 launches and one read-back instead of 22 and four).
+    const SortShape z = sort_shape(n);
+    if (n <= z.block_max) {
+        k_init_whole<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(w, (u32)n, perm, J.lcp, z.et);
+        SS_CHECK_LAUNCH();
+        return sort_rounds(J, w, 1, (u32)ceil_div(n, z.et), true);
+    }
     k_iota<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(perm, (u32)n);
     SS_CHECK_LAUNCH();
     k_init_single<<<1, 1, 0, st>>>(w.act, (u32)n, J.lcp, w.ctr, elem_tile(n));

@@ -17,7 +17,9 @@ enum { SEG_SKIP = 16, SEG_INB = 32 };
 enum {
     C_SMALL = 0, C_LARGE = 1, C_NEXT = 2, C_IDENT = 3, C_BND = 4,
     C_LTILES = 5, C_SMALLN = 6, C_NTILES = 7, C_ITILES = 8, C_LELEM = 9, C_NELEM = 12, C_TINY = 13,
-    C_TINYN = 14, C_BADSET = 15, C_MID = 16, C_NCTR = 17
+    C_TINYN = 14, C_BADSET = 15, C_MID = 16,
+    C_RNEXT = 17, C_RTILES = 18, C_RELEM = 19,  // what k_resolve leaves of the C_NEXT segments
+    C_NCTR = 20
 };
 // ctr[10..11]: 64-bit sum of size * skip over the routed segments
 
@@ -79,7 +81,7 @@ struct SortJob {
 void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c);
 // Host-driven rounds from nact segments in w.act covering `atiles` element
 // tiles of 2048 (their count, tiles and strings also in the counters).
-int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles);
+int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles, bool whole = false);
 // Elements per workgroup of the element-wise kernels, tile of the radix passes
 // and the size up to which segments are sorted in LDS, for a sort of n strings.
 struct SortShape {
