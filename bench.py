@@ -873,7 +873,7 @@ def main():
         kp, ks = (wprof, 1) if wprof else (prof, args.steps)
         out["kernels_ms_per_step"] = {k: v[0] / ks for k, v in sorted(kp.items(), key=lambda x: -x[1][0])}
         # each kernel's own bytes (its reads and writes as implemented, e.g.
-        # 40 B per element per merge level), not the pass formulas
+        # 20 B per element of the merge tiles), not the pass formulas
         out["kernels_impl_gbs"] = {k: (v[1] / (v[0] / 1e3) / 1e9 if v[0] > 0 else None) for k, v in kp.items()}
         if pipe.overlap and not args.no_one_stream:
             # The same kernels with the step on one stream (a few extra steps

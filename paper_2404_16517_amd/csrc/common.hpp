@@ -209,7 +209,66 @@ __device__ __forceinline__ u64 raw8_le(const u8 *__restrict__ bytes, const Raw8 
     return v;
 }
 
-// The same bytes packed big-endian into the top of a 64-bit word (byte a ->
+// Bytes [a, a+take) (take <= 16) as two little-endian words, the rest zero;
+// reads only inside [bytes, bytes + N).  Split in two so that callers can
+// issue the loads of several windows before combining any: issue() loads the
+// three aligned words around the window when all of them lie inside the
+// buffer, finish() shifts them into place (or reads bytes one by one near the
+// buffer's ends).
+struct Win16 {
+    u64 w0, w1, w2;
+    u64 a;
+    u32 take, sh;
+    bool ok;
+};
+
+__device__ __forceinline__ Win16 win16_issue(const u8 *__restrict__ bytes, u64 N, u64 a, u32 take)
+{
+    Win16 r;
+    r.a = a;
+    r.take = take;
+    const u8 *pb = bytes + a;
+    r.sh = (u32)((uintptr_t)pb & 7);
+    const u8 *base = pb - r.sh;  // aligned; derived from bytes, so a global-memory pointer
+    r.ok = take > 0 && base >= bytes && base + 24 <= bytes + N;
+    r.w0 = r.w1 = r.w2 = 0;
+    if (r.ok) {
+        const u64 *w = (const u64 *)base;
+        r.w0 = w[0];
+        r.w1 = w[1];
+        r.w2 = w[2];
+    }
+    return r;
+}
+
+__device__ __forceinline__ void win16_finish(const u8 *__restrict__ bytes, const Win16 &r, u64 &lo, u64 &hi)
+{
+    lo = hi = 0;
+    if (r.take == 0) return;
+    if (r.ok) {
+        if (r.sh == 0) {
+            lo = r.w0;
+            hi = r.w1;
+        } else {
+            lo = (r.w0 >> (8 * r.sh)) | (r.w1 << (64 - 8 * r.sh));
+            hi = (r.w1 >> (8 * r.sh)) | (r.w2 << (64 - 8 * r.sh));
+        }
+    } else {
+        for (u32 t = 0; t < r.take; t++) {
+            const u64 v = (u64)bytes[r.a + t];
+            if (t < 8) lo |= v << (8 * t);
+            else hi |= v << (8 * (t - 8));
+        }
+    }
+    if (r.take < 8) {
+        lo &= (1ull << (8 * r.take)) - 1ull;
+        hi = 0;
+    } else if (r.take < 16) {
+        hi &= r.take == 8 ? 0ull : ((1ull << (8 * (r.take - 8))) - 1ull);
+    }
+}
+
+// load_le with the bytes packed big-endian into the top of the word (byte a ->
 // bits 63..56), the rest zero: integer order of such words is byte order.
 __device__ __forceinline__ u64 load_be(const u8 *__restrict__ bytes, u64 N, u64 a, u32 take)
 {

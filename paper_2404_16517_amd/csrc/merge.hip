@@ -11,12 +11,15 @@
 // its rightmost such block, then its rightmost such 16-element chunk).  Each output 16-byte word then walks
 // the chain of its string.
 //
-// Merge.  The paper merges r runs with an LCP loser tree.  Here the runs are
-// merged pairwise in log2 k levels; each level is split into fixed-size output
-// ranges by merge-path co-ranking, and every thread merges its range with the
-// LCP rule: with h_a = lcp(last, a) and h_b = lcp(last, b), the larger of h_a,
-// h_b decides without touching characters, and only on equality are the
-// strings compared from h on.
+// Merge.  The paper merges r runs with an LCP loser tree, one element after
+// the other.  Here every element caches its 7 bytes at its group's common
+// prefix (found by one scan over the runs) as a 64-bit key, and the runs of a
+// group are merged by key in one pass over memory: sampled keys cut the runs
+// into tiles of about a thousand outputs (a tile holds all elements with keys
+// in one interval, so equal keys never part), and each tile's windows are merged
+// in LDS.  Different keys give the LCP of neighbours too.  Only elements whose
+// whole keys tie -- equal strings, mostly -- are compared as strings: small
+// ties directly, the others by further keys and the segmented sort.
 #include <string.h>
 
 #include <algorithm>
@@ -24,7 +27,7 @@
 
 #include <mutex>
 
-#include "common.hpp"
+#include "sort_core.hpp"
 
 #define PSV_NONE 0xFFFFFFFFu
 
@@ -897,118 +900,6 @@ __device__ __forceinline__ int fc_cmp(const FcView &V, u32 x, u32 y, u64 from, u
     return lx < ly ? -1 : (lx > ly ? 1 : 0);
 }
 
-#define MG_PER 64  // outputs per thread
-#define F_FIRST 0xFFFFFFFFu
-
-struct MergeLevel {
-    const u32 *G, *L, *F;  // element ids (FC positions), LCP with predecessor, first-LCP bound
-    u32 *Go, *Lo, *Fo;
-    const u64 *K;          // cached key: 7 bytes at the group depth + remaining length (capped at 8)
-    u64 *Ko;
-    const u32 *pg;         // per pair: group
-    const u32 *Cg;         // per group: common prefix length of all its strings
-    const u64 *PA0, *PA1, *PB1;  // per pair: run A = [PA0, PA1), run B = [PA1, PB1) in output space
-    const u32 *tstart;           // first thread of each pair (npairs+1)
-    u32 *pc;                     // per pair: lcp of the two runs' first strings
-    u8 *pfirst;                  // per pair: 1 if run A's first string comes first
-    u32 npairs;
-    FcView V;
-};
-
-__device__ __forceinline__ u32 min3u(u32 a, u32 b, u32 c) { return min(a, min(b, c)); }
-
-// Compare two elements of one group by their cached keys at the group depth C
-// (bytes [C, C+7) and the remaining length, capped at 8).  Different keys
-// decide alone: they order the two strings and give their LCP, whatever else
-// is known about them.  Equal keys of strings that end inside the key are
-// equal strings.  Otherwise the strings agree on [0, C+7), and `tie` compares
-// them from there (or from a larger known common prefix): only then are the
-// elements' ids and bounds needed, which lets callers read them lazily.
-template <class Tie>
-__device__ __forceinline__ int cmp_key(u64 kx, u64 ky, u32 C, u64 *lcp, Tie tie)
-{
-    if (kx != ky) {
-        *lcp = key_lcp(kx, ky, C);
-        return kx < ky ? -1 : 1;
-    }
-    const u32 cnt = (u32)(kx & 0xFF);
-    if (cnt < 8) {
-        *lcp = C + cnt;
-        return 0;
-    }
-    return tie(lcp);
-}
-
-// The same for elements whose strings are known to agree on [0, bound).
-__device__ __forceinline__ int cmp_elem(const FcView &V, u32 gx, u64 kx, u32 gy, u64 ky, u32 bound, u32 C,
-                                        u64 *lcp)
-{
-    return cmp_key(kx, ky, C, lcp, [&](u64 *l) { return fc_cmp(V, gx, gy, bound > C + 7 ? bound : C + 7, l); });
-}
-
-#define MW_NT 256
-// 5 outputs per thread: the LDS windows (MW_TILE + 2 entries of 20 bytes,
-// 25.6 KB) and at most 85 VGPRs fit six workgroups per compute unit
-#define MW_IPT 5
-#define MW_TILE (MW_NT * MW_IPT)  // outputs per workgroup
-
-// co-rank in global memory: number of A elements among the first d outputs
-__device__ u32 corank_global(const MergeLevel &M, u64 A0, u32 na, u64 B0, u32 nb, u32 d, u32 c, u32 C)
-{
-    const u32 *GA = M.G + A0, *FA = M.F + A0, *GB = M.G + B0, *FB = M.F + B0;
-    const u64 *KA = M.K + A0, *KB = M.K + B0;
-    u32 xlo = d > nb ? d - nb : 0, xhi = d < na ? d : na;
-    u64 tmp;
-    while (xlo < xhi) {
-        const u32 mid = (xlo + xhi) >> 1;
-        const u32 y = d - mid - 1;
-        // keys first: the ids and bounds are read only when the keys tie
-        const int r = cmp_key(KA[mid], KB[y], C, &tmp, [&](u64 *l) {
-            const u32 bd = min3u(FA[mid], c, FB[y]);
-            return fc_cmp(M.V, GA[mid], GB[y], bd > C + 7 ? bd : C + 7, l);
-        });
-        if (r <= 0) xlo = mid + 1;
-        else xhi = mid;
-    }
-    return xlo;
-}
-
-// Per output tile of one merge level: the LCP and order of its pair's two
-// first strings (from the group depth on, with the cached keys; written by the
-// pair's first tile) and the co-rank of the tile's first output, so that the
-// merge kernel starts without a global search.
-__global__ void k_merge_split(MergeLevel M, u32 nblocks, u32 *split)
-{
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nblocks) return;
-    u32 lo = 0, hi = M.npairs;
-    while (hi - lo > 1) {
-        u32 mid = (lo + hi) >> 1;
-        if (M.tstart[mid] <= t) lo = mid;
-        else hi = mid;
-    }
-    const u32 p = lo;
-    const u64 A0 = M.PA0[p], A1 = M.PA1[p], B1 = M.PB1[p];
-    const u32 na = (u32)(A1 - A0), nb = (u32)(B1 - A1);
-    const u32 C = M.Cg[M.pg[p]];
-    u32 c = 0;
-    u8 fa = 1;
-    if (na > 0 && nb > 0) {
-        u64 l;
-        const int r = cmp_elem(M.V, M.G[A0], M.K[A0], M.G[A1], M.K[A1], C, C, &l);
-        c = (u32)l;
-        fa = r <= 0 ? 1 : 0;
-    } else if (na == 0) {
-        fa = 0;
-    }
-    if (t == M.tstart[p]) {
-        M.pc[p] = c;
-        M.pfirst[p] = fa;
-    }
-    const u32 d0 = (t - M.tstart[p]) * MW_TILE;
-    split[t] = d0 >= na + nb ? na : corank_global(M, A0, na, A1, nb, d0, c, C);
-}
-
 // The merge's results: per output, the source (run, position in run), the
 // string id, the LCP with the previous output and the string length (src and
 // len optional).  sb/sid: the non-empty runs' front-coded starts, ascending,
@@ -1022,7 +913,8 @@ struct MergeOut {
     u32 *id, *lcp, *len;
 };
 
-__device__ __forceinline__ void merge_emit(const MergeOut &O, u64 x, u32 g, u32 l)
+// (the element's front-coded position g; its LCP is written apart)
+__device__ __forceinline__ void merge_emit(const MergeOut &O, u64 x, u32 g)
 {
     if (O.src) {
         u32 lo = 0, hi = O.kne;  // largest j with sb[j] <= g
@@ -1034,236 +926,29 @@ __device__ __forceinline__ void merge_emit(const MergeOut &O, u64 x, u32 g, u32 
         O.src[x] = ((u64)O.sid[lo] << 32) | (u64)(g - O.sb[lo]);
     }
     O.id[x] = O.fc_id[g];
-    O.lcp[x] = l;
     if (O.len) O.len[x] = O.fc_len[g];
 }
 
-// One merge level, merge-path style: each workgroup produces MW_TILE outputs of
-// one pair.  Its A and B windows (plus the element before each) are staged in
-// LDS; every thread co-ranks its MW_IPT outputs inside the window and merges them
-// with the LCP rule; outputs are written back through LDS.  The last level
-// (LAST) writes the merge's results instead of the next level's elements.
-template <bool LAST>
-__global__ __launch_bounds__(MW_NT, 6) void k_merge_level(MergeLevel M, u32 nblocks, const u32 *split, MergeOut O)
-{
-    __shared__ u32 sG[MW_TILE + 2], sL[MW_TILE + 2], sF[MW_TILE + 2];
-    __shared__ u64 sK[MW_TILE + 2];
-    const u32 blk = blockIdx.x;
-    if (blk >= nblocks) return;
-    u32 lo = 0, hi = M.npairs;
-    while (hi - lo > 1) {
-        u32 mid = (lo + hi) >> 1;
-        if (M.tstart[mid] <= blk) lo = mid;
-        else hi = mid;
-    }
-    const u32 p = lo;
-    const u64 A0 = M.PA0[p], A1 = M.PA1[p], B0 = A1, B1 = M.PB1[p];
-    const u32 na = (u32)(A1 - A0), nb = (u32)(B1 - B0);
-    const u32 tot = na + nb;
-    const u32 d0 = (blk - M.tstart[p]) * MW_TILE;
-    if (d0 >= tot) return;
-    const u32 d1 = min(tot, d0 + MW_TILE);
-    const u32 c = M.pc[p];
-    const u32 C = M.Cg[M.pg[p]];
-    const bool firstA = M.pfirst[p] != 0;
-    const u32 a0 = split[blk];
-    u32 a1 = (d1 == tot) ? na : split[blk + 1];
-    // Keep the windows inside both runs even if the co-ranks are not monotone
-    // (runs that violate the sortedness precondition): na >= a1 >= a0,
-    // a1 - a0 <= d1 - d0, and d1 - a1 <= nb.
-    {
-        const u32 lo = max(a0, d1 > nb ? d1 - nb : 0u);
-        const u32 hi = min(a0 + (d1 - d0), na);
-        a1 = a1 < lo ? lo : (a1 > hi ? hi : a1);
-    }
-    const u32 b0 = d0 - a0, b1 = d1 - a1;
-    const u32 wa = a1 - a0, wb = b1 - b0;
-    // LDS layout: [pa | A window (wa) | pb | B window (wb)], pa/pb = element before the window
-    const u32 baseA = 1, baseB = wa + 2;
-    for (u32 i = threadIdx.x; i < wa + 1; i += MW_NT) {
-        if (i == 0 && a0 == 0) continue;
-        const u64 gi = A0 + a0 + i - 1;
-        sG[i] = M.G[gi]; sL[i] = M.L[gi]; sF[i] = M.F[gi]; sK[i] = M.K[gi];
-    }
-    for (u32 i = threadIdx.x; i < wb + 1; i += MW_NT) {
-        if (i == 0 && b0 == 0) continue;
-        const u64 gi = B0 + b0 + i - 1;
-        sG[baseB - 1 + i] = M.G[gi]; sL[baseB - 1 + i] = M.L[gi]; sF[baseB - 1 + i] = M.F[gi];
-        sK[baseB - 1 + i] = M.K[gi];
-    }
-    __syncthreads();
-    const FcView &V = M.V;
-    const u32 dd = threadIdx.x * MW_IPT;  // local diagonal of this thread
-    const u32 dw = d1 - d0;
-    u32 oG[MW_IPT], oL[MW_IPT], oF[MW_IPT];
-    u64 oK[MW_IPT];
-    u32 cnt = 0;
-    if (dd < dw) {
-        cnt = min((u32)MW_IPT, dw - dd);
-        u64 tmp;
-        // co-rank inside the window (indices relative to a0 / b0).  Along the
-        // diagonal the cached keys alone say "A first" up to some x1, "tie"
-        // (equal keys of continuing strings) up to x2, then "B first"; both
-        // bounds are found from the keys, and only [x1, x2) is searched with
-        // string comparisons, so a wavefront compares strings once per
-        // halving of its widest tie range instead of at every search step
-        // where some lane's keys tie.
-        u32 xlo = dd > wb ? dd - wb : 0, xhi = dd < wa ? dd : wa;
-        auto key_side = [&](u32 x) -> int {  // -1: A first by the keys, 0: tie, 1: B first
-            const u64 ka = sK[baseA + x], kb = sK[baseB + (dd - x - 1)];
-            if (ka != kb) return ka < kb ? -1 : 1;
-            return (ka & 0xFF) < 8 ? -1 : 0;  // equal strings ending in the key: A first
-        };
-        u32 x1lo = xlo, x1hi = xhi;
-        while (x1lo < x1hi) {
-            const u32 mid = (x1lo + x1hi) >> 1;
-            if (key_side(mid) < 0) x1lo = mid + 1;
-            else x1hi = mid;
-        }
-        // (no tie at x1: the range is empty, as it is wherever keys decide)
-        u32 x2lo = x1lo, x2hi = (x1lo < xhi && key_side(x1lo) == 0) ? xhi : x1lo;
-        while (x2lo < x2hi) {
-            const u32 mid = (x2lo + x2hi) >> 1;
-            if (key_side(mid) <= 0) x2lo = mid + 1;
-            else x2hi = mid;
-        }
-        xlo = x1lo;
-        xhi = x2lo;
-        // (the LCPs of the last probes that moved each bound: the pairs on
-        // both sides of the co-rank, used below)
-        u64 lcp_lo = 0, lcp_hi = 0;
-        bool moved_lo = false, moved_hi = false;
-        while (xlo < xhi) {
-            const u32 mid = (xlo + xhi) >> 1;
-            const u32 ia = baseA + mid, ib = baseB + (dd - mid - 1);
-            if (cmp_elem(V, sG[ia], sK[ia], sG[ib], sK[ib], min3u(sF[ia], c, sF[ib]), C, &tmp) <= 0) {
-                xlo = mid + 1;
-                lcp_lo = tmp;
-                moved_lo = true;
-            } else {
-                xhi = mid;
-                lcp_hi = tmp;
-                moved_hi = true;
-            }
-        }
-        u32 a = xlo, b = dd - xlo;  // relative to the window
-        const u32 ga = a0 + a, gb = b0 + b;  // relative to the runs
-        u32 ha = 0, hb = 0;
-        if (d0 + dd > 0) {
-            // The previous output is A[ga-1] or B[gb-1] (LDS slots pa / pb).
-            // The LCPs across the co-rank, u = lcp(A[a-1], B[b]) and
-            // w = lcp(B[b-1], A[a]), are those of the search's last probes,
-            // or else the keys decide them (a pair outside the tie range);
-            // with p = lcp(A[a-1], A[a]) and q = lcp(B[b-1], B[b]) they say
-            // which predecessor is the larger: of two strings not above X,
-            // the one sharing more with X is the larger.  Only when both
-            // tests tie are the two predecessors compared.
-            const u32 pa = baseA + a - 1, pb = baseB + b - 1;
-            const bool hasA = a < wa, hasB = b < wb;
-            auto pair_lcp = [&](u32 ix, u32 iy, bool rec, u64 l) -> u32 {
-                if (rec) return (u32)l;
-                u64 t;
-                cmp_key(sK[ix], sK[iy], C, &t, [&](u64 *ll) { return fc_cmp(V, sG[ix], sG[iy], C + 7, ll); });
-                return (u32)t;
-            };
-            const u32 w = (hasA && gb > 0) ? pair_lcp(baseA + a, pb, moved_hi && xhi == a, lcp_hi) : 0u;
-            const u32 u = (hasB && ga > 0) ? pair_lcp(pa, baseB + b, moved_lo && xlo == a, lcp_lo) : 0u;
-            const u32 p = hasA ? sL[baseA + a] : 0u, q = hasB ? sL[baseB + b] : 0u;
-            bool lastA;
-            if (ga == 0) {
-                lastA = false;
-            } else if (gb == 0) {
-                lastA = true;
-            } else {
-                int dec = 0;
-                u32 bnd = 0;
-                if (hasA) {
-                    if (p != w) dec = p > w ? 1 : -1;
-                    bnd = p < w ? p : w;
-                }
-                if (dec == 0 && hasB) {
-                    if (u != q) dec = u > q ? 1 : -1;
-                    const u32 bq = u < q ? u : q;
-                    bnd = bq > bnd ? bq : bnd;
-                }
-                lastA = dec != 0 ? dec > 0 : cmp_elem(V, sG[pa], sK[pa], sG[pb], sK[pb], bnd, C, &tmp) > 0;
-            }
-            ha = hasA ? (lastA ? p : w) : 0u;
-            hb = hasB ? (lastA ? u : q) : 0u;
-        }
-#pragma unroll
-        for (u32 k = 0; k < MW_IPT; k++) {
-            if (k >= cnt) break;
-            bool takeA;
-            u32 outl;
-            const u32 ia = baseA + a, ib = baseB + b;
-            if (a >= wa) {
-                takeA = false;
-                outl = hb;
-            } else if (b >= wb) {
-                takeA = true;
-                outl = ha;
-            } else if (ha > hb) {
-                takeA = true;
-                outl = ha;
-            } else if (ha < hb) {
-                takeA = false;
-                outl = hb;
-            } else {
-                const u32 bound = min3u(sF[ia], c, sF[ib]);
-                const int r = cmp_elem(V, sG[ia], sK[ia], sG[ib], sK[ib], bound > ha ? bound : ha, C, &tmp);
-                outl = ha;
-                if (r <= 0) {
-                    takeA = true;
-                    hb = (u32)tmp;
-                } else {
-                    takeA = false;
-                    ha = (u32)tmp;
-                }
-            }
-            if (d0 + dd + k == 0) outl = 0;
-            if (takeA) {
-                oG[k] = sG[ia]; oL[k] = outl; oF[k] = firstA ? sF[ia] : min(c, sF[ia]); oK[k] = sK[ia];
-                a++;
-                if (a < wa) ha = sL[baseA + a];
-            } else {
-                oG[k] = sG[ib]; oL[k] = outl; oF[k] = firstA ? min(c, sF[ib]) : sF[ib]; oK[k] = sK[ib];
-                b++;
-                if (b < wb) hb = sL[baseB + b];
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (u32 k = 0; k < MW_IPT; k++) {
-        if (k < cnt) {
-            sG[dd + k] = oG[k]; sL[dd + k] = oL[k];
-            if (!LAST) { sF[dd + k] = oF[k]; sK[dd + k] = oK[k]; }
-        }
-    }
-    __syncthreads();
-    const u64 ob = A0 + d0;
-    for (u32 i = threadIdx.x; i < dw; i += MW_NT) {
-        if (LAST) merge_emit(O, ob + i, sG[i], sL[i]);
-        else { M.Go[ob + i] = sG[i]; M.Lo[ob + i] = sL[i]; M.Fo[ob + i] = sF[i]; M.Ko[ob + i] = sK[i]; }
-    }
-}
-
-#define RM_PARTS 32  // workgroups per run
-
 // Minimum LCP-with-predecessor over each run except its first element, i.e.
-// the LCP of the run's first and last strings: RM_PARTS workgroups per run
-// (blockIdx.y = part), one atomic each.
+// the LCP of the run's first and last strings: gridDim.y workgroups per run
+// (blockIdx.y = part), one atomic each.  The caller gives a run of the average
+// size a workgroup per 4096 entries, at most 64 of them: with 245 the atomics
+// on one word cost more than they save.  4 runs of 500,000 entries: 18 us with
+// one load in flight, 6.4 us with eight (13.8 us with 245 workgroups per run).
 __global__ __launch_bounds__(256) void k_run_min(const u64 *run_begin, const u64 *P, const u32 *e, u32 *runmin)
 {
     __shared__ u32 wmin[4];
     const u32 r = blockIdx.x;
     const u64 b = run_begin[r], n = P[r + 1] - P[r];
-    const u64 i0 = 1 + (n * blockIdx.y) / RM_PARTS, i1 = 1 + (n * (blockIdx.y + 1)) / RM_PARTS;
+    const u64 i0 = 1 + (n * blockIdx.y) / gridDim.y, i1 = 1 + (n * (blockIdx.y + 1)) / gridDim.y;
     u32 mn = 0xFFFFFFFFu;
-    for (u64 i = i0 + threadIdx.x; i < i1 && i < n; i += 256) {
-        const u32 v = e[b + i];
-        mn = v < mn ? v : mn;
+    const u64 end = i1 < n ? i1 : n;
+    for (u64 i = i0 + threadIdx.x; i < end; i += 8 * 256) {
+        u32 v[8];  // (eight loads in flight; past the end the first again)
+#pragma unroll
+        for (u32 q = 0; q < 8; q++) v[q] = e[b + (i + q * 256 < end ? i + q * 256 : i)];
+#pragma unroll
+        for (u32 q = 0; q < 8; q++) mn = v[q] < mn ? v[q] : mn;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -1299,32 +984,27 @@ __global__ void k_group_depth(const u64 *run_begin, const u64 *P, const u32 *run
     atomicMin(&Cg[g], v);
 }
 
-// ---- per-element state of the merge by one segmented scan over the runs
+// ---- the elements' keys by one scan over the runs
 //
 // Output position x of run r is front-coded entry g = run_begin[r] + x - P[r]
-// with LCP e_g to its predecessor (0 at the run start).  Its state is
-//   G = g, L = e_g, F = min e over (start, x] (the LCP with the run head; all
-//   ones at the start), K = bytes [C, C+7) of its string and min(d_g - C, 8),
-// C = the group's common prefix.  F and K follow a scan with the operator
-// (reset, m, p, v): F restarts at run starts and takes minima; the 7-byte
-// window at C keeps its first p bytes from the predecessor's window
-// (p = clamp(e_g - C, 0, 7)) and takes the rest, v, from the entry's literal.
+// with LCP e_g to its predecessor (0 at the run start).  Its key is bytes
+// [C, C+7) of its string and min(d_g - C, 8), C = the group's common prefix.
+// It follows a scan with the operator (p, v): the 7-byte window at C keeps its
+// first p bytes from the predecessor's window (p = clamp(e_g - C, 0, 7), none
+// at a run start) and takes the rest, v, from the entry's literal.
 struct MOp {
-    u32 rp;  // bit 3: reset, bits 0..2: p
-    u32 m;
+    u32 p;
     u64 v;
 };
 
-__device__ __forceinline__ MOp mop_id() { return MOp{7u, 0xFFFFFFFFu, 0ull}; }
+__device__ __forceinline__ MOp mop_id() { return MOp{7u, 0ull}; }
 
 // a, then b
 __device__ __forceinline__ MOp mop_cat(MOp a, MOp b)
 {
-    const u32 pa = a.rp & 7u, pb = b.rp & 7u;
-    const u64 keep = pb ? (~0ull << (64 - 8 * pb)) : 0ull;
+    const u64 keep = b.p ? (~0ull << (64 - 8 * b.p)) : 0ull;
     MOp r;
-    r.rp = ((a.rp | b.rp) & 8u) | (pa < pb ? pa : pb);
-    r.m = (b.rp & 8u) ? b.m : (a.m < b.m ? a.m : b.m);
+    r.p = a.p < b.p ? a.p : b.p;
     r.v = (a.v & keep) | (b.v & ~keep);
     return r;
 }
@@ -1332,18 +1012,8 @@ __device__ __forceinline__ MOp mop_cat(MOp a, MOp b)
 __device__ __forceinline__ MOp mop_shfl_up(MOp a, u32 d)
 {
     MOp r;
-    r.rp = __shfl_up(a.rp, d, 64);
-    r.m = __shfl_up(a.m, d, 64);
+    r.p = __shfl_up(a.p, d, 64);
     r.v = __shfl_up(a.v, d, 64);
-    return r;
-}
-
-__device__ __forceinline__ MOp mop_shfl(MOp a, u32 src)
-{
-    MOp r;
-    r.rp = __shfl(a.rp, src, 64);
-    r.m = __shfl(a.m, src, 64);
-    r.v = __shfl(a.v, src, 64);
     return r;
 }
 
@@ -1392,9 +1062,7 @@ __device__ __forceinline__ u32 run_of(const u64 *P, u32 k, u64 x)
     return lo;
 }
 
-// 7 elements per thread: the apply kernel's LDS operators take 28 KB; it runs
-// four workgroups per compute unit, with the registers to keep its elements'
-// entries and LCPs for the output pass without spilling
+// 7 elements per thread: the apply kernel's LDS operators take 28 KB
 #define MS_PER 7
 #define MS_ITEMS (256 * MS_PER)  // elements per workgroup
 
@@ -1455,11 +1123,9 @@ __device__ __forceinline__ void mscan_ops(const MScan &S, const MElems &E, MOp *
     }
 #pragma unroll
     for (u32 q = 0; q < MS_PER; q++) {
-        const bool st = (E.start >> q) & 1;
         const u32 C = E.C[q];
         MOp r;
-        r.rp = (st ? 8u : 0u) | p[q];
-        r.m = st ? 0xFFFFFFFFu : e[q];
+        r.p = p[q];
         r.v = (d[q] > C ? (d[q] - C < 8 ? d[q] - C : 8u) : 0u) |
               (__builtin_bswap64(raw8_le(S.V.suf, lit[q])) >> (8 * p[q]));
         o[q] = ((E.in >> q) & 1) ? r : mop_id();
@@ -1505,19 +1171,29 @@ __device__ __forceinline__ MOp block_mop_exclusive(MOp a, MOp carry)
     return mop_cat(pre, ex);
 }
 
-// The run of every scan block's first element (the run r with P[r] <= x <
-// P[r+1], x = j MS_ITEMS): each non-empty run writes it for the blocks that
-// start inside it.
-__global__ void k_block_runs(const u64 *P, u32 k, u32 nb, u32 *bfirst)
+// Initial values of a merge's counters and minima, and the run of every scan
+// block's first element (the run r with P[r] <= x < P[r+1], x = j MS_ITEMS).
+__global__ void k_merge_init(const u64 *P, u32 k, u32 nb, u32 *bfirst, u32 *runmin, u32 *Cg, u32 groups, u32 *ties,
+                             u32 *ctr)
 {
-    const u32 r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= k) return;
-    const u64 a = P[r], b = P[r + 1];
-    for (u64 j = (a + MS_ITEMS - 1) / MS_ITEMS; j * MS_ITEMS < b && j < nb; j++) bfirst[j] = r;
+    const u32 j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < k) runmin[j] = 0xFFFFFFFFu;
+    if (j < groups) Cg[j] = 0xFFFFFFFFu;
+    if (j < C_NCTR) ctr[j] = 0;
+    if (j == 0) *ties = 0;
+    if (j < nb) {
+        u32 lo = 0, hi = k;
+        while (hi - lo > 1) {
+            const u32 mid = (lo + hi) >> 1;
+            if (P[mid] <= (u64)j * MS_ITEMS) lo = mid;
+            else hi = mid;
+        }
+        bfirst[j] = lo;
+    }
 }
 
-// Phase 1: the operator of every MS_ITEMS-element block.  Its reset, p and m
-// parts need only each element's e and d.  Of its window, byte k (k < 7) is
+// Phase 1: the operator of every MS_ITEMS-element block.  Its p needs only each
+// element's e.  Of its window, byte k (k < 7) is
 // the one written by the block's last element with p <= k (a later element
 // with a larger p keeps it), and the count byte is the last element's, so at
 // most eight literal bytes are read per block instead of every element's.
@@ -1525,7 +1201,7 @@ __global__ __launch_bounds__(256) void k_mscan_reduce(MScan S, MOp *blk)
 {
     // per wavefront, per window byte k < 7 and the count (7): last supplier + 1, block-relative (0: none)
     __shared__ u32 s_wl[4][8];
-    __shared__ u32 s_rp[MS_ITEMS], s_m[MS_ITEMS];
+    __shared__ u32 s_p[MS_ITEMS];
     const u64 x0 = (u64)blockIdx.x * MS_ITEMS;
     MElems E;
     mscan_locate(S, x0, E);
@@ -1538,8 +1214,7 @@ __global__ __launch_bounds__(256) void k_mscan_reduce(MScan S, MOp *blk)
         const bool st = (E.start >> q) & 1;
         const u32 ee = st ? 0u : e[q], C = E.C[q];
         const u32 p = ee > C ? (ee - C < 7 ? ee - C : 7u) : 0u;
-        s_rp[i] = ((E.in >> q) & 1) ? ((st ? 8u : 0u) | p) : 0xFFu;  // (0xFF: out of range)
-        s_m[i] = st ? 0xFFFFFFFFu : ee;
+        s_p[i] = ((E.in >> q) & 1) ? p : 0xFFu;  // (0xFF: out of range)
     }
     __syncthreads();
     // this thread's MS_PER consecutive elements, in order
@@ -1548,14 +1223,9 @@ __global__ __launch_bounds__(256) void k_mscan_reduce(MScan S, MOp *blk)
 #pragma unroll
     for (u32 q = 0; q < MS_PER; q++) {
         const u32 i = threadIdx.x * MS_PER + q;
-        const u32 rp = s_rp[i];
-        if (rp == 0xFFu) break;  // (out of range from here on)
-        MOp o;
-        o.rp = rp;
-        o.m = s_m[i];
-        o.v = 0;
-        t = mop_cat(t, o);
-        const u32 p = rp & 7u;
+        const u32 p = s_p[i];
+        if (p == 0xFFu) break;  // (out of range from here on)
+        t.p = p < t.p ? p : t.p;
 #pragma unroll
         for (u32 k = 0; k < 7; k++)
             if (p <= k) lastk[k] = i + 1;
@@ -1569,7 +1239,7 @@ __global__ __launch_bounds__(256) void k_mscan_reduce(MScan S, MOp *blk)
         const u32 v = m ? (u32)__shfl((int)lastk[k], 63 - __clzll(m), 64) : 0u;
         if ((threadIdx.x & 63) == 0) s_wl[threadIdx.x >> 6][k] = v;
     }
-    t = block_mop_reduce(t);  // (reset, p, m); its window is filled below (its barriers complete s_wl)
+    t = block_mop_reduce(t);  // (p; its window is filled below, its barriers complete s_wl)
     u32 last[8];
 #pragma unroll
     for (u32 k = 0; k < 8; k++) last[k] = max(max(s_wl[0][k], s_wl[1][k]), max(s_wl[2][k], s_wl[3][k]));
@@ -1649,9 +1319,12 @@ __global__ __launch_bounds__(1024) void k_mscan_top(MOp *blk, u32 nb)
     }
 }
 
-// Phase 3: every element's inclusive operator -> G, L, F, K (written with
+// Phase 3: every element's inclusive operator, its key (written with
 // consecutive lanes on consecutive elements).
-__global__ __launch_bounds__(256, 4) void k_mscan_apply(MScan S, const MOp *blk, u32 *G, u32 *L, u32 *F, u64 *K)
+// Keys that fall within a run (runs are sorted by precondition) raise *bad: a
+// merge by key would then lose elements, and the groups are sorted as a whole
+// instead.
+__global__ __launch_bounds__(256, 4) void k_mscan_apply(MScan S, const MOp *blk, u64 *K, u32 *bad)
 {
     __shared__ MOp ops[MS_ITEMS];
     const u64 x0 = (u64)blockIdx.x * MS_ITEMS;
@@ -1676,29 +1349,756 @@ __global__ __launch_bounds__(256, 4) void k_mscan_apply(MScan S, const MOp *blk,
     for (u32 q = 0; q < MS_PER; q++) {
         const u32 i = threadIdx.x * MS_PER + q;
         st = mop_cat(st, ops[i]);
-        ops[i].m = st.m;
         ops[i].v = st.v;
     }
     __syncthreads();
+    bool fall = false;
 #pragma unroll
     for (u32 q = 0; q < MS_PER; q++) {
         const u32 i = q * 256 + threadIdx.x;
-        const u64 x = x0 + i;
         if (!((E.in >> q) & 1)) break;
-        G[x] = E.g[q];
-        L[x] = e[q];
-        F[x] = ops[i].m;
-        K[x] = ops[i].v;
+        const u64 v = ops[i].v;
+        K[x0 + i] = v;
+        if (!((E.start >> q) & 1)) fall |= (i ? ops[i - 1].v : blk[blockIdx.x].v) > v;
+    }
+    if (__ballot(fall) && (threadIdx.x & 63) == 0) *bad = 1u;
+}
+
+// ---- merging by key
+//
+// The non-empty runs, in order, are numbered j = 0, 1, ... over all groups;
+// group g has runs [gs[g], gs[g+1]).  Level 0 of a key list is the runs
+// themselves (run j at K[ps[j]], ps[j+1] - ps[j] keys); level v + 1 takes every
+// S-th key of every run of level v, beginning at positions spread over [0, S)
+// by the run's number (samples at the same positions of like runs would come in
+// lumps), so that a sample's rank among the samples times S is its rank without
+// bias.  A group of
+// more than MW_CAP keys in level v is cut into tiles of MW_TILE at keys of its
+// merged level v + 1; a smaller one is one tile.  Tile t of group g takes from
+// run j the keys in [threshold t, threshold t + 1): their positions are entries
+// t and t + 1 of the run's row in the group's bounds matrix.
+#define MW_NT 256
+#define MW_IPT 9  // (odd shares: the threads' blocked accesses then meet no bank conflicts)
+#define MW_CAP (MW_NT * MW_IPT)  // keys a tile can hold
+#define MW_TILE 1280             // keys of a tile on average
+#define MW_RUNS 2048             // runs of a group merged this way
+#define MW_FEW 512               // (a kernel of its own for so many: its windows' bounds take less LDS)
+#define MW_RANK 16               // groups of up to so many runs rank their samples directly
+#define MW_LEVELS 9
+
+// Sampling step of a group of kg runs.  A threshold cuts every run up to S/2
+// from where its samples say, so the sizes of tiles vary by about 0.4 S sqrt(kg)
+// about MW_TILE: these steps keep that at 150 or less, far below what a tile has
+// to spare.
+__device__ __host__ __forceinline__ u32 mw_step(u32 kg)
+{
+    return kg <= 16 ? 64u : (kg <= 64 ? 32u : (kg <= 512 ? 16u : 8u));
+}
+// Where run r of a group of kg starts sampling, how many samples a run of len
+// keys gives, and the sample that threshold t of nt tiles over tot keys takes
+// (of ns).
+__device__ __host__ __forceinline__ u32 mw_phase(u32 r, u32 kg) { return (2 * r + 1) * mw_step(kg) / (2 * kg); }
+__device__ __host__ __forceinline__ u64 mw_samples(u64 len, u32 r, u32 kg)
+{
+    const u32 S = mw_step(kg);
+    return (len + S - 1 - mw_phase(r, kg)) / S;
+}
+__device__ __forceinline__ u32 mw_cut(u32 t, u32 nt, u32 tot, u32 ns, u32 S)
+{
+    const u64 x = (u64)t * tot / ((u64)nt * S);
+    return x < ns ? (u32)x : ns - 1;
+}
+
+struct MwLevel {
+    const u64 *K;     // this level's keys
+    const u32 *ps;    // start of every run in K (runs + 1)
+    const u32 *gs;    // first run of every group (groups + 1)
+    const u32 *ts;    // first tile of every group (groups + 1)
+    const u32 *bo;    // first bounds entry of every group (groups + 1)
+    const u64 *spl;   // merged keys of the next level
+    const u32 *sps;   // its run starts: run j's samples begin at sps[j]
+    u32 groups;
+    u32 *bounds;
+    const u32 *bad;   // raised: some run is not sorted (nothing is merged)
+};
+
+// largest g in [0, n) with a[g] <= x
+__device__ __forceinline__ u32 mw_find(const u32 *a, u32 n, u32 x)
+{
+    u32 lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const u32 mid = (lo + hi) >> 1;
+        if (a[mid] <= x) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// Threshold t (0 < t < nt) of a group.
+__device__ __forceinline__ u64 mw_threshold(const MwLevel &M, u32 j0, u32 kg, u32 t, u32 nt)
+{
+    const u32 s0 = M.sps[j0], ns = M.sps[j0 + kg] - s0, tot = M.ps[j0 + kg] - M.ps[j0];
+    return M.spl[s0 + mw_cut(t, nt, tot, ns, mw_step(kg))];
+}
+
+// The sampled keys of level v (run j's at out[st[j]]).
+__global__ void k_mw_sample(const u64 *K, const u32 *ps, const u32 *gs, u32 groups, u32 kc, const u32 *st, u32 v,
+                            u64 *out)
+{
+    const u32 x = st[0] + blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= st[kc]) return;
+    const u32 j = mw_find(st, kc, x);
+    const u32 g = mw_find(gs, groups, j);
+    const u32 kg = gs[g + 1] - gs[g], S = mw_step(kg), ph = mw_phase(j - gs[g], kg);
+    u64 i = x - st[j];
+    for (u32 y = 0; y < v; y++) i = i * S + ph;
+    out[x] = K[ps[j] + i];
+}
+
+// Merged positions of the first-level samples of the groups of up to MW_RANK
+// runs: a sample's rank is its own index plus how many samples of each other
+// run lie below it (or equal it, in an earlier run).  That is one launch where
+// further levels take two more each; what it costs, samples x runs x
+// log(samples of a run) probes, is 1/4 of a probe per key and search step at 16
+// runs.  4M keys in 16 x 16 runs: 63 us with one search after the other, 33
+// us with four side by side.
+__global__ __launch_bounds__(256) void k_mw_rank(const u64 *K, const u32 *ps0, const u32 *ps, const u32 *gs,
+                                                 u32 groups, u32 kc, u64 *KM, const u32 *bad)
+{
+    const u32 x = ps[0] + blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= ps[kc]) return;
+    if (*bad) return;
+    const u32 j = mw_find(ps, kc, x);
+    const u32 g = mw_find(gs, groups, j);
+    const u32 j0 = gs[g], j1 = gs[g + 1];
+    const u32 kg = j1 - j0, S = mw_step(kg);
+    if (kg > MW_RANK) return;
+    const u64 key = K[ps0[j] + (u64)(x - ps[j]) * S + mw_phase(j - j0, kg)];
+    u32 r = ps[j0] + (x - ps[j]);
+    for (u32 o = j0; o < j1; o += 4) {  // four searches side by side: each is a chain of loads
+        const u64 *k[4];
+        u32 lo[4], n[4], most = 0;
+#pragma unroll
+        for (u32 q = 0; q < 4; q++) {
+            const bool on = o + q < j1 && o + q != j;
+            const u32 w = on ? o + q : j;
+            k[q] = K + ps0[w] + mw_phase(w - j0, kg);
+            lo[q] = 0;
+            n[q] = on ? ps[w + 1] - ps[w] : 0u;  // samples in doubt: [lo, lo + n)
+            most = n[q] > most ? n[q] : most;
+        }
+        for (; most; most >>= 1) {
+            u64 y[4];
+#pragma unroll
+            for (u32 q = 0; q < 4; q++) y[q] = k[q][n[q] ? (u64)(lo[q] + (n[q] >> 1)) * S : 0];
+#pragma unroll
+            for (u32 q = 0; q < 4; q++) {
+                const u32 h = n[q] >> 1;
+                const bool below = n[q] && (o + q < j ? y[q] <= key : y[q] < key);
+                lo[q] += below ? h + 1 : 0u;
+                n[q] = below ? n[q] - h - 1 : h;
+            }
+        }
+#pragma unroll
+        for (u32 q = 0; q < 4; q++) r += lo[q];
+    }
+    KM[r] = key;
+}
+
+// The bounds matrices of a level: row j, entry t of a group = how many keys of
+// its run j lie below threshold t (entry 0: none; the last: all).  Consecutive
+// lanes search one run for consecutive thresholds, so they read the same lines
+// (the launches of a merge of 256 runs of 31,250 keys: 170 us with lanes on
+// different runs, 45 us so).
+__global__ __launch_bounds__(256) void k_mw_bounds(MwLevel M, u32 total)
+{
+    const u32 x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= total) return;
+    if (*M.bad) return;
+    const u32 g = mw_find(M.bo, M.groups, x);
+    const u32 j0 = M.gs[g], kg = M.gs[g + 1] - j0, nt = M.ts[g + 1] - M.ts[g];
+    const u32 j = j0 + (x - M.bo[g]) / (nt + 1), row = (x - M.bo[g]) % (nt + 1);
+    const u32 p0 = M.ps[j], len = M.ps[j + 1] - p0;
+    u32 r = row == 0 ? 0u : len;
+    if (row > 0 && row < nt) {
+        const u64 t = mw_threshold(M, j0, kg, row, nt);
+        u32 lo = 0, hi = len;  // first position with a key >= t
+        while (lo < hi) {
+            const u32 mid = (lo + hi) >> 1;
+            if (M.K[p0 + mid] < t) lo = mid + 1;
+            else hi = mid;
+        }
+        r = lo;
+    }
+    M.bounds[x] = r;
+}
+
+#define TIE_SMALL 8  // tied segments of up to this many are sorted at once
+#define TIE_REC 1u  // a tied segment whose members' entries lie beside the order, and whose results are written
+
+struct MwOut {
+    u64 *keys;           // sample levels: the merged keys
+    const u32 *Cg;       // the rest: level 0
+    const u32 *rrun, *rbeg;  // every non-empty run's number and front-coded start
+    const u32 *fc_lcp, *fc_len;
+    const u64 *suf_off;
+    MergeOut O;
+    u32 *order;          // front-coded positions of tied elements, by output position
+    Seg *ties;           // runs of outputs with tied keys (C_RNEXT of them, C_RELEM elements)
+    Seg *over;           // segments handed to the sort as a whole (C_RTILES of them)
+    SortWs s;
+    u32 tile, block_max; // of that sort
+};
+
+// One segment to the sort of its size, and to the list of what is to be emitted.
+__device__ __forceinline__ void mw_route(const MwOut &W, Seg o)
+{
+    const u32 m = o.end - o.begin;
+    u32 *ctr = W.s.ctr;
+    W.over[atomicAdd(&ctr[C_RTILES], 1u)] = o;
+    if (m > W.block_max) {
+        W.s.largeA[atomicAdd(&ctr[C_LARGE], 1u)] = o;
+        atomicAdd(&ctr[C_LTILES], (m + W.tile - 1) / W.tile);
+        atomicAdd(&ctr[C_LELEM], m);
+    } else if (m <= WS_MAX) {
+        if (m > 1) W.s.tiny[atomicAdd(&ctr[C_TINY], 1u)] = o;
+    } else {
+        if (m <= BS_SMALL) W.s.small[atomicAdd(&ctr[C_SMALL], 1u)] = o;
+        else W.s.mid[atomicAdd(&ctr[C_MID], 1u)] = o;
+        atomicAdd(&ctr[C_SMALLN], m);
+    }
+    atomicAdd(&ctr[C_NELEM], m);
+}
+
+// Merge of one tile: the windows of its runs one after the other in LDS, then
+// ceil(log2 runs) levels, each merging neighbouring lists pairwise; a thread
+// finds where its outputs start (pair, then merge path) and merges them
+// serially, stepping over pair ends.  Keys alone are compared and earlier runs
+// win ties, so equal keys stay in (run, position) order.
+//
+// OUT (level 0): writes the merge's results; keys that differ give the LCPs.
+// Runs of outputs with equal keys whose strings go on become segments at depth
+// C + 7 if they come from more than one run (within one run their order and
+// LCPs stand).  A tile whose windows exceed MW_CAP (many copies of one key, or
+// a group with too few samples) becomes one segment for the segmented sort; in
+// a sample level its keys all become its lower threshold, which only makes
+// later tiles larger.
+//
+// Bounded by vector instructions: about 25 per element and level, against 8 B
+// in and 8 to 20 B out.  8M keys in 256 runs: 235 us over all levels, where
+// eight pairwise levels took 900 us; 16M keys in 16 x 16 runs: 305 us, against
+// 670 us of four.
+template <bool OUT, u32 RUNS>
+__global__ __launch_bounds__(MW_NT) void k_mw_tile(MwLevel M, MwOut W)
+{
+    __shared__ u64 sk[MW_CAP];
+    __shared__ u16 si[MW_CAP];
+    constexpr u32 R = RUNS / MW_NT;  // runs per thread, consecutive ones
+    __shared__ u32 woff[RUNS + 1], wlo[RUNS];
+    __shared__ u32 s_sum[MW_NT / 64], s_lo[MW_NT / 64];
+    __shared__ u64 s_prev[MW_NT / 64], s_min[MW_NT / 64];
+    __shared__ u32 s_n, s_el, s_base, s_big;
+    if (*M.bad) return;  // (uniform)
+    const u32 t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    // consecutive tiles on one XCD (workgroups go round the eight): neighbours
+    // share the lines of their windows' ends in its L2
+    const u32 per = gridDim.x / 8, tile = blockIdx.x < 8 * per ? (blockIdx.x & 7) * per + (blockIdx.x >> 3) : blockIdx.x;
+    const u32 g = mw_find(M.ts, M.groups, tile);
+    const u32 j0 = M.gs[g], kg = M.gs[g + 1] - j0;
+    const u32 row = tile - M.ts[g], nt1 = M.ts[g + 1] - M.ts[g] + 1;
+    const u32 *b = M.bounds + M.bo[g] + row;
+    u32 nr[R], inc = 0, sl = 0;
+    u64 prev = 0, mn = ~0ull;  // the largest key before the tile, the smallest in it (level 0)
+#pragma unroll
+    for (u32 q = 0; q < R; q++) {
+        const u32 w = R * t + q;
+        nr[q] = 0;
+        if (w < kg) {
+            const u32 lo = b[w * nt1];
+            nr[q] = b[w * nt1 + 1] - lo;
+            wlo[w] = lo;
+            sl += lo;
+            inc += nr[q];
+            if (OUT) {
+                const u64 *k = M.K + M.ps[j0 + w];
+                if (lo) { const u64 y = k[lo - 1]; prev = y > prev ? y : prev; }
+                if (nr[q]) { const u64 y = k[lo]; mn = y < mn ? y : mn; }
+            }
+        }
+    }
+    u32 ex = inc;  // (less its own below)
+#pragma unroll
+    for (u32 d = 1; d < 64; d <<= 1) {
+        const u32 y = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += y;
+        sl += __shfl_xor(sl, d, 64);
+        if (OUT) {
+            const u64 a = __shfl_xor(prev, d, 64), b = __shfl_xor(mn, d, 64);
+            prev = a > prev ? a : prev;
+            mn = b < mn ? b : mn;
+        }
+    }
+    if (lane == 63) {
+        s_sum[wv] = inc;
+        s_lo[wv] = sl;
+        if (OUT) {
+            s_prev[wv] = prev;
+            s_min[wv] = mn;
+        }
+    }
+    if (t == 0) s_n = s_el = s_big = 0;
+    __syncthreads();
+    ex = inc - ex;
+    u32 cnt = 0, before = 0;
+#pragma unroll
+    for (u32 w = 0; w < MW_NT / 64; w++) {
+        if (w < wv) ex += s_sum[w];
+        cnt += s_sum[w];
+        before += s_lo[w];  // keys of the group before this tile
+        if (OUT) {
+            prev = s_prev[w] > prev ? s_prev[w] : prev;
+            mn = s_min[w] < mn ? s_min[w] : mn;
+        }
+    }
+#pragma unroll
+    for (u32 q = 0; q < R; q++) {
+        if (R * t + q < kg) woff[R * t + q] = ex;
+        ex += nr[q];
+    }
+    if (t == 0) woff[kg] = cnt;
+    if (cnt == 0) return;  // (uniform)
+    __syncthreads();
+    const u32 X = M.ps[j0] + before;  // the tile's first output (level 0: in output space as well)
+    const u32 C = OUT ? W.Cg[g] : 0u;
+    // source of window element u: its run (of the group) and position in the run
+    auto run_at = [&](u32 u) { return mw_find(woff, kg, u); };
+    if (cnt > MW_CAP) {  // (uniform)
+        if (!OUT) {
+            const u64 low = row ? mw_threshold(M, j0, kg, row, M.ts[g + 1] - M.ts[g]) : 0ull;
+            for (u32 e = t; e < cnt; e += MW_NT) W.keys[X + e] = low;
+        } else {
+            // keys and entries into the sort's second pair (the first still
+            // holds the runs' keys)
+            for (u32 e = t; e < cnt; e += MW_NT) {
+                const u32 r = run_at(e), i = wlo[r] + (e - woff[r]);
+                W.s.keyB[X + e] = M.K[M.ps[j0 + r] + i];
+                W.s.valB[X + e] = W.rbeg[j0 + r] + i;
+            }
+            if (t == 0) {
+                W.O.lcp[X] = before ? key_lcp(prev, mn, C) : 0u;
+                mw_route(W, Seg{X, X + cnt, C, SEG_INB});
+            }
+        }
+        return;
+    }
+    for (u32 e = t; e < cnt; e += MW_NT) {
+        const u32 r = run_at(e);
+        sk[e] = M.K[M.ps[j0 + r] + wlo[r] + (e - woff[r])];
+        if (OUT) si[e] = (u16)e;
+    }
+    __syncthreads();
+    const u32 ipt = ((cnt + MW_NT - 1) / MW_NT) | 1u;
+    const u32 x0 = t * ipt;
+    for (u32 lv = 0; (1u << lv) < kg; lv++) {  // (uniform)
+        u64 k[MW_IPT];
+        u16 v[MW_IPT];
+        // lists of 2^lv windows: bounds of list i
+        auto at = [&](u32 i) { const u32 w = i << lv; return woff[w < kg ? w : kg]; };
+        if (x0 < cnt) {
+            u32 lo = 0, hi = (kg + (2u << lv) - 1) >> (lv + 1);  // largest pair starting at or before x0
+            while (hi - lo > 1) {
+                const u32 mid = (lo + hi) >> 1;
+                if (at(2 * mid) <= x0) lo = mid;
+                else hi = mid;
+            }
+            u32 p = lo;
+            u32 pb = at(2 * p), pa = at(2 * p + 1), pe = at(2 * p + 2);
+            const u32 d = x0 - pb, na = pa - pb, nb = pe - pa;
+            lo = d > nb ? d - nb : 0u;
+            hi = d < na ? d : na;
+            while (lo < hi) {
+                const u32 mid = (lo + hi) >> 1;
+                if (sk[pb + mid] <= sk[pa + d - 1 - mid]) lo = mid + 1;
+                else hi = mid;
+            }
+            u32 i = pb + lo, j = pa + d - lo;
+            u64 ka = i < pa ? sk[i] : 0ull, kb = j < pe ? sk[j] : 0ull;
+#pragma unroll
+            for (u32 q = 0; q < MW_IPT; q++) {
+                if (q < ipt && x0 + q < cnt) {
+                    while (i == pa && j == pe) {  // the next pair
+                        p++;
+                        pb = pe;
+                        pa = at(2 * p + 1);
+                        pe = at(2 * p + 2);
+                        i = pb;
+                        j = pa;
+                        ka = i < pa ? sk[i] : 0ull;
+                        kb = j < pe ? sk[j] : 0ull;
+                    }
+                    const bool first = j >= pe || (i < pa && ka <= kb);
+                    const u32 src = first ? i : j;
+                    k[q] = first ? ka : kb;
+                    if (OUT) v[q] = si[src];
+                    i += first ? 1u : 0u;
+                    j += first ? 0u : 1u;
+                    const u32 nx = src + 1;
+                    const u64 kn = nx < (first ? pa : pe) ? sk[nx] : 0ull;
+                    ka = first ? kn : ka;
+                    kb = first ? kb : kn;
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < MW_IPT; q++)
+            if (q < ipt && x0 + q < cnt) {
+                sk[x0 + q] = k[q];
+                if (OUT) si[x0 + q] = v[q];
+            }
+        __syncthreads();
+    }
+    if (!OUT) {
+        for (u32 e = t; e < cnt; e += MW_NT) W.keys[X + e] = sk[e];
+        return;
+    }
+    // first of the elements equal to element e (strides that double, then halve:
+    // most tied runs are short)
+    auto first_equal = [&](u32 e, u64 key) {
+        u32 s = 1;
+        for (; s <= e && sk[e - s] == key; s <<= 1) e -= s;
+        for (s >>= 1; s; s >>= 1)
+            if (s <= e && sk[e - s] == key) e -= s;
+        return e;
+    };
+    u32 lasts = 0, it = 0;  // bit per element of this thread: the last of a tied run from several runs
+    for (u32 e = t; e < cnt; e += MW_NT, it++) {
+        const u64 kb = sk[e];
+        const u32 u = si[e], r = run_at(u), i = wlo[r] + (u - woff[r]), G = W.rbeg[j0 + r] + i;
+        const u32 x = X + e;
+        const u32 c8 = (u32)(kb & 0xFF);
+        const u64 ka = e ? sk[e - 1] : prev;
+        u32 l;
+        bool tied = false;  // with a neighbour
+        if (e == 0) {
+            l = before ? key_lcp(ka, kb, C) : 0u;
+        } else if (ka != kb) {
+            l = key_lcp(ka, kb, C);
+        } else if (c8 < 8) {
+            l = C + c8;
+        } else {
+            l = W.fc_lcp[G];  // (right if the predecessor is of the same run: then it is entry G - 1)
+            tied = true;
+        }
+        W.O.id[x] = W.O.fc_id[G];
+        if (W.O.src) W.O.src[x] = ((u64)W.rrun[j0 + r] << 32) | i;
+        if (W.O.len) W.O.len[x] = W.O.fc_len[G];
+        W.O.lcp[x] = l;
+        const bool next = c8 == 8 && e + 1 < cnt && sk[e + 1] == kb;
+        if (tied || next) {
+            // the tied run's ends
+            const u32 a = first_equal(e, kb);
+            u32 y = e, s = 1;
+            for (; y + s < cnt && sk[y + s] == kb; s <<= 1) y += s;
+            for (s >>= 1; s; s >>= 1)
+                if (y + s < cnt && sk[y + s] == kb) y += s;
+            if (run_at(si[a]) != run_at(si[y])) {
+                // (with what a comparison needs of it, read here where the
+                // windows' entries are neighbours)
+                W.order[x] = G;
+                W.s.keyB[x] = W.suf_off[G];
+                W.s.mpr[x] = make_uint2(W.fc_len[G], W.fc_lcp[G]);
+                if (e == y) lasts |= 1u << it;
+            }
+        }
+    }
+    if (__syncthreads_or(lasts != 0)) {
+        for (int pass = 0; pass < 2; pass++) {  // counted, then written
+            for (u32 m = lasts; m; m &= m - 1) {
+                const u32 e = t + MW_NT * (u32)(__ffs((int)m) - 1);
+                const u32 a = first_equal(e, sk[e]);
+                const u32 slot = atomicAdd(&s_n, 1u);
+                if (pass == 0) {
+                    atomicAdd(&s_el, e + 1 - a);
+                    if (e + 1 - a > TIE_SMALL) s_big = 1;
+                } else W.ties[s_base + slot] = Seg{X + a, X + e + 1, C + 7, TIE_REC};
+            }
+            __syncthreads();
+            if (pass == 0 && t == 0) {
+                s_base = atomicAdd(&W.s.ctr[C_RNEXT], s_n);
+                atomicAdd(&W.s.ctr[C_RELEM], s_el);
+                if (s_big) W.s.ctr[C_TIEBIG] = 1;
+                s_n = 0;
+            }
+            __syncthreads();
+        }
     }
 }
 
-// The results straight from the elements, where no merge level runs (every
-// group holds at most one non-empty run).
-__global__ void k_merge_out(const u32 *G, const u32 *L, u32 n_out, MergeOut O)
+// Groups of more runs than a tile merge takes: all their elements as one
+// segment each, the keys where the scan left them (run order is output order).
+__global__ __launch_bounds__(256) void k_mw_whole(const u32 *wg, u32 nwg, const u32 *gs, const u32 *ps, u32 kc,
+                                                  u32 n_out, MwOut W)
 {
-    const u32 x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= n_out) return;
-    merge_emit(O, x, G[x], L[x]);
+    for (u32 x = blockIdx.x * blockDim.x + threadIdx.x; x < n_out; x += gridDim.x * blockDim.x) {
+        const u32 j = mw_find(ps, kc, x);
+        u32 lo = 0, hi = nwg;  // whether run j's group is one of them
+        while (lo < hi) {
+            const u32 mid = (lo + hi) >> 1;
+            if (gs[wg[mid] + 1] <= j) lo = mid + 1;
+            else hi = mid;
+        }
+        if (lo >= nwg || gs[wg[lo]] > j) continue;
+        const u32 g = wg[lo];
+        W.order[x] = W.rbeg[j] + (x - ps[j]);
+        if (x == ps[gs[g]]) {
+            const u32 cnt = ps[gs[g + 1]] - x;
+            W.O.lcp[x] = 0;
+            mw_route(W, Seg{x, x + cnt, W.Cg[g], 0});
+        }
+    }
+}
+
+// ---- tied keys
+//
+// Segments of outputs whose strings agree up to the segment's depth, in (run,
+// position) order; order[x] = the front-coded entry at output x.  Eight lanes
+// per 16 members.
+
+#define TIE_T 16  // members of a segment per eight lanes
+
+// A front-coded entry and what a comparison needs of it.
+struct FcEl {
+    u32 g, d, e;
+    u64 so;
+};
+
+__device__ __forceinline__ FcEl fc_el(const FcView &V, u32 g) { return FcEl{g, V.d[g], V.e[g], V.suf_off[g]}; }
+
+__device__ __forceinline__ FcEl fc_el_shfl(const FcEl &a, u32 src)  // within eight lanes
+{
+    return FcEl{__shfl(a.g, src, 8), __shfl(a.d, src, 8), __shfl(a.e, src, 8), __shfl(a.so, src, 8)};
+}
+
+// fc_cmp by eight lanes with the same arguments, 128 bytes a step.
+__device__ __forceinline__ int fc_cmp8(const FcView &V, const FcEl &X, const FcEl &Y, u64 from, u32 gl, u64 *lcp)
+{
+    const u32 x = X.g, y = Y.g, ex = X.e, ey = Y.e;
+    const u64 lx = X.d, ly = Y.d, sx = X.so, sy = Y.so;
+    const u64 m = lx < ly ? lx : ly;
+    u64 i = from < m ? from : m;
+    while (i < m) {
+        u64 px, ax, py, ay;  // the pieces that hold byte i
+        if (ex <= i) { px = sx + (i - ex); ax = lx - i; }
+        else fc_piece(V, x, i, &px, &ax);
+        if (ey <= i) { py = sy + (i - ey); ay = ly - i; }
+        else fc_piece(V, y, i, &py, &ay);
+        u64 run = ax < ay ? ax : ay;
+        run = run < m - i ? run : m - i;
+        for (u64 c = 0; c < run; c += 128) {
+            const u64 q = c + 16 * gl;
+            const u32 take = q < run ? (run - q < 16 ? (u32)(run - q) : 16u) : 0u;
+            const Win16 ra = win16_issue(V.suf, V.sufN, px + q, take), rb = win16_issue(V.suf, V.sufN, py + q, take);
+            u64 a0, a1, b0, b1;
+            win16_finish(V.suf, ra, a0, a1);
+            win16_finish(V.suf, rb, b0, b1);
+            const u64 d0 = a0 ^ b0, d1 = a1 ^ b1;
+            u32 f = 0xFFFFFFFFu;  // 2 (first differing byte) + (y smaller)
+            if (d0 | d1) {
+                const u64 d = d0 ? d0 : d1;
+                const u32 at = (u32)(__builtin_ctzll(d) >> 3);
+                const u32 av = (u32)((d0 ? a0 : a1) >> (8 * at)) & 0xFFu, bv = (u32)((d0 ? b0 : b1) >> (8 * at)) & 0xFFu;
+                f = (16 * gl + (d0 ? 0u : 8u) + at) * 2 + (av < bv ? 0u : 1u);
+            }
+#pragma unroll
+            for (int s = 1; s < 8; s <<= 1) {
+                const u32 z = __shfl_xor(f, s, 8);
+                f = z < f ? z : f;
+            }
+            if (f != 0xFFFFFFFFu) {
+                *lcp = i + c + (f >> 1);
+                return (f & 1) ? 1 : -1;
+            }
+        }
+        i += run;
+    }
+    *lcp = m;
+    return lx < ly ? -1 : (lx > ly ? 1 : 0);
+}
+
+// Tile counts of a list of segments; their comparison words (see k_tie_compare)
+// and the counters of the lists the round builds are reset.
+__global__ void k_tie_tiles(const Seg *list, u32 cnt, u32 *tiles, u64 *cmp, u32 *ctr)
+{
+    const u32 j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < cnt) {
+        tiles[j] = (list[j].end - list[j].begin + TIE_T - 1) / TIE_T;
+        if (cmp) cmp[j] = ~0ull;
+    }
+    if (ctr && j < C_NCTR) ctr[j] = 0;
+}
+
+// Segments of up to TIE_SMALL members (most are two equal strings), eight lanes
+// each: every pair is compared, a member's rank is the number before it and its
+// LCP the largest with one of those.  (Neighbours of one run -- which share the key, unlike a run end and the next start -- need no comparison:
+// their LCP is the run's.)  The tile merge has written the results in (run,
+// position) order, so those of members that stay where they are -- all of an
+// equal run's -- are final, the others are written again here.  Larger segments
+// are passed on to `big` (C_RNEXT of them, C_RELEM elements).
+//
+// Bounded by the latency of scattered reads (entry, then its length, LCP and
+// offset, then the bytes, 128 a step).  The ties of 4M text strings in 16 x 16
+// runs took about 1.9 ms inside the former pairwise merge, where one lane's
+// comparison held up its wavefront, and about 0.3 ms so.
+__global__ __launch_bounds__(256) void k_tie_small(const Seg *list, u32 cnt, FcView V, u32 *order, const u64 *rso,
+                                                   const uint2 *rde, MergeOut O, Seg *big, u32 *ctr)
+{
+    __shared__ u32 s_n, s_el, s_base;
+    if (threadIdx.x == 0) s_n = s_el = 0;
+    __syncthreads();
+    const u32 s = blockIdx.x * 32 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
+    Seg g{0, 0, 0, 0};
+    if (s < cnt) g = list[s];
+    const u32 m = g.end - g.begin;
+    u32 slot = 0;
+    const bool pass = m > TIE_SMALL && gl == 0;
+    if (pass) {
+        slot = atomicAdd(&s_n, 1u);
+        atomicAdd(&s_el, m);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_n) {
+        s_base = atomicAdd(&ctr[C_RNEXT], s_n);
+        atomicAdd(&ctr[C_RELEM], s_el);
+    }
+    __syncthreads();
+    if (pass) big[s_base + slot] = g;
+    // (no barrier from here on: a wavefront with long strings holds up no other)
+    if (m && m <= TIE_SMALL) {
+        FcEl E{0, 0, 0, 0};
+        if (gl < m) {
+            const u32 p = g.begin + gl;
+            if (g.aux & TIE_REC) {
+                const uint2 de = rde[p];
+                E = FcEl{order[p], de.x, de.y, rso[p]};
+            } else {
+                E = fc_el(V, order[p]);
+            }
+        }
+        u32 rank = 0, mx = 0;
+        for (u32 i = 0; i + 1 < m; i++) {
+            const FcEl A = fc_el_shfl(E, i);
+            for (u32 j = i + 1; j < m; j++) {
+                const FcEl B = fc_el_shfl(E, j);
+                u64 l = B.e;
+                const bool nb = B.g == A.g + 1 && B.e >= g.depth;
+                const bool after = !nb && fc_cmp8(V, A, B, g.depth, gl, &l) > 0;  // i after j
+                if (gl == (after ? i : j)) {
+                    rank++;
+                    mx = (u32)l > mx ? (u32)l : mx;
+                }
+            }
+        }
+        if (gl < m) {
+            const u32 p = g.begin + rank;
+            if (rank) O.lcp[p] = mx;
+            if (rank != gl) {
+                order[p] = E.g;
+                if (g.aux & TIE_REC) merge_emit(O, p, E.g);  // (else: with the larger segment it came from)
+            }
+        }
+    }
+}
+
+// Members of larger segments against the segment's first: the minimum over a
+// segment of 2 LCP + (equal) says how far all agree and whether all are equal.
+__global__ __launch_bounds__(256) void k_tie_compare(const Seg *list, const u32 *tiles, u32 cnt, FcView V,
+                                                     const u32 *order, u64 *cmp)
+{
+    const u32 t = blockIdx.x * 32 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
+    if (t >= tiles[cnt]) return;
+    const u32 s = seg_of_tile(tiles, cnt, t);
+    const Seg g = list[s];
+    const u32 p0 = g.begin + (t - tiles[s]) * TIE_T, p1 = g.end < p0 + TIE_T ? g.end : p0 + TIE_T;
+    const FcEl F = fc_el(V, order[g.begin]);
+    FcEl E[TIE_T / 8];
+#pragma unroll
+    for (u32 h = 0; h < TIE_T / 8; h++) E[h] = fc_el(V, order[p0 + 8 * h + gl < p1 ? p0 + 8 * h + gl : p0]);
+    u64 best = ~0ull;
+#pragma unroll
+    for (u32 h = 0; h < TIE_T / 8; h++)
+        for (u32 q = 0; q < 8 && p0 + 8 * h + q < p1; q++) {
+            if (p0 + 8 * h + q == g.begin) continue;
+            u64 l;
+            const int r = fc_cmp8(V, F, fc_el_shfl(E[h], q), g.depth, gl, &l);
+            const u64 w = 2 * l + (r == 0 ? 1u : 0u);
+            best = w < best ? w : best;
+        }
+    if (gl == 0 && best != ~0ull) atomicMin((unsigned long long *)&cmp[s], (unsigned long long)best);
+}
+
+// The larger segments after their comparison: equal strings are done (LCP =
+// length, in order already); of the others the keys at their exact common
+// prefix are written and the segment goes to the sort of its size.
+__global__ __launch_bounds__(256) void k_tie_keys(const Seg *list, const u32 *tiles, u32 cnt, FcView V,
+                                                  const u32 *order, u32 *lcp, const u64 *cmp, SortWs w, SortShape z)
+{
+    const u32 t = blockIdx.x * 32 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
+    if (t >= tiles[cnt]) return;
+    const u32 s = seg_of_tile(tiles, cnt, t);
+    const Seg g = list[s];
+    const u32 m = g.end - g.begin;
+    const u32 lt = t - tiles[s];
+    const u32 p0 = g.begin + lt * TIE_T, p1 = g.end < p0 + TIE_T ? g.end : p0 + TIE_T;
+    const u64 c = cmp[s];
+    const u64 dep = c >> 1;
+    if (c & 1) {
+        for (u32 p = p0 + gl; p < p1; p += 8)
+            if (p > g.begin) lcp[p] = (u32)dep;
+        return;
+    }
+    for (u32 p = p0 + gl; p < p1; p += 8) {
+        const u32 G = order[p];
+        const u64 d = V.d[G];
+        u64 v = 0;
+        u64 i = dep;
+        const u64 e = d < dep + 7 ? d : dep + 7;
+        while (i < e) {  // the pieces of [dep, dep + 7)
+            u64 pos, av;
+            fc_piece(V, G, i, &pos, &av);
+            const u32 take = (u32)(av < e - i ? av : e - i);
+            v |= load_be(V.suf, V.sufN, pos, take) >> (8 * (i - dep));
+            i += take;
+        }
+        w.keyA[p] = v | (d - dep < 8 ? d - dep : 8ull);
+    }
+    if (lt == 0 && gl == 0) {
+        const Seg o{g.begin, g.end, (u32)dep, 0};
+        if (m <= WS_MAX) {
+            w.tiny[atomicAdd(&w.ctr[C_TINY], 1u)] = o;
+            atomicAdd(&w.ctr[C_TINYN], m);
+        } else if (m <= z.block_max) {
+            if (m <= BS_SMALL) w.small[atomicAdd(&w.ctr[C_SMALL], 1u)] = o;
+            else w.mid[atomicAdd(&w.ctr[C_MID], 1u)] = o;
+            atomicAdd(&w.ctr[C_SMALLN], m);
+        } else {
+            w.largeA[atomicAdd(&w.ctr[C_LARGE], 1u)] = o;
+            atomicAdd(&w.ctr[C_LTILES], (m + z.tile - 1) / z.tile);
+            atomicAdd(&w.ctr[C_LELEM], m);
+        }
+    }
+}
+
+// The results of the tied elements, once their order is final.
+__global__ __launch_bounds__(256) void k_tie_emit(const Seg *list, const u32 *tiles, u32 cnt, const u32 *order,
+                                                  MergeOut O)
+{
+    const u32 t = blockIdx.x * 32 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
+    if (t >= tiles[cnt]) return;
+    const u32 s = seg_of_tile(tiles, cnt, t);
+    const Seg g = list[s];
+    const u32 p0 = g.begin + (t - tiles[s]) * TIE_T, p1 = g.end < p0 + TIE_T ? g.end : p0 + TIE_T;
+    for (u32 p = p0 + gl; p < p1; p += 8) merge_emit(O, p, order[p]);
 }
 
 // Host-plan header: [0] check flag, [1] literal-buffer size, [2, 2+k) run
@@ -1734,35 +2134,35 @@ __global__ __launch_bounds__(256) void k_check_merge_runs(const u64 *rb, const u
 
 struct MergeWs {
     DecWs dec;
-    u32 *G0, *G1, *L0, *L1, *F0, *F1, *pc, *tstart, *sid, *pg, *Cg, *rgroup, *rep, *split, *runmin, *bfirst, *ties;
+    SortWs sort;  // (its key arrays hold the merge's keys and samples before any tie is sorted)
+    u32 *sid, *plan, *Cg, *rgroup, *rep, *runmin, *bfirst, *ties, *order, *tiles;
+    Seg *segs, *over, *big;
     MOp *mblk;
-    u8 *pfirst;
-    u64 *PA0, *PA1, *PB1, *P, *sb, *K0, *K1;
+    u64 *P, *sb;
 };
 
 #define MERGE_MAX_K 65536
-// merge plan entries over all levels: <= 2k pairs plus one copy-through entry
-// per group and level (<= 18 levels)
-#define MERGE_PCAP(k) (20 * (size_t)(k) + 4)
+// words of the merge plan: per level run starts, tile starts and bounds starts;
+// the group starts, runs and their front-coded starts, groups taken whole
+#define MERGE_PLAN(k) ((3 * (size_t)MW_LEVELS + 6) * ((size_t)(k) + 4))
 
 static void merge_layout(u64 n_out, u64 n_fc, u64 k, MergeWs *w, WsArena *a, WsCounter *c)
 {
     dec_layout(n_fc, &w->dec, a, c);
+    sort_ws_layout(n_out, &w->sort, a, c);
 #define MT(field, T, cnt)                       \
     do {                                         \
         if (a) w->field = a->take<T>(cnt);       \
         else c->take<T>(cnt);                    \
     } while (0)
-    MT(G0, u32, n_out); MT(G1, u32, n_out); MT(L0, u32, n_out); MT(L1, u32, n_out);
-    MT(F0, u32, n_out); MT(F1, u32, n_out); MT(K0, u64, n_out); MT(K1, u64, n_out);
-    // host-planned arrays, in two contiguous blocks (each uploaded in one copy)
+    // host-planned arrays, in one contiguous block (uploaded in one copy)
     MT(P, u64, k + 2); MT(sb, u64, k + 2); MT(sid, u32, k + 2); MT(rgroup, u32, k + 2); MT(rep, u32, k + 2);
-    MT(PA0, u64, MERGE_PCAP(k)); MT(PA1, u64, MERGE_PCAP(k)); MT(PB1, u64, MERGE_PCAP(k));
-    MT(pg, u32, MERGE_PCAP(k)); MT(tstart, u32, MERGE_PCAP(k) + 64);
-    MT(Cg, u32, k + 2); MT(pc, u32, MERGE_PCAP(k)); MT(pfirst, u8, MERGE_PCAP(k));
-    MT(split, u32, n_out / MW_TILE + MERGE_PCAP(k) + 64);  // tiles of one level
+    MT(plan, u32, MERGE_PLAN(k));
+    MT(Cg, u32, k + 2);
     MT(runmin, u32, k + 2); MT(mblk, MOp, n_out / MS_ITEMS + 2); MT(bfirst, u32, n_out / MS_ITEMS + 2);
     MT(ties, u32, 4);
+    MT(order, u32, n_out); MT(segs, Seg, n_out / 2 + 2); MT(tiles, u32, n_out / 2 + 3);
+    MT(over, Seg, n_out / (MW_CAP + 1) + k + 2); MT(big, Seg, n_out / TIE_SMALL + 2);
 #undef MT
 }
 
@@ -1929,17 +2329,8 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
         return SS_ERR_WORKSPACE;
     }
 
-    // Strings are compared without decoding them, along psv chains over the
-    // whole front-coded array (built after the scan below).  Every comparison
-    // of two elements past their cached keys starts at byte C+7 or later of
-    // their group (the group depth compares run heads, whose e is 0), and a
-    // chain walk for byte i starts only at an entry with e > i: none takes
-    // place unless the scan finds adjacent strings of a run that share C+7
-    // bytes, and the chains are built only then.
-    k_fill_u32<<<1, 64, 0, st>>>(w.ties, 0u, 1);
-    SS_CHECK_LAUNCH();
     const FcView V{fc_lcp, fc_len, w.dec.psv, suf_off, suf, sufN};
-    // group of every run, first non-empty run of every group, group depths, keys
+    // group of every run, first non-empty run of every group
     std::vector<u32> rg(k), rep(groups, 0);
     for (u32 g = 0; g < groups; g++) {
         bool found = false;
@@ -1948,113 +2339,256 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
             if (!found && re[j] > rb[j]) { rep[g] = j; found = true; }
         }
     }
+    // The plan of the merge by key: the non-empty runs, and per level of the
+    // key lists their starts, tiles and bounds.
+    std::vector<u32> plan;
+    struct Lv { size_t ps, ts, bo; u32 tiles, bounds; };
+    std::vector<Lv> lv;
+    std::vector<u32> gs(groups + 1), whole;
+    std::vector<u64> len;  // of every non-empty run in the current level
+    std::vector<u32> rrun, rbeg;
+    for (u32 g = 0; g < groups; g++) {
+        gs[g] = (u32)rrun.size();
+        for (u32 j = go[g]; j < go[g + 1]; j++)
+            if (re[j] > rb[j]) {
+                rrun.push_back(j);
+                rbeg.push_back((u32)rb[j]);
+                len.push_back(re[j] - rb[j]);
+            }
+    }
+    const u32 kc = (u32)rrun.size();
+    gs[groups] = kc;
+    u32 nsample = 0;
+    bool few = true, ranked = false, leveled = false;
+    for (u32 v = 0; v < MW_LEVELS; v++) {
+        Lv L{plan.size(), 0, 0, 0, 0};
+        u32 at = v < 2 ? 0u : nsample;  // (levels 1, 2, ... lie behind each other in the sample array)
+        for (u32 j = 0; j < kc; j++) { plan.push_back(at); at += (u32)len[j]; }
+        plan.push_back(at);
+        if (v) nsample = at;
+        L.ts = plan.size();
+        std::vector<u32> bo(groups + 1);
+        bool more = false;
+        for (u32 g = 0; g < groups; g++) {
+            const u32 kg = gs[g + 1] - gs[g];
+            u64 tot = 0, ns = 0;
+            for (u32 j = gs[g]; j < gs[g + 1]; j++) { tot += len[j]; ns += mw_samples(len[j], j - gs[g], kg); }
+            plan.push_back(L.tiles);
+            bo[g] = L.bounds;
+            u32 nt = 1;
+            if (tot > MW_CAP && ns) nt = (u32)ceil_div(tot, MW_TILE);
+            // (a bounds matrix of a group must fit two words per key)
+            const bool take = kg <= MW_RUNS && (v || (nt + 1) * (u64)kg <= 2 * tot);
+            if (v == 0 && tot) few &= !take || kg <= MW_FEW;
+            if (v == 1 && tot) (kg <= MW_RANK ? ranked : leveled) = true;
+            if (tot == 0 || !take || (v == 1 && kg <= MW_RANK)) {
+                if (v == 0 && tot && !take) whole.push_back(g);
+                for (u32 j = gs[g]; j < gs[g + 1]; j++) len[j] = 0;
+                continue;
+            }
+            if (tot > MW_CAP) {
+                more |= ns > 0;
+                for (u32 j = gs[g]; j < gs[g + 1]; j++) len[j] = mw_samples(len[j], j - gs[g], kg);
+            } else {
+                for (u32 j = gs[g]; j < gs[g + 1]; j++) len[j] = 0;
+            }
+            L.tiles += nt;
+            L.bounds += (nt + 1) * kg;
+        }
+        plan.push_back(L.tiles);
+        L.bo = plan.size();
+        bo[groups] = L.bounds;
+        plan.insert(plan.end(), bo.begin(), bo.end());
+        lv.push_back(L);
+        if (!more) break;
+    }
+    const size_t p_gs = plan.size();
+    plan.insert(plan.end(), gs.begin(), gs.end());
+    const size_t p_rrun = plan.size();
+    plan.insert(plan.end(), rrun.begin(), rrun.end());
+    const size_t p_rbeg = plan.size();
+    plan.insert(plan.end(), rbeg.begin(), rbeg.end());
+    const size_t p_whole = plan.size();
+    plan.insert(plan.end(), whole.begin(), whole.end());
+    plan.resize(p_whole + groups);
+    // (the samples and their merge share the mismatch words' array, the bounds
+    // the boundary list: about n / 7 keys and at most 2 n words)
+    if (plan.size() > MERGE_PLAN(k) || 2ull * nsample > n_out) {
+        ss_set_error("internal: merge plan exceeds its workspace");
+        return SS_ERR_INVALID_ARG;
+    }
+    for (const Lv &L : lv)
+        if (L.bounds > 2 * n_out) {
+            ss_set_error("internal: merge bounds exceed their workspace");
+            return SS_ERR_INVALID_ARG;
+        }
     {
         const UpPart parts[] = {{w.P, P.data(), sizeof(u64) * (k + 1)},
                                 {w.sb, sbv.data(), sizeof(u64) * kne},
                                 {w.sid, sidv.data(), sizeof(u32) * kne},
                                 {w.rgroup, rg.data(), sizeof(u32) * k},
-                                {w.rep, rep.data(), sizeof(u32) * groups}};
-        SS_TRY(upload_parts(parts, 5, st));
+                                {w.rep, rep.data(), sizeof(u32) * groups},
+                                {w.plan, plan.data(), sizeof(u32) * plan.size()}};
+        SS_TRY(upload_parts(parts, 6, st));
     }
-    SS_HIP(hipMemsetAsync(w.Cg, 0xFF, sizeof(u32) * groups, st));
-    SS_HIP(hipMemsetAsync(w.runmin, 0xFF, sizeof(u32) * k, st));
-    k_run_min<<<dim3(k, RM_PARTS), 256, 0, st>>>(run_begin, w.P, fc_lcp, w.runmin);
+    SortWs &sw = w.sort;
+    const u32 nb = (u32)ceil_div(n_out, MS_ITEMS);
+    const u32 ni = std::max(std::max(nb, k), std::max(groups, (u32)C_NCTR));
+    k_merge_init<<<(unsigned)ceil_div(ni, 256), 256, 0, st>>>(w.P, k, nb, w.bfirst, w.runmin, w.Cg, groups, w.ties,
+                                                             sw.ctr);
+    SS_CHECK_LAUNCH();
+    const u64 rparts = ceil_div(n_out, (u64)k * 4096);
+    k_run_min<<<dim3(k, (unsigned)(rparts < 64 ? rparts : 64)), 256, 0, st>>>(run_begin, w.P, fc_lcp, w.runmin);
     SS_CHECK_LAUNCH();
     k_group_depth<<<(unsigned)ceil_div(k, 64), 64, 0, st>>>(run_begin, w.P, w.rgroup, w.rep, k, w.runmin, V, w.Cg);
     SS_CHECK_LAUNCH();
+    u32 *const unsorted = sw.ctr + C_BADSET;
+    u64 *K = sw.keyA, *KS = sw.mword, *KM = sw.mword + nsample;
+    u32 *bounds = (u32 *)sw.bnd;
     {
-        // front-coded LCP, length, literal offset and up to 7 literal bytes in (twice), state out
-        SS_PROF("k_mscan", st, (double)n_out * (2.0 * 24.0 + 20.0));
+        // front-coded LCP, length, literal offset and up to 7 literal bytes in, LCP once more, key out
+        SS_PROF("k_mscan", st, (double)n_out * (28.0 + 8.0));
         const MScan S{run_begin, w.P, w.rgroup, w.Cg, w.bfirst, k, (u32)n_out, V, w.ties};
-        const u32 nb = (u32)ceil_div(n_out, MS_ITEMS);
-        k_block_runs<<<(unsigned)ceil_div(k, 256), 256, 0, st>>>(w.P, k, nb, w.bfirst);
-        SS_CHECK_LAUNCH();
         k_mscan_reduce<<<nb, 256, 0, st>>>(S, w.mblk);
         SS_CHECK_LAUNCH();
         k_mscan_top<<<1, 1024, 0, st>>>(w.mblk, nb);
         SS_CHECK_LAUNCH();
-        k_mscan_apply<<<nb, 256, 0, st>>>(S, w.mblk, w.G0, w.L0, w.F0, w.K0);
+        k_mscan_apply<<<nb, 256, 0, st>>>(S, w.mblk, K, unsorted);
     }
     SS_CHECK_LAUNCH();
-    SS_TRY(psv_build(fc_lcp, n_fc, w.dec.psv, w.dec.tree, w.dec.cmin, w.dec.far, w.dec.fcnt, st, w.ties));
-    u32 *G = w.G0, *L = w.L0, *F = w.F0, *Go = w.G1, *Lo = w.L1, *Fo = w.F1;
-    u64 *K = w.K0, *Ko = w.K1;
-    std::vector<u32> pgv;
-    // segments of the output space per group
-    std::vector<std::vector<std::pair<u64, u64>>> segs(groups);
-    for (u32 g = 0; g < groups; g++)
-        for (u32 j = go[g]; j < go[g + 1]; j++) segs[g].push_back({P[j], P[j + 1]});
-    std::vector<u64> pa0, pa1, pb1;
-    std::vector<u32> ts;
-    // plan every level on the host, upload the plan once, launch all levels
-    struct LevelPlan { size_t off, ts_off; u32 npt; };
-    std::vector<LevelPlan> plan;
-    std::vector<u32> tsv;
-    for (;;) {
-        bool more = false;
-        for (auto &sg : segs) more |= sg.size() > 1;
-        if (!more) break;
-        LevelPlan L0{pa0.size(), tsv.size(), 0};
-        tsv.push_back(0);
-        std::vector<std::vector<std::pair<u64, u64>>> nxt(groups);
-        for (u32 g = 0; g < groups; g++) {
-            auto &sg = segs[g];
-            for (size_t m = 0; m < sg.size(); m += 2) {
-                const u64 A0 = sg[m].first, A1 = sg[m].second;
-                const u64 B1 = (m + 1 < sg.size()) ? sg[m + 1].second : A1;
-                nxt[g].push_back({A0, B1});
-                if (sg.size() == 1 && A1 == A0) continue;  // empty finished group: nothing to move
-                // pairs, odd runs and finished groups (copied through to the other buffer)
-                pa0.push_back(A0); pa1.push_back(A1); pb1.push_back(B1); pgv.push_back(g);
-                const u64 sz = B1 - A0;
-                tsv.push_back(tsv.back() + (u32)ceil_div(sz ? sz : 1, MW_TILE));
-            }
+    const u32 *pl = w.plan, *gsd = pl + p_gs;
+    const u32 nl = (u32)lv.size() - 1;  // sample levels
+    if (nl && nsample) {
+        for (u32 v = 1; leveled && v <= nl; v++) {
+            const u32 tot = plan[lv[v].ps + kc] - plan[lv[v].ps];
+            if (!tot) continue;
+            k_mw_sample<<<(unsigned)ceil_div(tot, 256), 256, 0, st>>>(K, pl + lv[0].ps, gsd, groups, kc, pl + lv[v].ps,
+                                                                     v, KS);
+            SS_CHECK_LAUNCH();
         }
-        L0.npt = (u32)(pa0.size() - L0.off);
-        plan.push_back(L0);
-        segs.swap(nxt);
-    }
-    const size_t npairs_all = pa0.size();
-    if (npairs_all > MERGE_PCAP(k)) {
-        ss_set_error("internal: merge plan exceeds its workspace");
-        return SS_ERR_INVALID_ARG;
-    }
-    if (npairs_all) {
-        const UpPart parts[] = {{w.PA0, pa0.data(), sizeof(u64) * npairs_all},
-                                {w.PA1, pa1.data(), sizeof(u64) * npairs_all},
-                                {w.PB1, pb1.data(), sizeof(u64) * npairs_all},
-                                {w.pg, pgv.data(), sizeof(u32) * npairs_all},
-                                {w.tstart, tsv.data(), sizeof(u32) * tsv.size()}};
-        SS_TRY(upload_parts(parts, 5, st));
+        if (ranked) {
+            const u32 tot = plan[lv[1].ps + kc];
+            k_mw_rank<<<(unsigned)ceil_div(tot, 256), 256, 0, st>>>(K, pl + lv[0].ps, pl + lv[1].ps, gsd, groups, kc,
+                                                                        KM, unsorted);
+            SS_CHECK_LAUNCH();
+        }
     }
     const MergeOut O{w.sb, w.sid, kne, fc_id, fc_len, out_src, out_id, out_lcp, out_len};
-    for (size_t li = 0; li < plan.size(); li++) {
-        const LevelPlan &lp = plan[li];
-        const bool last = li + 1 == plan.size();
-        MergeLevel M{G, L, F, Go, Lo, Fo, K, Ko, w.pg + lp.off, w.Cg, w.PA0 + lp.off, w.PA1 + lp.off,
-                     w.PB1 + lp.off, w.tstart + lp.ts_off, w.pc + lp.off, w.pfirst + lp.off, lp.npt, V};
-        const u32 nblk = tsv[lp.ts_off + lp.npt];
-        if (nblk > 0) {
-            k_merge_split<<<(unsigned)ceil_div(nblk, 64), 64, 0, st>>>(M, nblk, w.split);
-            SS_CHECK_LAUNCH();
-            if (last) {
-                // id, LCP, bound and key in, the string id gathered; id and LCP out
-                SS_PROF("k_merge_level", st, (double)n_out * 32.0);
-                k_merge_level<true><<<nblk, MW_NT, 0, st>>>(M, nblk, w.split, O);
-            } else {
-                // every element's id, LCP, bound and key read once and written once
-                SS_PROF("k_merge_level", st, (double)n_out * 40.0);
-                k_merge_level<false><<<nblk, MW_NT, 0, st>>>(M, nblk, w.split, O);
-            }
+    const SortShape z = sort_shape(n_out);
+    const MwOut W{KM, w.Cg, pl + p_rrun, pl + p_rbeg, fc_lcp, fc_len, suf_off, O, w.order, w.segs, w.over, sw, z.tile, z.block_max};
+    for (u32 v = nl + 1; v-- > 0;) {
+        const Lv &L = lv[v];
+        if (!L.tiles) continue;
+        const MwLevel M{v ? KS : K, pl + L.ps, gsd, pl + L.ts, pl + L.bo, KM, v < nl ? pl + lv[v + 1].ps : pl + L.ps,
+                        groups, bounds, unsorted};
+        k_mw_bounds<<<(unsigned)ceil_div(L.bounds, 256), 256, 0, st>>>(M, L.bounds);
+        SS_CHECK_LAUNCH();
+        if (v) {
+            if (few) k_mw_tile<false, MW_FEW><<<L.tiles, MW_NT, 0, st>>>(M, W);
+            else k_mw_tile<false, MW_RUNS><<<L.tiles, MW_NT, 0, st>>>(M, W);
+        } else {
+            // key, id, LCP bytes in; id and LCP out
+            SS_PROF("k_mw_tile", st, (double)n_out * 20.0);
+            if (few) k_mw_tile<true, MW_FEW><<<L.tiles, MW_NT, 0, st>>>(M, W);
+            else k_mw_tile<true, MW_RUNS><<<L.tiles, MW_NT, 0, st>>>(M, W);
         }
         SS_CHECK_LAUNCH();
-        std::swap(G, Go);
-        std::swap(L, Lo);
-        std::swap(F, Fo);
-        std::swap(K, Ko);
     }
-    if (plan.empty()) {
-        k_merge_out<<<(unsigned)ceil_div(n_out, 256), 256, 0, st>>>(G, L, (u32)n_out, O);
+    const u64 wb = ceil_div(n_out, 256);
+    auto take_whole = [&](u32 cnt) -> int {
+        k_mw_whole<<<(unsigned)(wb < 4096 ? wb : 4096), 256, 0, st>>>(pl + p_whole, cnt, gsd, pl + lv[0].ps, kc,
+                                                                      (u32)n_out, W);
+        SS_CHECK_LAUNCH();
+        return SS_OK;
+    };
+    if (!whole.empty()) SS_TRY(take_whole((u32)whole.size()));
+    u32 ctr[C_NCTR];
+    SS_TRY(ss_read_u32(sw.ctr, ctr, C_NCTR, st));
+    if (ctr[C_BADSET]) {
+        // runs that are not sorted: every group as one segment
+        whole.clear();
+        for (u32 g = 0; g < groups; g++)
+            if (gs[g + 1] > gs[g]) whole.push_back(g);
+        const UpPart parts[] = {{w.plan + p_whole, whole.data(), sizeof(u32) * whole.size()}};
+        SS_TRY(upload_parts(parts, 1, st));
+        k_fill_u32<<<1, 64, 0, st>>>(sw.ctr, 0u, C_NCTR);
+        SS_CHECK_LAUNCH();
+        SS_TRY(take_whole((u32)whole.size()));
+        SS_TRY(ss_read_u32(sw.ctr, ctr, C_NCTR, st));
+    }
+    const u32 nover = ctr[C_RTILES], eover = ctr[C_NELEM];
+    u32 nact = ctr[C_RNEXT], elems = ctr[C_RELEM];
+    const bool small_only = !nover && !ctr[C_TIEBIG];  // then the first round is the last: its counters aren't read
+    if (!nact && !nover) return SS_OK;
+    const SortJob J{nullptr, 0, nullptr, w.order, out_lcp, st, n_out, n_out};
+    if (nover) {
+        // segments too large for a tile: sorted by key, their ties join the others
+        k_fill_u32<<<1, 64, 0, st>>>(sw.ctr + C_NELEM, 0u, 1);
+        SS_CHECK_LAUNCH();
+        SS_TRY(sort_keyed(J, sw, ctr));
+        if (ctr[C_NEXT])
+            SS_HIP(hipMemcpyAsync(w.segs + nact, sw.nxt, sizeof(Seg) * ctr[C_NEXT], hipMemcpyDeviceToDevice, st));
+        nact += ctr[C_NEXT];
+        elems += ctr[C_NELEM];
+    }
+    // Tied keys.  Strings are compared without decoding them, along psv chains
+    // over the whole front-coded array.  A comparison starts at byte C + 7 or
+    // later of its group and a chain walk for byte i only at an entry with e >
+    // i: none takes place, and no chains are built, unless adjacent strings of
+    // a run share C + 7 bytes.
+    if (nact) SS_TRY(psv_build(fc_lcp, n_fc, w.dec.psv, w.dec.tree, w.dec.cmin, w.dec.far, w.dec.fcnt, st, w.ties));
+    auto tile_grid = [](u32 cnt, u32 el) { return (unsigned)ceil_div((u64)cnt + el / TIE_T, 32); };
+    auto tile_list = [&](const Seg *l, u32 cnt, u64 *cmp, u32 *c) -> int {
+        k_tie_tiles<<<(unsigned)ceil_div(cnt, 256), 256, 0, st>>>(l, cnt, w.tiles, cmp, c);
+        SS_CHECK_LAUNCH();
+        return ss_scan_exclusive<u32>(w.tiles, w.tiles, cnt, (u32 *)sw.scan_scratch, st);
+    };
+    // rounds: the list's small segments end; its large ones go to `big` -- the
+    // first round's stay there for the final emission -- and their ties, after
+    // a sort by the next keys, make the next list
+    const Seg *list = w.segs;
+    u32 nbig0 = 0, ebig0 = 0;
+    for (bool first = true; nact; first = false) {
+        Seg *big = first ? w.big : w.segs;
+        k_fill_u32<<<1, 64, 0, st>>>(sw.ctr, 0u, C_NCTR);
+        SS_CHECK_LAUNCH();
+        {
+            SS_PROF("k_tie_small", st, (double)elems * 24.0);  // entry, its LCP, length, offset; LCP out; not the bytes
+            k_tie_small<<<(unsigned)ceil_div(nact, 32), 256, 0, st>>>(list, nact, V, w.order, sw.keyB, sw.mpr, O, big,
+                                                                     sw.ctr);
+        }
+        SS_CHECK_LAUNCH();
+        if (small_only) break;
+        SS_TRY(ss_read_u32(sw.ctr, ctr, C_NCTR, st));
+        const u32 nbig = ctr[C_RNEXT], ebig = ctr[C_RELEM];
+        if (!nbig) break;
+        if (first) {
+            nbig0 = nbig;
+            ebig0 = ebig;
+        }
+        SS_TRY(tile_list(big, nbig, sw.mword, sw.ctr));
+        const unsigned tg = tile_grid(nbig, ebig);
+        {
+            SS_PROF("k_tie_compare", st, (double)ebig * 20.0);  // entry, its LCP, length, offset; not the bytes
+            k_tie_compare<<<tg, 256, 0, st>>>(big, w.tiles, nbig, V, w.order, sw.mword);
+        }
+        SS_CHECK_LAUNCH();
+        k_tie_keys<<<tg, 256, 0, st>>>(big, w.tiles, nbig, V, w.order, out_lcp, sw.mword, sw, z);
+        SS_CHECK_LAUNCH();
+        SS_TRY(sort_keyed(J, sw, ctr));
+        nact = ctr[C_NEXT];
+        elems = ctr[C_NELEM];
+        Seg *tmp = sw.act; sw.act = sw.nxt; sw.nxt = tmp;
+        list = sw.act;
+    }
+    if (nbig0) {
+        SS_TRY(tile_list(w.big, nbig0, nullptr, nullptr));
+        k_tie_emit<<<tile_grid(nbig0, ebig0), 256, 0, st>>>(w.big, w.tiles, nbig0, w.order, O);
+        SS_CHECK_LAUNCH();
+    }
+    if (nover) {
+        SS_TRY(tile_list(w.over, nover, nullptr, nullptr));
+        k_tie_emit<<<tile_grid(nover, eover), 256, 0, st>>>(w.over, w.tiles, nover, w.order, O);
         SS_CHECK_LAUNCH();
     }
     return SS_OK;

@@ -1068,7 +1068,6 @@ __global__ __launch_bounds__(NT) void k_ident(const Seg *segs, const u32 *tstart
 // 512 sets of 10^3..10^5 strings 349 -> 148 us; 16M D/N strings, whose segments
 // of 1,479 strings took a radix level (about 250 us) and 366 us in the register
 // sort, 266 us.
-__device__ __forceinline__ u32 bs_at(u32 i) { return i + i / BS_IPT; }  // (a pad per thread: no bank conflicts)
 
 template <bool LOOP, int NTB>
 __global__ __launch_bounds__(NTB) void k_block_sort(const Seg *list, const u32 *cntp, u64 *keys, u32 *vals,
@@ -1323,7 +1322,10 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
         const Seg g = gq[q];
         const u32 cnt = g.end - g.begin;
         u64 k0 = nk0, k1 = nk1;
-        u32 v0 = nv0, v1 = nv1;
+        // (keys of any payload are sorted with the element numbers, and the
+        // payload follows: its own order need not be the segment's)
+        u32 v0 = DEEP ? nv0 : e0, v1 = DEEP ? nv1 : e1;
+        const u32 pv0 = nv0, pv1 = nv1;
         if (q + 1 < WS_SPB / 4) fetch(gq[q + 1]);
         u32 P = 2;
         while (P < cnt) P <<= 1;
@@ -1429,6 +1431,12 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
             atomicAdd(&nq_tiles, (ns.end - ns.begin + et - 1) / et);
             atomicAdd(&nq_elems, ns.end - ns.begin);
         }
+        }
+        if (!DEEP) {
+            const u32 a0 = __shfl(pv0, v0 & 63, 64), b0 = __shfl(pv1, v0 & 63, 64);
+            const u32 a1 = __shfl(pv0, v1 & 63, 64), b1 = __shfl(pv1, v1 & 63, 64);
+            v0 = v0 < 64 ? a0 : b0;
+            v1 = v1 < 64 ? a1 : b1;
         }
         if (e0 < cnt) vals[g.begin + e0] = v0;
         if (e1 < cnt) vals[g.begin + e1] = v1;

@@ -19,7 +19,8 @@ enum {
     C_LTILES = 5, C_SMALLN = 6, C_NTILES = 7, C_ITILES = 8, C_LELEM = 9, C_NELEM = 12, C_TINY = 13,
     C_TINYN = 14, C_BADSET = 15, C_MID = 16,
     C_RNEXT = 17, C_RTILES = 18, C_RELEM = 19,  // what k_resolve leaves of the C_NEXT segments
-    C_NCTR = 20
+    C_TIEBIG = 20,  // (merge) some tied segment has more than TIE_SMALL members
+    C_NCTR = 21
 };
 // ctr[10..11]: 64-bit sum of size * skip over the routed segments
 
@@ -44,6 +45,9 @@ __device__ __forceinline__ u32 seg_of_tile(const u32 *tstart, u32 nseg, u32 t)
     }
     return lo;
 }
+
+// LDS slot of element i where threads own runs of 8 (a pad each: no bank conflicts)
+__device__ __forceinline__ u32 bs_at(u32 i) { return i + i / BS_IPT; }
 
 struct SortWs {
     u64 *keyA, *keyB, *mword;  // mword, mpr: each member's first mismatch with its segment's first string
@@ -90,7 +94,7 @@ struct SortShape {
 SortShape sort_shape(u64 n);
 // The sorts of one round over segments whose 64-bit keys (in w.keyA) the caller
 // computed and which it put into w.tiny, w.small, w.mid and w.largeA (counts
-// and totals in the counters): each is sorted by (key, payload order).  Runs of
+// and totals in the counters): each is sorted stably by key.  Runs of
 // equal keys whose low byte is 8 are appended to w.nxt.  h receives the
 // counters afterwards; J.lcp is written with values of no meaning.
 int sort_keyed(const SortJob &J, SortWs &w, u32 *h);
