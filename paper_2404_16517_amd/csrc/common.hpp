@@ -135,12 +135,18 @@ extern int g_dedup_logb;  // log2 of the bucket count (0: by the list length)
 // (in == out) is allowed.  Scratch: ss_scan_scratch_elems(n) elements of T.
 template <class T> u64 ss_scan_scratch_elems(u64 n);
 template <class T> int ss_scan_exclusive(const T *in, T *out, u64 n, T *scratch, hipStream_t s);
-// The same with the length read on the device, n = *n_dev * mult (a fixed
-// launch shape, no read-back; for captured graphs).  out[n] = total.
-// Scratch: ss_scan_dev_scratch_elems() elements of T.
-template <class T> u64 ss_scan_dev_scratch_elems();
-template <class T> int ss_scan_exclusive_dev(const T *in, T *out, const u32 *n_dev, u32 mult, T *scratch,
-                                             hipStream_t s);
+// The same in one launch with the length read on the device, n = *n_dev <=
+// n_max (no read-back; for captured graphs).  out[n] = total.  state:
+// SCAN_DEV_STATE words that a kernel before it has cleared.
+#define SCAN_DEV_G 1024
+#define SCAN_DEV_STATE (SCAN_DEV_G + 1)
+#define SCAN_DEV_MAX (SCAN_DEV_G * 4096)  // items up to which its ranges are read by one step each
+int ss_scan_exclusive_dev(const u32 *in, u32 *out, const u32 *n_dev, u64 n_max, u64 *state, hipStream_t s);
+
+__device__ __forceinline__ void scan_state_zero(u64 *state)  // by one workgroup
+{
+    for (u32 i = threadIdx.x; i < SCAN_DEV_STATE; i += blockDim.x) state[i] = 0;
+}
 
 // ------------------------------------------------------------ byte loads
 

@@ -101,9 +101,86 @@ __device__ __forceinline__ T block_max(T v)
 #define TILE_LOOP(t, count) \
     for (u32 t = blockIdx.x; LOOP ? (t < (count)) : (t == blockIdx.x); t += LOOP ? gridDim.x : 1u)
 
-__global__ void k_tile_counts(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out)
+// Exclusive scan of the tile counts of nseg segments by one workgroup of
+// LIST_NT threads (tstart[nseg] = total, which is returned).
+#define LIST_NT 1024
+#define LIST_ONE 4096  // lists of up to so many segments: one workgroup (three launches take longer)
+__device__ __forceinline__ u32 list_tiles(const Seg *segs, u32 nseg, u32 tile, u32 *tstart)
+{
+    __shared__ u32 wsum[LIST_NT / 64];
+    const u32 lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    u32 carry = 0;
+    for (u32 b = 0; b < nseg; b += LIST_NT) {
+        const u32 j = b + threadIdx.x;
+        const u32 v = j < nseg ? (segs[j].end - segs[j].begin + tile - 1) / tile : 0u;
+        u32 x = v;
+#pragma unroll
+        for (u32 o = 1; o < 64; o <<= 1) {
+            const u32 y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wsum[wv] = x;
+        __syncthreads();
+        u32 tot = 0;
+        x += carry - v;
+#pragma unroll
+        for (u32 w = 0; w < LIST_NT / 64; w++) {
+            if (w < wv) x += wsum[w];
+            tot += wsum[w];
+        }
+        if (j < nseg) tstart[j] = x;
+        carry += tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) tstart[nseg] = carry;
+    return carry;
+}
+
+// k_tile_counts and its scan for up to LIST_ONE segments.
+__global__ __launch_bounds__(LIST_NT) void k_list_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *tstart)
+{
+    list_tiles(segs, *nsegp, tile, tstart);
+}
+
+// k_round_begin, k_round_tiles and the scan for up to LIST_ONE segments.
+__global__ __launch_bounds__(LIST_NT) void k_round_start(const Seg *segs, u32 *ctr, u32 *hdr, u32 from, u32 tile,
+                                                         u32 *tstart, u32 *skipv)
+{
+    const u32 nseg = ctr[from];
+    __syncthreads();
+    if (threadIdx.x == 0) hdr[H_ACT] = nseg;
+    if (threadIdx.x < C_NCTR && threadIdx.x != C_BADSET) ctr[threadIdx.x] = 0;
+    for (u32 j = threadIdx.x; j < nseg; j += LIST_NT) skipv[j] = 0xFFFFFFFFu;
+    list_tiles(segs, nseg, tile, tstart);
+}
+
+// k_level_begin, k_level_tiles and the scan for up to LIST_ONE segments: one
+// launch, where four to six took longer than the level's work on small inputs
+// (sorting 100,000 D/N strings, two levels: 218 us with them, 199 us so).
+__global__ __launch_bounds__(LIST_NT) void k_level_start(const Seg *segs, u32 *ctr, u32 *hdr, u32 nb, u32 tile,
+                                                         u32 *tstart, u64 *smin, u64 *smax, u64 *hscan)
+{
+    const u32 nseg = ctr[C_LARGE];
+    scan_state_zero(hscan);
+    __syncthreads();
+    for (u32 j = threadIdx.x; j < nseg; j += LIST_NT) {
+        smin[j] = ~0ull;
+        smax[j] = 0;
+    }
+    const u32 tiles = list_tiles(segs, nseg, tile, tstart);
+    if (threadIdx.x == 0) {
+        hdr[H_LARGE] = nseg;
+        hdr[H_HIST] = nb * tiles;
+        ctr[C_LARGE] = 0;
+        ctr[C_LTILES] = 0;
+        ctr[C_LELEM] = 0;
+    }
+}
+
+__global__ void k_tile_counts(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u64 *dscan)
 {
     const u32 nseg = *nsegp;
+    if (blockIdx.x == 0) scan_state_zero(dscan);
     GSTRIDE(j, nseg) out[j] = (segs[j].end - segs[j].begin + tile - 1) / tile;
 }
 
@@ -118,9 +195,10 @@ __global__ void k_round_begin(u32 *ctr, u32 *hdr, u32 from)
 
 // Tile counts of the active segments for a round; also resets the segments'
 // skip minima.
-__global__ void k_round_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u32 *skipv)
+__global__ void k_round_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u32 *skipv, u64 *dscan)
 {
     const u32 nseg = *nsegp;
+    if (blockIdx.x == 0) scan_state_zero(dscan);
     GSTRIDE(j, nseg) {
         out[j] = (segs[j].end - segs[j].begin + tile - 1) / tile;
         skipv[j] = 0xFFFFFFFFu;
@@ -129,8 +207,9 @@ __global__ void k_round_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *
 
 // Start of a radix level: the radix list's length and its histogram length
 // go to the header, the counters of the next level's radix list are reset.
-__global__ void k_level_begin(u32 *ctr, u32 *hdr, u32 nb)
+__global__ void k_level_begin(u32 *ctr, u32 *hdr, u32 nb, u64 *hscan)
 {
+    scan_state_zero(hscan);
     if (threadIdx.x == 0) {
         hdr[H_LARGE] = ctr[C_LARGE];
         hdr[H_HIST] = nb * ctr[C_LTILES];
@@ -142,9 +221,11 @@ __global__ void k_level_begin(u32 *ctr, u32 *hdr, u32 nb)
 
 // Tile counts of the radix segments of a level; also resets their key minima
 // and maxima.
-__global__ void k_level_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u64 *smin, u64 *smax)
+__global__ void k_level_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u64 *smin, u64 *smax,
+                              u64 *dscan)
 {
     const u32 nseg = *nsegp;
+    if (blockIdx.x == 0) scan_state_zero(dscan);
     GSTRIDE(j, nseg) {
         out[j] = (segs[j].end - segs[j].begin + tile - 1) / tile;
         smin[j] = ~0ull;
@@ -1497,7 +1578,8 @@ void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c)
     TAKE(tstart, u32, nseg + 1);
     TAKE(hist, u32, nscan);
     TAKE(scan_scratch, u64, ss_scan_scratch_elems<u64>(nscan));
-    TAKE(dscan, u32, ss_scan_dev_scratch_elems<u32>());
+    TAKE(dscan, u64, SCAN_DEV_STATE);
+    TAKE(hscan, u64, SCAN_DEV_STATE);
     TAKE(ctr, u32, C_NCTR);
     TAKE(hdr, u32, H_NHDR);
 #undef TAKE
@@ -1542,17 +1624,28 @@ static u32 elem_tile(u64 n)
 
 static u32 digit_bits_for(u32 SM, u32 TL) { return (g_digit_bits == 11 && TL >= 4096 && SM >= 512) ? 11u : 8u; }
 
+// Strings per tile of the radix levels: g_tile, but in sorts of fewer than 256
+// such tiles smaller ones (100,000 D/N strings: 199 us with 25 workgroups of 4096,
+// 181 us with 98 of 1024; 64 sets of 100 to 10,000 strings 463 and 434 us).
+static u32 radix_tile(u64 n)
+{
+    u32 t = (u32)g_tile;
+    if (digit_bits_for((u32)g_small_max, t) == 8)
+        while (t >= 2048 && n < 256ull * t) t /= 2;
+    return t;
+}
+
 static RoundCtx round_ctx(const SortJob &J, SortWs &w)
 {
     const u32 sm = (u32)g_small_max, tl = (u32)g_tile;
     const SortShape z = sort_shape(J.n_total);
-    return RoundCtx{J, w, J.n_total, sm, tl, digit_bits_for(sm, tl), z.et, z.block_max};
+    return RoundCtx{J, w, J.n_total, sm, z.tile, digit_bits_for(sm, tl), z.et, z.block_max};
 }
 
-static int scan_u32(RoundCtx &C, u32 *arr, const u32 *n_dev, Known k)
+// The scan of a list's tile counts (the kernel before it cleared the state).
+static int scan_u32(RoundCtx &C, u32 *arr, const u32 *n_dev, u64 n_max)
 {
-    if (k.yes) return ss_scan_exclusive<u32>(arr, arr, k.v, (u32 *)C.w.scan_scratch, C.J.stream);
-    return ss_scan_exclusive_dev<u32>(arr, arr, n_dev, 1, C.w.dscan, C.J.stream);
+    return ss_scan_exclusive_dev(arr, arr, n_dev, n_max, C.w.dscan, C.J.stream);
 }
 
 // The part of a round before the radix levels: skip, keys, routing.  The round's
@@ -1566,13 +1659,16 @@ static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bo
     hipStream_t st = J.stream;
     const u64 n = C.n;
     const u32 *nactp = w.hdr + H_ACT;
-    if (!begun) {
+    const u64 most = nact.yes ? nact.v : n / 2;
+    if (!begun && most <= LIST_ONE) {
+        k_round_start<<<1, LIST_NT, 0, st>>>(w.act, w.ctr, w.hdr, from, C.ET, w.tstart, w.skipv);
+        SS_CHECK_LAUNCH();
+    } else if (!begun) {
         k_round_begin<<<1, 64, 0, st>>>(w.ctr, w.hdr, from);
         SS_CHECK_LAUNCH();
-        k_round_tiles<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, C.ET, w.tstart,
-                                                                                   w.skipv);
+        k_round_tiles<<<grid_of(most, 256, 1024), 256, 0, st>>>(w.act, nactp, C.ET, w.tstart, w.skipv, w.dscan);
         SS_CHECK_LAUNCH();
-        SS_TRY(scan_u32(C, w.tstart, nactp, nact));
+        SS_TRY(scan_u32(C, w.tstart, nactp, most));
     }
     const unsigned tg = atiles.yes ? grid_of(atiles.v, 1, 1u << 30) : 0u;  // (one tile per workgroup)
     {
@@ -1619,13 +1715,18 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     const SortJob &J = C.J;
     hipStream_t st = J.stream;
     const u64 n = C.n;
-    k_level_begin<<<1, 64, 0, st>>>(w.ctr, w.hdr, NB);
-    SS_CHECK_LAUNCH();
     const u32 *nlp = w.hdr + H_LARGE;
-    k_level_tiles<<<grid_of(nlarge.yes ? nlarge.v : n / 128, 256, 1024), 256, 0, st>>>(LA, nlp, C.TL, w.tstart,
-                                                                                     w.smin, w.smax);
-    SS_CHECK_LAUNCH();
-    SS_TRY(scan_u32(C, w.tstart, nlp, nlarge));
+    const u64 most = nlarge.yes ? nlarge.v : n / C.BM;  // radix segments have more than BM strings
+    if (most <= LIST_ONE) {
+        k_level_start<<<1, LIST_NT, 0, st>>>(LA, w.ctr, w.hdr, NB, C.TL, w.tstart, w.smin, w.smax, w.hscan);
+        SS_CHECK_LAUNCH();
+    } else {
+        k_level_begin<<<1, 256, 0, st>>>(w.ctr, w.hdr, NB, w.hscan);
+        SS_CHECK_LAUNCH();
+        k_level_tiles<<<grid_of(most, 256, 1024), 256, 0, st>>>(LA, nlp, C.TL, w.tstart, w.smin, w.smax, w.dscan);
+        SS_CHECK_LAUNCH();
+        SS_TRY(scan_u32(C, w.tstart, nlp, most));
+    }
     const unsigned tg = ltiles.yes ? grid_of(ltiles.v, 1, 1u << 30) : 0u;  // (one tile per workgroup)
     {
         SS_PROF("k_hist", st, (double)lelem * 8.0);  // read the keys
@@ -1633,8 +1734,10 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
         else k_hist<true, W><<<grid_of(n, C.TL, resident(k_hist<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax);
     }
     SS_CHECK_LAUNCH();
-    if (ltiles.yes) SS_TRY(ss_scan_exclusive<u32>(w.hist, w.hist, (u64)ltiles.v * NB, (u32 *)w.scan_scratch, st));
-    else SS_TRY(ss_scan_exclusive_dev<u32>(w.hist, w.hist, w.hdr + H_HIST, 1, w.dscan, st));
+    // (three launches once there are more items than one range per workgroup holds)
+    const u64 nh = (ltiles.yes ? ltiles.v : n / C.TL + n / C.BM) * (u64)NB;
+    if (ltiles.yes && nh > SCAN_DEV_MAX) SS_TRY(ss_scan_exclusive<u32>(w.hist, w.hist, nh, (u32 *)w.scan_scratch, st));
+    else SS_TRY(ss_scan_exclusive_dev(w.hist, w.hist, w.hdr + H_HIST, nh, w.hscan, st));
     EmitOut eo{w.tiny, w.small, w.mid, LB, w.nxt, w.ident, w.bnd, w.ctr, w.scat, w.kinds, C.BM, C.TL, C.ET};
     constexpr u32 SPG = EPB / Digits<W>::DPT;
     if (nlarge.yes) k_emit<false, W><<<grid_of(nlarge.v, SPG, 1u << 30), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, eo);
@@ -1708,10 +1811,15 @@ static int round_tail(RoundCtx &C, const u32 *h, bool keyed = false)
         SS_CHECK_LAUNCH();
     }
     if (!known || h[C_IDENT] > 0) {
-        k_tile_counts<<<grid_of(known ? h[C_IDENT] : n / 2, 256, 1024), 256, 0, st>>>(w.ident, w.ctr + C_IDENT,
-                                                                                    C.ET, w.tstart);
-        SS_CHECK_LAUNCH();
-        SS_TRY(scan_u32(C, w.tstart, w.ctr + C_IDENT, Known{known, known ? h[C_IDENT] : 0u}));
+        const u64 most = known ? h[C_IDENT] : n / 2;
+        if (most <= LIST_ONE) {
+            k_list_tiles<<<1, LIST_NT, 0, st>>>(w.ident, w.ctr + C_IDENT, C.ET, w.tstart);
+            SS_CHECK_LAUNCH();
+        } else {
+            k_tile_counts<<<grid_of(most, 256, 1024), 256, 0, st>>>(w.ident, w.ctr + C_IDENT, C.ET, w.tstart, w.dscan);
+            SS_CHECK_LAUNCH();
+            SS_TRY(scan_u32(C, w.tstart, w.ctr + C_IDENT, most));
+        }
         if (known)
             k_ident<false><<<grid_of(h[C_ITILES], 1, 1u << 30), NT, 0, st>>>(w.ident, w.tstart, w.ctr + C_IDENT, C.ET, lcp);
         else
@@ -1782,7 +1890,7 @@ int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles, bool whole)
 SortShape sort_shape(u64 n)
 {
     const u32 bm = 2 * (u32)g_small_max;
-    return SortShape{elem_tile(n), (u32)g_tile, bm < BS_MID ? bm : (u32)BS_MID};
+    return SortShape{elem_tile(n), radix_tile(n), bm < BS_MID ? bm : (u32)BS_MID};
 }
 
 int sort_keyed(const SortJob &J, SortWs &w, u32 *h)

@@ -61,7 +61,7 @@ struct SortWs {
     u8 *kinds;  // per radix segment and digit: what the bucket became
     u32 *tstart, *hist;
     u64 *scan_scratch;
-    u32 *dscan;  // scratch of the device-length scans
+    u64 *dscan, *hscan;  // state of the device-length scans: of lists, of histograms
     u32 *ctr;
     u32 *hdr;    // list lengths of the current round and level (device)
 };
