@@ -1557,7 +1557,7 @@ __device__ __forceinline__ void mw_route(const MwOut &W, Seg o)
     u32 *ctr = W.s.ctr;
     W.over[atomicAdd(&ctr[C_RTILES], 1u)] = o;
     if (m > W.block_max) {
-        W.s.largeA[atomicAdd(&ctr[C_LARGE], 1u)] = o;
+        W.s.largeA[atomicAdd(&ctr[C_LARGE], 1u)] = Seg{o.begin, o.end, o.depth, o.aux | SEG_NOROOT};
         atomicAdd(&ctr[C_LTILES], (m + W.tile - 1) / W.tile);
         atomicAdd(&ctr[C_LELEM], m);
     } else if (m <= WS_MAX) {
@@ -2082,7 +2082,7 @@ __global__ __launch_bounds__(256) void k_tie_keys(const Seg *list, const u32 *ti
             else w.mid[atomicAdd(&w.ctr[C_MID], 1u)] = o;
             atomicAdd(&w.ctr[C_SMALLN], m);
         } else {
-            w.largeA[atomicAdd(&w.ctr[C_LARGE], 1u)] = o;
+            w.largeA[atomicAdd(&w.ctr[C_LARGE], 1u)] = Seg{o.begin, o.end, o.depth, SEG_NOROOT};
             atomicAdd(&w.ctr[C_LTILES], (m + z.tile - 1) / z.tile);
             atomicAdd(&w.ctr[C_LELEM], m);
         }

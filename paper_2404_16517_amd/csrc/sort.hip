@@ -101,6 +101,98 @@ __device__ __forceinline__ T block_max(T v)
 #define TILE_LOOP(t, count) \
     for (u32 t = blockIdx.x; LOOP ? (t < (count)) : (t == blockIdx.x); t += LOOP ? gridDim.x : 1u)
 
+// ---- radix digits
+//
+// A level's digit is made of the next W varying bits of the segment's keys, in
+// up to three pieces of neighbouring bits (for letters: five bits of one byte and
+// three of the next), or, where these would reach less far, of the next W bits
+// whether they vary or not.  Bits that all keys of the round's segment share
+// order nothing, so digits order like keys; and a level uses up at least W of
+// the 64 bits, so there are at most 64 / W levels.  Which bits vary is found
+// where the keys are made (k_keys); segments whose keys come from elsewhere
+// take every bit as varying.  (Digits at byte boundaries have 26 values for
+// letters: 100,000 D/N strings took two levels and 176 us, now one and 129; 16M
+// in 16 sets three levels, now two.)
+//
+// Packed: piece q's shift in bits 10q..10q+5 and length in 10q+6..10q+9, then
+// (30..36) the key bits used up after this level, then (37..42) its lowest bit.
+template <u32 W>
+struct Digits {
+    static constexpr u32 NB = 1u << W;                 // buckets of a level
+    static constexpr u32 LEVELS = (64 + W - 1) / W;    // most levels of one key
+    static constexpr u32 DPT = NB / 256;               // digits per thread of a 256-thread workgroup
+};
+
+__device__ __forceinline__ u64 digit_spec(const Seg &g, const u64 *rmask, u32 W)
+{
+    const u32 used = g.aux & 63, root = g.aux >> SEG_ROOT;
+    const u64 mask = (root == (SEG_NOROOT >> SEG_ROOT) ? ~0ull : rmask[root]) & (~0ull >> used);
+    if (!mask) return 64ull << 30;  // (one key in the whole segment)
+    const u32 top = 63 - (u32)__clzll(mask);
+    u64 m = mask, spec = 0;
+    u32 bits = 0, low = top + 1;
+#pragma unroll
+    for (u32 q = 0; q < 3; q++) {
+        if (!m || bits == W) break;
+        const u32 hi = 63 - (u32)__clzll(m);
+        const u64 inv = ~(m << (63 - hi));
+        const u32 ones = inv ? (u32)__clzll(inv) : 64u, take = ones < W - bits ? ones : W - bits;
+        low = hi + 1 - take;
+        spec |= (u64)(low | (take << 6)) << (10 * q);
+        bits += take;
+        m &= low ? ~0ull >> (64 - low) : 0ull;
+    }
+    u32 next = m ? 64 - (u32)__clzll(m) : 0u;  // bits [0, next) are left
+    if (next && top + 1 - next < W) {
+        low = top + 1 - W;  // (not below 0: bits below the pieces are left)
+        if (top + 1 < W) low = 0;
+        spec = (u64)(low | ((top + 1 - low) << 6));
+        m = low ? mask & (~0ull >> (64 - low)) : 0ull;
+        next = m ? 64 - (u32)__clzll(m) : 0u;
+    }
+    return spec | ((u64)(64 - next) << 30) | ((u64)low << 37);
+}
+
+struct Digit {
+    u32 s[3], m[3], o[3];  // shift, mask, place in the digit
+    u32 used, low;
+};
+
+__device__ __forceinline__ Digit digit_unpack(u64 spec)  // the same for the whole wavefront
+{
+    spec = ((u64)__builtin_amdgcn_readfirstlane((u32)(spec >> 32)) << 32) | (u32)__builtin_amdgcn_readfirstlane((u32)spec);
+    Digit D;
+    u32 at = 0;
+#pragma unroll
+    for (int q = 2; q >= 0; q--) {
+        const u32 f = (u32)(spec >> (10 * q)) & 0x3FFu;
+        D.s[q] = f & 63;
+        D.m[q] = (1u << (f >> 6)) - 1u;
+        D.o[q] = at;
+        at += f >> 6;
+    }
+    D.used = (u32)(spec >> 30) & 127u;
+    D.low = (u32)(spec >> 37) & 63u;
+    return D;
+}
+
+__device__ __forceinline__ u32 digit_of(u64 k, const Digit &D)
+{
+    u32 d = 0;
+#pragma unroll
+    for (int q = 0; q < 3; q++) d |= ((u32)(k >> D.s[q]) & D.m[q]) << D.o[q];
+    return d;
+}
+
+// Key k with its digit replaced by d.
+__device__ __forceinline__ u64 digit_put(u64 k, u32 d, const Digit &D)
+{
+#pragma unroll
+    for (int q = 0; q < 3; q++)
+        k = (k & ~((u64)D.m[q] << D.s[q])) | ((u64)((d >> D.o[q]) & D.m[q]) << D.s[q]);
+    return k;
+}
+
 // Exclusive scan of the tile counts of nseg segments by one workgroup of
 // LIST_NT threads (tstart[nseg] = total, which is returned).
 #define LIST_NT 1024
@@ -144,13 +236,16 @@ __global__ __launch_bounds__(LIST_NT) void k_list_tiles(const Seg *segs, const u
 
 // k_round_begin, k_round_tiles and the scan for up to LIST_ONE segments.
 __global__ __launch_bounds__(LIST_NT) void k_round_start(const Seg *segs, u32 *ctr, u32 *hdr, u32 from, u32 tile,
-                                                         u32 *tstart, u32 *skipv)
+                                                         u32 *tstart, u32 *skipv, u64 *vary, u32 block_max)
 {
     const u32 nseg = ctr[from];
     __syncthreads();
     if (threadIdx.x == 0) hdr[H_ACT] = nseg;
     if (threadIdx.x < C_NCTR && threadIdx.x != C_BADSET) ctr[threadIdx.x] = 0;
-    for (u32 j = threadIdx.x; j < nseg; j += LIST_NT) skipv[j] = 0xFFFFFFFFu;
+    for (u32 j = threadIdx.x; j < nseg; j += LIST_NT) {
+        skipv[j] = 0xFFFFFFFFu;
+        if (segs[j].end - segs[j].begin > block_max) vary[segs[j].begin] = 0;
+    }
     list_tiles(segs, nseg, tile, tstart);
 }
 
@@ -158,7 +253,8 @@ __global__ __launch_bounds__(LIST_NT) void k_round_start(const Seg *segs, u32 *c
 // launch, where four to six took longer than the level's work on small inputs
 // (sorting 100,000 D/N strings, two levels: 218 us with them, 199 us so).
 __global__ __launch_bounds__(LIST_NT) void k_level_start(const Seg *segs, u32 *ctr, u32 *hdr, u32 nb, u32 tile,
-                                                         u32 *tstart, u64 *smin, u64 *smax, u64 *hscan)
+                                                         u32 *tstart, u64 *smin, u64 *smax, u64 *hscan,
+                                                         const u64 *rmask, u64 *dig)
 {
     const u32 nseg = ctr[C_LARGE];
     scan_state_zero(hscan);
@@ -166,6 +262,7 @@ __global__ __launch_bounds__(LIST_NT) void k_level_start(const Seg *segs, u32 *c
     for (u32 j = threadIdx.x; j < nseg; j += LIST_NT) {
         smin[j] = ~0ull;
         smax[j] = 0;
+        dig[j] = digit_spec(segs[j], rmask, (u32)__ffs((int)nb) - 1);
     }
     const u32 tiles = list_tiles(segs, nseg, tile, tstart);
     if (threadIdx.x == 0) {
@@ -194,14 +291,17 @@ __global__ void k_round_begin(u32 *ctr, u32 *hdr, u32 from)
 }
 
 // Tile counts of the active segments for a round; also resets the segments'
-// skip minima.
-__global__ void k_round_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u32 *skipv, u64 *dscan)
+// skip minima and, for those that may take radix levels, the varying bits of
+// their keys (kept where the segment begins in the second key array).
+__global__ void k_round_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u32 *skipv, u64 *dscan,
+                              u64 *vary, u32 block_max)
 {
     const u32 nseg = *nsegp;
     if (blockIdx.x == 0) scan_state_zero(dscan);
     GSTRIDE(j, nseg) {
         out[j] = (segs[j].end - segs[j].begin + tile - 1) / tile;
         skipv[j] = 0xFFFFFFFFu;
+        if (segs[j].end - segs[j].begin > block_max) vary[segs[j].begin] = 0;
     }
 }
 
@@ -222,7 +322,7 @@ __global__ void k_level_begin(u32 *ctr, u32 *hdr, u32 nb, u64 *hscan)
 // Tile counts of the radix segments of a level; also resets their key minima
 // and maxima.
 __global__ void k_level_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *out, u64 *smin, u64 *smax,
-                              u64 *dscan)
+                              u64 *dscan, const u64 *rmask, u64 *dig, u32 W)
 {
     const u32 nseg = *nsegp;
     if (blockIdx.x == 0) scan_state_zero(dscan);
@@ -230,6 +330,7 @@ __global__ void k_level_tiles(const Seg *segs, const u32 *nsegp, u32 tile, u32 *
         out[j] = (segs[j].end - segs[j].begin + tile - 1) / tile;
         smin[j] = ~0ull;
         smax[j] = 0;
+        dig[j] = digit_spec(segs[j], rmask, W);
     }
 }
 
@@ -484,9 +585,10 @@ template <bool LOOP, int NTB = NT>
 __global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 et,
                                              const u8 *bytes, u64 N, const u64 *off,
                                              const u32 *perm, const u32 *skipv, const u64 *mword,
-                                             const uint2 *mpr, u64 *keys)
+                                             const uint2 *mpr, u64 *keys, u64 *vary, u32 block_max)
 {
-    __shared__ u64 fw;
+    __shared__ u64 fw;  // key of the segment's first string
+    __shared__ u64 red[NTB / 64];
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
     TILE_LOOP(t, ntiles) {
@@ -512,9 +614,11 @@ __global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart
         const u32 f = perm[g.begin];
         const u64 fo = off[f], fl = off[f + 1] - fo;
         const u64 r = fl - d;  // the first string is a member: fl >= d
-        fw = load_be(bytes, N, fo + d, r < 7 ? (u32)r : 7u);
+        fw = load_be(bytes, N, fo + d, r < 7 ? (u32)r : 7u) | (r < 8 ? r : 8ull);
     }
     __syncthreads();
+    const bool radix = g.end - g.begin > block_max;  // (uniform) the bits where keys differ are wanted
+    u64 diff = 0;
     for (u32 i = b0 + threadIdx.x; i < b1; i += NTB) {
         const uint2 pr = mpr[i];
         const u32 k = pr.x - (u32)d;  // bytes shared with the first string beyond d
@@ -524,9 +628,25 @@ __global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart
             data = (fw & keep) | (mword[i] >> (8 * k));
         }
         const u32 cnt = pr.y + k < 8 ? pr.y + k : 8u;
-        keys[i] = (data & ~0xFFull) | cnt;
+        const u64 key = (data & ~0xFFull) | cnt;
+        keys[i] = key;
+        diff |= key ^ fw;
     }
-    __syncthreads();  // fw is rewritten by the next tile
+    if (radix) {
+        u32 lo = (u32)diff, hi = (u32)(diff >> 32);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            lo |= __shfl_xor(lo, o, 64);
+            hi |= __shfl_xor(hi, o, 64);
+        }
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ((u64)hi << 32) | lo;
+    }
+    __syncthreads();  // (also: fw is rewritten by the next tile)
+    if (radix && threadIdx.x == 0) {
+        u64 v = red[0];
+        for (int w = 1; w < NTB / 64; w++) v |= red[w];
+        if (v) atomicOr((unsigned long long *)&vary[g.begin], (unsigned long long)v);
+    }
     }
 }
 
@@ -536,7 +656,7 @@ __global__ __launch_bounds__(NTB) void k_keys(const Seg *segs, const u32 *tstart
 // on the few counters for 246 us; 11K of them now take 5 us.
 __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nactp, const u32 *skipv, u32 small_max,
                                                   u32 tile, Seg *tiny, Seg *small, Seg *mid, Seg *large,
-                                                  u32 *ctr)
+                                                  u32 *ctr, const u64 *vary, u64 *rmask)
 {
     enum { TY = 0, SM, MD, LG, TYN, SMN, LGT, LGN, CNT };  // list lengths, then their totals
     __shared__ u32 c[CNT], base[4];
@@ -550,12 +670,14 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
     const bool valid = j < nact;
     Seg g = {0, 0, 0, 0};
     u64 skn = 0;
+    bool root = false;  // the varying bits of its keys are known
     if (valid) {
         g = act[j];
         if (g.aux & SEG_SKIP) {
             g.depth += skipv[j];
             skn = (u64)(g.end - g.begin) * skipv[j];
         }
+        root = g.aux & SEG_SKIP;
         g.aux = 0;
     }
     const u32 sz = g.end - g.begin;
@@ -597,7 +719,12 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
     if (kind == TY) tiny[base[TY] + slot] = g;
     else if (kind == SM) small[base[SM] + slot] = g;
     else if (kind == MD) mid[base[MD] + slot] = g;
-    else if (kind == LG) large[base[LG] + slot] = g;
+    else if (kind == LG) {
+        const u32 at = base[LG] + slot;
+        g.aux = root ? at << SEG_ROOT : SEG_NOROOT;
+        large[at] = g;
+        rmask[at] = vary[g.begin];
+    }
     __syncthreads();  // the counters are reset for the next segments
     }
 }
@@ -727,21 +854,6 @@ __global__ __launch_bounds__(256) void k_resolve(const Seg *in, const u8 *bytes,
 // length byte).  Level l covers key bits [lo, hi) with hi = 64 - W l and
 // lo = max(0, hi - W); its histograms have 2^W buckets.
 
-template <u32 W>
-struct Digits {
-    static constexpr u32 NB = 1u << W;                 // buckets of a level
-    static constexpr u32 LEVELS = (64 + W - 1) / W;    // levels of one key
-    static constexpr u32 DPT = NB / 256;               // digits per thread of a 256-thread workgroup
-};
-
-template <u32 W>
-__device__ __forceinline__ u32 digit_of(u64 k, u32 level)
-{
-    const u32 hi = 64 - W * level;
-    const u32 lo = hi > W ? hi - W : 0u;
-    return (u32)(k >> lo) & ((1u << (hi - lo)) - 1u);
-}
-
 // Lanes of this wave holding the same W-bit digit (restricted to `valid`).
 template <u32 W>
 __device__ __forceinline__ u64 match_digit_w(u32 digit, bool valid)
@@ -759,7 +871,8 @@ __device__ __forceinline__ u64 match_digit_w(u32 digit, bool valid)
 // segment: hist[NB*tstart[s] + d*T_s + lt].  Also the segment's min and max key.
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
-                                             const u64 *keyA, const u64 *keyB, u32 *hist, u64 *smin, u64 *smax)
+                                             const u64 *keyA, const u64 *keyB, u32 *hist, u64 *smin, u64 *smax,
+                                             const u64 *dig)
 {
     constexpr u32 NB = Digits<W>::NB;
     __shared__ u32 h[NB];
@@ -771,7 +884,7 @@ __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart,
     const u64 *keys = (g.aux & SEG_INB) ? keyB : keyA;
     const u32 T = tstart[s + 1] - tstart[s];
     const u32 lt = t - tstart[s];
-    const u32 level = g.aux & 15;
+    const Digit D = digit_unpack(dig[s]);
     const u32 b0 = g.begin + lt * tile;
     const u32 b1 = min(g.end, b0 + tile);
     for (u32 d = threadIdx.x; d < NB; d += NT) h[d] = 0;
@@ -791,7 +904,7 @@ __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart,
             if (c >= b1) break;  // (uniform)
             const bool valid = c + threadIdx.x < b1;
             const u64 k = kq[q];
-            u32 d = digit_of<W>(k, level);
+            u32 d = digit_of(k, D);
             u64 peers = match_digit_w<W>(d, valid);
             if (valid) {
                 mn = k < mn ? k : mn;
@@ -835,12 +948,14 @@ struct EmitItem {
 
 template <u32 W>
 __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart, const u32 *hist, const u64 *smin,
-                                              const u64 *smax, const EmitOut &o, u32 s, u32 d, bool *scat)
+                                              const u64 *smax, const u64 *dig, const EmitOut &o, u32 s, u32 d,
+                                              bool *scat)
 {
     constexpr u32 NB = Digits<W>::NB;
     EmitItem it{K_NONE, Seg{0, 0, 0, 0}, false, make_uint2(0, 0)};
     const Seg g = segs[s];
-    const u32 level = g.aux & 15;
+    const Digit D = digit_unpack(dig[s]);
+    const u32 rt = g.aux & SEG_NOROOT;
     const u32 pf = g.aux & SEG_INB;  // where the segment's data is now
     const u64 mn = smin[s], mx = smax[s];
     // next-round and equal-string runs (and singletons) end in A: the settle
@@ -856,11 +971,11 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
         }
         return it;
     }
-    const u32 fd = (u32)__clzll(mn ^ mx) / W;  // first digit where the keys differ
-    if (fd > level) {
-        // digits level..fd-1 are common to the whole segment: no scatter needed
+    const u32 fd = (u32)__clzll(mn ^ mx);  // leading bits that all keys share
+    if (fd > 63 - D.low) {
+        // the whole digit is common to the segment: no scatter needed
         *scat = false;
-        if (d == 0) { it.kind = K_LARGE; it.ns = Seg{g.begin, g.end, g.depth, fd | pf}; }
+        if (d == 0) { it.kind = K_LARGE; it.ns = Seg{g.begin, g.end, g.depth, fd | pf | rt}; }
         return it;
     }
     *scat = true;
@@ -876,10 +991,10 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
     it.bv = make_uint2(sb, g.depth);
     it.ns = Seg{sb, se, g.depth, cf};
     if (cnt >= 2) {
-        if (level == Digits<W>::LEVELS - 1) {
-            // the last digit ends with the key's length byte: the bucket's
-            // keys are equal in all 64 bits
-            const u32 c8 = d & 0xFFu;
+        if (D.used == 64) {
+            // no varying bit is left: the bucket's keys are equal in all 64
+            // bits, and their last byte counts the strings' bytes
+            const u32 c8 = (u32)digit_put(mn, d, D) & 0xFFu;
             if (c8 == 8) { it.kind = K_NEXT; it.ns = Seg{sb, se, g.depth + 7, SEG_SKIP}; }
             else { it.kind = K_IDENT; it.ns = Seg{sb, se, g.depth + c8, 0}; }
         } else if (cnt <= WS_MAX) {
@@ -888,7 +1003,7 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
             it.kind = cnt <= BS_SMALL ? K_SMALL : K_MID;
         } else {
             it.kind = K_LARGE;
-            it.ns.aux = (level + 1) | cf;
+            it.ns.aux = D.used | cf | rt;
         }
     }
     return it;
@@ -903,7 +1018,7 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart, const u32 *nsegp,
                                               const u32 *hist, const u64 *smin, const u64 *smax,
-                                              EmitOut o)
+                                              const u64 *dig, EmitOut o)
 {
     constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, SPG = EPB / DPT;  // segments per group
     __shared__ u32 lcount[K_KINDS], lslot[K_KINDS], lsum[7], gbase[K_KINDS];
@@ -924,7 +1039,7 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
         it[q].bnd = false;
         if (s >= nseg) continue;
         bool sc = false;
-        it[q] = emit_item<W>(segs, tstart, hist, smin, smax, o, s, d, &sc);
+        it[q] = emit_item<W>(segs, tstart, hist, smin, smax, dig, o, s, d, &sc);
         if (d == 0) o.scat[s] = sc ? 1 : 0;
         o.kinds[NB * s + d] = (u8)it[q].kind;
         const EmitItem &x = it[q];
@@ -971,19 +1086,33 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
 }
 
 // Stable scatter of (key, payload) by the current digit into the other pair
-// of arrays (A -> B or B -> A, by the segment's flag).  run[d] is the next
-// free position of digit d; in each chunk of NT elements the wavefronts take
-// turns (wave 0 first, so that equal digits keep the input order), and in a
-// wave the first lane of each digit reserves that digit's slots for all its
-// peers; the others take the base from it by a shuffle.  The work per chunk
-// does not grow with the number of buckets.
+// of arrays (A -> B or B -> A, by the segment's flag), SC_ITEMS elements at a
+// time: every wavefront ranks its 512 by digit (the first lane of each digit
+// counts all its peers, and the steps' counts follow one another without a
+// barrier, as LDS serves a wavefront in order), one scan over digits and
+// wavefronts gives each element its place in the chunk sorted by digit, the
+// chunk is put in that order in LDS and written from there, so that neighbouring
+// lanes write neighbouring elements of a bucket.
+//
+// Bounded by its 24 B per element (81 us for 16M at the copy's rate).  16M keys
+// in 16 segments, about 200 buckets each: 222 us a level when every thread wrote
+// its element where it belongs and the wavefronts took turns at each 256, now
+// 103; 26 buckets took 112 then.  1024 elements a chunk: 4 % longer sorts.
+#define SC_PER 8  // elements per thread and chunk
+#define SC_ITEMS (SC_PER * NT)
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
                                                 const u32 *hist, const u8 *scat, u64 *keyA, u32 *valA,
-                                                u64 *keyB, u32 *valB)
+                                                u64 *keyB, u32 *valB, const u64 *dig)
 {
-    constexpr u32 NB = Digits<W>::NB;
-    __shared__ u32 run[NB];
+    constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, NW = NT / 64;
+    constexpr bool HALF = W > 8;  // counts (at most SC_ITEMS) in 16 bits, two to a word
+    constexpr u32 CW = HALF ? NB / 2 : NB;
+    __shared__ u64 sk[SC_ITEMS];
+    __shared__ u32 sv[SC_ITEMS];
+    __shared__ u32 cnt[NW][CW];  // per wavefront and digit: elements so far, then their place in the chunk
+    __shared__ u32 gofs[NB];     // output position of a bucket's element, less its place in the chunk
+    __shared__ u32 wsum[NW];
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
     TILE_LOOP(t, ntiles) {
@@ -998,56 +1127,108 @@ __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tsta
     const u32 ts = tstart[s];
     const u32 T = tstart[s + 1] - ts;
     const u32 lt = t - ts;
-    const u32 level = g.aux & 15;
+    const Digit D = digit_unpack(dig[s]);
     const u32 b0 = g.begin + lt * tile;
     const u32 b1 = min(g.end, b0 + tile);
     const u32 base = hist[NB * ts];
-    for (u32 d = threadIdx.x; d < NB; d += NT) run[d] = g.begin + hist[NB * ts + d * T + lt] - base;
-    __syncthreads();
     const u32 wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (u32 c0 = b0; c0 < b1; c0 += RX_PF * NT) {
-    // RX_PF chunks' keys and payloads loaded before any is placed
-    u64 kq[RX_PF];
-    u32 vq[RX_PF];
+    u32 run[DPT];  // next free position of the thread's digits, DPT neighbouring ones
 #pragma unroll
-    for (u32 q = 0; q < RX_PF; q++) {
-        const u32 i = c0 + q * NT + threadIdx.x;
-        kq[q] = 0;
-        vq[q] = 0;
-        if (i < b1) {
-            kq[q] = ksrc[i];
-            vq[q] = vsrc[i];
-        }
-    }
+    for (u32 r = 0; r < DPT; r++) run[r] = g.begin + hist[NB * ts + (threadIdx.x * DPT + r) * T + lt] - base;
+    for (u32 c0 = b0; c0 < b1; c0 += SC_ITEMS) {
+        const u32 m = b1 - c0 < SC_ITEMS ? b1 - c0 : SC_ITEMS;
+        u64 kq[SC_PER];
+        u32 vq[SC_PER], pos[SC_PER];
 #pragma unroll
-    for (u32 q = 0; q < RX_PF; q++) {
-        const u32 c = c0 + q * NT;
-        if (c >= b1) break;  // (uniform)
-        const u32 i = c + threadIdx.x;
-        const bool valid = i < b1;
-        const u64 k = kq[q];
-        const u32 v = vq[q];
-        const u32 d = digit_of<W>(k, level);
-        const u64 peers = match_digit_w<W>(d, valid);
-        const u32 rank = (u32)__popcll(peers & lanemask_lt());
-        u32 slot = 0;
-#pragma unroll
-        for (u32 w = 0; w < NT / 64; w++) {
-            if (wid == w && valid && rank == 0) {
-                slot = run[d];
-                run[d] = slot + (u32)__popcll(peers);
+        for (u32 q = 0; q < SC_PER; q++) {
+            const u32 i = (wid * SC_PER + q) * 64 + lane;
+            kq[q] = 0;
+            vq[q] = 0;
+            if (i < m) {
+                kq[q] = ksrc[c0 + i];
+                vq[q] = vsrc[c0 + i];
             }
+        }
+        for (u32 d = threadIdx.x; d < NW * CW; d += NT) (&cnt[0][0])[d] = 0;
+        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < SC_PER; q++) {
+            const bool valid = (wid * SC_PER + q) * 64 + lane < m;
+            const u32 d = digit_of(kq[q], D);
+            const u64 peers = match_digit_w<W>(d, valid);
+            const u32 rank = (u32)__popcll(peers & lanemask_lt());
+            u32 old = 0;
+            if (valid && rank == 0) {
+                const u32 np = (u32)__popcll(peers);
+                if (HALF) old = (atomicAdd(&cnt[wid][d >> 1], np << (16 * (d & 1))) >> (16 * (d & 1))) & 0xFFFFu;
+                else old = atomicAdd(&cnt[wid][d], np);
+            }
+            const int leader = valid ? __ffsll((unsigned long long)peers) - 1 : (int)lane;
+            pos[q] = __shfl(old, leader, 64) + rank;
+        }
+        __syncthreads();
+        {
+            u32 c[NW][DPT], sum = 0;
+#pragma unroll
+            for (u32 r = 0; r < DPT; r++)
+#pragma unroll
+                for (u32 w = 0; w < NW; w++) {
+                    const u32 d = threadIdx.x * DPT + r;
+                    c[w][r] = HALF ? (cnt[w][d >> 1] >> (16 * (d & 1))) & 0xFFFFu : cnt[w][d];
+                    sum += c[w][r];
+                }
+            u32 x = sum;
+#pragma unroll
+            for (u32 o = 1; o < 64; o <<= 1) {
+                const u32 y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
+            }
+            if (lane == 63) wsum[wid] = x;
             __syncthreads();
+            x -= sum;
+#pragma unroll
+            for (u32 w = 0; w < NW; w++)
+                if (w < wid) x += wsum[w];
+            u32 pk[NW];  // (16 bits: this thread's even digit, for the odd one's word)
+#pragma unroll
+            for (u32 r = 0; r < DPT; r++) {
+                const u32 d = threadIdx.x * DPT + r, x0 = x;
+                gofs[d] = run[r] - x0;
+#pragma unroll
+                for (u32 w = 0; w < NW; w++) {
+                    if (!HALF) cnt[w][d] = x;
+                    else if (r & 1) cnt[w][d >> 1] = pk[w] | (x << 16);
+                    else pk[w] = x;
+                    x += c[w][r];
+                }
+                run[r] += x - x0;
+            }
         }
-        const int leader = valid ? __ffsll((unsigned long long)peers) - 1 : (int)lane;
-        const u32 dst = __shfl(slot, leader, 64) + rank;
-        if (valid) {
-            kdst[dst] = k;
-            vdst[dst] = v;
+        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < SC_PER; q++) {
+            if ((wid * SC_PER + q) * 64 + lane < m) {
+                const u32 d = digit_of(kq[q], D);
+                const u32 x = pos[q] + (HALF ? (cnt[wid][d >> 1] >> (16 * (d & 1))) & 0xFFFFu : cnt[wid][d]);
+                sk[x] = kq[q];
+                sv[x] = vq[q];
+            }
         }
+        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < SC_PER; q++) {
+            const u32 x = q * NT + threadIdx.x;
+            if (x < m) {
+                const u64 k = sk[x];
+                const u32 dst = gofs[digit_of(k, D)] + x;
+                kdst[dst] = k;
+                vdst[dst] = sv[x];
+            }
+        }
+        // (the next chunk's first barrier comes before anything here is rewritten,
+        // but for the counts, which nothing above reads any more)
     }
-    }
-    __syncthreads();  // run is rewritten by the next tile
+    __syncthreads();  // (the next tile)
     }
 }
 
@@ -1058,7 +1239,7 @@ __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tsta
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_settle(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
                                                const u8 *scat, const u8 *kinds, const u64 *keyB,
-                                               const u32 *valB, u64 *keyA, u32 *valA)
+                                               const u32 *valB, u64 *keyA, u32 *valA, const u64 *dig)
 {
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
@@ -1066,7 +1247,7 @@ __global__ __launch_bounds__(NT) void k_settle(const Seg *segs, const u32 *tstar
     const u32 s = seg_of_tile(tstart, nseg, t);
     const Seg g = segs[s];
     const bool inb = g.aux & SEG_INB;
-    const u32 level = g.aux & 15;
+    const Digit D = digit_unpack(dig[s]);
     const u32 lt = t - tstart[s];
     const u32 b0 = g.begin + lt * tile;
     const u32 b1 = min(g.end, b0 + tile);
@@ -1083,7 +1264,7 @@ __global__ __launch_bounds__(NT) void k_settle(const Seg *segs, const u32 *tstar
                 kq[q] = i < b1 ? keyB[i] : 0ull;
             }
 #pragma unroll
-            for (u32 q = 0; q < RX_PF; q++) cq[q] = kd[digit_of<W>(kq[q], level)];
+            for (u32 q = 0; q < RX_PF; q++) cq[q] = kd[digit_of(kq[q], D)];
 #pragma unroll
             for (u32 q = 0; q < RX_PF; q++) {
                 const u32 i = c0 + q * NT + threadIdx.x;
@@ -1573,6 +1754,8 @@ void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c)
     TAKE(skipv, u32, nseg);
     TAKE(smin, u64, nlarge);
     TAKE(smax, u64, nlarge);
+    TAKE(rmask, u64, nlarge);
+    TAKE(dig, u64, nlarge);
     TAKE(scat, u8, nlarge);
     TAKE(kinds, u8, nkinds);
     TAKE(tstart, u32, nseg + 1);
@@ -1661,12 +1844,14 @@ static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bo
     const u32 *nactp = w.hdr + H_ACT;
     const u64 most = nact.yes ? nact.v : n / 2;
     if (!begun && most <= LIST_ONE) {
-        k_round_start<<<1, LIST_NT, 0, st>>>(w.act, w.ctr, w.hdr, from, C.ET, w.tstart, w.skipv);
+        k_round_start<<<1, LIST_NT, 0, st>>>(w.act, w.ctr, w.hdr, from, C.ET, w.tstart, w.skipv, w.keyB,
+                                            C.BM);
         SS_CHECK_LAUNCH();
     } else if (!begun) {
         k_round_begin<<<1, 64, 0, st>>>(w.ctr, w.hdr, from);
         SS_CHECK_LAUNCH();
-        k_round_tiles<<<grid_of(most, 256, 1024), 256, 0, st>>>(w.act, nactp, C.ET, w.tstart, w.skipv, w.dscan);
+        k_round_tiles<<<grid_of(most, 256, 1024), 256, 0, st>>>(w.act, nactp, C.ET, w.tstart, w.skipv, w.dscan, w.keyB,
+                                                                C.BM);
         SS_CHECK_LAUNCH();
         SS_TRY(scan_u32(C, w.tstart, nactp, most));
     }
@@ -1694,13 +1879,14 @@ static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bo
         uint2 *mp = sd ? J.seed_pos : w.mpr;
         SS_PROF("k_keys", st, (double)round_elems * 24.0);  // mismatch record in, key out
         if (atiles.yes && round_elems < 64ull * atiles.v)  // (small tiles: one wavefront each, as in the skip)
-            k_keys<false, 64><<<tg, 64, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
-        else if (atiles.yes) k_keys<false><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
-        else k_keys<true><<<grid_of(n, C.ET, resident(k_keys<true>, NT)), NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA);
+            k_keys<false, 64><<<tg, 64, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA, w.keyB, C.BM);
+        else if (atiles.yes) k_keys<false><<<tg, NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA, w.keyB, C.BM);
+        else k_keys<true><<<grid_of(n, C.ET, resident(k_keys<true>, NT)), NT, 0, st>>>(w.act, w.tstart, nactp, C.ET, J.bytes, J.N, J.off, J.vals, w.skipv, mw, mp, w.keyA, w.keyB, C.BM);
     }
     SS_CHECK_LAUNCH();
     k_classify<<<grid_of(nact.yes ? nact.v : n / 2, 256, 1024), 256, 0, st>>>(w.act, nactp, w.skipv, C.BM, C.TL,
-                                                                             w.tiny, w.small, w.mid, w.largeA, w.ctr);
+                                                                             w.tiny, w.small, w.mid, w.largeA, w.ctr, w.keyB,
+                                                                             w.rmask);
     SS_CHECK_LAUNCH();
     return SS_OK;
 }
@@ -1718,20 +1904,22 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     const u32 *nlp = w.hdr + H_LARGE;
     const u64 most = nlarge.yes ? nlarge.v : n / C.BM;  // radix segments have more than BM strings
     if (most <= LIST_ONE) {
-        k_level_start<<<1, LIST_NT, 0, st>>>(LA, w.ctr, w.hdr, NB, C.TL, w.tstart, w.smin, w.smax, w.hscan);
+        k_level_start<<<1, LIST_NT, 0, st>>>(LA, w.ctr, w.hdr, NB, C.TL, w.tstart, w.smin, w.smax, w.hscan,
+                                            w.rmask, w.dig);
         SS_CHECK_LAUNCH();
     } else {
         k_level_begin<<<1, 256, 0, st>>>(w.ctr, w.hdr, NB, w.hscan);
         SS_CHECK_LAUNCH();
-        k_level_tiles<<<grid_of(most, 256, 1024), 256, 0, st>>>(LA, nlp, C.TL, w.tstart, w.smin, w.smax, w.dscan);
+        k_level_tiles<<<grid_of(most, 256, 1024), 256, 0, st>>>(LA, nlp, C.TL, w.tstart, w.smin, w.smax, w.dscan,
+                                                                w.rmask, w.dig, W);
         SS_CHECK_LAUNCH();
         SS_TRY(scan_u32(C, w.tstart, nlp, most));
     }
     const unsigned tg = ltiles.yes ? grid_of(ltiles.v, 1, 1u << 30) : 0u;  // (one tile per workgroup)
     {
         SS_PROF("k_hist", st, (double)lelem * 8.0);  // read the keys
-        if (ltiles.yes) k_hist<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax);
-        else k_hist<true, W><<<grid_of(n, C.TL, resident(k_hist<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax);
+        if (ltiles.yes) k_hist<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax, w.dig);
+        else k_hist<true, W><<<grid_of(n, C.TL, resident(k_hist<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax, w.dig);
     }
     SS_CHECK_LAUNCH();
     // (three launches once there are more items than one range per workgroup holds)
@@ -1740,19 +1928,19 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     else SS_TRY(ss_scan_exclusive_dev(w.hist, w.hist, w.hdr + H_HIST, nh, w.hscan, st));
     EmitOut eo{w.tiny, w.small, w.mid, LB, w.nxt, w.ident, w.bnd, w.ctr, w.scat, w.kinds, C.BM, C.TL, C.ET};
     constexpr u32 SPG = EPB / Digits<W>::DPT;
-    if (nlarge.yes) k_emit<false, W><<<grid_of(nlarge.v, SPG, 1u << 30), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, eo);
-    else k_emit<true, W><<<grid_of(n / 128, SPG, resident(k_emit<true, W>, 256)), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, eo);
+    if (nlarge.yes) k_emit<false, W><<<grid_of(nlarge.v, SPG, 1u << 30), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, eo);
+    else k_emit<true, W><<<grid_of(n / 128, SPG, resident(k_emit<true, W>, 256)), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, eo);
     SS_CHECK_LAUNCH();
     {
         SS_PROF("k_scatter", st, (double)lelem * 24.0);  // key+payload in and out
-        if (ltiles.yes) k_scatter<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB);
-        else k_scatter<true, W><<<grid_of(n, C.TL, resident(k_scatter<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB);
+        if (ltiles.yes) k_scatter<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB, w.dig);
+        else k_scatter<true, W><<<grid_of(n, C.TL, resident(k_scatter<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB, w.dig);
     }
     SS_CHECK_LAUNCH();
     {
         SS_PROF("k_settle", st, (double)lelem * 8.0);  // at most the scattered keys read back
-        if (ltiles.yes) k_settle<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals);
-        else k_settle<true, W><<<grid_of(n, C.TL, resident(k_settle<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals);
+        if (ltiles.yes) k_settle<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals, w.dig);
+        else k_settle<true, W><<<grid_of(n, C.TL, resident(k_settle<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals, w.dig);
     }
     SS_CHECK_LAUNCH();
     return SS_OK;

@@ -3,14 +3,16 @@
 #include "common.hpp"
 
 // A contiguous range [begin, end) of sorted positions whose strings share a
-// known prefix of `depth` bytes.  aux: bits 0..3 = current key byte of a radix
-// pass, bit 4 = compute the common-prefix skip first, bit 5 = the segment's
-// keys and payload are in the B arrays (radix levels alternate between A and
-// B; everything final is in A).
+// known prefix of `depth` bytes.  aux: bits 0..5 = leading key bits that earlier
+// radix levels have used up, bit 6 = compute the common-prefix skip first, bit 7
+// = the segment's keys and payload are in the B arrays (radix levels alternate
+// between A and B; everything final is in A), bits 8..31 = the radix segment of
+// the round it descends from (whose varying key bits are known; SEG_NOROOT: not).
 struct Seg {
     u32 begin, end, depth, aux;
 };
-enum { SEG_SKIP = 16, SEG_INB = 32 };
+enum { SEG_SKIP = 64, SEG_INB = 128, SEG_ROOT = 8 };  // (SEG_ROOT: shift)
+#define SEG_NOROOT 0xFFFFFF00u
 
 // counters: list lengths, and the tile / element totals of the lists being
 // built (so that grids are known without reading the lists back)
@@ -57,6 +59,7 @@ struct SortWs {
     uint2 *bnd;
     u32 *skipv;
     u64 *smin, *smax;
+    u64 *rmask, *dig;  // per radix segment of a round its varying key bits; per radix segment its digit
     u8 *scat;
     u8 *kinds;  // per radix segment and digit: what the bucket became
     u32 *tstart, *hist;

@@ -47,7 +47,7 @@ __global__ void k_sfx_first(u32 n, SortWs w, u32 block_max, u32 tile)
         w.ctr[n <= BS_SMALL ? C_SMALL : C_MID] = 1;
         w.ctr[C_SMALLN] = n;
     } else {
-        w.largeA[0] = g;
+        w.largeA[0] = Seg{0, n, 0, SEG_NOROOT};
         w.ctr[C_LARGE] = 1;
         w.ctr[C_LTILES] = (n + tile - 1) / tile;
         w.ctr[C_LELEM] = n;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void k_sfx_step(const Seg *act, const u32 *tst
     else if (kind == TY) w.tiny[base[TY] + slot] = o;
     else if (kind == SM) w.small[base[SM] + slot] = o;
     else if (kind == MD) w.mid[base[MD] + slot] = o;
-    else if (kind == LG) w.largeA[base[LG] + slot] = o;
+    else if (kind == LG) w.largeA[base[LG] + slot] = Seg{o.begin, o.end, o.depth, SEG_NOROOT};
 }
 
 // Ranks of every suffix as if it were alone in its group: its position + 1.
