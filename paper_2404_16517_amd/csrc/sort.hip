@@ -1061,10 +1061,18 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
     return it;
 }
 
-#define EPB 8  // emit items per thread in k_emit: 8 segments of 256 digits, or 1 segment of 2048
+// Segments per workgroup in k_emit: two of 256 digits (an item per thread and
+// segment), or one of 2048.  Eight made fewer global atomics, but a chain of
+// scattered reads per thread and too few workgroups (suffix sorting of 8 MB
+// 2068 us, with two 2000, with one 2018).
+template <u32 W>
+struct EmitShape {
+    static constexpr u32 SPG = Digits<W>::DPT == 1 ? 2 : 1;
+    static constexpr u32 EPB = SPG * Digits<W>::DPT;  // items per thread
+};
 
 // Digit counts from the scanned histogram and emission of the sub-segments.
-// A workgroup takes 8 / DPT segments (thread x = digits x + 256 r, r < DPT):
+// A workgroup takes SPG segments (thread x = digits x + 256 r, r < DPT):
 // it counts its entries in LDS, reserves room in every list with one global
 // atomic per list, and then writes the entries.
 template <bool LOOP, u32 W>
@@ -1072,7 +1080,7 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
                                               const u32 *hist, const u64 *smin, const u64 *smax,
                                               const u64 *dig, EmitOut o)
 {
-    constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, SPG = EPB / DPT;  // segments per group
+    constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, SPG = EmitShape<W>::SPG, EPB = EmitShape<W>::EPB;  // segments per group
     __shared__ u32 lcount[K_KINDS], lslot[K_KINDS], lsum[7], gbase[K_KINDS];
     const u32 nseg = *nsegp;
     const u32 ngrp = LOOP ? (nseg + SPG - 1) / SPG : 0u;
@@ -1979,7 +1987,7 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     if (ltiles.yes && nh > SCAN_DEV_MAX) SS_TRY(ss_scan_exclusive<u32>(w.hist, w.hist, nh, (u32 *)w.scan_scratch, st));
     else SS_TRY(ss_scan_exclusive_dev(w.hist, w.hist, w.hdr + H_HIST, nh, w.hscan, st));
     EmitOut eo{w.tiny, w.small, w.mid, LB, w.nxt, w.ident, w.bnd, w.ctr, w.scat, w.kinds, C.BM, C.TL, C.ET};
-    constexpr u32 SPG = EPB / Digits<W>::DPT;
+    constexpr u32 SPG = EmitShape<W>::SPG;
     if (nlarge.yes) k_emit<false, W><<<grid_of(nlarge.v, SPG, 1u << 30), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, eo);
     else k_emit<true, W><<<grid_of(n / 128, SPG, resident(k_emit<true, W>, 256)), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, eo);
     SS_CHECK_LAUNCH();

@@ -383,40 +383,52 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan_dev(const u32 *in, u32 *out, c
     const u64 need = n <= SCAN_ITEMS ? 1 : (n + SCAN_ITEMS - 1) / SCAN_ITEMS;
     const u32 G = need < SCAN_DEV_G ? (u32)need : SCAN_DEV_G;  // ranges (the grid has at least as many workgroups)
     if (blockIdx.x >= G) return;
+    if (n == 0) {
+        if (threadIdx.x == 0) out[0] = 0;
+        return;
+    }
     u32 r = 0, carry = 0;
     if (G > 1) {  // (uniform)
         if (threadIdx.x == 0) s_r = atomicAdd((u32 *)state, 1u);
         __syncthreads();
         r = s_r;
     }
-    const u64 per = (n + G - 1) / G;
+    const u64 per = ((n + G - 1) / G + 15) & ~15ull;  // (whole 64-byte pieces)
     const u64 c0 = (u64)r * per < n ? (u64)r * per : n, c1 = c0 + per < n ? c0 + per : n;
-    if (G > 1) {
-        u32 sum = 0, tot;
-        for (u64 i = c0 + threadIdx.x; i < c1; i += SCAN_NT) sum += in[i];
-        (void)block_excl_scan<u32, SCAN_NT>(sum, &tot);
-        if (threadIdx.x == 0)
-            __hip_atomic_store(state + 1 + r, (1ull << 32) | tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sum = 0;
-        for (u32 q = threadIdx.x; q < r; q += SCAN_NT) {
-            u64 w;
-            while (!((w = __hip_atomic_load(state + 1 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32))
-                __builtin_amdgcn_s_sleep(1);
-            sum += (u32)w;
-        }
-        (void)block_excl_scan<u32, SCAN_NT>(sum, &carry);
-    }
-    for (u64 b = c0; b < c1; b += SCAN_ITEMS) {
-        const u64 e = (b + SCAN_ITEMS < c1) ? b + SCAN_ITEMS : c1;
-        // blocked: thread t takes SCAN_PER consecutive items
+    // a range of up to SCAN_ITEMS (any but in very long arrays) is read once
+    const bool once = per <= SCAN_ITEMS;
+    u32 v[SCAN_PER];
+    u32 sum = 0;
+    auto load = [&](u64 b, u64 e) {  // blocked: thread t takes SCAN_PER consecutive items
         const u64 t0 = b + (u64)threadIdx.x * SCAN_PER;
-        u32 v[SCAN_PER];
-        u32 sum = 0;
+        sum = 0;
 #pragma unroll
         for (int q = 0; q < SCAN_PER; q++) {
             v[q] = (t0 + q < e) ? in[t0 + q] : 0u;
             sum += v[q];
         }
+    };
+    if (once) load(c0, c1);
+    if (G > 1) {
+        u32 tot;
+        if (!once)
+            for (u64 i = c0 + threadIdx.x; i < c1; i += SCAN_NT) sum += in[i];
+        (void)block_excl_scan<u32, SCAN_NT>(sum, &tot);
+        if (threadIdx.x == 0)
+            __hip_atomic_store(state + 1 + r, (1ull << 32) | tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        u32 before = 0;
+        for (u32 q = threadIdx.x; q < r; q += SCAN_NT) {
+            u64 w;
+            while (!((w = __hip_atomic_load(state + 1 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32))
+                __builtin_amdgcn_s_sleep(1);
+            before += (u32)w;
+        }
+        (void)block_excl_scan<u32, SCAN_NT>(before, &carry);
+    }
+    for (u64 b = c0; b < c1; b += SCAN_ITEMS) {
+        const u64 e = (b + SCAN_ITEMS < c1) ? b + SCAN_ITEMS : c1;
+        const u64 t0 = b + (u64)threadIdx.x * SCAN_PER;
+        if (!once) load(b, e);
         u32 tot;
         u32 pre = block_excl_scan<u32, SCAN_NT>(sum, &tot) + carry;
 #pragma unroll
