@@ -252,13 +252,40 @@ __global__ __launch_bounds__(LIST_NT) void k_round_start(const Seg *segs, u32 *c
 // k_level_begin, k_level_tiles and the scan for up to LIST_ONE segments: one
 // launch, where four to six took longer than the level's work on small inputs
 // (sorting 100,000 D/N strings, two levels: 218 us with them, 199 us so).
-__global__ __launch_bounds__(LIST_NT) void k_level_start(const Seg *segs, u32 *ctr, u32 *hdr, u32 nb, u32 tile,
+//
+// WG: segments of up to wg_max strings are taken out and listed in wl (see
+// k_radix_wg).
+template <bool WG>
+__global__ __launch_bounds__(LIST_NT) void k_level_start(Seg *segs, u32 *ctr, u32 *hdr, u32 nb, u32 tile,
                                                          u32 *tstart, u64 *smin, u64 *smax, u64 *hscan,
-                                                         const u64 *rmask, u64 *dig)
+                                                         const u64 *rmask, u64 *dig, Seg *wl, u32 wg_max)
 {
-    const u32 nseg = ctr[C_LARGE];
+    u32 nseg = ctr[C_LARGE];
     scan_state_zero(hscan);
     __syncthreads();
+    if (WG) {
+        __shared__ u32 s_keep;
+        if (threadIdx.x == 0) s_keep = 0;
+        for (u32 b = 0; b < nseg; b += LIST_NT) {
+            const u32 j = b + threadIdx.x;
+            Seg x = {0, 0, 0, 0};
+            if (j < nseg) x = segs[j];
+            __syncthreads();  // (kept segments go to places already read)
+            const bool keep = x.end - x.begin > wg_max;
+            const u64 mk = __ballot(keep), ml = __ballot(j < nseg && !keep);
+            u32 ak = 0, al = 0;
+            if (__lane_id() == 0) {
+                if (mk) ak = atomicAdd(&s_keep, (u32)__popcll(mk));
+                if (ml) al = atomicAdd(&ctr[C_WG], (u32)__popcll(ml));
+            }
+            ak = __shfl(ak, 0, 64);
+            al = __shfl(al, 0, 64);
+            if (keep) segs[ak + (u32)__popcll(mk & lanemask_lt())] = x;
+            else if (j < nseg) wl[al + (u32)__popcll(ml & lanemask_lt())] = x;
+        }
+        __syncthreads();
+        nseg = s_keep;
+    }
     for (u32 j = threadIdx.x; j < nseg; j += LIST_NT) {
         smin[j] = ~0ull;
         smax[j] = 0;
@@ -998,6 +1025,45 @@ struct EmitItem {
     uint2 bv;
 };
 
+// ... once the segment is known not to share the whole digit (start: members in
+// lower buckets; mn: any of its keys).
+__device__ __forceinline__ EmitItem emit_bucket(const Seg &g, const Digit &D, u64 mn, u32 d, u32 start, u32 cnt,
+                                                u32 small_max)
+{
+    EmitItem it{K_NONE, Seg{0, 0, 0, 0}, false, make_uint2(0, 0)};
+    const u32 cf = (g.aux & SEG_INB) ? 0u : (u32)SEG_INB;  // the scatter writes the other arrays
+    const u32 sb = g.begin + start, se = sb + cnt;
+    it.bnd = cnt > 0 && start > 0;
+    it.bv = make_uint2(sb, g.depth);
+    it.ns = Seg{sb, se, g.depth, cf};
+    if (cnt >= 2) {
+        if (D.used == 64) {
+            // no varying bit is left: the bucket's keys are equal in all 64
+            // bits, and their last byte counts the strings' bytes
+            const u32 c8 = (u32)digit_put(mn, d, D) & 0xFFu;
+            if (c8 == 8) { it.kind = K_NEXT; it.ns = Seg{sb, se, g.depth + 7, SEG_SKIP}; }
+            else { it.kind = K_IDENT; it.ns = Seg{sb, se, g.depth + c8, 0}; }
+        } else if (cnt <= WS_MAX) {
+            it.kind = K_TINY;
+        } else if (cnt <= small_max) {
+            it.kind = cnt <= BS_SMALL ? K_SMALL : K_MID;
+        } else {
+            it.kind = K_LARGE;
+            it.ns.aux = D.used | cf | (g.aux & SEG_NOROOT);
+        }
+    }
+    return it;
+}
+
+// A segment of one key (all 8 bytes): it continues in the next round, or its
+// strings are equal.
+__device__ __forceinline__ EmitItem emit_whole(const Seg &g, u64 key)
+{
+    const u32 cnt = (u32)(key & 0xFF);
+    if (cnt == 8) return EmitItem{K_NEXT, Seg{g.begin, g.end, g.depth + 7, SEG_SKIP}, false, make_uint2(0, 0)};
+    return EmitItem{K_IDENT, Seg{g.begin, g.end, g.depth + cnt, 0}, false, make_uint2(0, 0)};
+}
+
 template <u32 W>
 __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart, const u32 *hist, const u64 *smin,
                                               const u64 *smax, const u64 *dig, const EmitOut &o, u32 s, u32 d,
@@ -1013,15 +1079,8 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
     // next-round and equal-string runs (and singletons) end in A: the settle
     // pass copies them there; the other kinds carry their buffer flag
     if (mn == mx) {
-        // one key for the whole segment (all 8 bytes): continue next round,
-        // or equal strings
         *scat = false;
-        const u32 cnt = (u32)(mn & 0xFF);
-        if (d == 0) {
-            if (cnt == 8) { it.kind = K_NEXT; it.ns = Seg{g.begin, g.end, g.depth + 7, SEG_SKIP}; }
-            else { it.kind = K_IDENT; it.ns = Seg{g.begin, g.end, g.depth + cnt, 0}; }
-        }
-        return it;
+        return d == 0 ? emit_whole(g, mn) : it;
     }
     const u32 fd = (u32)__clzll(mn ^ mx);  // leading bits that all keys share
     if (fd > 63 - D.low) {
@@ -1031,34 +1090,11 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
         return it;
     }
     *scat = true;
-    const u32 cf = pf ? 0u : (u32)SEG_INB;  // the scatter writes the other arrays
     const u32 ts = tstart[s];
     const u32 T = tstart[s + 1] - ts;
     const u32 e = NB * ts + d * T;
     const u32 base = hist[NB * ts];
-    const u32 start = hist[e] - base;
-    const u32 cnt = hist[e + T] - hist[e];
-    const u32 sb = g.begin + start, se = sb + cnt;
-    it.bnd = cnt > 0 && start > 0;
-    it.bv = make_uint2(sb, g.depth);
-    it.ns = Seg{sb, se, g.depth, cf};
-    if (cnt >= 2) {
-        if (D.used == 64) {
-            // no varying bit is left: the bucket's keys are equal in all 64
-            // bits, and their last byte counts the strings' bytes
-            const u32 c8 = (u32)digit_put(mn, d, D) & 0xFFu;
-            if (c8 == 8) { it.kind = K_NEXT; it.ns = Seg{sb, se, g.depth + 7, SEG_SKIP}; }
-            else { it.kind = K_IDENT; it.ns = Seg{sb, se, g.depth + c8, 0}; }
-        } else if (cnt <= WS_MAX) {
-            it.kind = K_TINY;
-        } else if (cnt <= o.small_max) {
-            it.kind = cnt <= BS_SMALL ? K_SMALL : K_MID;
-        } else {
-            it.kind = K_LARGE;
-            it.ns.aux = D.used | cf | rt;
-        }
-    }
-    return it;
+    return emit_bucket(g, D, mn, d, hist[e] - base, hist[e + T] - hist[e], o.small_max);
 }
 
 // Segments per workgroup in k_emit: two of 256 digits (an item per thread and
@@ -1071,30 +1107,84 @@ struct EmitShape {
     static constexpr u32 EPB = SPG * Digits<W>::DPT;  // items per thread
 };
 
+// The items of a workgroup into their lists: counted in LDS, one global atomic
+// per list, then written.  Before it, emit_zero; it ends with a barrier.
+struct EmitLds {
+    u32 count[K_KINDS], slot[K_KINDS], sum[7], base[K_KINDS];
+};
+
+__device__ __forceinline__ void emit_zero(EmitLds &L)
+{
+    if (threadIdx.x < K_KINDS) { L.count[threadIdx.x] = 0; L.slot[threadIdx.x] = 0; }
+    if (threadIdx.x < 7) L.sum[threadIdx.x] = 0;
+}
+
+template <u32 EPB>
+__device__ __forceinline__ void emit_push(const EmitItem (&it)[EPB], const EmitOut &o, EmitLds &L)
+{
+    const u32 tx = threadIdx.x;
+    __syncthreads();
+#pragma unroll
+    for (u32 q = 0; q < EPB; q++) {
+        const EmitItem &x = it[q];
+        const u32 cnt = x.ns.end - x.ns.begin;
+        if (x.bnd) atomicAdd(&L.count[0], 1u);
+        if (x.kind) atomicAdd(&L.count[x.kind], 1u);
+        if (x.kind == K_SMALL || x.kind == K_MID) atomicAdd(&L.sum[0], cnt);
+        if (x.kind == K_LARGE) { atomicAdd(&L.sum[1], (cnt + o.tile - 1) / o.tile); atomicAdd(&L.sum[2], cnt); }
+        if (x.kind == K_NEXT) { atomicAdd(&L.sum[3], (cnt + o.et - 1) / o.et); atomicAdd(&L.sum[4], cnt); }
+        if (x.kind == K_IDENT) atomicAdd(&L.sum[5], (cnt + o.et - 1) / o.et);
+        if (x.kind == K_TINY) atomicAdd(&L.sum[6], cnt);
+    }
+    __syncthreads();
+    // (a thread per counter: one after the other they took most of the kernel on
+    // small inputs)
+    static_assert(K_KINDS == 7, "counters of the lists");
+    if (tx < 14) {
+        u32 to = C_BND;
+        to = tx == K_SMALL ? (u32)C_SMALL : tx == K_LARGE ? (u32)C_LARGE : tx == K_NEXT ? (u32)C_NEXT : to;
+        to = tx == K_IDENT ? (u32)C_IDENT : tx == K_TINY ? (u32)C_TINY : tx == K_MID ? (u32)C_MID : to;
+        to = tx == 7 ? (u32)C_SMALLN : tx == 8 ? (u32)C_LTILES : tx == 9 ? (u32)C_LELEM : to;
+        to = tx == 10 ? (u32)C_NTILES : tx == 11 ? (u32)C_NELEM : tx == 12 ? (u32)C_ITILES : tx == 13 ? (u32)C_TINYN : to;
+        const u32 v = tx < 7 ? L.count[tx] : L.sum[tx - 7];
+        if (v) {
+            const u32 at = atomicAdd(&o.ctr[to], v);
+            if (tx < 7) L.base[tx] = at;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (u32 q = 0; q < EPB; q++) {
+        const EmitItem &x = it[q];
+        if (x.bnd) o.bnd[L.base[0] + atomicAdd(&L.slot[0], 1u)] = x.bv;
+        if (x.kind) {
+            const u32 a = L.base[x.kind] + atomicAdd(&L.slot[x.kind], 1u);
+            Seg *dst = x.kind == K_TINY ? o.tiny : x.kind == K_SMALL ? o.small : x.kind == K_MID ? o.mid
+                     : x.kind == K_LARGE ? o.large_next : x.kind == K_NEXT ? o.next : o.ident;
+            dst[a] = x.ns;
+        }
+    }
+    __syncthreads();  // the LDS counters are reset for the next group
+}
+
 // Digit counts from the scanned histogram and emission of the sub-segments.
-// A workgroup takes SPG segments (thread x = digits x + 256 r, r < DPT):
-// it counts its entries in LDS, reserves room in every list with one global
-// atomic per list, and then writes the entries.
+// A workgroup takes SPG segments (thread x = digits x + 256 r, r < DPT).
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart, const u32 *nsegp,
                                               const u32 *hist, const u64 *smin, const u64 *smax,
                                               const u64 *dig, EmitOut o)
 {
-    constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, SPG = EmitShape<W>::SPG, EPB = EmitShape<W>::EPB;  // segments per group
-    __shared__ u32 lcount[K_KINDS], lslot[K_KINDS], lsum[7], gbase[K_KINDS];
+    constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, SPG = EmitShape<W>::SPG, EPB = EmitShape<W>::EPB;
+    __shared__ EmitLds L;
     const u32 nseg = *nsegp;
     const u32 ngrp = LOOP ? (nseg + SPG - 1) / SPG : 0u;
     TILE_LOOP(grp, ngrp) {
-    const u32 s0 = grp * SPG;
-    const u32 tx = threadIdx.x;
-    if (tx < K_KINDS) { lcount[tx] = 0; lslot[tx] = 0; }
-    if (tx < 7) lsum[tx] = 0;
-    __syncthreads();
+    emit_zero(L);
     EmitItem it[EPB];
 #pragma unroll
     for (u32 q = 0; q < EPB; q++) {
-        const u32 s = s0 + q / DPT;
-        const u32 d = tx + 256u * (q % DPT);
+        const u32 s = grp * SPG + q / DPT;
+        const u32 d = threadIdx.x + 256u * (q % DPT);
         it[q].kind = K_NONE;
         it[q].bnd = false;
         if (s >= nseg) continue;
@@ -1102,46 +1192,8 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
         it[q] = emit_item<W>(segs, tstart, hist, smin, smax, dig, o, s, d, &sc);
         if (d == 0) o.scat[s] = sc ? 1 : 0;
         o.kinds[NB * s + d] = (u8)it[q].kind;
-        const EmitItem &x = it[q];
-        const u32 cnt = x.ns.end - x.ns.begin;
-        if (x.bnd) atomicAdd(&lcount[0], 1u);
-        if (x.kind) atomicAdd(&lcount[x.kind], 1u);
-        if (x.kind == K_SMALL || x.kind == K_MID) atomicAdd(&lsum[0], cnt);
-        if (x.kind == K_LARGE) { atomicAdd(&lsum[1], (cnt + o.tile - 1) / o.tile); atomicAdd(&lsum[2], cnt); }
-        if (x.kind == K_NEXT) { atomicAdd(&lsum[3], (cnt + o.et - 1) / o.et); atomicAdd(&lsum[4], cnt); }
-        if (x.kind == K_IDENT) atomicAdd(&lsum[5], (cnt + o.et - 1) / o.et);
-        if (x.kind == K_TINY) atomicAdd(&lsum[6], cnt);
     }
-    __syncthreads();
-    if (tx == 0) {
-        gbase[0] = lcount[0] ? atomicAdd(&o.ctr[C_BND], lcount[0]) : 0u;
-        gbase[K_SMALL] = lcount[K_SMALL] ? atomicAdd(&o.ctr[C_SMALL], lcount[K_SMALL]) : 0u;
-        gbase[K_LARGE] = lcount[K_LARGE] ? atomicAdd(&o.ctr[C_LARGE], lcount[K_LARGE]) : 0u;
-        gbase[K_NEXT] = lcount[K_NEXT] ? atomicAdd(&o.ctr[C_NEXT], lcount[K_NEXT]) : 0u;
-        gbase[K_IDENT] = lcount[K_IDENT] ? atomicAdd(&o.ctr[C_IDENT], lcount[K_IDENT]) : 0u;
-        gbase[K_TINY] = lcount[K_TINY] ? atomicAdd(&o.ctr[C_TINY], lcount[K_TINY]) : 0u;
-        gbase[K_MID] = lcount[K_MID] ? atomicAdd(&o.ctr[C_MID], lcount[K_MID]) : 0u;
-        if (lsum[0]) atomicAdd(&o.ctr[C_SMALLN], lsum[0]);
-        if (lsum[1]) atomicAdd(&o.ctr[C_LTILES], lsum[1]);
-        if (lsum[2]) atomicAdd(&o.ctr[C_LELEM], lsum[2]);
-        if (lsum[3]) atomicAdd(&o.ctr[C_NTILES], lsum[3]);
-        if (lsum[4]) atomicAdd(&o.ctr[C_NELEM], lsum[4]);
-        if (lsum[5]) atomicAdd(&o.ctr[C_ITILES], lsum[5]);
-        if (lsum[6]) atomicAdd(&o.ctr[C_TINYN], lsum[6]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (u32 q = 0; q < EPB; q++) {
-        const EmitItem &x = it[q];
-        if (x.bnd) o.bnd[gbase[0] + atomicAdd(&lslot[0], 1u)] = x.bv;
-        if (x.kind) {
-            const u32 a = gbase[x.kind] + atomicAdd(&lslot[x.kind], 1u);
-            Seg *dst = x.kind == K_TINY ? o.tiny : x.kind == K_SMALL ? o.small : x.kind == K_MID ? o.mid
-                     : x.kind == K_LARGE ? o.large_next : x.kind == K_NEXT ? o.next : o.ident;
-            dst[a] = x.ns;
-        }
-    }
-    __syncthreads();  // the LDS counters are reset for the next group
+    emit_push(it, o, L);
     }
 }
 
@@ -1159,20 +1211,130 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
 // its element where it belongs and the wavefronts took turns at each 256, now
 // 103; 26 buckets took 112 then.  1024 elements a chunk: 4 % longer sorts.
 #define SC_PER 8  // elements per thread and chunk
-#define SC_ITEMS (SC_PER * NT)
+template <u32 W, u32 NTB = NT>
+struct ScatterLds {
+    static constexpr u32 ITEMS = SC_PER * NTB;  // elements of a chunk
+    static constexpr bool HALF = W > 8;  // counts (at most ITEMS) in 16 bits, two to a word
+    static constexpr u32 CW = HALF ? Digits<W>::NB / 2 : Digits<W>::NB;
+    u64 sk[ITEMS];
+    u32 sv[ITEMS];
+    u32 cnt[NTB / 64][CW];    // per wavefront and digit: elements so far, then their place in the chunk
+    u32 gofs[Digits<W>::NB];  // output position of a bucket's element, less its place in the chunk
+    u32 wsum[NTB / 64];
+};
+
+// Elements [b0, b1) by digit D; run: see k_scatter (the first 256 threads').
+template <u32 W, u32 NTB = NT>
+__device__ __forceinline__ void scatter_range(ScatterLds<W, NTB> &L, const Digit &D, const u64 *ksrc, const u32 *vsrc,
+                                              u64 *kdst, u32 *vdst, u32 b0, u32 b1, u32 (&run)[Digits<W>::DPT])
+{
+    constexpr u32 DPT = Digits<W>::DPT, NW = NTB / 64, CW = ScatterLds<W, NTB>::CW, SC_ITEMS = ScatterLds<W, NTB>::ITEMS;
+    constexpr bool HALF = ScatterLds<W, NTB>::HALF;
+    const bool dt = NTB == 256 || threadIdx.x < 256;  // owns digits
+    const u32 wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (u32 c0 = b0; c0 < b1; c0 += SC_ITEMS) {
+        const u32 m = b1 - c0 < SC_ITEMS ? b1 - c0 : SC_ITEMS;
+        u64 kq[SC_PER];
+        u32 vq[SC_PER], pos[SC_PER];
+#pragma unroll
+        for (u32 q = 0; q < SC_PER; q++) {
+            const u32 i = (wid * SC_PER + q) * 64 + lane;
+            kq[q] = 0;
+            vq[q] = 0;
+            if (i < m) {
+                kq[q] = ksrc[c0 + i];
+                vq[q] = vsrc[c0 + i];
+            }
+        }
+        for (u32 d = threadIdx.x; d < NW * CW; d += NTB) (&L.cnt[0][0])[d] = 0;
+        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < SC_PER; q++) {
+            const bool valid = (wid * SC_PER + q) * 64 + lane < m;
+            const u32 d = digit_of(kq[q], D);
+            const u64 peers = match_digit_w<W>(d, valid);
+            const u32 rank = (u32)__popcll(peers & lanemask_lt());
+            u32 old = 0;
+            if (valid && rank == 0) {
+                const u32 np = (u32)__popcll(peers);
+                if (HALF) old = (atomicAdd(&L.cnt[wid][d >> 1], np << (16 * (d & 1))) >> (16 * (d & 1))) & 0xFFFFu;
+                else old = atomicAdd(&L.cnt[wid][d], np);
+            }
+            const int leader = valid ? __ffsll((unsigned long long)peers) - 1 : (int)lane;
+            pos[q] = __shfl(old, leader, 64) + rank;
+        }
+        __syncthreads();
+        {
+            u32 c[NW][DPT], sum = 0;
+#pragma unroll
+            for (u32 r = 0; r < DPT; r++)
+#pragma unroll
+                for (u32 w = 0; w < NW; w++) {
+                    const u32 d = threadIdx.x * DPT + r;
+                    c[w][r] = !dt ? 0u : HALF ? (L.cnt[w][d >> 1] >> (16 * (d & 1))) & 0xFFFFu : L.cnt[w][d];
+                    sum += c[w][r];
+                }
+            u32 x = sum;
+#pragma unroll
+            for (u32 o = 1; o < 64; o <<= 1) {
+                const u32 y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
+            }
+            if (lane == 63) L.wsum[wid] = x;
+            __syncthreads();
+            x -= sum;
+#pragma unroll
+            for (u32 w = 0; w < NW; w++)
+                if (w < wid) x += L.wsum[w];
+            u32 pk[NW];  // (16 bits: this thread's even digit, for the odd one's word)
+#pragma unroll
+            for (u32 r = 0; r < DPT; r++) {
+                if (!dt) break;
+                const u32 d = threadIdx.x * DPT + r, x0 = x;
+                L.gofs[d] = run[r] - x0;
+#pragma unroll
+                for (u32 w = 0; w < NW; w++) {
+                    if (!HALF) L.cnt[w][d] = x;
+                    else if (r & 1) L.cnt[w][d >> 1] = pk[w] | (x << 16);
+                    else pk[w] = x;
+                    x += c[w][r];
+                }
+                run[r] += x - x0;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < SC_PER; q++) {
+            if ((wid * SC_PER + q) * 64 + lane < m) {
+                const u32 d = digit_of(kq[q], D);
+                const u32 x = pos[q] + (HALF ? (L.cnt[wid][d >> 1] >> (16 * (d & 1))) & 0xFFFFu : L.cnt[wid][d]);
+                L.sk[x] = kq[q];
+                L.sv[x] = vq[q];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (u32 q = 0; q < SC_PER; q++) {
+            const u32 x = q * NTB + threadIdx.x;
+            if (x < m) {
+                const u64 k = L.sk[x];
+                const u32 dst = L.gofs[digit_of(k, D)] + x;
+                kdst[dst] = k;
+                vdst[dst] = L.sv[x];
+            }
+        }
+        // (the next chunk's first barrier comes before anything here is rewritten,
+        // but for the counts, which nothing above reads any more)
+    }
+}
+
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
                                                 const u32 *hist, const u8 *scat, u64 *keyA, u32 *valA,
                                                 u64 *keyB, u32 *valB, const u64 *dig)
 {
-    constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, NW = NT / 64;
-    constexpr bool HALF = W > 8;  // counts (at most SC_ITEMS) in 16 bits, two to a word
-    constexpr u32 CW = HALF ? NB / 2 : NB;
-    __shared__ u64 sk[SC_ITEMS];
-    __shared__ u32 sv[SC_ITEMS];
-    __shared__ u32 cnt[NW][CW];  // per wavefront and digit: elements so far, then their place in the chunk
-    __shared__ u32 gofs[NB];     // output position of a bucket's element, less its place in the chunk
-    __shared__ u32 wsum[NW];
+    constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT;
+    __shared__ ScatterLds<W> L;
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
     TILE_LOOP(t, ntiles) {
@@ -1191,104 +1353,140 @@ __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tsta
     const u32 b0 = g.begin + lt * tile;
     const u32 b1 = min(g.end, b0 + tile);
     const u32 base = hist[NB * ts];
-    const u32 wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
     u32 run[DPT];  // next free position of the thread's digits, DPT neighbouring ones
 #pragma unroll
     for (u32 r = 0; r < DPT; r++) run[r] = g.begin + hist[NB * ts + (threadIdx.x * DPT + r) * T + lt] - base;
-    for (u32 c0 = b0; c0 < b1; c0 += SC_ITEMS) {
-        const u32 m = b1 - c0 < SC_ITEMS ? b1 - c0 : SC_ITEMS;
-        u64 kq[SC_PER];
-        u32 vq[SC_PER], pos[SC_PER];
-#pragma unroll
-        for (u32 q = 0; q < SC_PER; q++) {
-            const u32 i = (wid * SC_PER + q) * 64 + lane;
-            kq[q] = 0;
-            vq[q] = 0;
-            if (i < m) {
-                kq[q] = ksrc[c0 + i];
-                vq[q] = vsrc[c0 + i];
-            }
-        }
-        for (u32 d = threadIdx.x; d < NW * CW; d += NT) (&cnt[0][0])[d] = 0;
-        __syncthreads();
-#pragma unroll
-        for (u32 q = 0; q < SC_PER; q++) {
-            const bool valid = (wid * SC_PER + q) * 64 + lane < m;
-            const u32 d = digit_of(kq[q], D);
-            const u64 peers = match_digit_w<W>(d, valid);
-            const u32 rank = (u32)__popcll(peers & lanemask_lt());
-            u32 old = 0;
-            if (valid && rank == 0) {
-                const u32 np = (u32)__popcll(peers);
-                if (HALF) old = (atomicAdd(&cnt[wid][d >> 1], np << (16 * (d & 1))) >> (16 * (d & 1))) & 0xFFFFu;
-                else old = atomicAdd(&cnt[wid][d], np);
-            }
-            const int leader = valid ? __ffsll((unsigned long long)peers) - 1 : (int)lane;
-            pos[q] = __shfl(old, leader, 64) + rank;
-        }
-        __syncthreads();
-        {
-            u32 c[NW][DPT], sum = 0;
-#pragma unroll
-            for (u32 r = 0; r < DPT; r++)
-#pragma unroll
-                for (u32 w = 0; w < NW; w++) {
-                    const u32 d = threadIdx.x * DPT + r;
-                    c[w][r] = HALF ? (cnt[w][d >> 1] >> (16 * (d & 1))) & 0xFFFFu : cnt[w][d];
-                    sum += c[w][r];
-                }
-            u32 x = sum;
-#pragma unroll
-            for (u32 o = 1; o < 64; o <<= 1) {
-                const u32 y = __shfl_up(x, o, 64);
-                if (lane >= o) x += y;
-            }
-            if (lane == 63) wsum[wid] = x;
-            __syncthreads();
-            x -= sum;
-#pragma unroll
-            for (u32 w = 0; w < NW; w++)
-                if (w < wid) x += wsum[w];
-            u32 pk[NW];  // (16 bits: this thread's even digit, for the odd one's word)
-#pragma unroll
-            for (u32 r = 0; r < DPT; r++) {
-                const u32 d = threadIdx.x * DPT + r, x0 = x;
-                gofs[d] = run[r] - x0;
-#pragma unroll
-                for (u32 w = 0; w < NW; w++) {
-                    if (!HALF) cnt[w][d] = x;
-                    else if (r & 1) cnt[w][d >> 1] = pk[w] | (x << 16);
-                    else pk[w] = x;
-                    x += c[w][r];
-                }
-                run[r] += x - x0;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (u32 q = 0; q < SC_PER; q++) {
-            if ((wid * SC_PER + q) * 64 + lane < m) {
-                const u32 d = digit_of(kq[q], D);
-                const u32 x = pos[q] + (HALF ? (cnt[wid][d >> 1] >> (16 * (d & 1))) & 0xFFFFu : cnt[wid][d]);
-                sk[x] = kq[q];
-                sv[x] = vq[q];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (u32 q = 0; q < SC_PER; q++) {
-            const u32 x = q * NT + threadIdx.x;
-            if (x < m) {
-                const u64 k = sk[x];
-                const u32 dst = gofs[digit_of(k, D)] + x;
-                kdst[dst] = k;
-                vdst[dst] = sv[x];
-            }
-        }
-        // (the next chunk's first barrier comes before anything here is rewritten,
-        // but for the counts, which nothing above reads any more)
-    }
+    scatter_range<W>(L, D, ksrc, vsrc, kdst, vdst, b0, b1, run);
     __syncthreads();  // (the next tile)
+    }
+}
+
+// All radix levels of a segment by one workgroup, for the sorts that a captured
+// graph repeats: their levels are enqueued whether or not there is work, and
+// eight levels of six launches, most of them empty, were 240 of 410 us for 64
+// sets of 100 to 10,000 strings.  Segments of up to WG_MAX strings come here
+// at once (32 elements a thread and pass), and what one or two levels over the
+// whole device leave, however large.  The segments of a level that need another wait
+// in `stack`, which holds one entry per `slot` = small_max + 1 strings: each
+// has more members than small_max, so those of one segment fit its own part.
+//
+// A workgroup of 1024: with 256 the sets of up to 10,000 strings took 46 us, now
+// 40.
+#define WG_NT 1024
+#define WG_MAX 32768
+// Levels over the whole device before it: none where no segment can be larger,
+// one where its share of a sort of 16 such segments is left, else two.
+static u32 wg_levels(u64 n) { return n <= WG_MAX ? 0 : (n <= 16 * WG_MAX ? 1 : 2); }
+__global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nwl, const Seg *la, const u32 *nla,
+                                                 Seg *stack, u32 slot, const u64 *rmask, u64 *keyA, u32 *valA,
+                                                 u64 *keyB, u32 *valB, EmitOut o)
+{
+    __shared__ ScatterLds<8, WG_NT> L;
+    __shared__ EmitLds E;
+    __shared__ u32 h[256], wsum[4], s_push;
+    __shared__ u8 kd[256];
+    const u32 nw = *nwl, total = nw + *nla;
+    const u32 t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    for (u32 s = blockIdx.x; s < total; s += gridDim.x) {  // (uniform over the workgroup)
+        Seg g = s < nw ? wl[s] : la[s - nw];
+        Seg *const st = stack + g.begin / slot;
+        u32 sp = 0;
+        for (;;) {
+            const bool inb = g.aux & SEG_INB;
+            const u64 *ksrc = inb ? keyB : keyA;
+            const u32 *vsrc = inb ? valB : valA;
+            const Digit D = digit_unpack(digit_spec(g, rmask, 8));
+            if (t < 256) h[t] = 0;
+            if (t == 0) s_push = 0;
+            emit_zero(E);
+            __syncthreads();
+            u64 mn = ~0ull, mx = 0;
+            for (u32 c0 = g.begin; c0 < g.end; c0 += RX_PF * WG_NT) {
+                u64 kq[RX_PF];
+#pragma unroll
+                for (u32 q = 0; q < RX_PF; q++) {
+                    const u32 i = c0 + q * WG_NT + t;
+                    kq[q] = i < g.end ? ksrc[i] : 0;
+                }
+#pragma unroll
+                for (u32 q = 0; q < RX_PF; q++) {
+                    if (c0 + q * WG_NT >= g.end) break;  // (uniform)
+                    const bool valid = c0 + q * WG_NT + t < g.end;
+                    const u32 d = digit_of(kq[q], D);
+                    const u64 peers = match_digit_w<8>(d, valid);
+                    if (valid) {
+                        mn = kq[q] < mn ? kq[q] : mn;
+                        mx = kq[q] > mx ? kq[q] : mx;
+                        if ((peers & lanemask_lt()) == 0) atomicAdd(&h[d], (u32)__popcll(peers));
+                    }
+                }
+            }
+            mn = block_min<u64, WG_NT>(mn);
+            mx = ~block_min<u64, WG_NT>(~mx);  // (its barriers: h is complete)
+            const u32 fd = mn == mx ? 64u : (u32)__clzll(mn ^ mx);
+            EmitItem it[1] = {EmitItem{K_NONE, Seg{0, 0, 0, 0}, false, make_uint2(0, 0)}};
+            if (fd < 64 && fd > 63 - D.low) {  // the whole digit is common
+                g.aux = fd | (g.aux & (SEG_INB | SEG_NOROOT));
+                __syncthreads();
+                continue;
+            }
+            if (fd == 64) {
+                if (t == 0) it[0] = emit_whole(g, mn);
+                emit_push(it, o, E);
+                if (inb)
+                    for (u32 i = g.begin + t; i < g.end; i += WG_NT) {
+                        keyA[i] = keyB[i];
+                        valA[i] = valB[i];
+                    }
+            } else {
+                const u32 cnt = t < 256 ? h[t] : 0u;
+                u32 x = cnt;
+#pragma unroll
+                for (u32 d = 1; d < 64; d <<= 1) {
+                    const u32 y = __shfl_up(x, d, 64);
+                    if (lane >= d) x += y;
+                }
+                if (lane == 63 && wid < 4) wsum[wid] = x;
+                __syncthreads();
+                x -= cnt;
+#pragma unroll
+                for (u32 w = 0; w < 4; w++)
+                    if (w < wid) x += wsum[w];
+                if (t < 256) {
+                    it[0] = emit_bucket(g, D, mn, t, x, cnt, o.small_max);
+                    kd[t] = (u8)it[0].kind;
+                }
+                if (it[0].kind == K_LARGE) {
+                    st[sp + atomicAdd(&s_push, 1u)] = it[0].ns;
+                    it[0].kind = K_NONE;
+                }
+                emit_push(it, o, E);
+                sp += s_push;
+                u32 run[1] = {g.begin + x};
+                scatter_range<8, WG_NT>(L, D, ksrc, vsrc, inb ? keyA : keyB, inb ? valA : valB, g.begin, g.end, run);
+                __syncthreads();
+                if (!inb)  // what no later kernel rewrites back to A
+                    for (u32 c0 = g.begin; c0 < g.end; c0 += RX_PF * WG_NT) {
+                        u64 kq[RX_PF];
+#pragma unroll
+                        for (u32 q = 0; q < RX_PF; q++) {
+                            const u32 i = c0 + q * WG_NT + t;
+                            kq[q] = i < g.end ? keyB[i] : 0;
+                        }
+#pragma unroll
+                        for (u32 q = 0; q < RX_PF; q++) {
+                            const u32 i = c0 + q * WG_NT + t, c = kd[digit_of(kq[q], D)];
+                            if (i < g.end && (c == K_NONE || c == K_NEXT || c == K_IDENT)) {
+                                keyA[i] = kq[q];
+                                valA[i] = valB[i];
+                            }
+                        }
+                    }
+            }
+            __syncthreads();  // (s_push, h, kd and the stack's entry)
+            if (sp == 0) break;
+            g = st[--sp];
+        }
     }
 }
 
@@ -1810,6 +2008,7 @@ void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c)
     TAKE(ident, Seg, nseg);
     TAKE(largeA, Seg, nlarge);
     TAKE(largeB, Seg, nlarge);
+    TAKE(wgl, Seg, nlarge);
     TAKE(bnd, uint2, n + 1);
     TAKE(skipv, u32, nseg);
     TAKE(smin, u64, nlarge);
@@ -1954,7 +2153,7 @@ static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bo
 // One radix level over the list LA (its length in ctr[C_LARGE] when the level
 // starts); its sub-lists go to LB and the round's lists.
 template <u32 W>
-static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltiles, u64 lelem)
+static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltiles, u64 lelem, bool wg)
 {
     constexpr u32 NB = Digits<W>::NB;
     SortWs &w = C.w;
@@ -1964,8 +2163,9 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     const u32 *nlp = w.hdr + H_LARGE;
     const u64 most = nlarge.yes ? nlarge.v : n / C.BM;  // radix segments have more than BM strings
     if (most <= LIST_ONE) {
-        k_level_start<<<1, LIST_NT, 0, st>>>(LA, w.ctr, w.hdr, NB, C.TL, w.tstart, w.smin, w.smax, w.hscan,
-                                            w.rmask, w.dig);
+        auto *const start = wg ? k_level_start<true> : k_level_start<false>;
+        start<<<1, LIST_NT, 0, st>>>(LA, w.ctr, w.hdr, NB, C.TL, w.tstart, w.smin, w.smax, w.hscan,
+                                            w.rmask, w.dig, w.wgl, WG_MAX);
         SS_CHECK_LAUNCH();
     } else {
         k_level_begin<<<1, 256, 0, st>>>(w.ctr, w.hdr, NB, w.hscan);
@@ -2006,10 +2206,10 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     return SS_OK;
 }
 
-static int radix_level(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltiles, u64 lelem)
+static int radix_level(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltiles, u64 lelem, bool wg = false)
 {
-    return C.W == 11 ? radix_level_w<11>(C, LA, LB, nlarge, ltiles, lelem)
-                     : radix_level_w<8>(C, LA, LB, nlarge, ltiles, lelem);
+    return C.W == 11 ? radix_level_w<11>(C, LA, LB, nlarge, ltiles, lelem, wg)
+                     : radix_level_w<8>(C, LA, LB, nlarge, ltiles, lelem, wg);
 }
 
 // The part of a round after the radix levels: small sorts, boundary LCPs,
@@ -2174,14 +2374,22 @@ static int sort_rounds_device(const SortJob &J, SortWs &w, u32 rounds, u32 *stat
 {
     Seg *const act0 = w.act;
     RoundCtx C = round_ctx(J, w);
-    const u32 levels = C.W == 11 ? Digits<11>::LEVELS : Digits<8>::LEVELS;
+    // (the list of radix segments must fit one workgroup's pass to be split by size)
+    const bool wg = C.W == 8 && J.n_total / C.BM <= LIST_ONE;
+    const u32 levels = wg ? wg_levels(J.n_total) : (C.W == 11 ? Digits<11>::LEVELS : Digits<8>::LEVELS);
     const Known unknown{false, 0};
     for (u32 r = 0; r < rounds; r++) {
         SS_TRY(round_head(C, unknown, unknown, 0));
         Seg *LA = w.largeA, *LB = w.largeB;
         for (u32 l = 0; l < levels; l++) {
-            SS_TRY(radix_level(C, LA, LB, unknown, unknown, 0));
+            SS_TRY(radix_level(C, LA, LB, unknown, unknown, 0, wg));
             Seg *tmp = LA; LA = LB; LB = tmp;
+        }
+        if (wg) {
+            const EmitOut eo{w.tiny, w.small, w.mid, LB, w.nxt, w.ident, w.bnd, w.ctr, w.scat, w.kinds, C.BM, C.TL, C.ET};
+            k_radix_wg<<<grid_of(J.n_total, C.BM + 1, resident(k_radix_wg, WG_NT)), WG_NT, 0, J.stream>>>(
+                w.wgl, w.ctr + C_WG, LA, w.ctr + C_LARGE, LB, C.BM + 1, w.rmask, w.keyA, J.vals, w.keyB, w.valB, eo);
+            SS_CHECK_LAUNCH();
         }
         SS_TRY(round_tail(C, nullptr));
         Seg *tmp = w.act; w.act = w.nxt; w.nxt = tmp;

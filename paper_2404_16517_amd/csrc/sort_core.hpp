@@ -22,7 +22,8 @@ enum {
     C_TINYN = 14, C_BADSET = 15, C_MID = 16,
     C_RNEXT = 17, C_RTILES = 18, C_RELEM = 19,  // what k_resolve leaves of the C_NEXT segments
     C_TIEBIG = 20,  // (merge) some tied segment has more than TIE_SMALL members
-    C_NCTR = 21
+    C_WG = 21,  // radix segments left to one workgroup each (device-driven sorts)
+    C_NCTR = 22
 };
 // ctr[10..11]: 64-bit sum of size * skip over the routed segments
 
@@ -55,7 +56,7 @@ struct SortWs {
     u64 *keyA, *keyB, *mword;  // mword, mpr: each member's first mismatch with its segment's first string
     uint2 *mpr;
     u32 *valB, *lcp_scratch;
-    Seg *act, *nxt, *tiny, *small, *mid, *ident, *largeA, *largeB;
+    Seg *act, *nxt, *tiny, *small, *mid, *ident, *largeA, *largeB, *wgl;
     uint2 *bnd;
     u32 *skipv;
     u64 *smin, *smax;
