@@ -102,14 +102,16 @@ def lib():
     return _lib
 
 
+# Addresses and streams go to the library as plain integers: building a stream
+# object and a pointer object per argument took a third of the host time of a
+# small call (sorting 48 strings: 9.6 us a call with them, 6.8 without; the kernel 5.2).
+
 def _p(t: torch.Tensor | None):
-    if t is None:
-        return None
-    return ctypes.c_void_p(t.data_ptr()) if t.numel() else None
+    return t.data_ptr() if t is not None and t.numel() else None
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _check(rc: int):
