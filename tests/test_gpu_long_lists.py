@@ -16,6 +16,7 @@ DEV = "cuda:0"
     (5000, 300, 128, 4096, False), (5000, 300, 128, 4096, True),            # ... and on the first
     (4096, 300, 128, 4096, False), (4097, 300, 128, 4096, True),
     (1, 17_000_000, 1024, 1024, False),                                    # 4.2M histogram entries
+    (100, 25_000, 1024, 4096, False), (800, 3000, 128, 4096, False), (40, 60_000, 128, 1024, False),  # narrow digits
     (1, 2049, 1024, 4096, False), (3, 30_000, 1024, 4096, False), (3, 30_000, 1024, 8192, True),  # small tiles
 ])
 def test_long_lists(sets, per, small_max, tile, device_driven):
