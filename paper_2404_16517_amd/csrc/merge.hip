@@ -1388,11 +1388,11 @@ __global__ __launch_bounds__(256, 4) void k_mscan_apply(MScan S, const MOp *blk,
 
 // Sampling step of a group of kg runs.  A threshold cuts every run up to S/2
 // from where its samples say, so the sizes of tiles vary by about 0.4 S sqrt(kg)
-// about MW_TILE: these steps keep that at 150 or less, far below what a tile has
-// to spare.
+// about MW_TILE: these steps keep that at 205 or less, a fifth of what a tile has
+// to spare (half the steps: 256 runs of 31,250 keys 581 us instead of 556).
 __device__ __host__ __forceinline__ u32 mw_step(u32 kg)
 {
-    return kg <= 16 ? 64u : (kg <= 64 ? 32u : (kg <= 512 ? 16u : 8u));
+    return kg <= 64 ? 64u : (kg <= 256 ? 32u : (kg <= 1024 ? 16u : 8u));
 }
 // Where run r of a group of kg starts sampling, how many samples a run of len
 // keys gives, and the sample that threshold t of nt tiles over tot keys takes
