@@ -1194,6 +1194,18 @@ __global__ __launch_bounds__(256) void k_flags(const u64 *keys, int kin, const u
     }
 }
 
+// Empties the table, the duplicate marks of A entries and a list counter in one
+// launch (three fills took 5 us each between rounds of a few).
+__global__ __launch_bounds__(256) void k_tab_clear(ulonglong2 *tab, u64 pairs, u8 *dupf, u32 A, u32 *ctr)
+{
+    const u64 x0 = (u64)blockIdx.x * blockDim.x + threadIdx.x, step = (u64)gridDim.x * blockDim.x;
+    for (u64 x = x0; x < pairs; x += step) tab[x] = make_ulonglong2(TAB_EMPTY, TAB_EMPTY);
+    u64 *d8 = (u64 *)dupf;
+    for (u64 x = x0; x < A / 8; x += step) d8[x] = 0;
+    if (x0 < (A & 7u)) dupf[(A & ~7u) + x0] = 0;
+    if (x0 == 0) *ctr = 0;
+}
+
 // Insert every active key into the table (linear probing).  A slot holds the
 // low 32 bits of a key and the list position of the entry that brought it
 // first; an entry that finds its key there (the low bits equal, and the key
@@ -2109,8 +2121,10 @@ static int pd_run(const uint8_t *bytes, uint64_t N, const uint64_t *offsets, uin
             dd_used = true;
         } else if (mode == DM_TABLE) {
             logT = tab_log(Ah);
-            SS_HIP(hipMemsetAsync(w.tab, 0xFF, sizeof(u64) << logT, st));
-            SS_HIP(hipMemsetAsync(w.dupt, 0, Ah, st));
+            const u64 pairs = 1ull << (logT - 1), cb = ceil_div(pairs, 256 * 8);
+            k_tab_clear<<<(unsigned)(cb < 4096 ? cb : 4096), 256, 0, st>>>((ulonglong2 *)w.tab, pairs, w.dupt, Ah,
+                                                                          ctr + (ci ^ 1));
+            SS_CHECK_LAUNCH();
             {
                 SS_PROF("k_tab_insert", st, (double)Ah * 28.0);  // list entry, key, slot read + write
                 k_tab_insert<<<(unsigned)ceil_div(Ah, 256), 256, 0, st>>>(keys, kin, act, ctr + ci, w.tab, logT,
@@ -2119,7 +2133,7 @@ static int pd_run(const uint8_t *bytes, uint64_t N, const uint64_t *offsets, uin
             SS_CHECK_LAUNCH();
             dupf = w.dupt;
         }
-        SS_HIP(hipMemsetAsync(ctr + (ci ^ 1), 0, sizeof(u32), st));
+        if (!logT) SS_HIP(hipMemsetAsync(ctr + (ci ^ 1), 0, sizeof(u32), st));
         {
             // list entry, offsets, key, slot, dist or next entry (and a carried key)
             SS_PROF("k_dedup", st, (double)Ah * ((mode == DM_TABLE ? 25.0 : 24.0) + (pend_next ? 16.0 : 0.0)));
