@@ -62,6 +62,17 @@ def _samples(dev):
     }
 
 
+def choose(timings: dict) -> str:
+    """The fastest setting, with 11-bit digits only where they are 5 % faster:
+    their histograms grow with the number of tiles, and on 16 sets they lose what
+    they gain on a sample of four (seeded sort of 16M D/N strings 1.39 ms, with
+    8-bit digits 0.99)."""
+    by = {bits: min((k for k in timings if k.startswith(f"{bits},")), key=timings.get, default=None) for bits in (8, 11)}
+    if by[11] and (not by[8] or timings[by[11]] < 0.95 * timings[by[8]]):
+        return by[11]
+    return by[8]
+
+
 def autotune(reps: int = 3, out: str | None = None) -> dict:
     import torch
     import paper_2404_16517_amd as ss
@@ -92,7 +103,7 @@ def autotune(reps: int = 3, out: str | None = None) -> dict:
                             torch.cuda.synchronize()
                             ts.append(time.perf_counter() - t0)
                         timings[f"{bits},{sm},{tile}"] = statistics.median(ts) * 1e3
-            best = min(timings, key=timings.get)
+            best = choose(timings)
             bits, sm, tile = (int(x) for x in best.split(","))
             table["workloads"][name] = {"digit_bits": bits, "small_max": sm, "tile": tile, "ms": timings[best],
                                         "strings": s.n, "bytes": s.N, "ms_all": timings}
