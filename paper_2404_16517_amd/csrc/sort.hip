@@ -963,6 +963,11 @@ __device__ __forceinline__ u64 match_digit_w(u32 digit, bool valid)
 
 // Per-tile histogram of the segment's current digit, digit-major per
 // segment: hist[NB*tstart[s] + d*T_s + lt].  Also the segment's min and max key.
+//
+// Bounded by its 8 B per key (27 us for 16M) and the vector unit.  One LDS add
+// per key, whatever the digits: finding the lanes that share a digit first, to
+// add once for all of them, costs more than even 64 adds on one word (16M keys
+// in 16 segments 54 us a level, now 41).
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
                                              const u64 *keyA, const u64 *keyB, u32 *hist, u64 *smin, u64 *smax,
@@ -998,12 +1003,10 @@ __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart,
             if (c >= b1) break;  // (uniform)
             const bool valid = c + threadIdx.x < b1;
             const u64 k = kq[q];
-            u32 d = digit_of(k, D);
-            u64 peers = match_digit_w<W>(d, valid);
             if (valid) {
                 mn = k < mn ? k : mn;
                 mx = k > mx ? k : mx;
-                if ((peers & lanemask_lt()) == 0) atomicAdd(&h[d], (u32)__popcll(peers));
+                atomicAdd(&h[digit_of(k, D)], 1u);
             }
         }
     }
@@ -1427,12 +1430,10 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
                 for (u32 q = 0; q < RX_PF; q++) {
                     if (c0 + q * WG_NT >= g.end) break;  // (uniform)
                     const bool valid = c0 + q * WG_NT + t < g.end;
-                    const u32 d = digit_of(kq[q], D);
-                    const u64 peers = match_digit_w<8>(d, valid);
                     if (valid) {
                         mn = kq[q] < mn ? kq[q] : mn;
                         mx = kq[q] > mx ? kq[q] : mx;
-                        if ((peers & lanemask_lt()) == 0) atomicAdd(&h[d], (u32)__popcll(peers));
+                        atomicAdd(&h[digit_of(kq[q], D)], 1u);
                     }
                 }
             }
