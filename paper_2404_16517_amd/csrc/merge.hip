@@ -842,64 +842,6 @@ __device__ __forceinline__ void fc_piece(const FcView &V, u32 g, u64 k, u64 *pos
     *avail = h - k;
 }
 
-// Three-way comparison of front-coded strings x and y from byte `from`
-// (they agree on [0, from)); *lcp receives their LCP.  Merges call it where
-// cached keys tie, in lockstep wavefronts where one lane's comparison holds
-// up the others, so its chain of dependent loads is kept short: both
-// strings' lengths, LCPs and literal offsets are loaded together; a string
-// whose own literal holds byte `from` (the usual case) is read from there
-// without a chain walk, otherwise its piece is found along its psv chain;
-// the two pieces are then compared 32 bytes a round, every word of a round
-// loaded before any is compared, until one piece ends.
-#define FC_ROUND 4  // 8-byte words per comparison round
-
-__device__ __forceinline__ int fc_cmp(const FcView &V, u32 x, u32 y, u64 from, u64 *lcp)
-{
-    const u64 lx = V.d[x], ly = V.d[y];
-    const u32 ex = V.e[x], ey = V.e[y];
-    const u64 sx = V.suf_off[x], sy = V.suf_off[y];
-    const u64 m = lx < ly ? lx : ly;
-    u64 i = from < m ? from : m;
-    u64 px = 0, ax = 0, py = 0, ay = 0;
-    if (i < m) {
-        if (ex <= i) { px = sx + (i - ex); ax = lx - i; }
-        else fc_piece(V, x, i, &px, &ax);
-        if (ey <= i) { py = sy + (i - ey); ay = ly - i; }
-        else fc_piece(V, y, i, &py, &ay);
-    }
-    while (i < m) {
-        if (ax == 0) fc_piece(V, x, i, &px, &ax);
-        if (ay == 0) fc_piece(V, y, i, &py, &ay);
-        u64 run = ax < ay ? ax : ay;
-        run = run < m - i ? run : m - i;
-        while (run > 0) {
-            const u32 take = run < 8 * FC_ROUND ? (u32)run : 8u * FC_ROUND;
-            u64 wa[FC_ROUND], wb[FC_ROUND];
-#pragma unroll
-            for (u32 q = 0; q < FC_ROUND; q++) {
-                const u32 tq = take > 8 * q ? (take - 8 * q < 8 ? take - 8 * q : 8u) : 0u;
-                wa[q] = tq ? load_be(V.suf, V.sufN, px + 8 * q, tq) : 0ull;
-                wb[q] = tq ? load_be(V.suf, V.sufN, py + 8 * q, tq) : 0ull;
-            }
-#pragma unroll
-            for (u32 q = 0; q < FC_ROUND; q++) {
-                if (wa[q] != wb[q]) {
-                    *lcp = i + 8 * q + (__clzll(wa[q] ^ wb[q]) >> 3);
-                    return wa[q] < wb[q] ? -1 : 1;
-                }
-            }
-            px += take;
-            py += take;
-            ax -= take;
-            ay -= take;
-            i += take;
-            run -= take;
-        }
-    }
-    *lcp = m;
-    return lx < ly ? -1 : (lx > ly ? 1 : 0);
-}
-
 // The merge's results: per output, the source (run, position in run), the
 // string id, the LCP with the previous output and the string length (src and
 // len optional).  sb/sid: the non-empty runs' front-coded starts, ascending,
@@ -966,22 +908,25 @@ __global__ __launch_bounds__(256) void k_run_min(const u64 *run_begin, const u64
 
 // Common prefix length of each group: every string of run r shares
 // min(lcp(head of the group's first run, head of r), runmin[r]) bytes with the
-// group's first head.
-__global__ void k_group_depth(const u64 *run_begin, const u64 *P, const u32 *run_group, const u32 *rep, u32 k,
-                              const u32 *runmin, FcView V, u32 *Cg)
+// group's first head.  A wavefront per run: heads are whole in their literals
+// (e = 0), so 512 bytes of both are compared at once (a thread per run: 31 us
+// where the heads share 250 bytes, now 8).
+__global__ __launch_bounds__(256) void k_group_depth(const u64 *run_begin, const u64 *P, const u32 *run_group,
+                                                     const u32 *rep, u32 k, const u32 *runmin, FcView V, u32 *Cg)
 {
-    const u32 r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= k) return;
+    const u32 r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= k) return;  // (uniform over the wavefront)
     if (P[r + 1] == P[r]) return;
     const u32 g = run_group[r];
     const u32 r0 = rep[g];
     u32 v = runmin[r];
     if (r0 != r) {
+        const u32 a = (u32)run_begin[r0], b = (u32)run_begin[r];
         u64 l;
-        fc_cmp(V, (u32)run_begin[r0], (u32)run_begin[r], 0, &l);
+        wave_str_cmp(V.suf, V.sufN, V.suf_off[a], V.d[a], V.suf_off[b], V.d[b], &l);
         v = min(v, (u32)l);
     }
-    atomicMin(&Cg[g], v);
+    if ((threadIdx.x & 63) == 0) atomicMin(&Cg[g], v);
 }
 
 // ---- the elements' keys by one scan over the runs
@@ -1880,7 +1825,11 @@ __device__ __forceinline__ FcEl fc_el_shfl(const FcEl &a, u32 src)  // within ei
     return FcEl{__shfl(a.g, src, 8), __shfl(a.d, src, 8), __shfl(a.e, src, 8), __shfl(a.so, src, 8)};
 }
 
-// fc_cmp by eight lanes with the same arguments, 128 bytes a step.
+// Three-way comparison of front-coded strings X and Y from byte `from` (they
+// agree on [0, from)) by eight lanes with the same arguments, 128 bytes a step;
+// *lcp receives their LCP.  A string whose own literal holds the byte (the usual
+// case) is read from there without a chain walk, otherwise its piece is found
+// along its psv chain.
 __device__ __forceinline__ int fc_cmp8(const FcView &V, const FcEl &X, const FcEl &Y, u64 from, u32 gl, u64 *lcp)
 {
     const u32 x = X.g, y = Y.g, ex = X.e, ey = Y.e;
@@ -2440,7 +2389,7 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
     const u64 rparts = ceil_div(n_out, (u64)k * 4096);
     k_run_min<<<dim3(k, (unsigned)(rparts < 64 ? rparts : 64)), 256, 0, st>>>(run_begin, w.P, fc_lcp, w.runmin);
     SS_CHECK_LAUNCH();
-    k_group_depth<<<(unsigned)ceil_div(k, 64), 64, 0, st>>>(run_begin, w.P, w.rgroup, w.rep, k, w.runmin, V, w.Cg);
+    k_group_depth<<<(unsigned)ceil_div(k, 4), 256, 0, st>>>(run_begin, w.P, w.rgroup, w.rep, k, w.runmin, V, w.Cg);
     SS_CHECK_LAUNCH();
     u32 *const unsorted = sw.ctr + C_BADSET;
     u64 *K = sw.keyA, *KS = sw.mword, *KM = sw.mword + nsample;
