@@ -823,6 +823,7 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
     }
 }
 
+#define RS_BUF 256    // runs a workgroup collects before it updates the counters
 #define RS_MAX 16     // runs of up to this many tied strings are compared directly
 #define RS_CMP 1024   // ... over this many bytes past their common prefix
 
@@ -836,15 +837,29 @@ __global__ __launch_bounds__(256) void k_classify(const Seg *act, const u32 *nac
 //
 // Bounded by the latency of scattered reads: two lines per string.  A round's
 // skip, keys, routing and sort took 1.1 ms for 446K such runs (4M text
-// strings); this takes 190 us, and the whole sort 2.6 -> 1.9 ms.
+// strings); this takes 199 us (227 with three updates of the counters per 32 runs:
+// they queue where the chip's L2s meet).
 __global__ __launch_bounds__(256) void k_resolve(const Seg *in, const u8 *bytes, u64 N, const u64 *off,
                                                  u32 *vals, u32 *lcp, Seg *out, u32 *ctr, u32 et)
 {
+    __shared__ Seg buf[RS_BUF];  // what goes on, until it is worth an update of the counters
     __shared__ u32 s_cnt, s_tiles, s_elems, s_base;
     const u32 nin = ctr[C_NEXT];
-    for (u32 s0 = blockIdx.x * 32; s0 < nin; s0 += gridDim.x * 32) {  // (uniform over the workgroup)
+    auto flush = [&]() {  // (by the whole workgroup, after a barrier)
+        if (threadIdx.x == 0) {
+            s_base = atomicAdd(&ctr[C_RNEXT], s_cnt);
+            static_assert(C_RTILES % 2 == 0 && C_RELEM == C_RTILES + 1, "both counters in one 8-byte word");
+            atomicAdd((unsigned long long *)&ctr[C_RTILES], ((unsigned long long)s_elems << 32) | s_tiles);
+        }
+        __syncthreads();
+        for (u32 k = threadIdx.x; k < s_cnt; k += 256) out[s_base + k] = buf[k];
+        __syncthreads();
+        if (threadIdx.x == 0) s_cnt = s_tiles = s_elems = 0;
+        __syncthreads();
+    };
     if (threadIdx.x == 0) s_cnt = s_tiles = s_elems = 0;
     __syncthreads();
+    for (u32 s0 = blockIdx.x * 32; s0 < nin; s0 += gridDim.x * 32) {  // (uniform over the workgroup)
     const u32 s = s0 + (threadIdx.x >> 3), gl = threadIdx.x & 7;
     bool keep = false;
     Seg g = {0, 0, 0, 0};
@@ -918,26 +933,15 @@ __global__ __launch_bounds__(256) void k_resolve(const Seg *in, const u8 *bytes,
             }
         }
     }
-    const u64 b = __ballot(keep && gl == 0);
-    u32 slot = 0;
-    if (b) {  // (uniform over the wavefront)
-        if (__lane_id() == 0) slot = atomicAdd(&s_cnt, (u32)__popcll(b));
-        slot = __shfl(slot, 0, 64) + (u32)__popcll(b & lanemask_lt());
-        if (keep && gl == 0) {
-            atomicAdd(&s_tiles, (g.end - g.begin + et - 1) / et);
-            atomicAdd(&s_elems, g.end - g.begin);
-        }
+    if (keep && gl == 0) {
+        buf[atomicAdd(&s_cnt, 1u)] = g;
+        atomicAdd(&s_tiles, (g.end - g.begin + et - 1) / et);
+        atomicAdd(&s_elems, g.end - g.begin);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && s_cnt) {
-        s_base = atomicAdd(&ctr[C_RNEXT], s_cnt);
-        atomicAdd(&ctr[C_RTILES], s_tiles);
-        atomicAdd(&ctr[C_RELEM], s_elems);
+    if (s_cnt > RS_BUF - 32) flush();  // (uniform)
     }
-    __syncthreads();
-    if (keep && gl == 0) out[s_base + slot] = g;
-    __syncthreads();  // the counts are reset for the next runs
-    }
+    if (s_cnt) flush();  // (uniform: the last iteration ended with a barrier)
 }
 
 // ------------------------------------------------------------ radix passes
@@ -1608,12 +1612,12 @@ __global__ __launch_bounds__(NT) void k_ident(const Seg *segs, const u32 *tstart
 template <bool LOOP, int NTB>
 __global__ __launch_bounds__(NTB) void k_block_sort(const Seg *list, const u32 *cntp, u64 *keys, u32 *vals,
                                                     const u64 *keyB, const u32 *valB, u32 *lcp, Seg *next, u32 *ctr,
-                                                    u32 et)
+                                                    u32 *elems)
 {
     constexpr u32 CAP = NTB * BS_IPT;
     __shared__ u64 sk[CAP + NTB];
     __shared__ u32 sv[CAP + NTB];
-    __shared__ u32 nq_count, nq_tiles, nq_elems, nq_base;
+    __shared__ u32 nq_count, nq_elems, nq_base;
     const u32 nlist = LOOP ? *cntp : 0u;
     TILE_LOOP(sg, nlist) {
     const Seg g = list[sg];
@@ -1632,7 +1636,7 @@ __global__ __launch_bounds__(NTB) void k_block_sort(const Seg *list, const u32 *
             v[q] = vs[g.begin + e0 + q];
         }
     }
-    if (threadIdx.x == 0) nq_count = nq_tiles = nq_elems = 0;
+    if (threadIdx.x == 0) nq_count = nq_elems = 0;
 #pragma unroll
     for (u32 r = 0; r < BS_IPT; r++) {
 #pragma unroll
@@ -1706,7 +1710,9 @@ __global__ __launch_bounds__(NTB) void k_block_sort(const Seg *list, const u32 *
         else if (e + 1 == cnt || sk[bs_at(e + 1)] != kb) lasts |= 1u << it;
     }
     if (__syncthreads_or(lasts != 0)) {
-        // tied runs, published with one atomic per counter: counted, then written
+        // tied runs: counted, then written.  (One update of a global counter, two
+        // where the caller wants their members counted: such updates queue, and
+        // with three of them 5,623 segments of text took 219 us, now 97.)
         for (int pass = 0; pass < 2; pass++) {
             for (u32 m = lasts; m; m &= m - 1) {
                 const u32 e = threadIdx.x + NTB * (u32)(__ffs((int)m) - 1);
@@ -1720,7 +1726,6 @@ __global__ __launch_bounds__(NTB) void k_block_sort(const Seg *list, const u32 *
                 const u32 sz = e + 1 - x;
                 const u32 slot = atomicAdd(&nq_count, 1u);
                 if (pass == 0) {
-                    atomicAdd(&nq_tiles, (sz + et - 1) / et);
                     atomicAdd(&nq_elems, sz);
                 } else {
                     next[nq_base + slot] = Seg{g.begin + x, g.begin + e + 1, g.depth + 7, SEG_SKIP};
@@ -1729,8 +1734,7 @@ __global__ __launch_bounds__(NTB) void k_block_sort(const Seg *list, const u32 *
             __syncthreads();
             if (pass == 0 && threadIdx.x == 0) {
                 nq_base = atomicAdd(&ctr[C_NEXT], nq_count);
-                atomicAdd(&ctr[C_NTILES], nq_tiles);
-                atomicAdd(&ctr[C_NELEM], nq_elems);
+                if (elems) atomicAdd(elems, nq_elems);
                 nq_count = 0;
             }
             __syncthreads();
@@ -1821,14 +1825,14 @@ __device__ __forceinline__ bool shfl_down_b(bool b, u32 lane, bool from_next)
 template <bool LOOP, bool DEEP = true>
 __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *ntinyp, u64 *keys, u32 *vals,
                                                    const u64 *keyB, const u32 *valB, u32 *lcp, Seg *next, u32 *ctr,
-                                                   const u8 *bytes, u64 N, const u64 *off, u32 et)
+                                                   const u8 *bytes, u64 N, const u64 *off, u32 *elems)
 {
     __shared__ Seg nq[WS_SPB * (WS_MAX / 2)];
-    __shared__ u32 nq_count, nq_tiles, nq_elems, nq_base;
+    __shared__ u32 nq_count, nq_elems, nq_base;
     const u32 ntiny = *ntinyp;
     const u32 ngrp = LOOP ? (ntiny + WS_SPB - 1) / WS_SPB : 0u;
     TILE_LOOP(grp, ngrp) {
-    if (threadIdx.x == 0) { nq_count = 0; nq_tiles = 0; nq_elems = 0; }
+    if (threadIdx.x == 0) { nq_count = 0; nq_elems = 0; }
     __syncthreads();
     const u32 lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const u32 e0 = lane, e1 = lane + 64;
@@ -1956,7 +1960,6 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
             const u32 f = hibit(s0 & le);
             const Seg ns{g.begin + f, g.begin + e0 + 1, dep + 7, SEG_SKIP};
             nq[atomicAdd(&nq_count, 1u)] = ns;
-            atomicAdd(&nq_tiles, (ns.end - ns.begin + et - 1) / et);
             atomicAdd(&nq_elems, ns.end - ns.begin);
         }
         if (end1) {
@@ -1964,7 +1967,6 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
             const u32 f = mm ? 64u + hibit(mm) : hibit(s0);
             const Seg ns{g.begin + f, g.begin + e1 + 1, dep + 7, SEG_SKIP};
             nq[atomicAdd(&nq_count, 1u)] = ns;
-            atomicAdd(&nq_tiles, (ns.end - ns.begin + et - 1) / et);
             atomicAdd(&nq_elems, ns.end - ns.begin);
         }
         }
@@ -1980,8 +1982,7 @@ __global__ __launch_bounds__(256) void k_wave_sort(const Seg *tiny, const u32 *n
     __syncthreads();
     if (threadIdx.x == 0 && nq_count) {
         nq_base = atomicAdd(&ctr[C_NEXT], nq_count);
-        atomicAdd(&ctr[C_NTILES], nq_tiles);
-        atomicAdd(&ctr[C_NELEM], nq_elems);
+        if (elems) atomicAdd(elems, nq_elems);
     }
     __syncthreads();
     for (u32 k = threadIdx.x; k < nq_count; k += 256) next[nq_base + k] = nq[k];
@@ -2240,17 +2241,18 @@ static int round_tail(RoundCtx &C, const u32 *h, bool keyed = false)
     const u64 n = C.n;
     u32 *lcp = J.lcp;
     const bool known = h != nullptr;
+    u32 *const elems = keyed ? w.ctr + C_NELEM : nullptr;  // members of the tied runs, where the caller counts them
     if (!known || h[C_TINY] > 0) {
         SS_PROF("k_wave_sort", st, known ? (double)h[C_TINYN] * 28.0 : 0.0);  // key+payload in/out, LCP out
         if (known && keyed)
             k_wave_sort<false, false><<<grid_of(h[C_TINY], WS_SPB, 1u << 30), 256, 0, st>>>(
-                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, C.ET);
+                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, elems);
         else if (known)
             k_wave_sort<false><<<grid_of(h[C_TINY], WS_SPB, 1u << 30), 256, 0, st>>>(
-                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, C.ET);
+                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, elems);
         else
             k_wave_sort<true><<<grid_of(n / 2, WS_SPB, resident(k_wave_sort<true>, 256)), 256, 0, st>>>(
-                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, C.ET);
+                w.tiny, w.ctr + C_TINY, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, J.bytes, J.N, J.off, elems);
         SS_CHECK_LAUNCH();
     }
     if (!known || h[C_SMALL] > 0 || h[C_MID] > 0) {
@@ -2258,17 +2260,17 @@ static int round_tail(RoundCtx &C, const u32 *h, bool keyed = false)
         if (known) {
             if (h[C_SMALL])
                 k_block_sort<false, BS_SMALL / BS_IPT><<<h[C_SMALL], BS_SMALL / BS_IPT, 0, st>>>(
-                    w.small, w.ctr + C_SMALL, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+                    w.small, w.ctr + C_SMALL, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, elems);
             if (h[C_MID])
                 k_block_sort<false, BS_MID / BS_IPT><<<h[C_MID], BS_MID / BS_IPT, 0, st>>>(
-                    w.mid, w.ctr + C_MID, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+                    w.mid, w.ctr + C_MID, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, elems);
         } else {
             const auto ks = k_block_sort<true, BS_SMALL / BS_IPT>;
             const auto km = k_block_sort<true, BS_MID / BS_IPT>;
             ks<<<grid_of(n, WS_MAX, resident(ks, BS_SMALL / BS_IPT)), BS_SMALL / BS_IPT, 0, st>>>(
-                w.small, w.ctr + C_SMALL, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+                w.small, w.ctr + C_SMALL, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, elems);
             km<<<grid_of(n, BS_SMALL, resident(km, BS_MID / BS_IPT)), BS_MID / BS_IPT, 0, st>>>(
-                w.mid, w.ctr + C_MID, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, C.ET);
+                w.mid, w.ctr + C_MID, w.keyA, J.vals, w.keyB, w.valB, lcp, w.nxt, w.ctr, elems);
         }
         SS_CHECK_LAUNCH();
     }
@@ -2351,7 +2353,7 @@ int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles, bool whole)
         }
         SS_CHECK_LAUNCH();
         SS_TRY(ss_read_u32(w.ctr, h, C_NCTR, J.stream));
-        ss_prof_add_bytes("k_resolve", (double)h[C_NELEM] * 20.0);  // offsets, payload; not the bytes compared
+        ss_prof_add_bytes("k_resolve", (double)h[C_NEXT] * 40.0);  // offsets, payload of two; not the bytes compared
         nact = h[C_RNEXT];
         atiles = h[C_RTILES];
         round_elems = h[C_RELEM];
@@ -2380,10 +2382,30 @@ int sort_keyed(const SortJob &J, SortWs &w, u32 *h)
 // can be captured in a graph); rounds and levels without work find empty
 // lists.  hdr[H_REMAIN] receives the number of segments still unresolved
 // afterwards (0: the sort is complete).
-__global__ void k_remaining(const u32 *ctr, u32 *hdr, u32 *status)
+// Their tiles and members go to ctr, for a continuation by the host.
+__global__ __launch_bounds__(1024) void k_remaining(u32 *ctr, u32 *hdr, u32 *status, const Seg *left, u32 et)
 {
-    hdr[H_REMAIN] = ctr[C_NEXT];
-    if (status) *status = ctr[C_NEXT];
+    __shared__ u32 s_tiles, s_elems;
+    if (threadIdx.x == 0) s_tiles = s_elems = 0;
+    __syncthreads();
+    const u32 cnt = ctr[C_NEXT];
+    u32 tiles = 0, elems = 0;
+    for (u32 j = threadIdx.x; j < cnt; j += 1024) {
+        const u32 m = left[j].end - left[j].begin;
+        tiles += (m + et - 1) / et;
+        elems += m;
+    }
+    if (elems) {
+        atomicAdd(&s_tiles, tiles);
+        atomicAdd(&s_elems, elems);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        ctr[C_NTILES] = s_tiles;
+        ctr[C_NELEM] = s_elems;
+        hdr[H_REMAIN] = cnt;
+        if (status) *status = cnt;
+    }
 }
 
 // The next round's segments back into the first list (after an odd number of
@@ -2418,7 +2440,7 @@ static int sort_rounds_device(const SortJob &J, SortWs &w, u32 rounds, u32 *stat
         SS_TRY(round_tail(C, nullptr));
         Seg *tmp = w.act; w.act = w.nxt; w.nxt = tmp;
     }
-    k_remaining<<<1, 1, 0, J.stream>>>(w.ctr, w.hdr, status);
+    k_remaining<<<1, 1024, 0, J.stream>>>(w.ctr, w.hdr, status, w.act, C.ET);
     SS_CHECK_LAUNCH();
     if (w.act != act0) {
         k_copy_segs<<<grid_of(J.n_total / 2, 256, 1024), 256, 0, J.stream>>>(w.act, w.ctr + C_NEXT, act0);
