@@ -1489,7 +1489,7 @@ struct MwOut {
     const u64 *suf_off;
     MergeOut O;
     u32 *order;          // front-coded positions of tied elements, by output position
-    Seg *ties;           // runs of outputs with tied keys (C_RNEXT of them, C_RELEM elements)
+    Seg *ties;           // runs of outputs with tied keys (C_RNEXT of them)
     Seg *over;           // segments handed to the sort as a whole (C_RTILES of them)
     SortWs s;
     u32 tile, block_max; // of that sort
@@ -1542,7 +1542,7 @@ __global__ __launch_bounds__(MW_NT) void k_mw_tile(MwLevel M, MwOut W)
     __shared__ u32 woff[RUNS + 1], wlo[RUNS];
     __shared__ u32 s_sum[MW_NT / 64], s_lo[MW_NT / 64];
     __shared__ u64 s_prev[MW_NT / 64], s_min[MW_NT / 64];
-    __shared__ u32 s_n, s_el, s_base, s_big;
+    __shared__ u32 s_n, s_base, s_big;
     if (*M.bad) return;  // (uniform)
     const u32 t = threadIdx.x, lane = t & 63, wv = t >> 6;
     // consecutive tiles on one XCD (workgroups go round the eight): neighbours
@@ -1591,7 +1591,7 @@ __global__ __launch_bounds__(MW_NT) void k_mw_tile(MwLevel M, MwOut W)
             s_min[wv] = mn;
         }
     }
-    if (t == 0) s_n = s_el = s_big = 0;
+    if (t == 0) s_n = s_big = 0;
     __syncthreads();
     ex = inc - ex;
     u32 cnt = 0, before = 0;
@@ -1764,14 +1764,12 @@ __global__ __launch_bounds__(MW_NT) void k_mw_tile(MwLevel M, MwOut W)
                 const u32 a = first_equal(e, sk[e]);
                 const u32 slot = atomicAdd(&s_n, 1u);
                 if (pass == 0) {
-                    atomicAdd(&s_el, e + 1 - a);
                     if (e + 1 - a > TIE_SMALL) s_big = 1;
                 } else W.ties[s_base + slot] = Seg{X + a, X + e + 1, C + 7, TIE_REC};
             }
             __syncthreads();
             if (pass == 0 && t == 0) {
                 s_base = atomicAdd(&W.s.ctr[C_RNEXT], s_n);
-                atomicAdd(&W.s.ctr[C_RELEM], s_el);
                 if (s_big) W.s.ctr[C_TIEBIG] = 1;
                 s_n = 0;
             }
@@ -2466,7 +2464,7 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
         SS_TRY(ss_read_u32(sw.ctr, ctr, C_NCTR, st));
     }
     const u32 nover = ctr[C_RTILES], eover = ctr[C_NELEM];
-    u32 nact = ctr[C_RNEXT], elems = ctr[C_RELEM];
+    u32 nact = ctr[C_RNEXT];
     const bool small_only = !nover && !ctr[C_TIEBIG];  // then the first round is the last: its counters aren't read
     if (!nact && !nover) return SS_OK;
     const SortJob J{nullptr, 0, nullptr, w.order, out_lcp, st, n_out, n_out};
@@ -2478,7 +2476,6 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
         if (ctr[C_NEXT])
             SS_HIP(hipMemcpyAsync(w.segs + nact, sw.nxt, sizeof(Seg) * ctr[C_NEXT], hipMemcpyDeviceToDevice, st));
         nact += ctr[C_NEXT];
-        elems += ctr[C_NELEM];
     }
     // Tied keys.  Strings are compared without decoding them, along psv chains
     // over the whole front-coded array.  A comparison starts at byte C + 7 or
@@ -2502,7 +2499,7 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
         k_fill_u32<<<1, 64, 0, st>>>(sw.ctr, 0u, C_NCTR);
         SS_CHECK_LAUNCH();
         {
-            SS_PROF("k_tie_small", st, (double)elems * 24.0);  // entry, its LCP, length, offset; LCP out; not the bytes
+            SS_PROF("k_tie_small", st, (double)nact * 48.0);  // of two: entry, its LCP, length, offset; LCP out; not the bytes
             k_tie_small<<<(unsigned)ceil_div(nact, 32), 256, 0, st>>>(list, nact, V, w.order, sw.keyB, sw.mpr, O, big,
                                                                      sw.ctr);
         }
@@ -2526,7 +2523,6 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
         SS_CHECK_LAUNCH();
         SS_TRY(sort_keyed(J, sw, ctr));
         nact = ctr[C_NEXT];
-        elems = ctr[C_NELEM];
         Seg *tmp = sw.act; sw.act = sw.nxt; sw.nxt = tmp;
         list = sw.act;
     }
