@@ -49,6 +49,41 @@ __device__ __forceinline__ u32 seg_of_tile(const u32 *tstart, u32 nseg, u32 t)
     return lo;
 }
 
+// Exclusive scan of the tile counts of nseg segments by one workgroup of
+// LIST_NT threads (tstart[nseg] = total, which is returned).
+#define LIST_NT 1024
+#define LIST_ONE 4096  // lists of up to so many segments: one workgroup (three launches take longer)
+__device__ __forceinline__ u32 list_tiles(const Seg *segs, u32 nseg, u32 tile, u32 *tstart)
+{
+    __shared__ u32 wsum[LIST_NT / 64];
+    const u32 lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    u32 carry = 0;
+    for (u32 b = 0; b < nseg; b += LIST_NT) {
+        const u32 j = b + threadIdx.x;
+        const u32 v = j < nseg ? (segs[j].end - segs[j].begin + tile - 1) / tile : 0u;
+        u32 x = v;
+#pragma unroll
+        for (u32 o = 1; o < 64; o <<= 1) {
+            const u32 y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wsum[wv] = x;
+        __syncthreads();
+        u32 tot = 0;
+        x += carry - v;
+#pragma unroll
+        for (u32 w = 0; w < LIST_NT / 64; w++) {
+            if (w < wv) x += wsum[w];
+            tot += wsum[w];
+        }
+        if (j < nseg) tstart[j] = x;
+        carry += tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) tstart[nseg] = carry;
+    return carry;
+}
+
 // LDS slot of element i where threads own runs of 8 (a pad each: no bank conflicts)
 __device__ __forceinline__ u32 bs_at(u32 i) { return i + i / BS_IPT; }
 

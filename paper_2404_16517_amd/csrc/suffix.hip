@@ -63,6 +63,14 @@ __global__ void k_sfx_tiles(const Seg *act, u32 nact, u32 *out, u32 *ctr)
     if (j < C_NCTR) ctr[j] = 0;
 }
 
+// The same and the scan of the counts for up to LIST_ONE groups, in one launch
+// (the later steps are launches and read-backs more than work).
+__global__ __launch_bounds__(LIST_NT) void k_sfx_tiles_one(const Seg *act, u32 nact, u32 *tstart, u32 *ctr)
+{
+    if (threadIdx.x < C_NCTR) ctr[threadIdx.x] = 0;
+    list_tiles(act, nact, SFX_T, tstart);
+}
+
 // One doubling step over the groups, eight lanes per 64 members: groups of up
 // to eight are sorted by rank(i + h) at once (each lane counts the smaller
 // keys), and what stays tied goes to the next list; of larger ones the keys are
@@ -273,9 +281,14 @@ extern "C" int ss_suffix_sort(const uint8_t *text, uint64_t N, uint32_t *sa, uin
         // corrects those of the groups still tied)
         Seg *tmp = sw.act; sw.act = sw.nxt; sw.nxt = tmp;
         const unsigned tg = (unsigned)ceil_div((u64)nact + elems / SFX_T, 32);  // (at most one part tile per group)
-        k_sfx_tiles<<<(unsigned)ceil_div(nact, 256), 256, 0, st>>>(sw.act, nact, w.tiles, sw.ctr);
-        SS_CHECK_LAUNCH();
-        SS_TRY(ss_scan_exclusive<u32>(w.tiles, w.tiles, nact, (u32 *)sw.scan_scratch, st));
+        if (nact <= LIST_ONE) {
+            k_sfx_tiles_one<<<1, LIST_NT, 0, st>>>(sw.act, nact, w.tiles, sw.ctr);
+            SS_CHECK_LAUNCH();
+        } else {
+            k_sfx_tiles<<<(unsigned)ceil_div(nact, 256), 256, 0, st>>>(sw.act, nact, w.tiles, sw.ctr);
+            SS_CHECK_LAUNCH();
+            SS_TRY(ss_scan_exclusive<u32>(w.tiles, w.tiles, nact, (u32 *)sw.scan_scratch, st));
+        }
         k_sfx_rank<true><<<tg, 256, 0, st>>>(sw.act, w.tiles, nact, sa, w.rank);
         SS_CHECK_LAUNCH();
         k_sfx_step<<<tg, 256, 0, st>>>(sw.act, w.tiles, nact, w.rank, N, h, sa, sw, z);
