@@ -529,9 +529,8 @@ size_t ss_profile_names(char *buf, size_t cap);
  *                      1024; default 1024).
  *   SS_TUNE_TILE       elements per workgroup in radix passes (1024..16384,
  *                      power of two; default 4096).
- *   SS_TUNE_DIGIT_BITS radix digit width: 8 (a level per key byte, 256
- *                      buckets) or 11 (six levels per 64-bit key, 2048
- *                      buckets); 11 takes effect only with a tile >= 4096 and
+ *   SS_TUNE_DIGIT_BITS radix digit width: 8 varying key bits a level (256
+ *                      buckets) or 11 (2048 buckets); 11 takes effect only with a tile >= 4096 and
  *                      SMALL_MAX >= 512, else 8 is used (default 8).
  *   SS_TUNE_DEDUP      prefix doubling's duplicate detection: 0 = a global
  *                      hash table (default); 1 = buckets of keys counted in
