@@ -1210,10 +1210,11 @@ struct ScatterLds {
     u32 wsum[NTB / 64];
 };
 
-// Elements [b0, b1) by digit D; run: see k_scatter (the first 256 threads').
-template <u32 W, u32 NTB = NT>
-__device__ __forceinline__ void scatter_range(ScatterLds<W, NTB> &L, const Digit &D, const u64 *ksrc, const u32 *vsrc,
-                                              u64 *kdst, u32 *vdst, u32 b0, u32 b1, u32 (&run)[Digits<W>::DPT])
+// Elements [b0, b1) by digit(key); run: see k_scatter (the first 256 threads').
+template <u32 W, u32 NTB = NT, class DG>
+__device__ __forceinline__ void scatter_range(ScatterLds<W, NTB> &L, const DG &digit, const u64 *ksrc,
+                                              const u32 *vsrc, u64 *kdst, u32 *vdst, u32 b0, u32 b1,
+                                              u32 (&run)[Digits<W>::DPT])
 {
     constexpr u32 DPT = Digits<W>::DPT, NW = NTB / 64, CW = ScatterLds<W, NTB>::CW, SC_ITEMS = ScatterLds<W, NTB>::ITEMS;
     constexpr bool HALF = ScatterLds<W, NTB>::HALF;
@@ -1238,7 +1239,7 @@ __device__ __forceinline__ void scatter_range(ScatterLds<W, NTB> &L, const Digit
 #pragma unroll
         for (u32 q = 0; q < SC_PER; q++) {
             const bool valid = (wid * SC_PER + q) * 64 + lane < m;
-            const u32 d = digit_of(kq[q], D);
+            const u32 d = digit(kq[q]);
             const u64 peers = match_digit_w<W>(d, valid);
             const u32 rank = (u32)__popcll(peers & lanemask_lt());
             u32 old = 0;
@@ -1293,7 +1294,7 @@ __device__ __forceinline__ void scatter_range(ScatterLds<W, NTB> &L, const Digit
 #pragma unroll
         for (u32 q = 0; q < SC_PER; q++) {
             if ((wid * SC_PER + q) * 64 + lane < m) {
-                const u32 d = digit_of(kq[q], D);
+                const u32 d = digit(kq[q]);
                 const u32 x = pos[q] + (HALF ? (L.cnt[wid][d >> 1] >> (16 * (d & 1))) & 0xFFFFu : L.cnt[wid][d]);
                 L.sk[x] = kq[q];
                 L.sv[x] = vq[q];
@@ -1305,7 +1306,7 @@ __device__ __forceinline__ void scatter_range(ScatterLds<W, NTB> &L, const Digit
             const u32 x = q * NTB + threadIdx.x;
             if (x < m) {
                 const u64 k = L.sk[x];
-                const u32 dst = L.gofs[digit_of(k, D)] + x;
+                const u32 dst = L.gofs[digit(k)] + x;
                 kdst[dst] = k;
                 vdst[dst] = L.sv[x];
             }
@@ -1343,7 +1344,7 @@ __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tsta
     u32 run[DPT];  // next free position of the thread's digits, DPT neighbouring ones
 #pragma unroll
     for (u32 r = 0; r < DPT; r++) run[r] = g.begin + hist[NB * ts + (threadIdx.x * DPT + r) * T + lt] - base;
-    scatter_range<W>(L, D, ksrc, vsrc, kdst, vdst, b0, b1, run);
+    scatter_range<W>(L, [&](u64 k) { return digit_of(k, D); }, ksrc, vsrc, kdst, vdst, b0, b1, run);
     __syncthreads();  // (the next tile)
     }
 }
@@ -1360,6 +1361,7 @@ __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tsta
 // A workgroup of 1024: with 256 the sets of up to 10,000 strings took 46 us, now
 // 40.
 #define WG_NT 1024
+#define WG_HEAVY 8192  // strings from which a segment's keys are sampled for one that an eighth of them share
 #define WG_MAX 32768
 // Levels over the whole device before it: none where no segment can be larger,
 // one where its share of a sort of 16 such segments is left, else two.
@@ -1383,6 +1385,26 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
             const u64 *ksrc = inb ? keyB : keyA;
             const u32 *vsrc = inb ? valB : valA;
             const Digit D = digit_unpack(digit_spec(g, rmask, 8, false));
+            // a key that many of a long segment's strings share is taken out
+            // first, with the smaller and the larger ones beside it: as digits
+            // it would keep them together for up to eight levels, one workgroup
+            // over all of them each time
+            bool heavy = false;
+            u64 hk = 0;
+            if (g.end - g.begin > WG_HEAVY) {
+                hk = ksrc[g.begin + (u32)((u64)(g.end - g.begin) * lane / 64)];  // (the same in every wavefront)
+                u32 c = 0;
+                for (u32 l = 0; l < 64; l++) c += __shfl(hk, l, 64) == hk ? 1u : 0u;
+                u32 best = (c << 6) | lane;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const u32 y = __shfl_xor(best, d, 64);
+                    best = y > best ? y : best;
+                }
+                hk = __shfl(hk, best & 63, 64);
+                heavy = (best >> 6) >= 8;
+            }
+            auto digit = [&](u64 k) { return heavy ? (k < hk ? 0u : (k == hk ? 1u : 2u)) : digit_of(k, D); };
             if (t < 256) h[t] = 0;
             if (t == 0) s_push = 0;
             emit_zero(E);
@@ -1402,7 +1424,7 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
                     if (valid) {
                         mn = kq[q] < mn ? kq[q] : mn;
                         mx = kq[q] > mx ? kq[q] : mx;
-                        atomicAdd(&h[digit_of(kq[q], D)], 1u);
+                        atomicAdd(&h[digit(kq[q])], 1u);
                     }
                 }
             }
@@ -1410,7 +1432,7 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
             mx = ~block_min<u64, WG_NT>(~mx);  // (its barriers: h is complete)
             const u32 fd = mn == mx ? 64u : (u32)__clzll(mn ^ mx);
             EmitItem it[1] = {EmitItem{K_NONE, Seg{0, 0, 0, 0}, false, make_uint2(0, 0)}};
-            if (fd < 64 && fd > 63 - D.low) {  // the whole digit is common
+            if (!heavy && fd < 64 && fd > 63 - D.low) {  // the whole digit is common
                 g.aux = fd | (g.aux & (SEG_INB | SEG_NOROOT));
                 __syncthreads();
                 continue;
@@ -1438,7 +1460,9 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
                 for (u32 w = 0; w < 4; w++)
                     if (w < wid) x += wsum[w];
                 if (t < 256) {
-                    it[0] = emit_bucket(g, D, mn, t, x, cnt, o.small_max);
+                    Digit B = D;  // what a bucket's members share: the digit, all of the key, or nothing more
+                    if (heavy) B.used = t == 1 ? 64u : (g.aux & 63);
+                    it[0] = emit_bucket(g, B, heavy ? hk : mn, heavy ? digit_of(hk, D) : t, x, cnt, o.small_max);
                     kd[t] = (u8)it[0].kind;
                 }
                 if (it[0].kind == K_LARGE) {
@@ -1448,7 +1472,7 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
                 emit_push(it, o, E);
                 sp += s_push;
                 u32 run[1] = {g.begin + x};
-                scatter_range<8, WG_NT>(L, D, ksrc, vsrc, inb ? keyA : keyB, inb ? valA : valB, g.begin, g.end, run);
+                scatter_range<8, WG_NT>(L, digit, ksrc, vsrc, inb ? keyA : keyB, inb ? valA : valB, g.begin, g.end, run);
                 __syncthreads();
                 if (!inb)  // what no later kernel rewrites back to A
                     for (u32 c0 = g.begin; c0 < g.end; c0 += RX_PF * WG_NT) {
@@ -1460,7 +1484,7 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
                         }
 #pragma unroll
                         for (u32 q = 0; q < RX_PF; q++) {
-                            const u32 i = c0 + q * WG_NT + t, c = kd[digit_of(kq[q], D)];
+                            const u32 i = c0 + q * WG_NT + t, c = kd[digit(kq[q])];
                             if (i < g.end && (c == K_NONE || c == K_NEXT || c == K_IDENT)) {
                                 keyA[i] = kq[q];
                                 valA[i] = valB[i];
@@ -2076,14 +2100,14 @@ static int scan_u32(RoundCtx &C, u32 *arr, const u32 *n_dev, u64 n_max)
 // segments are w.act, their number in counter `from` (or, `begun`, the header,
 // tiles and skip minima are set already).
 static int round_head(RoundCtx &C, Known nact, Known atiles, u64 round_elems, bool first = false, u32 from = C_NEXT,
-                      bool begun = false)
+                      bool begun = false, u64 bound = 0)
 {
     SortWs &w = C.w;
     const SortJob &J = C.J;
     hipStream_t st = J.stream;
     const u64 n = C.n;
     const u32 *nactp = w.hdr + H_ACT;
-    const u64 most = nact.yes ? nact.v : n / 2;
+    const u64 most = nact.yes ? nact.v : (bound ? bound : n / 2);  // (bound: on a number not known)
     if (!begun && most <= LIST_ONE) {
         k_round_start<<<1, LIST_NT, 0, st>>>(w.act, w.ctr, w.hdr, from, C.ET, w.tstart, w.skipv, w.keyB,
                                             C.BM);
@@ -2381,16 +2405,22 @@ __global__ void k_copy_segs(const Seg *src, const u32 *cnt, Seg *dst)
     GSTRIDE(j, c) dst[j] = src[j];
 }
 
-static int sort_rounds_device(const SortJob &J, SortWs &w, u32 rounds, u32 *status)
+// (cont: the first round's segments are not the sets)
+static int sort_rounds_device(const SortJob &J, SortWs &w, u32 rounds, u32 *status, u32 num_sets, bool cont)
 {
     Seg *const act0 = w.act;
     RoundCtx C = round_ctx(J, w);
-    // (the list of radix segments must fit one workgroup's pass to be split by size)
-    const bool wg = C.W == 8 && J.n_total / C.BM <= LIST_ONE;
-    const u32 levels = wg ? wg_levels(J.n_total) : (C.W == 11 ? Digits<11>::LEVELS : Digits<8>::LEVELS);
+    // One workgroup per radix segment: in small sorts, or where the sets are small
+    // on average, so that a segment too long for one is the exception (a set of
+    // 300,000 strings, half of them sharing seven bytes, among 63 small ones: 670
+    // us, with all levels over the device 1,130).  (The list of radix segments must
+    // fit one workgroup's pass to be split by size.)
+    const bool wg = C.W == 8 && J.n_total / C.BM <= LIST_ONE &&
+                    (J.n_total <= 16 * WG_MAX || J.n_total / num_sets <= WG_MAX / 4);
     const Known unknown{false, 0};
     for (u32 r = 0; r < rounds; r++) {
-        SS_TRY(round_head(C, unknown, unknown, 0));
+        const u32 levels = wg ? wg_levels(J.n_total) : (C.W == 11 ? Digits<11>::LEVELS : Digits<8>::LEVELS);
+        SS_TRY(round_head(C, unknown, unknown, 0, false, C_NEXT, false, r || cont ? 0 : num_sets));
         Seg *LA = w.largeA, *LB = w.largeB;
         for (u32 l = 0; l < levels; l++) {
             SS_TRY(radix_level(C, LA, LB, unknown, unknown, 0, wg));
@@ -2807,7 +2837,7 @@ extern "C" int ss_sort_batch_device(const uint8_t *bytes, uint64_t N, const uint
         k_drop_if_bad<<<1, 1, 0, st>>>(w.ctr, status);
         SS_CHECK_LAUNCH();
     }
-    SS_TRY(sort_rounds_device(J, w, rounds, status));
+    SS_TRY(sort_rounds_device(J, w, rounds, status, num_sets, flags & SS_BATCH_CONTINUE));
     if (!(flags & SS_BATCH_GLOBAL_IDS)) {
         k_localize<<<(unsigned)ceil_div(n, 256 * LOC_PER), 256, 0, st>>>(set_off, num_sets, (u32)n, perm_local,
                                                                w.ctr + C_NEXT);
