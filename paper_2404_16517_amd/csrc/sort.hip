@@ -810,17 +810,19 @@ __global__ __launch_bounds__(256) void k_resolve(const Seg *in, const u8 *bytes,
     __shared__ Seg buf[RS_BUF];  // what goes on, until it is worth an update of the counters
     __shared__ u32 s_cnt, s_tiles, s_elems, s_base;
     const u32 nin = ctr[C_NEXT];
+    u32 held = 0;  // entries of buf: counted by the barrier itself, so that every thread decides alike
     auto flush = [&]() {  // (by the whole workgroup, after a barrier)
         if (threadIdx.x == 0) {
-            s_base = atomicAdd(&ctr[C_RNEXT], s_cnt);
+            s_base = atomicAdd(&ctr[C_RNEXT], held);
             static_assert(C_RTILES % 2 == 0 && C_RELEM == C_RTILES + 1, "both counters in one 8-byte word");
             atomicAdd((unsigned long long *)&ctr[C_RTILES], ((unsigned long long)s_elems << 32) | s_tiles);
         }
         __syncthreads();
-        for (u32 k = threadIdx.x; k < s_cnt; k += 256) out[s_base + k] = buf[k];
+        for (u32 k = threadIdx.x; k < held; k += 256) out[s_base + k] = buf[k];
         __syncthreads();
         if (threadIdx.x == 0) s_cnt = s_tiles = s_elems = 0;
         __syncthreads();
+        held = 0;
     };
     if (threadIdx.x == 0) s_cnt = s_tiles = s_elems = 0;
     __syncthreads();
@@ -903,10 +905,12 @@ __global__ __launch_bounds__(256) void k_resolve(const Seg *in, const u8 *bytes,
         atomicAdd(&s_tiles, (g.end - g.begin + et - 1) / et);
         atomicAdd(&s_elems, g.end - g.begin);
     }
-    __syncthreads();
-    if (s_cnt > RS_BUF - 32) flush();  // (uniform)
+    // (s_cnt itself may not be read for this: a wavefront that is ahead adds to it
+    // again before a late one has read it, and only some would enter the flush)
+    held += (u32)__syncthreads_count(keep && gl == 0);
+    if (held > RS_BUF - 32) flush();
     }
-    if (s_cnt) flush();  // (uniform: the last iteration ended with a barrier)
+    if (held) flush();
 }
 
 // ------------------------------------------------------------ radix passes

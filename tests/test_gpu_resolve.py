@@ -53,3 +53,31 @@ def test_tied_runs(members, tie, batch):
     ref = oracle.sort(b, o)
     np.testing.assert_array_equal(perm.cpu().numpy().view(np.uint32), ref)
     np.testing.assert_array_equal(lcp.cpu().numpy().view(np.uint32), oracle.lcp(b, o, ref))
+
+
+def test_many_surviving_runs():
+    """More runs that go on than 8 x 32 per workgroup of the largest grid (2048):
+    what a workgroup collects is published in the middle of its runs and again at
+    the end.  Triples that share 45 bytes and then differ, every 50th run of 17
+    strings (passed on uncompared), in random input order."""
+    groups, filler = 600_000, 40
+    size = np.where(np.arange(groups) % 50 == 49, 17, 3)
+    assert groups > 8 * 32 * 2048 and size.sum() < 2**31
+    grp = np.repeat(np.arange(groups), size)
+    last = np.arange(grp.size) - np.repeat(np.cumsum(size) - size, size)
+    rank = np.random.default_rng(3).permutation(grp.size)  # input index i holds sorted string rank[i]
+    digits = np.stack([grp // 26 ** (4 - d) % 26 for d in range(5)], axis=1)
+    rows = np.full((grp.size, 6 + filler), 65, dtype=np.uint8)
+    rows[:, :5] += digits.astype(np.uint8)
+    rows[:, -1] += last.astype(np.uint8)
+    want = np.empty(grp.size, dtype=np.int64)
+    want[rank] = np.arange(grp.size)
+    lcp_want = np.where(grp[1:] == grp[:-1], 5 + filler, np.argmax(digits[1:] != digits[:-1], axis=1))
+    print(f"[surviving runs] groups={groups} n={grp.size}", flush=True)
+    b = torch.from_numpy(rows[rank].reshape(-1)).to("cuda:0")
+    o = torch.arange(grp.size + 1, dtype=torch.int64, device="cuda:0") * (6 + filler)
+    perm, lcp = ss.sort(b, o)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(perm.cpu().numpy(), want)
+    np.testing.assert_array_equal(lcp.cpu().numpy()[1:], lcp_want)
+    assert lcp[0].item() == 0
