@@ -1444,16 +1444,18 @@ __global__ __launch_bounds__(256) void k_dedup(const u64 *keys, int kin, const u
 #define PS_MAX 2048   // strings of a one-launch prefix doubling
 #define PS_NT 1024
 #define PS_LOG 12     // log2 of its key table's slots (twice the strings)
-#define PS_LIMBS 32   // a round of up to this many limbs: one thread per string
+#define PS_BYTES (256u << 10)  // bytes up to which one workgroup hashes them (see pd_run)
+#define PS_WAVE 11    // time of a wavefront's string, in limbs of a thread's
 
 // All rounds of prefix doubling over up to PS_MAX strings by one workgroup,
 // nothing read back in between: the Horner value of every string in LDS,
 // continued limb by limb each round (the same key as the matrix form's: H B +
 // m), the keys' multiplicities in an LDS table whose slots hold a key and a
-// mark for a second one.  A round of few limbs has one thread per string; a
-// longer one (the few strings left by then) one wavefront per string, the
-// lanes on consecutive stretches of limbs, front-padded with zero limbs and
-// combined by a tree of products with B^(stretch 2^k).
+// mark for a second one.  A round takes one thread per string, or one wavefront
+// per string, the lanes on consecutive stretches of limbs, front-padded with
+// zero limbs and combined by a tree of products with B^(stretch 2^k): whichever
+// takes less time for its limbs and strings (0.6 us a limb and 1,024 strings
+// against 6.7 us, for the tree and two powers, and 0.6 us per 64 limbs, for 16).
 //
 // Latency bounds it: 2 to 4 us a round.  1,000 text strings took 65 launches and
 // 9 read-backs in the general form; now one launch of 30 us (with the sort's
@@ -1480,7 +1482,8 @@ __global__ __launch_bounds__(PS_NT) void k_pd_small(u32 n, const u8 *bytes, u64 
         const u16 *act = list[cur];
         for (u32 x = t; x < (1u << PS_LOG); x += PS_NT) tab[x] = TAB_EMPTY;
         // keys of the active strings' l-prefixes: limbs [lprev / 4, ceil(min(l, len) / 4))
-        if ((l - lprev) / 4 <= PS_LIMBS) {
+        const u64 limbs = (l - lprev) / 4;
+        if (limbs * ((A + PS_NT - 1) / PS_NT) <= (PS_WAVE + limbs / 64) * ((A + PS_NT / 64 - 1) / (PS_NT / 64))) {
             for (u32 j = t; j < A; j += PS_NT) {
                 const u32 i = act[j];
                 const u64 o = off[i], len = off[i + 1] - o;
@@ -1501,9 +1504,9 @@ __global__ __launch_bounds__(PS_NT) void k_pd_small(u32 n, const u8 *bytes, u64 
                 const u32 i = act[j];
                 const u64 o = off[i], len = off[i + 1] - o;
                 const u64 m = len < l ? len : l;
-                const u64 limbs = m > lprev ? (m - lprev + 3) / 4 : 0ull;
-                const u64 c = (limbs + 63) / 64;            // limbs of a lane's stretch
-                const long long f = (long long)limbs - 64ll * (long long)c + (long long)(c * lane);  // its first (< 0: padding)
+                const u64 own = m > lprev ? (m - lprev + 3) / 4 : 0ull;
+                const u64 c = (own + 63) / 64;              // limbs of a lane's stretch
+                const long long f = (long long)own - 64ll * (long long)c + (long long)(c * lane);  // its first (< 0: padding)
                 u64 h = 0;
                 for (u64 q = 0; q < c; q++) {
                     const long long p = f + (long long)q;
@@ -1515,8 +1518,8 @@ __global__ __launch_bounds__(PS_NT) void k_pd_small(u32 n, const u8 *bytes, u64 
                 u64 bc = 1;  // B^c
                 for (u64 e = c, b = KR_B; e; e >>= 1, b = mulmod61(b, b))
                     if (e & 1) bc = mulmod61(bc, b);
-                u64 bl = 1;  // B^limbs, for the value so far
-                for (u64 e = limbs, b = KR_B; e; e >>= 1, b = mulmod61(b, b))
+                u64 bl = 1;  // B^own, for the value so far
+                for (u64 e = own, b = KR_B; e; e >>= 1, b = mulmod61(b, b))
                     if (e & 1) bl = mulmod61(bl, b);
                 for (u32 d = 1; d < 64; d <<= 1) {  // lanes [x, x + 2d) combine their halves
                     const u64 right = __shfl_down(h, d, 64);
@@ -1902,8 +1905,13 @@ static int pd_run(const uint8_t *bytes, uint64_t N, const uint64_t *offsets, uin
     }
     // Few strings whose first pass nobody else continues: one launch (unless a
     // form of the duplicate detection is asked for).  Above 2,048 strings the
-    // one workgroup's LDS is full.
-    if (parts == (PD_FIRST | PD_ROUNDS) && n <= PS_MAX && g_dedup_mode == 0) {
+    // one workgroup's LDS is full, and one compute unit hashes about 1.5 B/ns
+    // where the general form has the whole device: strings that share all but 10
+    // bytes, this against the general form: 512 KB in 262 strings 235 us and 187,
+    // 256 KB in 131 strings 192 and 189, in 1,310 strings 66 and 121, 64 KB and less
+    // always below two thirds; 2,000 strings of 100,000 bytes took 46.7 ms
+    // against 1.8.
+    if (parts == (PD_FIRST | PD_ROUNDS) && n <= PS_MAX && N <= PS_BYTES && g_dedup_mode == 0) {
         {
             SS_PROF("k_pd_small", st, (double)n * 12.0);  // offsets in, dist out; not the bytes hashed
             k_pd_small<<<1, PS_NT, 0, st>>>((u32)n, bytes, N, offsets, init_len, hash_bits, dist_approx, w.ctr);
