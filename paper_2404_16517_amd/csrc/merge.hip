@@ -264,6 +264,7 @@ static int psv_build(const u32 *e, u64 n, u32 *psv, u32 *T, u32 *cm, u32 *farl, 
 #define DC_NT 256
 #define DC_SPAN 16384  // output bytes a chunk covers at most (64 per thread)
 #define DC_WU 2        // words a thread has in flight
+#define DC_MID 32      // bytes between the literals up to which a string's own thread fetches them
 // copy words of a chunk: 16-byte words of the span, and two shared ones per piece
 #define DC_WORDS (DC_SPAN / 16 + 4 * DC_NT + 2)
 
@@ -342,7 +343,10 @@ __device__ __forceinline__ void buf_or(u64 *buf, u32 at, u64 v)
 // equal strings share their head), and only what lies between walks the psv
 // chain.  The two literal pieces of every string are cut at the buffer's
 // 16-byte words, and the words dealt evenly to the threads, which keep DC_WU
-// of them in flight.
+// of them in flight.  What lies between is a few bytes in short strings, which
+// the string's thread fetches itself; more than DC_MID are dealt out by words
+// as well, a chain walk each (20,000 strings of 5,000 bytes, their LCPs uniform:
+// 1520 us a call where one thread fetched all of them, now 242).
 //
 // The bytes in and out bound it at best; in practice the latency of the loads
 // and the vector instructions per word.  2M text strings (132 MB out): 566 us
@@ -351,7 +355,7 @@ __device__ __forceinline__ void buf_or(u64 *buf, u32 at, u64 v)
 // up to four pieces and their shifts: 560 instructions a word); 160 us with
 // four lanes per string (one load in flight per lane); 103 us in this form.
 // Nothing is written unless status is null or 0.
-__global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, const u64 *suf_off, const u8 *suf,
+__global__ __launch_bounds__(DC_NT, 5) void k_decode(const u32 *e, const u32 *d, const u64 *suf_off, const u8 *suf,
                                                   const u32 *psv, u32 n, const u64 *out_off, const u32 *status,
                                                   u8 *out)
 {
@@ -359,7 +363,11 @@ __global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, co
     __shared__ u16 s_at[2 * DC_NT], s_end[2 * DC_NT], s_base[2 * DC_NT], s_own[DC_WORDS];
     __shared__ u32 s_wsum[DC_NT / 64];
     __shared__ DOp s_tot[DC_NT / 64], s_carry;
-    __shared__ u32 s_r0;
+    // bytes between a string's literals that are dealt out: from byte s_mk of the
+    // string, buffer positions [s_ma, s_mb); s_mid: some string has them
+    __shared__ u64 s_mk[DC_NT];
+    __shared__ u16 s_ma[DC_NT], s_mb[DC_NT];
+    __shared__ u32 s_r0, s_mid;
     __shared__ __attribute__((aligned(16))) u64 buf[DC_SPAN / 8 + 2];
     if (status && *status != 0) return;  // (uniform)
     const u64 total = out_off[n], sufN = suf_off[n];
@@ -397,6 +405,7 @@ __global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, co
             }
             s_carry = c;
             s_r0 = r;
+            s_mid = 0;
         }
     }
     __syncthreads();
@@ -475,6 +484,7 @@ __global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, co
         // copies of as many 16-byte words as they touch.
         const u32 lead = (u32)((uintptr_t)(out + c0) & 15);
         u32 wc0 = 0, wc1 = 0;  // words of the two pieces
+        s_ma[t] = s_mb[t] = 0;
         if (t < ns && oo < c1) {
             const u64 k0 = oo < c0 ? c0 - oo : 0ull;  // bytes [k0, kend) lie in the chunk
             const u64 kend = (oo + di < c1 ? oo + di : c1) - oo;
@@ -493,6 +503,13 @@ __global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, co
             s_src[2 * t] = src;
             if (q > k) wc0 = (u32)((q + rel + 15) / 16 - (k + rel) / 16);
             k = q;
+            if (k + DC_MID < eb) {
+                s_mk[t] = k;
+                s_ma[t] = (u16)(k + rel);
+                s_mb[t] = (u16)(eb + rel);
+                s_mid = 1;
+                k = eb;
+            }
             while (k < eb) {
                 u32 h = ei, j = psv[r0 + t], ej = e[j];
                 while (ej > k) {
@@ -537,6 +554,7 @@ __global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, co
             oo_n = out_off[rn];
         }
         __syncthreads();
+        const bool mids = s_mid != 0;  // (written before the barrier above, reset after the next)
         // The copies: DC_WU words a thread in flight, each loaded as five
         // 4-byte words and shifted into place (a piece's end words, shared with
         // the pieces beside it, are or-ed in)
@@ -595,6 +613,70 @@ __global__ __launch_bounds__(DC_NT) void k_decode(const u32 *e, const u32 *d, co
             }
         }
         __syncthreads();
+        if (t == 0) s_mid = 0;
+        if (mids) {  // (uniform)
+            u32 mbase = s_ma[t] < s_mb[t] ? (s_mb[t] + 15u) / 16 - s_ma[t] / 16 : 0u;
+            const u32 own = mbase;
+#pragma unroll
+            for (u32 q = 1; q < 64; q <<= 1) {
+                const u32 y = __shfl_up(mbase, q, 64);
+                if (lane >= q) mbase += y;
+            }
+            if (lane == 63) s_wsum[wv] = mbase;
+            __syncthreads();
+            u32 nm = 0;
+            for (u32 w = 0; w < DC_NT / 64; w++) {
+                if (w < wv) mbase += s_wsum[w];
+                nm += s_wsum[w];
+            }
+            s_base[t] = (u16)(mbase - own);
+            __syncthreads();
+            // two neighbouring words to a thread: they mostly lie in one piece of the
+            // chain, which is then found once
+            u32 lo = DC_NT, h = 0;  // string, and where its current piece [ej, h) ends
+            u64 pos = 0;            // byte k of the piece is at suf + pos + k
+            for (u32 g0 = 2 * t; g0 < nm; g0 += g0 & 1 ? 2 * DC_NT - 1 : 1) {
+                if (lo == DC_NT || (lo + 1 < DC_NT && s_base[lo + 1] <= g0)) {
+                    u32 hi = DC_NT;  // the last string whose words start at or before g0
+                    for (lo = 0; hi - lo > 1;) {
+                        const u32 mid = (lo + hi) >> 1;
+                        if (s_base[mid] <= g0) lo = mid;
+                        else hi = mid;
+                    }
+                    h = 0;
+                }
+                const u32 at = s_ma[lo], w = at / 16 + (g0 - s_base[lo]);
+                u32 x = 16 * w < at ? at : 16 * w;
+                const u32 end = s_mb[lo] < 16 * w + 16 ? s_mb[lo] : 16 * w + 16;
+                u64 k = s_mk[lo] + (x - at), v0 = 0, v1 = 0;
+                while (x < end) {
+                    if (k >= h) {  // (byte k < e of the string)
+                        h = e[r0 + lo];
+                        u32 j = psv[r0 + lo], ej = e[j];
+                        while (ej > k) {
+                            h = ej;
+                            j = psv[j];
+                            ej = e[j];
+                        }
+                        pos = suf_off[j] - ej;
+                    }
+                    const u32 m = end - x < h - k ? end - x : (u32)(h - k), sh = 8 * (x - 16 * w);
+                    u64 a0, a1;
+                    win16_finish(suf, win16_issue(suf, sufN, pos + k, m), a0, a1);
+                    if (sh >= 64) {
+                        v1 |= a0 << (sh - 64);
+                    } else {
+                        v0 |= a0 << sh;
+                        v1 |= (a1 << sh) | (sh ? a0 >> (64 - sh) : 0ull);
+                    }
+                    x += m;
+                    k += m;
+                }
+                if (v0) atomicOr((unsigned long long *)&buf[2 * w], (unsigned long long)v0);
+                if (v1) atomicOr((unsigned long long *)&buf[2 * w + 1], (unsigned long long)v1);
+            }
+            __syncthreads();
+        }
         const u32 span = (u32)(c1 - c0);
         // and out, in aligned 16-byte words; the buffer is cleared behind
         const u32 nw = (span + lead + 15) / 16;
