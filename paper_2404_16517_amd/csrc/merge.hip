@@ -1577,12 +1577,15 @@ struct MwOut {
     u32 tile, block_max; // of that sort
 };
 
-// One segment to the sort of its size, and to the list of what is to be emitted.
-__device__ __forceinline__ void mw_route(const MwOut &W, Seg o)
+// One segment to the sort of its size, and to the list of what is to be emitted
+// (from: the tile it is, or MW_GROUP: a whole group).
+#define MW_GROUP 0xFFFFFFFFu
+#define MW_EQUAL 0x80000000u  // a tile of one key, in its final order but for ties
+__device__ __forceinline__ void mw_route(const MwOut &W, Seg o, u32 from)
 {
     const u32 m = o.end - o.begin;
     u32 *ctr = W.s.ctr;
-    W.over[atomicAdd(&ctr[C_RTILES], 1u)] = o;
+    W.over[atomicAdd(&ctr[C_RTILES], 1u)] = Seg{o.begin, o.end, o.depth, from};
     if (m > W.block_max) {
         W.s.largeA[atomicAdd(&ctr[C_LARGE], 1u)] = Seg{o.begin, o.end, o.depth, o.aux | SEG_NOROOT};
         atomicAdd(&ctr[C_LTILES], (m + W.tile - 1) / W.tile);
@@ -1607,9 +1610,10 @@ __device__ __forceinline__ void mw_route(const MwOut &W, Seg o)
 // Runs of outputs with equal keys whose strings go on become segments at depth
 // C + 7 if they come from more than one run (within one run their order and
 // LCPs stand).  A tile whose windows exceed MW_CAP (many copies of one key, or
-// a group with too few samples) becomes one segment for the segmented sort; in
-// a sample level its keys all become its lower threshold, which only makes
-// later tiles larger.
+// a group with too few samples) becomes one segment for the segmented sort
+// (k_mw_over copies its windows), or, if all its keys are one, is in order as it
+// is; in a sample level its keys all become its lower
+// threshold, which only makes later tiles larger.
 //
 // Bounded by vector instructions: about 25 per element and level, against 8 B
 // in and 8 to 20 B out.  8M keys in 256 runs: 235 us over all levels, where
@@ -1704,16 +1708,34 @@ __global__ __launch_bounds__(MW_NT) void k_mw_tile(MwLevel M, MwOut W)
             const u64 low = row ? mw_threshold(M, j0, kg, row, M.ts[g + 1] - M.ts[g]) : 0ull;
             for (u32 e = t; e < cnt; e += MW_NT) W.keys[X + e] = low;
         } else {
-            // keys and entries into the sort's second pair (the first still
-            // holds the runs' keys)
-            for (u32 e = t; e < cnt; e += MW_NT) {
-                const u32 r = run_at(e), i = wlo[r] + (e - woff[r]);
-                W.s.keyB[X + e] = M.K[M.ps[j0 + r] + i];
-                W.s.valB[X + e] = W.rbeg[j0 + r] + i;
+            u64 mx = 0;  // its largest key
+#pragma unroll
+            for (u32 q = 0; q < R; q++)
+                if (nr[q]) {
+                    const u64 y = M.K[M.ps[j0 + R * t + q] + wlo[R * t + q] + nr[q] - 1];
+                    mx = y > mx ? y : mx;
+                }
+#pragma unroll
+            for (u32 d = 1; d < 64; d <<= 1) {
+                const u64 y = __shfl_xor(mx, d, 64);
+                mx = y > mx ? y : mx;
             }
+            if (lane == 0) s_min[wv] = mx;
+            __syncthreads();
             if (t == 0) {
+                for (u32 w = 0; w < MW_NT / 64; w++) mx = s_min[w] > mx ? s_min[w] : mx;
                 W.O.lcp[X] = before ? key_lcp(prev, mn, C) : 0u;
-                mw_route(W, Seg{X, X + cnt, C, SEG_INB});
+                if (mx != mn) {
+                    mw_route(W, Seg{X, X + cnt, C, SEG_INB}, tile);
+                } else {
+                    const u32 c8 = (u32)(mn & 0xFF);
+                    W.over[atomicAdd(&W.s.ctr[C_RTILES], 1u)] = Seg{X, X + cnt, C + c8, tile | MW_EQUAL};
+                    atomicAdd(&W.s.ctr[C_NELEM], cnt);
+                    if (c8 == 8) {
+                        W.ties[atomicAdd(&W.s.ctr[C_RNEXT], 1u)] = Seg{X, X + cnt, C + 7, 0};
+                        W.s.ctr[C_TIEBIG] = 1;
+                    }
+                }
             }
         }
         return;
@@ -1879,7 +1901,69 @@ __global__ __launch_bounds__(256) void k_mw_whole(const u32 *wg, u32 nwg, const 
         if (x == ps[gs[g]]) {
             const u32 cnt = ps[gs[g + 1]] - x;
             W.O.lcp[x] = 0;
-            mw_route(W, Seg{x, x + cnt, W.Cg[g], 0});
+            mw_route(W, Seg{x, x + cnt, W.Cg[g], 0}, MW_GROUP);
+        }
+    }
+}
+
+// Keys and entries of the tiles that became segments, MW_OVER at a time, into
+// the sort's second pair (the first still holds the runs' keys); of those with
+// one key the order, which is final but for ties, and the LCPs of strings that
+// end in it.  They may hold most of the input (few distinct strings): copying 1M
+// copies of one string from 8 runs took the tile's own workgroup 1150 us.
+#define MW_OVER 2048
+template <u32 RUNS>
+__global__ __launch_bounds__(MW_NT) void k_mw_over(MwLevel M, MwOut W, const u32 *tstart, u32 nover)
+{
+    constexpr u32 R = RUNS / MW_NT;
+    __shared__ u32 woff[RUNS + 1], wlo[RUNS], s_sum[MW_NT / 64];
+    const u32 t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    if (blockIdx.x >= tstart[nover]) return;
+    const u32 s = seg_of_tile(tstart, nover, blockIdx.x);
+    const Seg o = W.over[s];
+    if (o.aux == MW_GROUP) return;  // (uniform, as all of this)
+    const u32 tile = o.aux & ~MW_EQUAL, g = mw_find(M.ts, M.groups, tile);
+    const u32 j0 = M.gs[g], kg = M.gs[g + 1] - j0;
+    const u32 row = tile - M.ts[g], nt1 = M.ts[g + 1] - M.ts[g] + 1;
+    const u32 *b = M.bounds + M.bo[g] + row;
+    u32 nr[R], inc = 0;
+#pragma unroll
+    for (u32 q = 0; q < R; q++) {
+        const u32 w = R * t + q;
+        nr[q] = 0;
+        if (w < kg) {
+            wlo[w] = b[w * nt1];
+            nr[q] = b[w * nt1 + 1] - wlo[w];
+            inc += nr[q];
+        }
+    }
+    u32 ex = inc;  // (less its own below)
+#pragma unroll
+    for (u32 d = 1; d < 64; d <<= 1) {
+        const u32 y = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += y;
+    }
+    if (lane == 63) s_sum[wv] = inc;
+    __syncthreads();
+    ex = inc - ex;
+#pragma unroll
+    for (u32 w = 0; w < MW_NT / 64; w++)
+        if (w < wv) ex += s_sum[w];
+#pragma unroll
+    for (u32 q = 0; q < R; q++) {
+        if (R * t + q < kg) woff[R * t + q] = ex;
+        ex += nr[q];
+    }
+    __syncthreads();
+    const u32 cnt = o.end - o.begin, e0 = (blockIdx.x - tstart[s]) * MW_OVER, e1 = cnt < e0 + MW_OVER ? cnt : e0 + MW_OVER;
+    for (u32 e = e0 + t; e < e1; e += MW_NT) {
+        const u32 r = mw_find(woff, kg, e), i = wlo[r] + (e - woff[r]);
+        if (o.aux & MW_EQUAL) {
+            W.order[o.begin + e] = W.rbeg[j0 + r] + i;
+            if (e) W.O.lcp[o.begin + e] = o.depth;
+        } else {
+            W.s.keyB[o.begin + e] = M.K[M.ps[j0 + r] + i];
+            W.s.valB[o.begin + e] = W.rbeg[j0 + r] + i;
         }
     }
 }
@@ -1955,13 +2039,13 @@ __device__ __forceinline__ int fc_cmp8(const FcView &V, const FcEl &X, const FcE
     return lx < ly ? -1 : (lx > ly ? 1 : 0);
 }
 
-// Tile counts of a list of segments; their comparison words (see k_tie_compare)
+// Tile counts (per members each) of a list of segments; their comparison words (see k_tie_compare)
 // and the counters of the lists the round builds are reset.
-__global__ void k_tie_tiles(const Seg *list, u32 cnt, u32 *tiles, u64 *cmp, u32 *ctr)
+__global__ void k_tie_tiles(const Seg *list, u32 cnt, u32 per, u32 *tiles, u64 *cmp, u32 *ctr)
 {
     const u32 j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j < cnt) {
-        tiles[j] = (list[j].end - list[j].begin + TIE_T - 1) / TIE_T;
+        tiles[j] = (list[j].end - list[j].begin + per - 1) / per;
         if (cmp) cmp[j] = ~0ull;
     }
     if (ctr && j < C_NCTR) ctr[j] = 0;
@@ -2063,7 +2147,10 @@ __global__ __launch_bounds__(256) void k_tie_compare(const Seg *list, const u32 
             const u64 w = 2 * l + (r == 0 ? 1u : 0u);
             best = w < best ? w : best;
         }
-    if (gl == 0 && best != ~0ull) atomicMin((unsigned long long *)&cmp[s], (unsigned long long)best);
+    // (a segment's tiles meet on its word: only what would change it as it is read
+    // is committed; it only ever falls)
+    if (gl == 0 && best < __hip_atomic_load(&cmp[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMin((unsigned long long *)&cmp[s], (unsigned long long)best);
 }
 
 // The larger segments after their comparison: equal strings are done (LCP =
@@ -2505,11 +2592,15 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
     const MergeOut O{w.sb, w.sid, kne, fc_id, fc_len, out_src, out_id, out_lcp, out_len};
     const SortShape z = sort_shape(n_out);
     const MwOut W{KM, w.Cg, pl + p_rrun, pl + p_rbeg, fc_lcp, fc_len, suf_off, O, w.order, w.segs, w.over, sw, z.tile, z.block_max};
+    auto level = [&](u32 v) {
+        const Lv &L = lv[v];
+        return MwLevel{v ? KS : K, pl + L.ps, gsd, pl + L.ts, pl + L.bo, KM, v < nl ? pl + lv[v + 1].ps : pl + L.ps,
+                       groups, bounds, unsorted};
+    };
     for (u32 v = nl + 1; v-- > 0;) {
         const Lv &L = lv[v];
         if (!L.tiles) continue;
-        const MwLevel M{v ? KS : K, pl + L.ps, gsd, pl + L.ts, pl + L.bo, KM, v < nl ? pl + lv[v + 1].ps : pl + L.ps,
-                        groups, bounds, unsorted};
+        const MwLevel M = level(v);
         k_mw_bounds<<<(unsigned)ceil_div(L.bounds, 256), 256, 0, st>>>(M, L.bounds);
         SS_CHECK_LAUNCH();
         if (v) {
@@ -2550,8 +2641,19 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
     const bool small_only = !nover && !ctr[C_TIEBIG];  // then the first round is the last: its counters aren't read
     if (!nact && !nover) return SS_OK;
     const SortJob J{nullptr, 0, nullptr, w.order, out_lcp, st, n_out, n_out};
+    // (lists of segments, in tiles of `per` members)
+    auto tile_list = [&](const Seg *l, u32 cnt, u32 per, u64 *cmp, u32 *c) -> int {
+        k_tie_tiles<<<(unsigned)ceil_div(cnt, 256), 256, 0, st>>>(l, cnt, per, w.tiles, cmp, c);
+        SS_CHECK_LAUNCH();
+        return ss_scan_exclusive<u32>(w.tiles, w.tiles, cnt, (u32 *)sw.scan_scratch, st);
+    };
     if (nover) {
         // segments too large for a tile: sorted by key, their ties join the others
+        SS_TRY(tile_list(w.over, nover, MW_OVER, nullptr, nullptr));
+        const unsigned og = (unsigned)(nover + eover / MW_OVER);
+        if (few) k_mw_over<MW_FEW><<<og, MW_NT, 0, st>>>(level(0), W, w.tiles, nover);
+        else k_mw_over<MW_RUNS><<<og, MW_NT, 0, st>>>(level(0), W, w.tiles, nover);
+        SS_CHECK_LAUNCH();
         k_fill_u32<<<1, 64, 0, st>>>(sw.ctr + C_NELEM, 0u, 1);
         SS_CHECK_LAUNCH();
         SS_TRY(sort_keyed(J, sw, ctr));
@@ -2566,11 +2668,6 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
     // a run share C + 7 bytes.
     if (nact) SS_TRY(psv_build(fc_lcp, n_fc, w.dec.psv, w.dec.tree, w.dec.cmin, w.dec.far, w.dec.fcnt, st, w.ties));
     auto tile_grid = [](u32 cnt, u32 el) { return (unsigned)ceil_div((u64)cnt + el / TIE_T, 32); };
-    auto tile_list = [&](const Seg *l, u32 cnt, u64 *cmp, u32 *c) -> int {
-        k_tie_tiles<<<(unsigned)ceil_div(cnt, 256), 256, 0, st>>>(l, cnt, w.tiles, cmp, c);
-        SS_CHECK_LAUNCH();
-        return ss_scan_exclusive<u32>(w.tiles, w.tiles, cnt, (u32 *)sw.scan_scratch, st);
-    };
     // rounds: the list's small segments end; its large ones go to `big` -- the
     // first round's stay there for the final emission -- and their ties, after
     // a sort by the next keys, make the next list
@@ -2594,7 +2691,7 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
             nbig0 = nbig;
             ebig0 = ebig;
         }
-        SS_TRY(tile_list(big, nbig, sw.mword, sw.ctr));
+        SS_TRY(tile_list(big, nbig, TIE_T, sw.mword, sw.ctr));
         const unsigned tg = tile_grid(nbig, ebig);
         {
             SS_PROF("k_tie_compare", st, (double)ebig * 20.0);  // entry, its LCP, length, offset; not the bytes
@@ -2609,12 +2706,12 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
         list = sw.act;
     }
     if (nbig0) {
-        SS_TRY(tile_list(w.big, nbig0, nullptr, nullptr));
+        SS_TRY(tile_list(w.big, nbig0, TIE_T, nullptr, nullptr));
         k_tie_emit<<<tile_grid(nbig0, ebig0), 256, 0, st>>>(w.big, w.tiles, nbig0, w.order, O);
         SS_CHECK_LAUNCH();
     }
     if (nover) {
-        SS_TRY(tile_list(w.over, nover, nullptr, nullptr));
+        SS_TRY(tile_list(w.over, nover, TIE_T, nullptr, nullptr));
         k_tie_emit<<<tile_grid(nover, eover), 256, 0, st>>>(w.over, w.tiles, nover, w.order, O);
         SS_CHECK_LAUNCH();
     }
