@@ -959,11 +959,17 @@ __device__ __forceinline__ void merge_emit(const MergeOut &O, u64 x, u32 g)
 // size a workgroup per 4096 entries, at most 64 of them: with 245 the atomics
 // on one word cost more than they save.  4 runs of 500,000 entries: 18 us with
 // one load in flight, 6.4 us with eight (13.8 us with 245 workgroups per run).
-__global__ __launch_bounds__(256) void k_run_min(const u64 *run_begin, const u64 *P, const u32 *e, u32 *runmin)
+// Runs of more than `limit` entries, far above the average, are listed and take
+// a launch of their own with 64 workgroups each: one run of 8M among 1,023 of 100
+// took 783 us without it.
+#define RM_PARTS 64
+__global__ __launch_bounds__(256) void k_run_min(const u32 *list, u64 limit, const u64 *run_begin, const u64 *P,
+                                                 const u32 *e, u32 *runmin)
 {
     __shared__ u32 wmin[4];
-    const u32 r = blockIdx.x;
+    const u32 r = list ? list[blockIdx.x] : blockIdx.x;
     const u64 b = run_begin[r], n = P[r + 1] - P[r];
+    if (!list && n > limit) return;  // (uniform)
     const u64 i0 = 1 + (n * blockIdx.y) / gridDim.y, i1 = 1 + (n * (blockIdx.y + 1)) / gridDim.y;
     u32 mn = 0xFFFFFFFFu;
     const u64 end = i1 < n ? i1 : n;
@@ -2259,8 +2265,8 @@ struct MergeWs {
 
 #define MERGE_MAX_K 65536
 // words of the merge plan: per level run starts, tile starts and bounds starts;
-// the group starts, runs and their front-coded starts, groups taken whole
-#define MERGE_PLAN(k) ((3 * (size_t)MW_LEVELS + 6) * ((size_t)(k) + 4))
+// the group starts, runs and their front-coded starts, groups taken whole, long runs
+#define MERGE_PLAN(k) ((3 * (size_t)MW_LEVELS + 7) * ((size_t)(k) + 4))
 
 static void merge_layout(u64 n_out, u64 n_fc, u64 k, MergeWs *w, WsArena *a, WsCounter *c)
 {
@@ -2527,6 +2533,12 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
     const size_t p_whole = plan.size();
     plan.insert(plan.end(), whole.begin(), whole.end());
     plan.resize(p_whole + groups);
+    const u64 rparts = std::min<u64>(ceil_div(n_out, (u64)k * 4096), RM_PARTS);
+    const u64 rlimit = rparts < RM_PARTS ? rparts * 32768 : ~0ull;  // (16 steps of a workgroup)
+    const size_t p_long = plan.size();
+    for (u32 j = 0; j < k; j++)
+        if (re[j] - rb[j] > rlimit) plan.push_back(j);
+    const u32 nlong = (u32)(plan.size() - p_long);
     // (the samples and their merge share the mismatch words' array, the bounds
     // the boundary list: about n / 7 keys and at most 2 n words)
     if (plan.size() > MERGE_PLAN(k) || 2ull * nsample > n_out) {
@@ -2553,9 +2565,15 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
     k_merge_init<<<(unsigned)ceil_div(ni, 256), 256, 0, st>>>(w.P, k, nb, w.bfirst, w.runmin, w.Cg, groups, w.ties,
                                                              sw.ctr);
     SS_CHECK_LAUNCH();
-    const u64 rparts = ceil_div(n_out, (u64)k * 4096);
-    k_run_min<<<dim3(k, (unsigned)(rparts < 64 ? rparts : 64)), 256, 0, st>>>(run_begin, w.P, fc_lcp, w.runmin);
-    SS_CHECK_LAUNCH();
+    {
+        SS_PROF("k_run_min", st, (double)n_out * 4.0);  // front-coded LCP in
+        k_run_min<<<dim3(k, (unsigned)rparts), 256, 0, st>>>(nullptr, rlimit, run_begin, w.P, fc_lcp, w.runmin);
+        SS_CHECK_LAUNCH();
+        if (nlong) {
+            k_run_min<<<dim3(nlong, RM_PARTS), 256, 0, st>>>(w.plan + p_long, rlimit, run_begin, w.P, fc_lcp, w.runmin);
+            SS_CHECK_LAUNCH();
+        }
+    }
     k_group_depth<<<(unsigned)ceil_div(k, 4), 256, 0, st>>>(run_begin, w.P, w.rgroup, w.rep, k, w.runmin, V, w.Cg);
     SS_CHECK_LAUNCH();
     u32 *const unsorted = sw.ctr + C_BADSET;
