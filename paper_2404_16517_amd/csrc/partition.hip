@@ -428,10 +428,12 @@ __global__ void k_add_base(u64 *a, u64 n, u64 base)
     if (i < n) a[i] += base;
 }
 
-#define CS_NT 256     // strings per workgroup in the literal copy (one thread each)
+#define CS_NT 256     // threads per workgroup in the literal copy, strings per workgroup (one thread each)
+#define CS_FEW 16     // ... strings per workgroup where literals have CS_LONG bytes or more on average
+#define CS_LONG 512
 #define CS_BUF 4096   // LDS staging bytes (short literals: at most 16 B per string on average)
 
-// Literal bytes of strings [i0, i0+256) (string i's bytes [e_i, d_i) go to
+// Literal bytes of strings [i0, i0+S) (string i's bytes [e_i, d_i) go to
 // suf[suf_off[i] ..]; lit_src[i] = offset of byte e_i, written in sorted order
 // by k_fc_meta).  When the workgroup's output span fits the LDS buffer (short
 // literals, as distinguishing prefixes of D/N strings leave them) each
@@ -445,16 +447,19 @@ __global__ void k_add_base(u64 *a, u64 n, u64 base)
 // Bounded by the lines of the source that the literals touch (4M text strings:
 // about 1.1 GB with the output, 230 us at the copy's rate).  With 4 lanes per
 // string (waiting for the longest of their wavefront) and 8-byte words they took
-// 323 us, now 181.
+// 323 us, now 181.  Long literals by 256 strings would leave most of the device
+// idle: 20,000 strings of 5,000 bytes that share 2,500 took a call of 378 us so, by
+// 16 181; 2,000 of 100,000 bytes 8914 and 513.
+template <u32 S>
 __global__ __launch_bounds__(CS_NT) void k_fc_copy(const u8 *bytes, u64 N, u32 n, const u64 *lit_src,
                                                    const u64 *suf_off, u8 *suf)
 {
     __shared__ uint4 buf4[CS_BUF / 16];
-    __shared__ u64 so_s[CS_NT + 1];
+    __shared__ u64 so_s[S + 1];
     u8 *buf = (u8 *)buf4;
     u64 *ls_s = (u64 *)buf4;  // the literals' sources (where the buffer is not used)
-    const u32 i0 = blockIdx.x * CS_NT;
-    const u32 i1 = (i0 + CS_NT < n) ? i0 + CS_NT : n;
+    const u32 i0 = blockIdx.x * S;
+    const u32 i1 = (i0 + S < n) ? i0 + S : n;
     const u64 S0 = suf_off[i0], S1 = suf_off[i1];
     const u64 span = S1 - S0;
     const u32 mis = (u32)(((uintptr_t)(suf + S0)) & 15);  // buf[mis] holds output byte S0
@@ -605,7 +610,10 @@ static int encode_impl(const uint8_t *bytes, uint64_t N, const uint64_t *offsets
         {
             // literal bytes read and written; per string its perm, offsets, e and suf_off
             SS_PROF("k_fc_copy", st, 2.0 * (double)total + (double)n * 16.0);
-            k_fc_copy<<<(unsigned)ceil_div(n, CS_NT), CS_NT, 0, st>>>(bytes, N, (u32)n, lit_src, suf_off, suf);
+            if (total >= (u64)CS_LONG * n)
+                k_fc_copy<CS_FEW><<<(unsigned)ceil_div(n, CS_FEW), CS_NT, 0, st>>>(bytes, N, (u32)n, lit_src, suf_off, suf);
+            else
+                k_fc_copy<CS_NT><<<(unsigned)ceil_div(n, CS_NT), CS_NT, 0, st>>>(bytes, N, (u32)n, lit_src, suf_off, suf);
         }
         SS_CHECK_LAUNCH();
     }
