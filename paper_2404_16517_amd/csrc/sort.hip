@@ -198,6 +198,33 @@ __device__ __forceinline__ u32 digit_of(u64 k, const Digit &D)
     return d;
 }
 
+// ---- digits by splitters
+//
+// Where one workgroup takes what the levels over the whole device leave
+// (k_radix_wg), these must leave no long segment, whatever its keys: bits would
+// keep strings that share most of a key together (2M strings, 95 % of them
+// sharing six bytes: 15.4 ms, with all levels over the device 1.4).  So segments
+// of more than SPLIT_MIN strings with more than SPLIT_SKEW of a sample of 1024 in
+// one digit of bits are divided by up to SPLITS of their own keys, every eighth of
+// the sorted sample: digit 2 i + 1 is the i-th of them, 2 i what lies before it.
+// A bucket between two then has a 50th of the segment or so, and one of a key is
+// done.  (Without skew bits divide finer: 520,000 random strings 304 us, by
+// splitters 434.)
+#define SPLIT_MIN 131072
+#define SPLITS 127  // (a table has one entry more)
+#define SPLIT_SAMPLE 1024
+#define SPLIT_SKEW 128
+#define SPLIT_LIST 80  // segments of a level (sorts that get here have 4096 times 2048 strings and a few)
+#define SPLIT_FLAG (1ull << 63)  // in a segment's digit: by the splitters of this index
+
+__device__ __forceinline__ u32 split_digit(const u64 *tab, u64 k)  // tab: ascending, past the last ~0
+{
+    u32 i = 0;
+#pragma unroll
+    for (u32 d = 64; d; d >>= 1) i += tab[i + d - 1] < k ? d : 0u;
+    return 2 * i + (tab[i] == k ? 1u : 0u);
+}
+
 // Key k with its digit replaced by d.
 __device__ __forceinline__ u64 digit_put(u64 k, u32 d, const Digit &D)
 {
@@ -205,6 +232,48 @@ __device__ __forceinline__ u64 digit_put(u64 k, u32 d, const Digit &D)
     for (int q = 0; q < 3; q++)
         k = (k & ~((u64)D.m[q] << D.s[q])) | ((u64)((d >> D.o[q]) & D.m[q]) << D.s[q]);
     return k;
+}
+
+// Whether segment [b, e) of keys is to be divided by splitters instead of the
+// digit D, and if so these into tab; by a workgroup of SPLIT_SAMPLE.
+__device__ __forceinline__ bool split_choose(const u64 *keys, u32 b, u32 e, const Digit &D, u64 *tab)
+{
+    __shared__ u64 sk[SPLIT_SAMPLE];
+    __shared__ u32 s_kept[2], h[256];
+    const u32 t = threadIdx.x, m = e - b, step = m / SPLIT_SAMPLE;
+    if (t < 256) h[t] = 0;
+    // (somewhere in the t-th part of the segment: inputs repeat at even distances)
+    const u64 key = keys[b + (u32)((u64)m * t / SPLIT_SAMPLE) + ((t * 2654435761u) >> 8) % step];
+    sk[t] = key;
+    __syncthreads();
+    atomicAdd(&h[digit_of(key, D)], 1u);
+    __syncthreads();
+    if (!__syncthreads_or(t < 256 && h[t] > SPLIT_SKEW)) return false;  // (its barrier: h is free again)
+    for (u32 k = 2; k <= SPLIT_SAMPLE; k <<= 1)
+        for (u32 j = k >> 1; j; j >>= 1) {
+            __syncthreads();
+            const u32 y = t ^ j;
+            if (y > t) {
+                const u64 x0 = sk[t], x1 = sk[y];
+                if ((x0 > x1) == ((t & k) == 0)) {
+                    sk[t] = x1;
+                    sk[y] = x0;
+                }
+            }
+        }
+    __syncthreads();
+    constexpr u32 EVERY = SPLIT_SAMPLE / (SPLITS + 1);
+    const u64 mine = t < SPLITS ? sk[(t + 1) * EVERY] : ~0ull;
+    const bool keep = t < SPLITS && (t == 0 || mine != sk[t * EVERY]);
+    const u64 m64 = __ballot(keep);
+    if (t < 128 && (t & 63) == 0) s_kept[t >> 6] = (u32)__popcll(m64);
+    __syncthreads();
+    if (t < 128) {
+        if (keep) tab[(t >= 64 ? s_kept[0] : 0u) + (u32)__popcll(m64 & lanemask_lt())] = mine;
+        if (t >= s_kept[0] + s_kept[1]) tab[t] = ~0ull;
+    }
+    __syncthreads();  // (the next segment)
+    return true;
 }
 
 // k_tile_counts and its scan for up to LIST_ONE segments.
@@ -234,11 +303,12 @@ __global__ __launch_bounds__(LIST_NT) void k_round_start(const Seg *segs, u32 *c
 //
 // WG: segments of up to wg_max strings are taken out and listed in wl (see
 // k_radix_wg).
+// Those of more than SPLIT_MIN whose keys are skewed get splitters.
 template <bool WG>
 __global__ __launch_bounds__(LIST_NT) void k_level_start(Seg *segs, u32 *ctr, u32 *hdr, u32 nb, u32 tile,
                                                          u32 *tstart, u64 *smin, u64 *smax, u64 *hscan,
                                                          const u64 *rmask, u64 *dig, bool narrow, Seg *wl,
-                                                         u32 wg_max)
+                                                         u32 wg_max, const u64 *keyA, const u64 *keyB, u64 *split)
 {
     u32 nseg = ctr[C_LARGE];
     scan_state_zero(hscan);
@@ -266,10 +336,30 @@ __global__ __launch_bounds__(LIST_NT) void k_level_start(Seg *segs, u32 *ctr, u3
         __syncthreads();
         nseg = s_keep;
     }
+    __shared__ u32 s_nbig, s_big[SPLIT_LIST];  // segments to be divided by splitters
+    if (WG && threadIdx.x == 0) s_nbig = 0;
+    __syncthreads();
     for (u32 j = threadIdx.x; j < nseg; j += LIST_NT) {
         smin[j] = ~0ull;
         smax[j] = 0;
+        if (WG && segs[j].end - segs[j].begin > SPLIT_MIN) {
+            const u32 x = atomicAdd(&s_nbig, 1u);
+            if (x < SPLIT_LIST) s_big[x] = j;
+        }
         dig[j] = digit_spec(segs[j], rmask, (u32)__ffs((int)nb) - 1, narrow);
+    }
+    if (WG) {
+        __syncthreads();
+        static_assert(LIST_NT == SPLIT_SAMPLE, "a sample per thread");
+        const u32 nbig = s_nbig < SPLIT_LIST ? s_nbig : SPLIT_LIST;
+        for (u32 x = 0; x < nbig; x++) {  // (uniform)
+            const u32 j = s_big[x];
+            const Seg g = segs[j];
+            const Digit D = digit_unpack(digit_spec(g, rmask, (u32)__ffs((int)nb) - 1, narrow));
+            if (split_choose((g.aux & SEG_INB) ? keyB : keyA, g.begin, g.end, D, split + (SPLITS + 1) * x) &&
+                threadIdx.x == 0)
+                dig[j] = SPLIT_FLAG | x;
+        }
     }
     const u32 tiles = list_tiles(segs, nseg, tile, tstart);
     if (threadIdx.x == 0) {
@@ -934,6 +1024,28 @@ __device__ __forceinline__ u64 match_digit_w(u32 digit, bool valid)
     return m;
 }
 
+// A level's digit of a segment, by bits or (SP: where segments may have them) by
+// splitters, which are read into LDS.  set() is called by the whole workgroup,
+// after a barrier that ends the use of the last; the digit is used after another.
+template <bool SP>
+struct LevelDigit {
+    Digit D;
+    const u64 *tab;
+    bool by;
+    __device__ __forceinline__ void set(u64 spec, const u64 *split)
+    {
+        D = digit_unpack(spec);
+        by = SP && (spec & SPLIT_FLAG);
+        if (SP && by) {
+            __shared__ u64 lds[SPLITS + 1];
+            tab = lds;
+            const u64 *src = split + (SPLITS + 1) * (u64)(u32)spec;
+            for (u32 i = threadIdx.x; i < SPLITS + 1; i += blockDim.x) lds[i] = src[i];
+        }
+    }
+    __device__ __forceinline__ u32 operator()(u64 k) const { return SP && by ? split_digit(tab, k) : digit_of(k, D); }
+};
+
 // Per-tile histogram of the segment's current digit, digit-major per
 // segment: hist[NB*tstart[s] + d*T_s + lt].  Also the segment's min and max key.
 //
@@ -944,10 +1056,11 @@ __device__ __forceinline__ u64 match_digit_w(u32 digit, bool valid)
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
                                              const u64 *keyA, const u64 *keyB, u32 *hist, u64 *smin, u64 *smax,
-                                             const u64 *dig)
+                                             const u64 *dig, const u64 *split)
 {
     constexpr u32 NB = Digits<W>::NB;
     __shared__ u32 h[NB];
+    LevelDigit<LOOP && W == 8> digit;
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
     TILE_LOOP(t, ntiles) {
@@ -956,7 +1069,7 @@ __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart,
     const u64 *keys = (g.aux & SEG_INB) ? keyB : keyA;
     const u32 T = tstart[s + 1] - tstart[s];
     const u32 lt = t - tstart[s];
-    const Digit D = digit_unpack(dig[s]);
+    digit.set(dig[s], split);
     const u32 b0 = g.begin + lt * tile;
     const u32 b1 = min(g.end, b0 + tile);
     for (u32 d = threadIdx.x; d < NB; d += NT) h[d] = 0;
@@ -979,7 +1092,7 @@ __global__ __launch_bounds__(NT) void k_hist(const Seg *segs, const u32 *tstart,
             if (valid) {
                 mn = k < mn ? k : mn;
                 mx = k > mx ? k : mx;
-                atomicAdd(&h[digit_of(k, D)], 1u);
+                atomicAdd(&h[digit(k)], 1u);
             }
         }
     }
@@ -1017,9 +1130,9 @@ struct EmitItem {
 };
 
 // ... once the segment is known not to share the whole digit (start: members in
-// lower buckets; mn: any of its keys).
-__device__ __forceinline__ EmitItem emit_bucket(const Seg &g, const Digit &D, u64 mn, u32 d, u32 start, u32 cnt,
-                                                u32 small_max)
+// lower buckets; used: the key bits that all its members share; c8: the keys' last
+// byte, if that is all 64).
+__device__ __forceinline__ EmitItem emit_bucket(const Seg &g, u32 used, u32 c8, u32 start, u32 cnt, u32 small_max)
 {
     EmitItem it{K_NONE, Seg{0, 0, 0, 0}, false, make_uint2(0, 0)};
     const u32 cf = (g.aux & SEG_INB) ? 0u : (u32)SEG_INB;  // the scatter writes the other arrays
@@ -1028,10 +1141,9 @@ __device__ __forceinline__ EmitItem emit_bucket(const Seg &g, const Digit &D, u6
     it.bv = make_uint2(sb, g.depth);
     it.ns = Seg{sb, se, g.depth, cf};
     if (cnt >= 2) {
-        if (D.used == 64) {
+        if (used == 64) {
             // no varying bit is left: the bucket's keys are equal in all 64
             // bits, and their last byte counts the strings' bytes
-            const u32 c8 = (u32)digit_put(mn, d, D) & 0xFFu;
             if (c8 == 8) { it.kind = K_NEXT; it.ns = Seg{sb, se, g.depth + 7, SEG_SKIP}; }
             else { it.kind = K_IDENT; it.ns = Seg{sb, se, g.depth + c8, 0}; }
         } else if (cnt <= WS_MAX) {
@@ -1040,7 +1152,7 @@ __device__ __forceinline__ EmitItem emit_bucket(const Seg &g, const Digit &D, u6
             it.kind = cnt <= BS_SMALL ? K_SMALL : K_MID;
         } else {
             it.kind = K_LARGE;
-            it.ns.aux = D.used | cf | (g.aux & SEG_NOROOT);
+            it.ns.aux = used | cf | (g.aux & SEG_NOROOT);
         }
     }
     return it;
@@ -1057,13 +1169,15 @@ __device__ __forceinline__ EmitItem emit_whole(const Seg &g, u64 key)
 
 template <u32 W>
 __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart, const u32 *hist, const u64 *smin,
-                                              const u64 *smax, const u64 *dig, const EmitOut &o, u32 s, u32 d,
-                                              bool *scat)
+                                              const u64 *smax, const u64 *dig, const u64 *split, const EmitOut &o,
+                                              u32 s, u32 d, bool *scat)
 {
     constexpr u32 NB = Digits<W>::NB;
     EmitItem it{K_NONE, Seg{0, 0, 0, 0}, false, make_uint2(0, 0)};
     const Seg g = segs[s];
-    const Digit D = digit_unpack(dig[s]);
+    const u64 spec = dig[s];
+    const Digit D = digit_unpack(spec);
+    const bool by = spec & SPLIT_FLAG;
     const u32 rt = g.aux & SEG_NOROOT;
     const u32 pf = g.aux & SEG_INB;  // where the segment's data is now
     const u64 mn = smin[s], mx = smax[s];
@@ -1074,7 +1188,7 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
         return d == 0 ? emit_whole(g, mn) : it;
     }
     const u32 fd = (u32)__clzll(mn ^ mx);  // leading bits that all keys share
-    if (fd > 63 - D.low) {
+    if (!by && fd > 63 - D.low) {
         // the whole digit is common to the segment: no scatter needed
         *scat = false;
         if (d == 0) { it.kind = K_LARGE; it.ns = Seg{g.begin, g.end, g.depth, fd | pf | rt}; }
@@ -1085,7 +1199,12 @@ __device__ __forceinline__ EmitItem emit_item(const Seg *segs, const u32 *tstart
     const u32 T = tstart[s + 1] - ts;
     const u32 e = NB * ts + d * T;
     const u32 base = hist[NB * ts];
-    return emit_bucket(g, D, mn, d, hist[e] - base, hist[e + T] - hist[e], o.small_max);
+    u32 used = D.used, c8 = (u32)digit_put(mn, d, D) & 0xFFu;
+    if (by) {
+        used = d & 1 ? 64u : g.aux & 63u;
+        c8 = d & 1 ? (u32)split[(SPLITS + 1) * (u64)(u32)spec + (d >> 1)] & 0xFFu : 0u;
+    }
+    return emit_bucket(g, used, c8, hist[e] - base, hist[e + T] - hist[e], o.small_max);
 }
 
 // Segments per workgroup in k_emit: two of 256 digits (an item per thread and
@@ -1163,7 +1282,7 @@ __device__ __forceinline__ void emit_push(const EmitItem (&it)[EPB], const EmitO
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart, const u32 *nsegp,
                                               const u32 *hist, const u64 *smin, const u64 *smax,
-                                              const u64 *dig, EmitOut o)
+                                              const u64 *dig, const u64 *split, EmitOut o)
 {
     constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT, SPG = EmitShape<W>::SPG, EPB = EmitShape<W>::EPB;
     __shared__ EmitLds L;
@@ -1180,7 +1299,7 @@ __global__ __launch_bounds__(256) void k_emit(const Seg *segs, const u32 *tstart
         it[q].bnd = false;
         if (s >= nseg) continue;
         bool sc = false;
-        it[q] = emit_item<W>(segs, tstart, hist, smin, smax, dig, o, s, d, &sc);
+        it[q] = emit_item<W>(segs, tstart, hist, smin, smax, dig, split, o, s, d, &sc);
         if (d == 0) o.scat[s] = sc ? 1 : 0;
         o.kinds[NB * s + d] = (u8)it[q].kind;
     }
@@ -1323,10 +1442,11 @@ __device__ __forceinline__ void scatter_range(ScatterLds<W, NTB> &L, const DG &d
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
                                                 const u32 *hist, const u8 *scat, u64 *keyA, u32 *valA,
-                                                u64 *keyB, u32 *valB, const u64 *dig)
+                                                u64 *keyB, u32 *valB, const u64 *dig, const u64 *split)
 {
     constexpr u32 NB = Digits<W>::NB, DPT = Digits<W>::DPT;
     __shared__ ScatterLds<W> L;
+    LevelDigit<LOOP && W == 8> digit;
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
     TILE_LOOP(t, ntiles) {
@@ -1341,14 +1461,14 @@ __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tsta
     const u32 ts = tstart[s];
     const u32 T = tstart[s + 1] - ts;
     const u32 lt = t - ts;
-    const Digit D = digit_unpack(dig[s]);
+    digit.set(dig[s], split);
     const u32 b0 = g.begin + lt * tile;
     const u32 b1 = min(g.end, b0 + tile);
     const u32 base = hist[NB * ts];
     u32 run[DPT];  // next free position of the thread's digits, DPT neighbouring ones
 #pragma unroll
     for (u32 r = 0; r < DPT; r++) run[r] = g.begin + hist[NB * ts + (threadIdx.x * DPT + r) * T + lt] - base;
-    scatter_range<W>(L, [&](u64 k) { return digit_of(k, D); }, ksrc, vsrc, kdst, vdst, b0, b1, run);
+    scatter_range<W>(L, digit, ksrc, vsrc, kdst, vdst, b0, b1, run);
     __syncthreads();  // (the next tile)
     }
 }
@@ -1358,7 +1478,9 @@ __global__ __launch_bounds__(NT) void k_scatter(const Seg *segs, const u32 *tsta
 // eight levels of six launches, most of them empty, were 240 of 410 us for 64
 // sets of 100 to 10,000 strings.  Segments of up to WG_MAX strings come here
 // at once (32 elements a thread and pass), and what one or two levels over the
-// whole device leave, however large.  The segments of a level that need another wait
+// whole device leave: of segments above SPLIT_MIN about an eighth at most (see
+// there), of smaller ones all if their keys are skewed (100,000 strings, 95 % of them
+// sharing six bytes: 785 us, with all levels over the device 1125).  The segments of a level that need another wait
 // in `stack`, which holds one entry per `slot` = small_max + 1 strings: each
 // has more members than small_max, so those of one segment fit its own part.
 //
@@ -1464,9 +1586,9 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
                 for (u32 w = 0; w < 4; w++)
                     if (w < wid) x += wsum[w];
                 if (t < 256) {
-                    Digit B = D;  // what a bucket's members share: the digit, all of the key, or nothing more
-                    if (heavy) B.used = t == 1 ? 64u : (g.aux & 63);
-                    it[0] = emit_bucket(g, B, heavy ? hk : mn, heavy ? digit_of(hk, D) : t, x, cnt, o.small_max);
+                    // what a bucket's members share: the digit, all of the key, or nothing more
+                    const u32 used = heavy ? (t == 1 ? 64u : (g.aux & 63)) : D.used;
+                    it[0] = emit_bucket(g, used, (u32)(heavy ? hk : digit_put(mn, t, D)) & 0xFFu, x, cnt, o.small_max);
                     kd[t] = (u8)it[0].kind;
                 }
                 if (it[0].kind == K_LARGE) {
@@ -1510,21 +1632,27 @@ __global__ __launch_bounds__(WG_NT) void k_radix_wg(const Seg *wl, const u32 *nw
 template <bool LOOP, u32 W>
 __global__ __launch_bounds__(NT) void k_settle(const Seg *segs, const u32 *tstart, const u32 *nsegp, u32 tile,
                                                const u8 *scat, const u8 *kinds, const u64 *keyB,
-                                               const u32 *valB, u64 *keyA, u32 *valA, const u64 *dig)
+                                               const u32 *valB, u64 *keyA, u32 *valA, const u64 *dig,
+                                               const u64 *split)
 {
+    LevelDigit<LOOP && W == 8> digit;
     const u32 nseg = *nsegp;
     const u32 ntiles = LOOP ? tstart[nseg] : 0u;
     TILE_LOOP(t, ntiles) {
     const u32 s = seg_of_tile(tstart, nseg, t);
     const Seg g = segs[s];
     const bool inb = g.aux & SEG_INB;
-    const Digit D = digit_unpack(dig[s]);
     const u32 lt = t - tstart[s];
     const u32 b0 = g.begin + lt * tile;
     const u32 b1 = min(g.end, b0 + tile);
     const u8 *kd = kinds + Digits<W>::NB * s;
     if (scat[s]) {
         if (inb) continue;  // scattered into A
+        const u64 spec = dig[s];
+        const bool by = LOOP && W == 8 && (spec & SPLIT_FLAG);  // (uniform)
+        if (by) __syncthreads();  // (an earlier tile's splitters are in use no more)
+        digit.set(spec, split);
+        if (by) __syncthreads();
         for (u32 c0 = b0; c0 < b1; c0 += RX_PF * NT) {
             // RX_PF chunks' keys, then their buckets' kinds, loaded before any is used
             u64 kq[RX_PF];
@@ -1535,7 +1663,7 @@ __global__ __launch_bounds__(NT) void k_settle(const Seg *segs, const u32 *tstar
                 kq[q] = i < b1 ? keyB[i] : 0ull;
             }
 #pragma unroll
-            for (u32 q = 0; q < RX_PF; q++) cq[q] = kd[digit_of(kq[q], D)];
+            for (u32 q = 0; q < RX_PF; q++) cq[q] = kd[digit(kq[q])];
 #pragma unroll
             for (u32 q = 0; q < RX_PF; q++) {
                 const u32 i = c0 + q * NT + threadIdx.x;
@@ -2025,6 +2153,7 @@ void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c)
     TAKE(smax, u64, nlarge);
     TAKE(rmask, u64, nlarge);
     TAKE(dig, u64, nlarge);
+    TAKE(split, u64, (SPLITS + 1) * (n / SPLIT_MIN + 1 < SPLIT_LIST ? n / SPLIT_MIN + 1 : (u64)SPLIT_LIST));
     TAKE(scat, u8, nlarge);
     TAKE(kinds, u8, nkinds);
     TAKE(tstart, u32, nseg + 1);
@@ -2177,7 +2306,7 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     if (most <= LIST_ONE) {
         auto *const start = wg ? k_level_start<true> : k_level_start<false>;
         start<<<1, LIST_NT, 0, st>>>(LA, w.ctr, w.hdr, NB, C.TL, w.tstart, w.smin, w.smax, w.hscan,
-                                            w.rmask, w.dig, narrow, w.wgl, WG_MAX);
+                                            w.rmask, w.dig, narrow, w.wgl, WG_MAX, w.keyA, w.keyB, w.split);
         SS_CHECK_LAUNCH();
     } else {
         k_level_begin<<<1, 256, 0, st>>>(w.ctr, w.hdr, NB, w.hscan);
@@ -2190,8 +2319,8 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     const unsigned tg = ltiles.yes ? grid_of(ltiles.v, 1, 1u << 30) : 0u;  // (one tile per workgroup)
     {
         SS_PROF("k_hist", st, (double)lelem * 8.0);  // read the keys
-        if (ltiles.yes) k_hist<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax, w.dig);
-        else k_hist<true, W><<<grid_of(n, C.TL, resident(k_hist<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax, w.dig);
+        if (ltiles.yes) k_hist<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax, w.dig, w.split);
+        else k_hist<true, W><<<grid_of(n, C.TL, resident(k_hist<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.keyA, w.keyB, w.hist, w.smin, w.smax, w.dig, w.split);
     }
     SS_CHECK_LAUNCH();
     // (three launches once there are more items than one range per workgroup holds)
@@ -2200,19 +2329,19 @@ static int radix_level_w(RoundCtx &C, Seg *LA, Seg *LB, Known nlarge, Known ltil
     else SS_TRY(ss_scan_exclusive_dev(w.hist, w.hist, w.hdr + H_HIST, nh, w.hscan, st));
     EmitOut eo{w.tiny, w.small, w.mid, LB, w.nxt, w.ident, w.bnd, w.ctr, w.scat, w.kinds, C.BM, C.TL, C.ET};
     constexpr u32 SPG = EmitShape<W>::SPG;
-    if (nlarge.yes) k_emit<false, W><<<grid_of(nlarge.v, SPG, 1u << 30), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, eo);
-    else k_emit<true, W><<<grid_of(n / 128, SPG, resident(k_emit<true, W>, 256)), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, eo);
+    if (nlarge.yes) k_emit<false, W><<<grid_of(nlarge.v, SPG, 1u << 30), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, w.split, eo);
+    else k_emit<true, W><<<grid_of(n / 128, SPG, resident(k_emit<true, W>, 256)), 256, 0, st>>>(LA, w.tstart, nlp, w.hist, w.smin, w.smax, w.dig, w.split, eo);
     SS_CHECK_LAUNCH();
     {
         SS_PROF("k_scatter", st, (double)lelem * 24.0);  // key+payload in and out
-        if (ltiles.yes) k_scatter<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB, w.dig);
-        else k_scatter<true, W><<<grid_of(n, C.TL, resident(k_scatter<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB, w.dig);
+        if (ltiles.yes) k_scatter<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB, w.dig, w.split);
+        else k_scatter<true, W><<<grid_of(n, C.TL, resident(k_scatter<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.hist, w.scat, w.keyA, J.vals, w.keyB, w.valB, w.dig, w.split);
     }
     SS_CHECK_LAUNCH();
     {
         SS_PROF("k_settle", st, (double)lelem * 8.0);  // at most the scattered keys read back
-        if (ltiles.yes) k_settle<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals, w.dig);
-        else k_settle<true, W><<<grid_of(n, C.TL, resident(k_settle<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals, w.dig);
+        if (ltiles.yes) k_settle<false, W><<<tg, NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals, w.dig, w.split);
+        else k_settle<true, W><<<grid_of(n, C.TL, resident(k_settle<true, W>, NT)), NT, 0, st>>>(LA, w.tstart, nlp, C.TL, w.scat, w.kinds, w.keyB, w.valB, w.keyA, J.vals, w.dig, w.split);
     }
     SS_CHECK_LAUNCH();
     return SS_OK;
@@ -2415,10 +2544,14 @@ static int sort_rounds_device(const SortJob &J, SortWs &w, u32 rounds, u32 *stat
     Seg *const act0 = w.act;
     RoundCtx C = round_ctx(J, w);
     // One workgroup per radix segment: in small sorts, or where the sets are small
-    // on average, so that a segment too long for one is the exception (a set of
-    // 300,000 strings, half of them sharing seven bytes, among 63 small ones: 670
-    // us, with all levels over the device 1,130).  (The list of radix segments must
-    // fit one workgroup's pass to be split by size.)
+    // on average, so that a segment too long for one is the exception.  One set
+    // among small ones of 50, with all levels over the device and so: 300,000 random
+    // strings 865 and 256 us, half of them sharing seven bytes 1132 and 396; 2M among
+    // 300 sets 1047 and 441, 1271 and 796; 7M among 1,000 sets 2125 and 859, 2661 and
+    // 1258.  (Where keys tie in pairs by the hundred thousand the next round, without
+    // their direct comparison, can cost more than it gains: 2M strings, half of
+    // them sharing three bytes, 1169 and 1877.)  (The list of radix segments must fit
+    // one workgroup's pass to be split by size.)
     const bool wg = C.W == 8 && J.n_total / C.BM <= LIST_ONE &&
                     (J.n_total <= 16 * WG_MAX || J.n_total / num_sets <= WG_MAX / 4);
     const Known unknown{false, 0};

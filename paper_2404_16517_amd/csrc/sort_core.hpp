@@ -96,6 +96,7 @@ struct SortWs {
     u32 *skipv;
     u64 *smin, *smax;
     u64 *rmask, *dig;  // per radix segment of a round its varying key bits; per radix segment its digit
+    u64 *split;  // splitters of the segments that a level divides by them (see SPLIT_MIN)
     u8 *scat;
     u8 *kinds;  // per radix segment and digit: what the bucket became
     u32 *tstart, *hist;
