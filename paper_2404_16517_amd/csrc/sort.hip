@@ -15,10 +15,11 @@
 //          remaining length capped at 8, so that integer order is string order
 //          over that window, end-of-string below every byte;
 //       3. sorts each segment by (key, input index): segments larger than the
-//          LDS cutover go through MSD byte passes (histogram, global scan,
-//          stable scatter); segments of up to 128 strings are sorted by one
-//          wavefront each with a bitonic network in registers; the others are
-//          packed into LDS tiles and sorted by a bitonic network in LDS;
+//          LDS cutover go through MSD radix levels over digits of their varying
+//          key bits (histogram, global scan, stable scatter); segments of up to
+//          128 strings are sorted by one wavefront each with a bitonic network
+//          in registers; the others by one workgroup each with a merge sort in
+//          LDS;
 //       4. where neighbours' keys differ the LCP is final and is written; runs
 //          of equal keys whose strings continue become next round's segments
 //          at depth + 7; runs of equal keys whose strings end are equal
@@ -130,7 +131,10 @@ struct Digits {
 // takes the fifty of a full digit, and the scatter writes longer runs.  Where
 // the strings are skewed it can cost another level of launches, so only levels of
 // NARROW_MIN strings and more do it: 16M D/N strings in 16 sets 5410 -> 5300 us,
-// 512 sets 964 -> 924, but 200,000 text strings 589 -> 661, 1M D/N 264 -> 272.
+// 512 sets 964 -> 924, but 200,000 text strings 589 -> 661, 1M D/N 264 -> 272.  Text
+// strings without and with it: 1M 853 and 951, 2M 1044 and 1038, 2.5M 1169 and
+// 1157, 3M 1240 and 1205, 6M 1844 and 1729; D/N strings: 2M 378 and 384, 3M 446
+// and 431, 4M 566 and 541, 6M 712 and 710.
 #define NARROW_TO 512
 #define NARROW_MIN 2000000
 __device__ __forceinline__ u64 digit_spec(const Seg &g, const u64 *rmask, u32 W, bool narrow)
@@ -1005,11 +1009,10 @@ __global__ __launch_bounds__(256) void k_resolve(const Seg *in, const u8 *bytes,
 
 // ------------------------------------------------------------ radix passes
 //
-// A radix level sorts a segment by one digit of the 64-bit key.  The digit
-// width W is 8 bits (eight levels per key, one per byte) or 11 bits (six
-// levels: five of 11 bits and a last one of 9 that ends with the key's
-// length byte).  Level l covers key bits [lo, hi) with hi = 64 - W l and
-// lo = max(0, hi - W); its histograms have 2^W buckets.
+// A radix level sorts a segment by one digit of the 64-bit key, W = 8 or 11 bits
+// wide: which bits, the segment's keys decide (Digits, above), so a key takes at
+// most eight or six levels and mostly one to three.  The histograms have 2^W
+// buckets.
 
 // Lanes of this wave holding the same W-bit digit (restricted to `valid`).
 template <u32 W>

@@ -124,7 +124,7 @@ struct SortJob {
 
 void sort_ws_layout(u64 n, SortWs *w, WsArena *a, WsCounter *c);
 // Host-driven rounds from nact segments in w.act covering `atiles` element
-// tiles of 2048 (their count, tiles and strings also in the counters).
+// tiles (of sort_shape's et; their count, tiles and strings also in the counters).
 int sort_rounds(const SortJob &J, SortWs &w, u32 nact, u32 atiles, bool whole = false);
 // Elements per workgroup of the element-wise kernels, tile of the radix passes
 // and the size up to which segments are sorted in LDS, for a sort of n strings.
