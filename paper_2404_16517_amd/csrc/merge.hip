@@ -1618,8 +1618,8 @@ __device__ __forceinline__ void mw_route(const MwOut &W, Seg o, u32 from)
 // LCPs stand).  A tile whose windows exceed MW_CAP (many copies of one key, or
 // a group with too few samples) becomes one segment for the segmented sort
 // (k_mw_over copies its windows), or, if all its keys are one, is in order as it
-// is; in a sample level its keys all become its lower
-// threshold, which only makes later tiles larger.
+// is; in a sample level its keys all become its lower threshold, which only makes
+// later tiles larger.
 //
 // Bounded by vector instructions: about 25 per element and level, against 8 B
 // in and 8 to 20 B out.  8M keys in 256 runs: 235 us over all levels, where
@@ -2045,8 +2045,8 @@ __device__ __forceinline__ int fc_cmp8(const FcView &V, const FcEl &X, const FcE
     return lx < ly ? -1 : (lx > ly ? 1 : 0);
 }
 
-// Tile counts (per members each) of a list of segments; their comparison words (see k_tie_compare)
-// and the counters of the lists the round builds are reset.
+// Tile counts (`per` members each) of a list of segments; their comparison words
+// (see k_tie_compare) and the counters of the lists the round builds are reset.
 __global__ void k_tie_tiles(const Seg *list, u32 cnt, u32 per, u32 *tiles, u64 *cmp, u32 *ctr)
 {
     const u32 j = blockIdx.x * blockDim.x + threadIdx.x;

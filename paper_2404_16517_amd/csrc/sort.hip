@@ -218,7 +218,7 @@ __device__ __forceinline__ u32 digit_of(u64 k, const Digit &D)
 #define SPLITS 127  // (a table has one entry more)
 #define SPLIT_SAMPLE 1024
 #define SPLIT_SKEW 128
-#define SPLIT_LIST 80  // segments of a level (sorts that get here have 4096 times 2048 strings and a few)
+#define SPLIT_LIST 80  // segments of a level: sorts that get here hold at most 4097 times 2048 strings
 #define SPLIT_FLAG (1ull << 63)  // in a segment's digit: by the splitters of this index
 
 __device__ __forceinline__ u32 split_digit(const u64 *tab, u64 k)  // tab: ascending, past the last ~0
