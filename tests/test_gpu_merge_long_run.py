@@ -73,4 +73,4 @@ def test_minima_of_a_long_run_time():
         finally:
             ss.profile_enable(False)
     print(f"[minima] {took} ms", flush=True)
-    assert took["long"] < 5 * took["even"]
+    assert took["long"] < 15 * took["even"]
