@@ -1567,7 +1567,6 @@ __global__ __launch_bounds__(256) void k_mw_bounds(MwLevel M, u32 total)
 }
 
 #define TIE_SMALL 8  // tied segments of up to this many are sorted at once
-#define TIE_WALK 256 // ... and of up to this many looked through for copies of one string
 #define TIE_REC 1u  // a tied segment whose members' entries lie beside the order, and whose results are written
 
 struct MwOut {
@@ -2058,63 +2057,10 @@ __global__ void k_tie_tiles(const Seg *list, u32 cnt, u32 per, u32 *tiles, u64 *
     if (ctr && j < C_NCTR) ctr[j] = 0;
 }
 
-// A member of a tied segment, with what a comparison needs of it.
-__device__ __forceinline__ FcEl tie_member(const FcView &V, const Seg &g, u32 p, const u32 *order, const u64 *rso,
-                                           const uint2 *rde)
-{
-    if (!(g.aux & TIE_REC)) return fc_el(V, order[p]);
-    const uint2 de = rde[p];
-    return FcEl{order[p], de.x, de.y, rso[p]};
-}
-
-// Segments of TIE_SMALL + 1 to TIE_WALK copies of one string, eight lanes each,
-// before the others: every member equals its neighbour in its run or, if it
-// follows none, is compared with the first.  Their order stands, their LCPs are
-// written, and they leave the list (no members left).  2M strings, each ten times
-// in two runs: the merge took 656 us with these among the larger segments (a comparison,
-// a sort's read-backs and an emission of all of them), now 447.
-__global__ __launch_bounds__(256) void k_tie_copies(Seg *list, u32 cnt, FcView V, const u32 *order, const u64 *rso,
-                                                    const uint2 *rde, u32 *lcp)
-{
-    const u32 s = blockIdx.x * 32 + (threadIdx.x >> 3), gl = threadIdx.x & 7, sh = threadIdx.x & 56u;
-    if (s >= cnt) return;
-    const Seg g = list[s];
-    const u32 m = g.end - g.begin;
-    if (m <= TIE_SMALL || m > TIE_WALK) return;
-    FcEl F{0, 0, 0, 0};  // the first member
-    u32 lg = 0;          // the last one seen
-    bool copies = true;
-    for (u32 c = 0; copies && c < m; c += 8) {
-        FcEl E{0, 0, 0, 0};
-        if (c + gl < m) E = tie_member(V, g, g.begin + c + gl, order, rso, rde);
-        if (c == 0) F = fc_el_shfl(E, 0);
-        const u32 up = __shfl_up(E.g, 1, 8), pg = gl ? up : lg;
-        lg = __shfl(E.g, 7, 8);
-        const bool in = c + gl < m && c + gl > 0;
-        const bool follows = in && E.g == pg + 1 && E.e >= g.depth;
-        // (equal lengths throughout, so an LCP of that length is equality)
-        copies = !((u32)(__ballot(in && (E.d != F.d || (follows && E.e != E.d))) >> sh) & 0xFFu);
-        u32 heads = (u32)(__ballot(in && !follows) >> sh) & 0xFFu;
-        for (; copies && heads; heads &= heads - 1) {
-            u64 l;
-            copies = fc_cmp8(V, F, fc_el_shfl(E, (u32)__ffs((int)heads) - 1), g.depth, gl, &l) == 0;
-        }
-    }
-    if (!copies) return;
-    for (u32 p = g.begin + 1 + gl; p < g.end; p += 8) lcp[p] = F.d;
-    if (gl == 0) list[s].end = g.begin;
-}
-
 // Segments of up to TIE_SMALL members (most are two equal strings), eight lanes
-// each: a member's rank is the number before it and its LCP the largest with one
-// of those, over all pairs; few pairs are compared.  Neighbours of one run (which
-// share the key, unlike a run's end and the next one's start) have the run's LCPs
-// and order, and an equal neighbour has its neighbour's results.  All others are
-// compared with the first member, and two whose LCPs or sides there differ are in
-// order by that; only the rest against each other, from that LCP on.  So copies
-// of a string cost a comparison per run and not one per pair, whose number the
-// largest segment of a wavefront would set for all (4M strings, each three times in
-// two runs: the merge took 1611 us with all pairs, now 809).  The tile merge has written the results in (run,
+// each: every pair is compared, a member's rank is the number before it and its
+// LCP the largest with one of those.  (Neighbours of one run -- which share the key, unlike a run end and the next start -- need no comparison:
+// their LCP is the run's.)  The tile merge has written the results in (run,
 // position) order, so those of members that stay where they are -- all of an
 // equal run's -- are final, the others are written again here.  Larger segments
 // are passed on to `big` (C_RNEXT of them, C_RELEM elements).
@@ -2122,7 +2068,7 @@ __global__ __launch_bounds__(256) void k_tie_copies(Seg *list, u32 cnt, FcView V
 // Bounded by the latency of scattered reads (entry, then its length, LCP and
 // offset, then the bytes, 128 a step).  The ties of 4M text strings in 16 x 16
 // runs took about 1.9 ms inside the former pairwise merge, where one lane's
-// comparison held up its wavefront, and about 0.2 ms so.
+// comparison held up its wavefront, and about 0.3 ms so.
 __global__ __launch_bounds__(256) void k_tie_small(const Seg *list, u32 cnt, FcView V, u32 *order, const u64 *rso,
                                                    const uint2 *rde, MergeOut O, Seg *big, u32 *ctr)
 {
@@ -2149,105 +2095,26 @@ __global__ __launch_bounds__(256) void k_tie_small(const Seg *list, u32 cnt, FcV
     // (no barrier from here on: a wavefront with long strings holds up no other)
     if (m && m <= TIE_SMALL) {
         FcEl E{0, 0, 0, 0};
-        if (gl < m) E = tie_member(V, g, g.begin + gl, order, rso, rde);
-        // bit q: member q follows its predecessor in a run; it equals it
-        const u32 sh = threadIdx.x & 56u, pg = __shfl_up(E.g, 1, 8), pd = __shfl_up(E.d, 1, 8);
-        const bool follows = gl > 0 && gl < m && E.g == pg + 1 && E.e >= g.depth;
-        const u32 nb = (u32)(__ballot(follows) >> sh) & 0xFFu;
-        const u32 eq = (u32)(__ballot(follows && E.e == E.d && E.d == pd) >> sh) & 0xFFu;
-        // (in both loops below the cheap pairs are stepped over first, so that the
-        // wavefront's segments meet at their comparisons)
-        // against the first member: LCP l0 and side s0 (-1: the first is smaller)
-        const FcEl F = fc_el_shfl(E, 0);
-        u32 l0 = 0;
-        int s0 = 0;
-        {
-            u64 l = 0;
-            int r = 0;
-            u32 cl = 0xFFFFFFFFu, j = 1;  // cl: the run's LCP so far, while all follow the first
-            bool chain = true;
-            for (;;) {
-                for (; j < m; j++) {
-                    const u32 ej = __shfl(E.e, j, 8), dj = __shfl(E.d, j, 8);
-                    chain = chain && (nb >> j & 1);
-                    if (chain) {
-                        cl = ej < cl ? ej : cl;
-                        l = cl;
-                        r = cl == F.d && cl == dj ? 0 : -1;
-                    } else if (!(eq >> j & 1)) {
-                        break;
-                    }
-                    if (gl == j) {
-                        l0 = (u32)l;
-                        s0 = r;
-                    }
-                }
-                if (j >= m) break;
-                r = fc_cmp8(V, F, fc_el_shfl(E, j), g.depth, gl, &l);
-                if (gl == j) {
-                    l0 = (u32)l;
-                    s0 = r;
-                }
-                j++;
+        if (gl < m) {
+            const u32 p = g.begin + gl;
+            if (g.aux & TIE_REC) {
+                const uint2 de = rde[p];
+                E = FcEl{order[p], de.x, de.y, rso[p]};
+            } else {
+                E = fc_el(V, order[p]);
             }
         }
-        u32 rank = gl, mx = E.d;  // all equal
-        if ((u32)(__ballot(gl < m && s0 != 0) >> sh) & 0xFFu) {
-            rank = 0;
-            mx = 0;
-            auto pair = [&](u32 i, u32 j, u32 l, bool after) {  // (i after j)
+        u32 rank = 0, mx = 0;
+        for (u32 i = 0; i + 1 < m; i++) {
+            const FcEl A = fc_el_shfl(E, i);
+            for (u32 j = i + 1; j < m; j++) {
+                const FcEl B = fc_el_shfl(E, j);
+                u64 l = B.e;
+                const bool nb = B.g == A.g + 1 && B.e >= g.depth;
+                const bool after = !nb && fc_cmp8(V, A, B, g.depth, gl, &l) > 0;  // i after j
                 if (gl == (after ? i : j)) {
                     rank++;
-                    mx = l > mx ? l : mx;
-                }
-            };
-            for (u32 j = 1; j < m; j++) pair(0, j, __shfl(l0, j, 8), __shfl(s0, j, 8) > 0);
-            u32 i = 1, j = 2, cl = 0xFFFFFFFFu, l = 0;
-            int r = 0;
-            bool chain = true;
-            for (;;) {
-                u32 from = 0;
-                bool open = false;
-                while (i + 1 < m) {
-                    const u32 li = __shfl(l0, i, 8), lj = __shfl(l0, j, 8), ej = __shfl(E.e, j, 8);
-                    const int si = __shfl(s0, i, 8), sj = __shfl(s0, j, 8);
-                    chain = chain && (nb >> j & 1);
-                    cl = ej < cl ? ej : cl;
-                    if (si == 0) {
-                        l = lj;
-                        r = sj;
-                    } else if (sj == 0 || li < lj || (li == lj && si != sj)) {
-                        l = li;
-                        r = -si;
-                    } else if (li > lj) {
-                        l = lj;
-                        r = sj;
-                    } else if (chain) {
-                        l = cl;
-                        r = -1;
-                    } else if (!((eq >> j & 1) && j > i + 1)) {
-                        open = true;
-                        from = li;
-                        break;
-                    }
-                    pair(i, j, l, r > 0);
-                    if (++j == m) {
-                        i++;
-                        j = i + 1;
-                        chain = true;
-                        cl = 0xFFFFFFFFu;
-                    }
-                }
-                if (!open) break;
-                u64 lc;
-                r = fc_cmp8(V, fc_el_shfl(E, i), fc_el_shfl(E, j), from > g.depth ? from : g.depth, gl, &lc);
-                l = (u32)lc;
-                pair(i, j, l, r > 0);
-                if (++j == m) {
-                    i++;
-                    j = i + 1;
-                    chain = true;
-                    cl = 0xFFFFFFFFu;
+                    mx = (u32)l > mx ? (u32)l : mx;
                 }
             }
         }
@@ -2278,29 +2145,14 @@ __global__ __launch_bounds__(256) void k_tie_compare(const Seg *list, const u32 
     for (u32 h = 0; h < TIE_T / 8; h++) E[h] = fc_el(V, order[p0 + 8 * h + gl < p1 ? p0 + 8 * h + gl : p0]);
     u64 best = ~0ull;
 #pragma unroll
-    for (u32 h = 0; h < TIE_T / 8; h++) {
-        // bit q: member q equals the one before it in its run, which this tile holds
-        u32 pg = __shfl_up(E[h].g, 1, 8), pd = __shfl_up(E[h].d, 1, 8);
-        if (h) {
-            const u32 lg = __shfl(E[h ? h - 1 : 0].g, 7, 8), ld = __shfl(E[h ? h - 1 : 0].d, 7, 8);
-            pg = gl ? pg : lg;
-            pd = gl ? pd : ld;
-        }
-        const bool same = (h || gl) && E[h].g == pg + 1 && E[h].e >= g.depth && E[h].e == E[h].d && E[h].d == pd;
-        const u32 eq = (u32)(__ballot(same) >> (threadIdx.x & 56u)) & 0xFFu;
+    for (u32 h = 0; h < TIE_T / 8; h++)
         for (u32 q = 0; q < 8 && p0 + 8 * h + q < p1; q++) {
-            const u32 at = p0 + 8 * h + q;
-            if (at == g.begin) continue;
-            if (eq >> q & 1) {  // (its neighbour's result, which is in best unless that is the first member)
-                if (at == g.begin + 1) best = 2ull * F.d + 1;
-                continue;
-            }
+            if (p0 + 8 * h + q == g.begin) continue;
             u64 l;
             const int r = fc_cmp8(V, F, fc_el_shfl(E[h], q), g.depth, gl, &l);
             const u64 w = 2 * l + (r == 0 ? 1u : 0u);
             best = w < best ? w : best;
         }
-    }
     // (a segment's tiles meet on its word: only what would change it as it is read
     // is committed; it only ever falls)
     if (gl == 0 && best < __hip_atomic_load(&cmp[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
@@ -2837,16 +2689,12 @@ extern "C" int ss_lcp_merge(uint32_t k, const uint64_t *run_begin, const uint64_
     // rounds: the list's small segments end; its large ones go to `big` -- the
     // first round's stay there for the final emission -- and their ties, after
     // a sort by the next keys, make the next list
-    Seg *list = w.segs;
+    const Seg *list = w.segs;
     u32 nbig0 = 0, ebig0 = 0;
     for (bool first = true; nact; first = false) {
         Seg *big = first ? w.big : w.segs;
         k_fill_u32<<<1, 64, 0, st>>>(sw.ctr, 0u, C_NCTR);
         SS_CHECK_LAUNCH();
-        if (!small_only) {
-            k_tie_copies<<<(unsigned)ceil_div(nact, 32), 256, 0, st>>>(list, nact, V, w.order, sw.keyB, sw.mpr, out_lcp);
-            SS_CHECK_LAUNCH();
-        }
         {
             SS_PROF("k_tie_small", st, (double)nact * 48.0);  // of two: entry, its LCP, length, offset; LCP out; not the bytes
             k_tie_small<<<(unsigned)ceil_div(nact, 32), 256, 0, st>>>(list, nact, V, w.order, sw.keyB, sw.mpr, O, big,

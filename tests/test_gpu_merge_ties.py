@@ -1,9 +1,7 @@
-"""Tied segments of a merge, where most pairs of members are ordered without being
-compared: copies inside and across runs, prefixes, members that leave the first
-one at the same or at different places and sides, segments around 8 (ordered at
-once) and 256 members (looked through for copies), copies with one deviating
-member.  Exact against the oracle; and long equal neighbours of one run are not
-read."""
+"""Tied segments of a merge: copies inside and across runs, prefixes, members that
+leave the first one at the same or at different places and sides, segments around
+8 members (ordered at once), 16 and 256, copies with one deviating member.  Exact
+against the oracle; and what long or many equal neighbours of one run cost."""
 import statistics
 import time
 
@@ -18,6 +16,8 @@ from tests.test_gpu_parity import _runs_from_oracle
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+PAIRS = ("every pair of a tied segment is compared: the kernels that left most comparisons out are taken back, after a "
+         "GPU fault in a run that held them, whose cause was not found")
 TAILS = [b"", b"a", b"ab", b"abc", b"abd", b"b", b"ba", b"bab", b"c", b"\x00", b"m" * 30, b"m" * 30 + b"a", b"m" * 29 + b"z"]
 
 
@@ -57,6 +57,7 @@ def test_tied_members(kind, k):
         np.testing.assert_array_equal(ln, by_id[ids])
 
 
+@pytest.mark.skip(reason=PAIRS)
 def test_long_equal_neighbours_time():
     """Three strings of 5 MB, all but equal, in one of two runs whose other strings
     tie with them: the runs' LCPs order them.  Comparing the first with the third took
@@ -89,6 +90,7 @@ def test_long_equal_neighbours_time():
     assert took[5_000_000] < 10 * took[30]
 
 
+@pytest.mark.skip(reason=PAIRS)
 def test_copies_time():
     """2M strings in two runs, each ten times, against 2M distinct ones: 4.5 times as
     long when all pairs were compared and larger segments sorted, now 2.2 times."""
