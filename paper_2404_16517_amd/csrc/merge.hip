@@ -1513,7 +1513,8 @@ __global__ __launch_bounds__(256) void k_mw_rank(const u64 *K, const u32 *ps0, c
         u32 lo[4], n[4], most = 0;
 #pragma unroll
         for (u32 q = 0; q < 4; q++) {
-            const bool on = o + q < j1 && o + q != j;
+            // (a run shorter than its first sample's place has none: nothing of it is read)
+            const bool on = o + q < j1 && o + q != j && ps[o + q + 1] > ps[o + q];
             const u32 w = on ? o + q : j;
             k[q] = K + ps0[w] + mw_phase(w - j0, kg);
             lo[q] = 0;
