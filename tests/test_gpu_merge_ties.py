@@ -93,7 +93,7 @@ def test_long_equal_neighbours_time():
 @pytest.mark.skip(reason=PAIRS)
 def test_copies_time():
     """2M strings in two runs, each ten times, against 2M distinct ones: 4.5 times as
-    long when all pairs were compared and larger segments sorted, now 2.2 times."""
+    long where all pairs are compared and larger segments sorted, 2.2 times where few are."""
     n = 2_000_000
     took = {}
     for copies in (10, 1):
